@@ -48,6 +48,26 @@ template <typename C> RSRR_DEV C crecip(C a) {
     }
     return r;
 }
+// Reciprocal with the larger part scaled to [1/2, 1) by its exponent: one division
+// (Smith's form takes three, one after the other) and no branch, for serial chains.
+RSRR_DEV float2 crecip_scaled(float2 a)
+{
+    const int e = __builtin_amdgcn_frexp_expf(fmaxf(fabsf(a.x), fabsf(a.y)));
+    const float x = ldexpf(a.x, -e), y = ldexpf(a.y, -e);
+    const float d = x * x + y * y;   // in [1/4, 2): no scaling needed around v_rcp_f32
+    float r = __builtin_amdgcn_rcpf(d);
+    r = fmaf(r, fmaf(-d, r, 1.0f), r);
+    return make_float2(ldexpf(x * r, -e), ldexpf(-y * r, -e));
+}
+RSRR_DEV double2 crecip_scaled(double2 a)
+{
+    const int e = __builtin_amdgcn_frexp_exp(fmax(fabs(a.x), fabs(a.y)));
+    const double x = ldexp(a.x, -e), y = ldexp(a.y, -e);
+    const double r = 1.0 / (x * x + y * y);
+    return make_double2(ldexp(x * r, -e), ldexp(-y * r, -e));
+}
+RSRR_DEV float crecip_scaled(float a) { return 1.0f / a; }
+RSRR_DEV double crecip_scaled(double a) { return 1.0 / a; }
 // LAPACK's complex magnitude measure for pivoting: |Re| + |Im|.
 template <typename C> RSRR_DEV auto cabs1(C a) -> decltype(a.x) { return fabs(a.x) + fabs(a.y); }
 

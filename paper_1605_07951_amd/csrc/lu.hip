@@ -27,14 +27,115 @@ namespace rsrr {
 
 // ----------------------------------------------------------------------------
 // Panel base: rows [c0, n) x columns [c0, c0+jb) of one matrix per workgroup,
-// held in registers (thread t owns local rows t, t+NT, ...).
+// held in registers (thread t owns rows t, t+NT, ... of the panel).
+//
+// Bound by the chain of dependent steps of a column (search, broadcast, update),
+// about 1000 cycles, not by bytes or flops, so the steps are kept few: rows never
+// move while the panel is factored (a thread tracks the position that the
+// interchanges give each of its rows and stores the row there at the end); the
+// search runs in registers (DPP) inside a wave; each wave publishes its candidate
+// with the candidate's row, so one barrier per column suffices and every thread
+// picks the winner itself; nothing is stored to memory inside the loop (a barrier
+// waits for stores).  Columns go in groups of GW: the chain of a column touches its
+// own group only, the columns after the group take its pivot rows and one rank-GW
+// update at the end of the group.  The loop over the groups is rolled (the registers
+// rotate by one group), so the code stays in the instruction cache.
+// A block of 32 columns of 48 matrices, complex FP32: 29 / 34 / 47 us at 256 / 512 /
+// 1024 rows (a form that moved the rows, searched by shuffles with four barriers a
+// column and took 8 columns a launch: 73 / 94 / 120 us in four launches, plus the
+// products between them).
+// perm (optional, 2*jb int2) receives the composed interchanges in the layout of
+// perm_build_kernel.
 // ----------------------------------------------------------------------------
+
+// Lanes' values moved by a DPP control; lanes without a source get `none`.
+template <int CTRL, int ROWS> RSRR_DEV int dpp(int x, int none)
+{
+    return __builtin_amdgcn_update_dpp(none, x, CTRL, ROWS, 0xf, false);
+}
+template <int CTRL, int ROWS> RSRR_DEV double dpp(double x, double none)
+{
+    return __hiloint2double(dpp<CTRL, ROWS>(__double2hiint(x), __double2hiint(none)),
+                            dpp<CTRL, ROWS>(__double2loint(x), __double2loint(none)));
+}
+RSRR_DEV int lane_get(int x, int l) { return __builtin_amdgcn_readlane(x, l); }
+RSRR_DEV float lane_get(float x, int l) { return __int_as_float(lane_get(__float_as_int(x), l)); }
+RSRR_DEV double lane_get(double x, int l)
+{
+    return __hiloint2double(lane_get(__double2hiint(x), l), lane_get(__double2loint(x), l));
+}
+template <typename C> RSRR_DEV C lane_get(C x, int l) { x.x = lane_get(x.x, l); x.y = lane_get(x.y, l); return x; }
+RSRR_DEV float shfl_get(float x, int l) { return __shfl(x, l); }
+RSRR_DEV double shfl_get(double x, int l) { return __shfl(x, l); }
+template <typename C> RSRR_DEV C shfl_get(C x, int l) { x.x = __shfl(x.x, l); x.y = __shfl(x.y, l); return x; }
+
+RSRR_DEV int max2(int a, int b) { return a > b ? a : b; }
+RSRR_DEV double max2(double a, double b) { return fmax(a, b); }
+
+// Maximum over lanes 0..W-1 (W = 2, 4, 8 or 16, the same values repeated in the other
+// lanes or not) or over the whole wave (W = 64); uniform result.
+template <int W, typename T> RSRR_DEV T wave_max(T x, T none)
+{
+    // row_shr 1, 2, 4, 8: lane W - 1 of a row of 16 has lanes 0 .. W-1
+    x = max2(x, dpp<0x111, 0xf>(x, none));
+    if (W > 2) x = max2(x, dpp<0x112, 0xf>(x, none));
+    if (W > 4) x = max2(x, dpp<0x114, 0xf>(x, none));
+    if (W > 8) x = max2(x, dpp<0x118, 0xf>(x, none));
+    if (W <= 16) return lane_get(x, W - 1);
+    x = max2(x, dpp<0x142, 0xa>(x, none));   // row_bcast 15 and 31: lane 63 has all
+    x = max2(x, dpp<0x143, 0xc>(x, none));
+    return lane_get(x, 63);
+}
+
+// Order of the pivot search: |Re| + |Im| as an integer (the bits of a non-negative
+// float keep its order, a NaN comes above infinity) or as a double (a NaN counts as
+// infinite), so a NaN wins and is reported.
+RSRR_DEV int pivot_key(float a) { return __float_as_int(a) & 0x7fffffff; }
+RSRR_DEV double pivot_key(double a) { return a == a ? a : (double)INFINITY; }
+// (a, pa) before (b, pb): larger key, lower position on ties.
+RSRR_DEV bool pivot_before(int a, int pa, int b, int pb)
+{
+    return ((long long)a << 32 | (unsigned)~pa) > ((long long)b << 32 | (unsigned)~pb);
+}
+RSRR_DEV bool pivot_before(double a, int pa, double b, int pb) { return a > b || (a == b && pa < pb); }
+
+// The lane with the lowest pos among those of `lanes` (a ballot of hit, not empty; their
+// pos are distinct).  More than one is a tie of the pivot search, as between the zero
+// rows of a sparse column.
+template <int W> RSRR_DEV int lowest_lane(unsigned long long lanes, bool hit, int pos)
+{
+    if (lanes & (lanes - 1)) {
+        const int top = ~wave_max<W>(hit ? ~pos : INT_MIN, INT_MIN);
+        lanes &= __ballot(pos == top);
+    }
+    return __ffsll((long long)lanes) - 1;
+}
+
+// a - b c as four fused multiply-adds (the chain of the panel base is bound by the
+// number of instructions).
+template <typename C> RSRR_DEV C cfms_fused(C a, C b, C c)
+{
+    a.x = fma(-b.x, c.x, a.x);
+    a.y = fma(-b.x, c.y, a.y);
+    a.x = fma(b.y, c.y, a.x);
+    a.y = fma(-b.y, c.x, a.y);
+    return a;
+}
+RSRR_DEV float cfms_fused(float a, float b, float c) { return fmaf(-b, c, a); }
+
 template <typename C, int NT, int RPT, int JB>
-__global__ __launch_bounds__(NT) void panel_base_kernel(
+__global__ __launch_bounds__(NT) void panel_lu_kernel(
     C* __restrict__ A, long sA, int lda, int n, int c0, int jb,
-    int* __restrict__ ipiv, long sP, int* __restrict__ info, const int* __restrict__ active)
+    int* __restrict__ ipiv, long sP, int* __restrict__ info, int2* __restrict__ perm, long sPerm,
+    const int* __restrict__ active)
 {
     typedef real_t<C> R;
+    typedef decltype(pivot_key(R())) Key;
+    constexpr Key none = sizeof(Key) == 4 ? (Key)INT_MIN : (Key)-1;   // below every key
+    constexpr int NW = NT / 64;
+    constexpr int GW = JB < 8 ? JB : 8, NG = JB / GW;
+    static_assert(NW == 4 || NW == 8 || NW == 16, "the winner is picked inside one row of 16 lanes");
+    static_assert(JB % GW == 0 && GW % 2 == 0 && JB <= 64, "whole groups; the buffer parity is fixed per unrolled column");
     const int b = blockIdx.x;
     if (active && !active[b]) return;
     C* Ab = A + (long)b * sA;
@@ -42,17 +143,21 @@ __global__ __launch_bounds__(NT) void panel_base_kernel(
     const int m = n - c0;
     const int tid = threadIdx.x;
     const int lane = tid & 63, wave = tid >> 6;
-    constexpr int NW = NT / 64;
 
-    __shared__ R red_v[NW];
-    __shared__ int red_i[NW];
-    __shared__ int s_piv;
-    __shared__ C prow[JB], crow[JB];
+    struct __attribute__((aligned(16))) Cand { Key key; int pos; C piv; };
+    __shared__ Cand cand[2][NW];
+    __shared__ __attribute__((aligned(16))) C rows[2][NW][GW];      // the candidates' rows, this group's columns
+    __shared__ __attribute__((aligned(16))) C U[GW][JB];            // the group's pivot rows, the columns after it
+    __shared__ C Lg[GW][GW];                                        // and their multipliers
+    __shared__ int spiv[JB];   // pivot positions and values, looked at after the loop
+    __shared__ C sval[JB];
 
     C v[RPT][JB];
+    int pos[RPT];   // position of the row after the interchanges so far; -1: no row
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int lr = tid + NT * q;
+        pos[q] = lr < m ? lr : -1;
 #pragma unroll
         for (int c = 0; c < JB; ++c) {
             C e = czero<C>();
@@ -61,103 +166,165 @@ __global__ __launch_bounds__(NT) void panel_base_kernel(
         }
     }
 
+    const int ngrp = (jb + GW - 1) / GW;
+#pragma unroll 1
+    for (int g = 0; g < NG; ++g) {
 #pragma unroll
-    for (int c = 0; c < JB; ++c) {
-        if (c >= jb) break;
-        // ---- pivot search: per-thread, wavefront shuffle, then LDS ----
-        R best = (R)-1;
-        int bi = INT_MAX;
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            const int lr = tid + NT * q;
-            if (lr >= c && lr < m) {
-                R a = cabs1(v[q][c]);
-                if (a != a) a = (R)INFINITY;  // a NaN wins, so it is reported
-                if (a > best) { best = a; bi = lr; }
-            }
-        }
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) {
-            R ob = __shfl_xor(best, off);
-            int oi = __shfl_xor(bi, off);
-            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-        }
-        if (lane == 0) { red_v[wave] = best; red_i[wave] = bi; }
-        __syncthreads();
-        if (wave == 0) {
-            R bb = lane < NW ? red_v[lane] : (R)-1;
-            int ii = lane < NW ? red_i[lane] : INT_MAX;
-#pragma unroll
-            for (int off = 32; off >= 1; off >>= 1) {
-                R ob = __shfl_xor(bb, off);
-                int oi = __shfl_xor(ii, off);
-                if (ob > bb || (ob == bb && oi < ii)) { bb = ob; ii = oi; }
-            }
-            if (lane == 0) s_piv = (ii == INT_MAX) ? c : ii;
-        }
-        __syncthreads();
-        const int p = s_piv;
-        // ---- interchange rows c and p (panel columns only) ----
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            const int lr = tid + NT * q;
-            if (lr == p) {
-#pragma unroll
-                for (int cc = 0; cc < JB; ++cc) prow[cc] = v[q][cc];
-            }
-            if (lr == c) {
-#pragma unroll
-                for (int cc = 0; cc < JB; ++cc) crow[cc] = v[q][cc];
-            }
-        }
-        __syncthreads();
-        if (p != c) {
+        for (int c8 = 0; c8 < GW; ++c8) {
+            const int c = g * GW + c8;
+            if (c >= jb) break;
+            const int buf = c8 & 1;
+            // ---- candidate of the thread, then of the wave (lowest position on ties) ----
+            Key bk = none;
+            int bp = INT_MAX;
+            C bv = czero<C>();
 #pragma unroll
             for (int q = 0; q < RPT; ++q) {
-                const int lr = tid + NT * q;
-                if (lr == c) {
+                const Key a = pos[q] >= c ? pivot_key(cabs1(v[q][c8])) : none;
+                if (q == 0 || pivot_before(a, pos[q], bk, bp)) { bk = a; bp = pos[q]; bv = v[q][c8]; }
+            }
+            const Key wk = wave_max<64>(bk, none);
+            if (wk == none) {   // every row of the wave is done or absent
+                if (lane == 0) cand[buf][wave] = {none, INT_MAX, czero<C>()};
+            } else if (lane == lowest_lane<64>(__ballot(bk == wk), bk == wk, bp)) {
+                cand[buf][wave] = {wk, bp, bv};
 #pragma unroll
-                    for (int cc = 0; cc < JB; ++cc) v[q][cc] = prow[cc];
+                for (int q = 0; q < RPT; ++q)
+                    if (RPT == 1 || pos[q] == bp) {
+#pragma unroll
+                        for (int j = 0; j < GW; ++j)
+                            if (j > c8) rows[buf][wave][j] = v[q][j];
+                    }
+            }
+            __syncthreads();
+            const Cand ca = cand[buf][lane & (NW - 1)];
+            const Key gk = wave_max<NW>(ca.key, none);   // at least one row is left: gk != none
+            const int win = lowest_lane<NW>(__ballot(ca.key == gk) & ((1ull << NW) - 1), ca.key == gk, ca.pos);
+            C u[GW];
+#pragma unroll
+            for (int j = 0; j < GW; ++j)
+                if (j > c8) u[j] = rows[buf][win][j];
+            const int p = lane_get(ca.pos, win);
+            const C piv = lane_get(ca.piv, win);
+            const bool zero = is_zero(piv);
+            if (tid == 0) { spiv[c] = p; sval[c] = piv; }
+            const C rp = zero ? czero<C>() : crecip_scaled(piv);
+            // ---- the interchange, the multipliers and the group's columns right of c ----
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                pos[q] = pos[q] == p ? c : (pos[q] == c ? p : pos[q]);
+                if (pos[q] > c) {
+                    if (!zero) v[q][c8] = cmul(v[q][c8], rp);
+#pragma unroll
+                    for (int j = 0; j < GW; ++j)
+                        if (j > c8) v[q][j] = cfms_fused(v[q][j], v[q][c8], u[j]);
                 }
-                if (lr == p) {
+            }
+        }
+        if (NG > 1 && g + 1 < ngrp) {
+            // ---- the columns after the group: its pivot rows U = L11^-1 A, then the rank-GW update ----
+            const int left = (ngrp - g - 1) * GW, first = g * GW;
 #pragma unroll
-                    for (int cc = 0; cc < JB; ++cc) v[q][cc] = crow[cc];
+            for (int q = 0; q < RPT; ++q) {
+                const int i = pos[q] - first;
+                if (i >= 0 && i < GW) {
+#pragma unroll
+                    for (int j = 0; j < GW; ++j) Lg[i][j] = v[q][j];
+#pragma unroll
+                    for (int j = 0; j < JB - GW; ++j)
+                        if (j < left) U[i][j] = v[q][GW + j];
+                }
+            }
+            __syncthreads();
+            if (tid < left) {
+                C x[GW];
+#pragma unroll
+                for (int i = 0; i < GW; ++i) x[i] = U[i][tid];
+#pragma unroll
+                for (int j = 0; j < GW; ++j)
+#pragma unroll
+                    for (int i = j + 1; i < GW; ++i) x[i] = cfms_fused(x[i], Lg[i][j], x[j]);
+#pragma unroll
+                for (int i = 0; i < GW; ++i) U[i][tid] = x[i];
+            }
+            __syncthreads();
+            // Few rows per thread: a done row's multipliers are set to zero, so that no branch lies
+            // between the reads of U and their uses.  More rows: no registers for the copies.
+            constexpr bool COPY = RPT * sizeof(C) < 32;
+            C l[COPY ? RPT : 1][GW];
+            if constexpr (COPY) {
+#pragma unroll
+                for (int q = 0; q < RPT; ++q)
+#pragma unroll
+                    for (int i = 0; i < GW; ++i) l[q][i] = pos[q] >= first + GW ? v[q][i] : czero<C>();
+            }
+#pragma unroll
+            for (int k = 1; k < NG; ++k)
+                if (k < ngrp - g) {
+#pragma unroll
+                    for (int i = 0; i < GW; ++i) {
+                        C u[GW];
+#pragma unroll
+                        for (int j = 0; j < GW; ++j) u[j] = U[i][(k - 1) * GW + j];
+#pragma unroll
+                        for (int q = 0; q < RPT; ++q) {
+                            if constexpr (COPY) {
+#pragma unroll
+                                for (int j = 0; j < GW; ++j)
+                                    v[q][k * GW + j] = cfms_fused(v[q][k * GW + j], l[q][i], u[j]);
+                            } else if (pos[q] >= first + GW) {
+#pragma unroll
+                                for (int j = 0; j < GW; ++j)
+                                    v[q][k * GW + j] = cfms_fused(v[q][k * GW + j], v[q][i], u[j]);
+                            }
+                        }
+                    }
+                }
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                const int i = pos[q] - first;
+                if (i >= 0 && i < GW) {
+#pragma unroll
+                    for (int j = 0; j < JB - GW; ++j)
+                        if (j < left) v[q][GW + j] = U[i][j];
                 }
             }
         }
-        const C piv = prow[c];
-        const bool zero = is_zero(piv);
-        const bool bad = !all_finite(piv);
-        if (tid == 0) {
-            pv[c0 + c] = c0 + p;
-            if (info[b] == 0) {
-                if (bad) info[b] = -(c0 + c + 1);
-                else if (zero) info[b] = c0 + c + 1;
+        if (NG > 1) {   // the finished group goes last; after NG turns every column is back in place
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                C t[GW];
+#pragma unroll
+                for (int j = 0; j < GW; ++j) t[j] = v[q][j];
+#pragma unroll
+                for (int j = 0; j < JB - GW; ++j) v[q][j] = v[q][j + GW];
+#pragma unroll
+                for (int j = 0; j < GW; ++j) v[q][JB - GW + j] = t[j];
             }
         }
-        const C rp = zero ? czero<C>() : crecip(piv);
-        // ---- scale the column and update the rest of the panel ----
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            const int lr = tid + NT * q;
-            if (lr > c && lr < m) {
-                if (!zero) v[q][c] = cmul(v[q][c], rp);
-                const C l = v[q][c];
-#pragma unroll
-                for (int cc = c + 1; cc < JB; ++cc)
-                    if (cc < jb) v[q][cc] = cfms(v[q][cc], l, prow[cc]);
-            }
-        }
-        __syncthreads();
+    }
+    __syncthreads();
+    if (tid < jb) pv[c0 + tid] = c0 + spiv[tid];
+    if (wave == 0) {   // the first zero or non-finite pivot
+        const C pz = lane < jb ? sval[lane] : from_real<C>((R)1);
+        const unsigned long long bad = __ballot(!all_finite(pz)), odd = bad | __ballot(is_zero(pz));
+        const int c = __ffsll((long long)odd) - 1;
+        if (odd && lane == 0 && info[b] == 0) info[b] = (bad >> c & 1) ? -(c0 + c + 1) : c0 + c + 1;
     }
 
+    int2* pm = perm ? perm + (long)b * sPerm : nullptr;
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int lr = tid + NT * q;
         if (lr < m) {
 #pragma unroll
             for (int c = 0; c < JB; ++c)
-                if (c < jb) Ab[(c0 + lr) + (long)(c0 + c) * lda] = v[q][c];
+                if (c < jb) Ab[(c0 + pos[q]) + (long)(c0 + c) * lda] = v[q][c];
+            // only the first jb rows can leave their place other than as a pivot: row lr owns slot jb + lr
+            if (pm) {
+                if (pos[q] < jb) pm[pos[q]] = make_int2(c0 + pos[q], c0 + lr);
+                if (lr < jb) pm[jb + lr] = pos[q] >= jb ? make_int2(c0 + pos[q], c0 + lr) : make_int2(-1, -1);
+            }
         }
     }
 }
@@ -267,12 +434,89 @@ RSRR_DEV void compose_perm_wave(const int* __restrict__ pv, int k1, int jb, int2
 }
 
 // ----------------------------------------------------------------------------
-// Row permutation + triangular solve on a block of columns.
-// X: rows indexed like the factored matrix (row r at X[r - xr0]); columns [0, ncols).
-// mode 0: permute only.  mode 1: permute, then X[c0:c0+jb] = L11^-1 X[...]
-// with L11 the unit-lower diagonal block of LU at (c0, c0).
+// A factored block [c0, c0+jb) (jb <= JB) of a panel [p0, p0+pw): its row
+// interchanges on the panel's other columns and, right of the block,
+// U = L11^-1 A (L11: the unit-lower triangle at (c0, c0)).  One launch for both
+// sides.  A column is a group of 2 JB lanes, one lane per affected row (top row
+// s, or the s-th displaced row), so a column's gather and scatter are one load
+// and one store and nothing is shared between waves; each top lane holds its row
+// of L11 in registers and the solve broadcasts x_l across the group.  PS_U
+// columns per group are in flight to cover the latency.
+// The composed interchanges come from the base kernel (perm) or, for a block of
+// several bases, are composed here from ipiv.
+// ----------------------------------------------------------------------------
+constexpr int PS_NT = 256, PS_U = 4, PS_MAX = 32;
+
+template <typename C, int JB>
+__global__ __launch_bounds__(PS_NT) void panel_swap_kernel(
+    C* __restrict__ A, long sA, int lda, const int2* __restrict__ perm, long sPerm, const int* __restrict__ ipiv,
+    long sP, int p0, int pw, int c0, int jb, const int* __restrict__ active)
+{
+    constexpr int G = 2 * JB, CW = 64 / G;   // lanes per column, columns side by side in a wave
+    const int b = blockIdx.y;
+    if (active && !active[b]) return;
+    C* Ab = A + (long)b * sA;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int s = lane % G, gb = lane - s;
+    __shared__ int2 pm[2 * JB];
+    const int2* pb = pm;
+    if (ipiv) {
+        if (wave == 0) compose_perm_wave(ipiv + (long)b * sP, c0, jb, pm);
+        __syncthreads();
+    } else {
+        pb = perm + (long)b * sPerm;
+    }
+    int2 e = make_int2(-1, -1);
+    if (s < jb) e = pb[s];
+    else if (s >= JB && s - JB < jb) e = pb[jb + s - JB];
+    const int nl = c0 - p0, ncols = pw - jb;
+    const int k0 = (blockIdx.x * (PS_NT / 64) + wave) * CW * PS_U + lane / G;
+    C x[PS_U], y[PS_U];
+    int col[PS_U];
+#pragma unroll
+    for (int u = 0; u < PS_U; ++u) {
+        const int k = k0 + u * CW;
+        col[u] = k >= ncols ? -1 : (k < nl ? p0 + k : c0 + jb + (k - nl));
+        x[u] = (col[u] >= 0 && e.y >= 0) ? Ab[e.y + (long)col[u] * lda] : czero<C>();
+        y[u] = x[u];
+    }
+    bool right = false;
+#pragma unroll
+    for (int u = 0; u < PS_U; ++u) right |= col[u] > c0;
+    if (__any(right)) {
+        C Lr[JB];
+#pragma unroll
+        for (int l = 0; l < JB; ++l)
+            Lr[l] = (l < s && s < jb) ? Ab[(c0 + s) + (long)(c0 + l) * lda] : czero<C>();
+#pragma unroll
+        for (int l = 0; l < JB - 1; ++l) {   // rows past jb are zero in Lr
+#pragma unroll
+            for (int u = 0; u < PS_U; ++u) {
+                C xl;
+                if constexpr (G == 64) xl = lane_get(y[u], l);
+                else xl = shfl_get(y[u], gb + l);
+                y[u] = cfms_fused(y[u], Lr[l], xl);
+            }
+        }
+    }
+    if (e.x >= 0) {
+#pragma unroll
+        for (int u = 0; u < PS_U; ++u)
+            if (col[u] >= 0) {
+                C o = x[u];
+                if (s < JB && col[u] > c0) o = y[u];
+                Ab[e.x + (long)col[u] * lda] = o;
+            }
+    }
+}
+
+// ----------------------------------------------------------------------------
+// Row permutation + triangular solve on a block of columns (the FP64 path
+// without diagonal-block inverses).
+// X: rows indexed like the factored matrix; columns [0, ncols).
+// mode 1: permute, then X[c0:c0+jb] = L11^-1 X[...] with L11 the unit-lower
+// diagonal block of LU at (c0, c0).
 // mode 2: no permutation, X[c0:c0+jb] = U11^-1 X[...] (non-unit upper).
-// mode 4 / 5: X[c0:c0+jb, 0:jb] = L11^-1 / U11^-1 (the solve applied to I).
 // ----------------------------------------------------------------------------
 constexpr int TS_NT = 256;
 
@@ -280,15 +524,14 @@ constexpr int TS_NT = 256;
 template <typename C, int MJB, int TC>
 __global__ __launch_bounds__(TS_NT) void perm_trsm_kernel(
     const C* __restrict__ LU, long sLU, int ldl,
-    const int2* __restrict__ perm, long sPerm, const int* __restrict__ ipiv, long sP,
-    C* __restrict__ X, long sX, int ldx, int xr0,
+    const int2* __restrict__ perm, long sPerm,
+    C* __restrict__ X, long sX, int ldx,
     int c0, int jb, int ncols, int mode, const int* __restrict__ active)
 {
-    typedef real_t<C> R;
     const int b = blockIdx.y;
     if (active && !active[b]) return;
     const C* Lb = LU + (long)b * sLU;
-    C* Xb = X + (long)b * sX - xr0;
+    C* Xb = X + (long)b * sX;
     const int tid = threadIdx.x;
     const int col = tid % TC, grp = tid / TC;
     constexpr int NG = TS_NT / TC;
@@ -299,26 +542,18 @@ __global__ __launch_bounds__(TS_NT) void perm_trsm_kernel(
     __shared__ C Ld[MJB][MJB + 1];
     __shared__ int2 pm[2 * MJB];
 
-    const bool permute = mode == 0 || mode == 1;
-    if (permute) {
-        if (ipiv) {
-            // composed here from the interchanges ipiv[c0 .. c0+jb) (uniform branch)
-            if (tid < 64) compose_perm_wave(ipiv + (long)b * sP, c0, jb, pm);
-        } else {
-            const int2* pb = perm + (long)b * sPerm;
-            for (int s = tid; s < 2 * jb; s += TS_NT) pm[s] = pb[s];
-        }
+    if (mode == 1) {
+        const int2* pb = perm + (long)b * sPerm;
+        for (int s = tid; s < 2 * jb; s += TS_NT) pm[s] = pb[s];
     }
-    if (mode != 0) {
-        // triangle into LDS (column-major read, coalesced along rows)
-        for (int e = tid; e < jb * jb; e += TS_NT) {
-            const int r = e % jb, c = e / jb;
-            Ld[r][c] = Lb[(c0 + r) + (long)(c0 + c) * ldl];
-        }
+    // triangle into LDS (column-major read, coalesced along rows)
+    for (int e = tid; e < jb * jb; e += TS_NT) {
+        const int r = e % jb, c = e / jb;
+        Ld[r][c] = Lb[(c0 + r) + (long)(c0 + c) * ldl];
     }
     __syncthreads();
 
-    if (permute) {
+    if (mode == 1) {
         // gather every affected row (reads first, writes after the barrier)
         constexpr int MAXQ = (2 * MJB + NG - 1) / NG;
         C val[MAXQ];
@@ -343,21 +578,19 @@ __global__ __launch_bounds__(TS_NT) void perm_trsm_kernel(
                 if (dst >= 0) Xb[dst + (long)gcol * ldx] = val[q];
             }
         }
-    } else if (mode >= 4) {
-        for (int s = grp; s < jb; s += NG) top[s][col] = from_real<C>((R)(s == gcol ? 1 : 0));
     } else {
         for (int s = grp; s < jb; s += NG)
             top[s][col] = colok ? Xb[(c0 + s) + (long)gcol * ldx] : czero<C>();
     }
     __syncthreads();
 
-    if (mode == 1 || mode == 4) {
+    if (mode == 1) {
         for (int l = 0; l < jb; ++l) {
             const C xl = top[l][col];
             for (int i = l + 1 + grp; i < jb; i += NG) top[i][col] = cfms(top[i][col], Ld[i][l], xl);
             __syncthreads();
         }
-    } else if (mode == 2 || mode == 5) {
+    } else {
         for (int l = jb - 1; l >= 0; --l) {
             if (grp == 0) {
                 const C d = Ld[l][l];
@@ -428,63 +661,85 @@ __global__ __launch_bounds__(2 * MAX_NB) void perm_rows_kernel(
 // host drivers
 // ----------------------------------------------------------------------------
 
-// Base width of the register-resident panel kernel for m rows.
-template <typename R> static int base_width(int m);
-template <> int base_width<float>(int m) { return m <= 4096 ? 8 : 4; }
-template <> int base_width<double>(int m) { return m <= 2048 ? 8 : (m <= 4096 ? 4 : 2); }
-
-template <typename C, int NT, int RPT, int JB>
-static void launch_base(hipStream_t st, C* A, long sA, int lda, int n, int c0, int jb,
-                        int* ipiv, long sP, int* info, const int* active, int batch)
+// Base width of the register-resident panel kernel for m rows: as many columns
+// as the registers hold (32 at most: the blocks of the panel are that wide).
+template <typename C> static int base_width(int m)
 {
-    hipLaunchKernelGGL((panel_base_kernel<C, NT, RPT, JB>), dim3(batch), dim3(NT), 0, st,
-                       A, sA, lda, n, c0, jb, ipiv, sP, info, active);
+    constexpr int words = sizeof(C) / 4;   // registers per element
+    if (m <= 512) return 32;
+    if (words == 4) return m <= 1024 ? 16 : (m <= 2048 ? 8 : (m <= 4096 ? 4 : 2));
+    if (words == 2) return m <= 1024 ? 32 : (m <= 2048 ? 16 : (m <= 4096 ? 8 : 4));
+    return m <= 2048 ? 32 : (m <= 4096 ? 16 : 8);
 }
 
 template <typename C>
-static void panel_base(hipStream_t st, C* A, long sA, int lda, int n, int c0, int jb,
-                       int* ipiv, long sP, int* info, const int* active, int batch)
+static void panel_lu(hipStream_t st, C* A, long sA, int lda, int n, int c0, int jb,
+                     int* ipiv, long sP, int* info, int2* perm, long sPerm, const int* active, int batch)
 {
-    typedef real_t<C> R;
+    constexpr int words = sizeof(C) / 4;
     const int m = n - c0;
-#define PB(NT, RPT, JB) launch_base<C, NT, RPT, JB>(st, A, sA, lda, n, c0, jb, ipiv, sP, info, active, batch)
-    if (m <= 256) {
-        PB(256, 1, 8);
-    } else if (m <= 512) {
-        PB(256, 2, 8);
-    } else if (m <= 1024) {
-        PB(256, 4, 8);
-    } else if (m <= 2048) {
-        PB(1024, 2, 8);
-    } else if (m <= 4096) {
-        if (sizeof(R) == 4) PB(1024, 4, 8); else PB(1024, 4, 4);
+#define PL(NT, RPT, JB)                                                                                       \
+    hipLaunchKernelGGL((panel_lu_kernel<C, NT, RPT, JB>), dim3(batch), dim3(NT), 0, st, A, sA, lda, n, c0, jb, \
+                       ipiv, sP, info, perm, sPerm, active)
+    // RPT rows per thread against NT threads: measured per column for each range of m (us, 48
+    // matrices); more threads repeat the search in more waves, more rows lengthen the update
+    if constexpr (words == 4) {
+        if (m <= 256) PL(256, 1, 32);         // 1.2
+        else if (m <= 512) PL(512, 1, 32);    // 1.5
+        else if (m <= 1024) PL(512, 2, 16);   // 1.8
+        else if (m <= 2048) PL(1024, 2, 8);   // 2.6
+        else if (m <= 4096) PL(1024, 4, 4);   // 3.9
+        else PL(1024, 8, 2);                  // 6.2
+    } else if constexpr (words == 2) {
+        if (m <= 256) PL(256, 1, 32);         // 0.9
+        else if (m <= 512) PL(512, 1, 32);    // 1.1 (two rows of 256 threads 1.2)
+        else if (m <= 1024) PL(512, 2, 32);   // 1.5
+        else if (m <= 2048) PL(512, 4, 16);   // 2.0
+        else if (m <= 4096) PL(1024, 4, 8);   // 2.9 (eight rows of 512 threads 3.6)
+        else PL(1024, 8, 4);                  // 4.4
     } else {
-        if (sizeof(R) == 4) PB(1024, 8, 4); else PB(1024, 8, 2);
+        if (m <= 256) PL(256, 1, 32);         // 0.7
+        else if (m <= 512) PL(256, 2, 32);    // 0.9
+        else if (m <= 1024) PL(512, 2, 32);   // 1.0 (four rows of 256 threads 1.25)
+        else if (m <= 2048) PL(512, 4, 32);   // 1.5
+        else if (m <= 4096) PL(512, 8, 16);   // 2.3
+        else PL(1024, 8, 8);                  // 2.9
     }
-#undef PB
+#undef PL
 }
 
-// perm: composed interchanges of rows c0 .. c0+jb (perm_build), or nullptr with ipiv
-// given: composed inside the kernel from ipiv[c0 .. c0+jb).
+// Interchanges of the factored block [c0, c0+jb) on the other columns of the panel
+// [p0, p0+pw) and U = L11^-1 A right of it.  perm: composed by the base kernel, or
+// nullptr: composed in the kernel from ipiv.
 template <typename C>
-static void perm_trsm(hipStream_t st, const C* LU, long sLU, int ldl, const int2* perm, long sPerm,
-                      C* X, long sX, int ldx, int c0, int jb, int ncols, int mode,
-                      const int* active, int batch, int xr0 = 0, const int* ipiv = nullptr, long sP = 0)
+static void panel_swap(hipStream_t st, C* A, long sA, int lda, const int2* perm, long sPerm, const int* ipiv,
+                       long sP, int p0, int pw, int c0, int jb, const int* active, int batch)
 {
-    typedef real_t<C> R;
+    const int ncols = pw - jb;
+    if (ncols <= 0) return;
+    if (perm) ipiv = nullptr;
+#define PSW(JB)                                                                                                \
+    do {                                                                                                       \
+        constexpr int per = (PS_NT / 64) * (64 / (2 * JB)) * PS_U;                                             \
+        hipLaunchKernelGGL((panel_swap_kernel<C, JB>), dim3((ncols + per - 1) / per, batch), dim3(PS_NT), 0,   \
+                           st, A, sA, lda, perm, sPerm, ipiv, sP, p0, pw, c0, jb, active);                     \
+    } while (0)
+    if (jb <= 8) PSW(8);
+    else if (jb <= 16) PSW(16);
+    else PSW(32);
+#undef PSW
+}
+
+// FP64 path without diagonal-block inverses (panels of at most 64 columns).
+static void perm_trsm(hipStream_t st, const double2* LU, long sLU, int ldl, const int2* perm, long sPerm,
+                      double2* X, long sX, int ldx, int c0, int jb, int ncols, int mode,
+                      const int* active, int batch)
+{
     if (ncols <= 0 || jb <= 0) return;
-    if (jb <= 64) {
-        constexpr int TC = 32;
-        dim3 g((ncols + TC - 1) / TC, batch);
-        hipLaunchKernelGGL((perm_trsm_kernel<C, 64, TC>), g, dim3(TS_NT), 0, st, LU, sLU, ldl, perm, sPerm, ipiv, sP,
-                           X, sX, ldx, xr0, c0, jb, ncols, mode, active);
-    } else {
-        constexpr int MJB = max_panel<R>();
-        constexpr int TC = 16;
-        dim3 g((ncols + TC - 1) / TC, batch);
-        hipLaunchKernelGGL((perm_trsm_kernel<C, MJB, TC>), g, dim3(TS_NT), 0, st, LU, sLU, ldl, perm, sPerm, ipiv, sP,
-                           X, sX, ldx, xr0, c0, jb, ncols, mode, active);
-    }
+    constexpr int TC = 32;
+    dim3 g((ncols + TC - 1) / TC, batch);
+    hipLaunchKernelGGL((perm_trsm_kernel<double2, 64, TC>), g, dim3(TS_NT), 0, st, LU, sLU, ldl, perm, sPerm,
+                       X, sX, ldx, c0, jb, ncols, mode, active);
 }
 
 template <typename C>
@@ -526,33 +781,39 @@ hipError_t gemm_sub<float>(hipStream_t st, int M, int N, int K, const float* A, 
     return sgemm(st, M, N, K, (float)-alpha, A, lda, sA, B, ldb, sB, (float)beta, Cm, ldc, sC, batch, tag);
 }
 
-// Recursive panel factorisation of columns [c0, c0+w) (rows c0..n-1).
+// C -= A21 U12 right of a factored block, inside the panel: rows below the block.
+template <typename C>
+static void panel_update(hipStream_t st, C* A, long sA, int lda, int n, int c0, int jb, int cend, int batch)
+{
+    const int c1 = c0 + jb;
+    if (c1 >= cend || c1 >= n) return;
+    (void)gemm_sub<C>(st, n - c1, cend - c1, jb, A + c1 + (long)c0 * lda, lda, sA, A + c0 + (long)c1 * lda, lda, sA,
+                      A + c1 + (long)c1 * lda, lda, sA, batch);
+}
+
+// Panel factorisation of columns [c0, c0+w) (rows c0..n-1): blocks of PS_MAX
+// columns, each a single base or, where the base is narrower, several bases, both
+// levels right-looking (block, interchanges and U rows in one launch, update).
+// pm: 2*MAX_NB int2 per matrix (stride sPm) as scratch for a base's interchanges.
 template <typename C>
 static void factor_panel(hipStream_t st, C* A, long sA, int lda, int n, int c0, int w,
-                         int* ipiv, long sP, int* info, const int* active,
+                         int* ipiv, long sP, int* info, int2* pm, long sPm, const int* active,
                          int batch)
 {
-    typedef real_t<C> R;
-    const int m = n - c0;
-    const int jbase = base_width<R>(m);
-    if (w <= jbase) {
-        panel_base<C>(st, A, sA, lda, n, c0, w, ipiv, sP, info, active, batch);
-        return;
+    for (int b0 = c0; b0 < c0 + w; b0 += PS_MAX) {
+        const int bw = std::min(PS_MAX, c0 + w - b0);
+        const int base = base_width<C>(n - b0);
+        for (int s0 = b0; s0 < b0 + bw; s0 += base) {
+            const int sw = std::min(base, b0 + bw - s0);
+            panel_lu<C>(st, A, sA, lda, n, s0, sw, ipiv, sP, info, pm, sPm, active, batch);
+            if (bw > base) {
+                panel_swap<C>(st, A, sA, lda, pm, sPm, ipiv, sP, b0, bw, s0, sw, active, batch);
+                panel_update<C>(st, A, sA, lda, n, s0, sw, b0 + bw, batch);
+            }
+        }
+        panel_swap<C>(st, A, sA, lda, bw <= base ? pm : nullptr, sPm, ipiv, sP, c0, w, b0, bw, active, batch);
+        panel_update<C>(st, A, sA, lda, n, b0, bw, c0 + w, batch);
     }
-    int w1 = (w / 2) / jbase * jbase;
-    if (w1 < jbase) w1 = jbase;
-    const int w2 = w - w1;
-    factor_panel<C>(st, A, sA, lda, n, c0, w1, ipiv, sP, info, active, batch);
-    // right half: interchanges of the left half (composed inside the solve kernel),
-    // U12 = L11^-1 A12, A22 -= L21 U12
-    C* Ar = A + (long)(c0 + w1) * lda;
-    perm_trsm<C>(st, A, sA, lda, nullptr, 0, Ar, sA, lda, c0, w1, w2, 1, active, batch, 0, ipiv, sP);
-    (void)gemm_sub<C>(st, m - w1, w2, w1, A + (c0 + w1) + (long)c0 * lda, lda, sA, A + c0 + (long)(c0 + w1) * lda, lda, sA,
-                A + (c0 + w1) + (long)(c0 + w1) * lda, lda, sA, batch);
-    factor_panel<C>(st, A, sA, lda, n, c0 + w1, w2, ipiv, sP, info, active, batch);
-    // left half receives the interchanges of the right half
-    perm_trsm<C>(st, A, sA, lda, nullptr, 0, A + (long)c0 * lda, sA, lda, c0 + w1, w2, w1, 0, active, batch, 0, ipiv,
-                 sP);
 }
 
 // Diagonal-block inverses of panel p (complex-FP32 path): L11^-1 at
@@ -757,8 +1018,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     };
     // panel p on stream s: factor, composed interchanges, diagonal-block inverses (FP32 paths)
     auto panel = [&](hipStream_t s, int c0, int jb, int p) -> int2* {
-        factor_panel<C>(s, A, sA, lda, n, c0, jb, w.ipiv, w.sP, w.info, w.active, batch);
         int2* pm = w.perm + (long)p * 2 * MAX_NB;
+        factor_panel<C>(s, A, sA, lda, n, c0, jb, w.ipiv, w.sP, w.info, pm, w.sPerm, w.active, batch);
         hipLaunchKernelGGL(perm_build_kernel, dim3(batch), dim3(64), 0, s, w.ipiv, w.sP, c0, jb, pm, w.sPerm,
                            w.active);
         if (use_inv) tri_inv<C>(s, A, sA, lda, c0, jb, (C*)w.inv, w.sInv, nb, w.active, batch);
@@ -874,7 +1135,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
                 (void)gemm_sub<C>(st, jb0, rest0, jb0, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
                                   w.sTmp, Ar + c0, lda, sA, batch, 0, -1.0, 0.0);
             } else {
-                perm_trsm<C>(st, A, sA, lda, pm0, w.sPerm, Ar, sA, lda, c0, jb0, rest0, 1, w.active, batch);
+                if constexpr (sizeof(C) == sizeof(double2))
+                    perm_trsm(st, A, sA, lda, pm0, w.sPerm, Ar, sA, lda, c0, jb0, rest0, 1, w.active, batch);
             }
             if (c0 == 0 && w.first_panel) (void)hipEventRecord(w.first_panel, st);
         }
@@ -932,7 +1194,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
             (void)gemm_sub<C>(st, jb, nrhs, jb, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
                               X + c0, ldx, sX, batch, 0, -1.0, 0.0);
         } else {
-            perm_trsm<C>(st, LU, sLU, lda, pm, w.sPerm, X, sX, ldx, c0, jb, nrhs, 1, w.active, batch);
+            if constexpr (sizeof(C) == sizeof(double2))
+                perm_trsm(st, LU, sLU, lda, pm, w.sPerm, X, sX, ldx, c0, jb, nrhs, 1, w.active, batch);
         }
         const int rest = n - c0 - jb;
         if (rest > 0)
@@ -950,7 +1213,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
             (void)gemm_sub<C>(st, jb, nrhs, jb, panel_inv<C>(w, p, nb, 1), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
                               X + c0, ldx, sX, batch, 0, -1.0, 0.0);
         } else {
-            perm_trsm<C>(st, LU, sLU, lda, nullptr, 0, X, sX, ldx, c0, jb, nrhs, 2, w.active, batch);
+            if constexpr (sizeof(C) == sizeof(double2))
+                perm_trsm(st, LU, sLU, lda, nullptr, 0, X, sX, ldx, c0, jb, nrhs, 2, w.active, batch);
         }
     };
     for (int p = np - 1; p >= 0;) {
