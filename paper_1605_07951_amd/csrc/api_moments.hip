@@ -7,12 +7,14 @@
 // factor divided by the capacity C (the scaling Sec. 3.3 recommends against
 // under- and overflow).  For a fixed probe column l the blocks form an
 // n x N matrix (stride L lds between points) and M's columns alpha L + l an
-// n x K matrix, so M is one batched FP64 MFMA GEMM over the L probe columns
-// with the small N x K table c^T as the right operand.  The table is formed
-// on the device (one thread per point) from the points copied next to it.
+// n x K matrix: a batch of L products with the small N x K table c^T as the
+// right operand.  At most 32 moments: one stream over S (moments_stream_kernel);
+// more: one batched FP64 MFMA GEMM.  The table is formed on the device (one
+// wavefront per point) from the points copied next to it.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -33,31 +35,82 @@ namespace {
 std::mutex g_scratch_mu;
 std::vector<double2*> g_scratch_ptr;  // by device ordinal
 
-// c_{alpha,i} = omega_i zeta_i^alpha (column alpha, ld N), zeta_i = (z_i - gamma)/rho,
-// log omega_i = -sum_{j != i} log((zeta_i - zeta_j)/C): one thread per point.
-__global__ __launch_bounds__(256) void moment_weights_kernel(const double2* __restrict__ z, int N, int K, double gre,
-                                                             double gim, double rho, double cap,
-                                                             double2* __restrict__ cw)
+// c_{alpha,i} = omega_i zeta_i^alpha at cw[i si + alpha sa], zeta_i = (z_i - gamma)/rho,
+// log omega_i = -sum_{j != i} log((zeta_i - zeta_j)/C): one wavefront per point, its
+// lanes over j (the logarithms and angles of a point one after the other in one
+// thread took 30 us at N = 64).
+__global__ __launch_bounds__(64) void moment_weights_kernel(const double2* __restrict__ z, int N, int K, double gre,
+                                                            double gim, double rho, double cap,
+                                                            double2* __restrict__ cw, int si, int sa)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= N) return;
+    const int i = blockIdx.x;
     const double2 zi = make_double2((z[i].x - gre) / rho, (z[i].y - gim) / rho);
     double lr = 0.0, li = 0.0;
-    for (int j = 0; j < N; ++j) {
+    for (int j = threadIdx.x; j < N; j += 64) {
         if (j == i) continue;
         const double2 zj = make_double2((z[j].x - gre) / rho, (z[j].y - gim) / rho);
         const double dx = (zi.x - zj.x) / cap, dy = (zi.y - zj.y) / cap;
         lr -= log(hypot(dx, dy));
         li -= atan2(dy, dx);
     }
+    for (int off = 32; off >= 1; off >>= 1) {
+        lr += __shfl_xor(lr, off);
+        li += __shfl_xor(li, off);
+    }
+    if (threadIdx.x != 0) return;
     double sn, cs;
     sincos(li, &sn, &cs);
     const double m = exp(lr);
     double2 w = make_double2(m * cs, m * sn);
     for (int a = 0; a < K; ++a) {
-        cw[(long)a * N + i] = w;
+        cw[(long)i * si + (long)a * sa] = w;
         w = cmul(w, zi);
     }
+}
+
+// M = S Z for KC of the K moments: a thread per (row, probe column) walks the N
+// points, reads S once, coalesced along the rows, and keeps its KC sums in registers;
+// the coefficients (cw, N x K with the moment fastest) are the same for every lane
+// and come through the scalar cache.  Bound by the stream over S: n = 4096, N = L = 64,
+// K = 16 (335 MB) 178 us as a GEMM, whose 64-wide tiles left three quarters of the
+// matrix core's columns empty, 72 us (4.7 TB/s) here.
+constexpr int MS_NT = 256;
+template <int KC>
+__global__ __launch_bounds__(MS_NT) void moments_stream_kernel(int n, int N, int L, const double2* __restrict__ S,
+                                                               int lds, const double2* __restrict__ cw, int K,
+                                                               double2* __restrict__ M, int ldm)
+{
+    const int row = blockIdx.x * MS_NT + threadIdx.x, l = blockIdx.y, a0 = blockIdx.z * KC;
+    if (row >= n) return;
+    const double2* s = S + row + (long)l * lds;
+    const long step = (long)L * lds;
+    double2 acc[KC];
+#pragma unroll
+    for (int a = 0; a < KC; ++a) acc[a] = make_double2(0.0, 0.0);
+    auto add = [&](int i, auto whole) {
+        const double2 v = s[i * step];
+        const double2* c = cw + (long)i * K + a0;
+#pragma unroll
+        for (int a = 0; a < KC; ++a) {
+            const double2 w = c[decltype(whole)::value ? a : min(a, K - 1 - a0)];
+            acc[a].x = fma(w.x, v.x, acc[a].x);
+            acc[a].y = fma(w.x, v.y, acc[a].y);
+            acc[a].x = fma(-w.y, v.y, acc[a].x);
+            acc[a].y = fma(w.y, v.x, acc[a].y);
+        }
+    };
+    // whole chunks of moments read their coefficients as one block
+    if (a0 + KC <= K) {
+#pragma unroll 8
+        for (int i = 0; i < N; ++i) add(i, std::true_type{});
+    } else {
+#pragma unroll 2
+        for (int i = 0; i < N; ++i) add(i, std::false_type{});
+    }
+    double2* m = M + row + (long)l * ldm;
+#pragma unroll
+    for (int a = 0; a < KC; ++a)
+        if (a0 + a < K) m[(long)(a0 + a) * L * ldm] = acc[a];
 }
 
 rsrr_status check_args(rsrr_ctx* c, int n, int N, int L, const double* S, int lds, const double* z,
@@ -89,12 +142,26 @@ rsrr_status moments_run(rsrr_ctx* c, int n, int N, int L, const double* S, int l
     double2* zd_ = work;
     double2* cw = work + N;
     RSRR_HIP(hipMemcpyAsync(zd_, z, (size_t)N * 16, hipMemcpyHostToDevice, c->stream));
-    hipLaunchKernelGGL(moment_weights_kernel, dim3((N + 255) / 256), dim3(256), 0, c->stream, zd_, N, K, gamma[0],
-                       gamma[1], rho, capacity, cw);
+    // Up to 32 moments: the stream (S read once per 16 of them); more: the GEMM, whose tiles are
+    // then at least half used.  The grid of the stream has the probe columns in y.
+    const bool stream = K <= 32 && L <= 65535;
+    hipLaunchKernelGGL(moment_weights_kernel, dim3(N), dim3(64), 0, c->stream, zd_, N, K, gamma[0], gamma[1], rho,
+                       capacity, cw, stream ? K : 1, stream ? 1 : N);
     RSRR_HIP(hipGetLastError());
-    // batch l: A = S + l lds (n x N, ld L lds), C = M + l ldm (n x K, ld L ldm)
-    RSRR_HIP(zgemm(c->stream, 0, 0, n, K, N, 1.0, (const double2*)S, L * lds, lds, cw, N, 0, 0.0, (double2*)M,
-                   L * ldm, ldm, L));
+    if (stream) {
+#define MS_L(KC)                                                                                                   \
+    hipLaunchKernelGGL(moments_stream_kernel<KC>, dim3((n + MS_NT - 1) / MS_NT, L, (K + KC - 1) / KC), dim3(MS_NT), \
+                       0, c->stream, n, N, L, (const double2*)S, lds, cw, K, (double2*)M, ldm)
+        if (K <= 4) MS_L(4);
+        else if (K <= 8) MS_L(8);
+        else MS_L(16);
+#undef MS_L
+        RSRR_HIP(hipGetLastError());
+    } else {
+        // batch l: A = S + l lds (n x N, ld L lds), C = M + l ldm (n x K, ld L ldm)
+        RSRR_HIP(zgemm(c->stream, 0, 0, n, K, N, 1.0, (const double2*)S, L * lds, lds, cw, N, 0, 0.0, (double2*)M,
+                       L * ldm, ldm, L));
+    }
     RSRR_HIP(hipStreamSynchronize(c->stream));
     return RSRR_OK;
 }

@@ -63,3 +63,17 @@ def test_moment_variant_of_ssrr(R, ctx):
     assert ins.sum() == oin.size == 32
     assert _match(out["lam"][ins], oin) < 1e-9 and _match(oin, out["lam"][ins]) < 1e-9
     assert _match(out["lam"][ins], P.qep_roots(nep.extra["c"], nep.extra["k"])) < 1e-9
+
+
+@pytest.mark.parametrize("K", [1, 4, 5, 8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("n", [1, 255, 257])
+def test_moments_stream_and_gemm_edges(R, ctx, n, K):
+    """Both sides of the row blocks and of the moment counts per pass; above 32 moments the GEMM."""
+    N, L = 40, 3
+    rng = np.random.default_rng(n + K)
+    Sh = rng.standard_normal((n, N * L)) + 1j * rng.standard_normal((n, N * L))
+    z, _ = R.rsrr_contour(1.0 + 2.0j, 1.5, 0.8, N)
+    cap = (1.5 + 0.8) / (2 * 1.5)
+    M = R.from_colmajor(R.rsrr_moments(ctx, R.colmajor(Sh)[0], n, z, L, K, 1.0 + 2.0j, 1.5, cap), n)
+    Mo = O.moments(Sh, z, L, K, 1.0 + 2.0j, 1.5, cap)
+    assert np.linalg.norm(M - Mo) <= 1e-13 * np.linalg.norm(Mo)
