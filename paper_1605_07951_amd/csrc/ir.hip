@@ -1,6 +1,8 @@
 // Element-wise and reduction kernels of the mixed-precision refinement
 // (complex FP32 solves, FP64 residuals) and of the probe/solution copies.
 // All operate on a batch of n x L column blocks (stride per point).
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -278,92 +280,183 @@ __global__ __launch_bounds__(EW_NT) void ir_decide_kernel(int M, int Lmax, const
 }
 
 
-// R_b = U_b - T_b X_b in FP64 for at most RS_LC right-hand sides: the product is
-// skinny, so it is a stream over T (HBM bound) rather than an MFMA GEMM.  One
-// workgroup per RW * RPT rows of one matrix; a chunk of 64 rows of X is staged
-// in LDS and read by broadcast; each thread keeps the L sums of its RPT rows
-// (rows threadIdx.x + r RW, so every load of T stays coalesced) in registers
-// and walks k in order (deterministic).  With RPT rows per thread one
-// broadcast read of X(k, c) serves RPT loads of T: at L = 8 and above the
-// broadcast reads would otherwise use as much LDS bandwidth as the stream
-// over T uses HBM.  At L <= 2 (the GMRES operator) four rows per thread keep
-// more loads of T in flight.  Matrices with active[b] == 0 are skipped.  RW rows
-// (= threads) per workgroup: 64 for small matrices, so that there are enough
-// workgroups, 256 otherwise.
-constexpr int RS_KD = 4;
-template <int LC, int RW, int RPT>
-__global__ __launch_bounds__(RW) void resid_skinny_kernel(int n, int L, const double2* __restrict__ T, int ldt,
+// R_b = U_b - T_b X_b (U null: T_b X_b) in FP64 for at most 16 right-hand sides: the
+// product is skinny, so it is a stream over T, bound by HBM where there are enough
+// rows.  A workgroup takes the rows of one row block of one matrix; its W waves split
+// the columns of T (a contiguous range each) and their partial sums are added in the
+// order of the waves, so that small matrices and few points still keep many loads in
+// flight (one workgroup per 1024 rows that walked all columns ran n = 3000, 32 points,
+// L = 2 at 3.7 TB/s on 96 workgroups; n = 200, L = 16, 32 points took 141 us).  Nothing
+// is shared before that sum, so there is no barrier in the loop.  Matrices with
+// active[b] == 0 are skipped.
+//
+// Up to 8 columns (resid_stream_kernel): a lane owns RPT rows, the loads of T are
+// coalesced, and X(k, c), the same for the whole wave, comes through the scalar cache.
+// 9 to 16 columns (resid_mfma_kernel): v_mfma_f64_16x16x4f64 on four 16-row blocks per
+// wave; a lane loads whole complex entries and the real and imaginary parts go through
+// separate instructions (inner index: four consecutive k).
+
+// The waves' partial sums (acc: NV values per lane) added in order into wave 0's.
+template <int NV, int W>
+RSRR_DEV void wave_partials(double2 (&acc)[NV], double2* lds, int wave, int lane)
+{
+    if (wave > 0) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) lds[((wave - 1) * NV + v) * 64 + lane] = acc[v];
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int w = 1; w < W; ++w)
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] = cadd(acc[v], lds[((w - 1) * NV + v) * 64 + lane]);
+    }
+}
+
+template <int LC, int RPT, int W>
+__global__ __launch_bounds__(64 * W) void resid_stream_kernel(int n, int L, const double2* __restrict__ T, int ldt,
+                                                              long sT, const double2* __restrict__ X, int ldx,
+                                                              long sX, const double2* __restrict__ U, int ldu,
+                                                              long sU, double2* __restrict__ R, int ldr, long sR,
+                                                              const int* __restrict__ active)
+{
+    constexpr int KU = LC <= 4 ? 4 : 2;   // columns of T in flight per row (X(k .. k+KU, :) fits the scalar registers)
+    __shared__ double2 part[(W - 1) * RPT * LC * 64];
+    const int b = blockIdx.y;
+    if (active && !active[b]) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int row0 = blockIdx.x * 64 * RPT + lane;
+    const int per = ((n + W - 1) / W + KU - 1) / KU * KU;
+    const int k0 = min(n, wave * per), k1 = min(n, k0 + per);
+    const double2* Xb = X + b * sX;
+    const double2* Tb = T + b * sT;
+    int rr[RPT];   // rows past the end read the last row and are not stored
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) rr[r] = min(row0 + 64 * r, n - 1);
+    int xc[LC];    // columns past L read the last one and are not stored
+#pragma unroll
+    for (int c = 0; c < LC; ++c) xc[c] = min(c, L - 1);
+    double2 acc[RPT * LC];
+#pragma unroll
+    for (int v = 0; v < RPT * LC; ++v) acc[v] = make_double2(0.0, 0.0);
+    auto step = [&](int k, auto ku) {
+        constexpr int KN = decltype(ku)::value;
+        double2 t[KN][RPT];
+#pragma unroll
+        for (int u = 0; u < KN; ++u)
+#pragma unroll
+            for (int r = 0; r < RPT; ++r) t[u][r] = Tb[rr[r] + (long)(k + u) * ldt];
+#pragma unroll
+        for (int c = 0; c < LC; ++c)
+#pragma unroll
+            for (int u = 0; u < KN; ++u) {
+                const double2 x = Xb[(k + u) + (long)xc[c] * ldx];
+#pragma unroll
+                for (int r = 0; r < RPT; ++r) {
+                    double2& a = acc[r * LC + c];
+                    a.x = fma(t[u][r].x, x.x, a.x);
+                    a.y = fma(t[u][r].x, x.y, a.y);
+                    a.x = fma(-t[u][r].y, x.y, a.x);
+                    a.y = fma(t[u][r].y, x.x, a.y);
+                }
+            }
+    };
+    int k = k0;
+#pragma unroll 2
+    for (; k + KU <= k1; k += KU) step(k, std::integral_constant<int, KU>{});
+    for (; k < k1; ++k) step(k, std::integral_constant<int, 1>{});
+    wave_partials<RPT * LC, W>(acc, part, wave, lane);
+    if (wave > 0) return;
+    double2* Rb = R + b * sR;
+    const double2* Ub = U ? U + b * sU : nullptr;
+#pragma unroll
+    for (int r = 0; r < RPT; ++r) {
+        const int row = row0 + 64 * r;
+        if (row >= n) continue;
+#pragma unroll
+        for (int c = 0; c < LC; ++c)
+            if (c < L) {
+                double2 v = acc[r * LC + c];
+                if (Ub) v = csub(Ub[row + (long)c * ldu], v);
+                Rb[row + (long)c * ldr] = v;
+            }
+    }
+}
+
+template <int W>
+__global__ __launch_bounds__(64 * W) void resid_mfma_kernel(int n, int L, const double2* __restrict__ T, int ldt,
                                                             long sT, const double2* __restrict__ X, int ldx, long sX,
                                                             const double2* __restrict__ U, int ldu, long sU,
                                                             double2* __restrict__ R, int ldr, long sR,
                                                             const int* __restrict__ active)
 {
-    constexpr int KC = 64;
-    __shared__ double2 xs[KC][LC];
+    constexpr int RB = 4;   // 16-row blocks per wave
+    __shared__ double2 part[(W - 1) * RB * 4 * 64];
     const int b = blockIdx.y;
     if (active && !active[b]) return;
-    const int row0 = blockIdx.x * RW * RPT + threadIdx.x;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int li = lane & 15, kq = lane >> 4;
+    const int row0 = blockIdx.x * 16 * RB + li;
+    const int per = ((n + W - 1) / W + 3) / 4 * 4;
+    const int k0 = min(n, wave * per), k1 = min(n, k0 + per);
     const double2* Tb = T + b * sT;
-    const double2* Xb = X + b * sX;
-    bool ok[RPT];
+    const double2* Xc = X + b * sX + (long)min(li, L - 1) * ldx;   // columns past L are not stored
+    int rr[RB];
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) ok[r] = row0 + r * RW < n;
-    double2 acc[RPT][LC];
+    for (int x = 0; x < RB; ++x) rr[x] = min(row0 + 16 * x, n - 1);
+    doublex4 accR[RB], accI[RB];
 #pragma unroll
-    for (int r = 0; r < RPT; ++r)
+    for (int x = 0; x < RB; ++x) accR[x] = accI[x] = doublex4{0.0, 0.0, 0.0, 0.0};
+    // G groups of four k: all loads first; past the wave's range T counts as zero
+    auto step = [&](int k, auto groups) {
+        constexpr int G = decltype(groups)::value;
+        double2 xv[G], t[G][RB];
 #pragma unroll
-        for (int c = 0; c < LC; ++c) acc[r][c] = make_double2(0.0, 0.0);
-    for (int k0 = 0; k0 < n; k0 += KC) {
-        for (int e = threadIdx.x; e < KC * LC; e += RW) {
-            const int kk = e % KC, c = e / KC;
-            xs[kk][c] = (k0 + kk < n && c < L) ? Xb[(k0 + kk) + (long)c * ldx] : make_double2(0.0, 0.0);
-        }
-        __syncthreads();
-        if (ok[0]) {
-            const int kend = min(KC, n - k0);
-            const double2* tp = Tb + row0 + (long)k0 * ldt;
-            // RS_KD columns of T in flight per thread; past kend the last
-            // column is loaded again and multiplied by the zero rows of xs
-            for (int kk0 = 0; kk0 < kend; kk0 += RS_KD) {
-                double2 t[RS_KD][RPT];
+        for (int g = 0; g < G; ++g) {
+            const int kk = k + 4 * g + kq, kc = min(kk, k1 - 1);
+            xv[g] = Xc[kc];
 #pragma unroll
-                for (int u = 0; u < RS_KD; ++u) {
-                    const long kc = min(kk0 + u, kend - 1);
-#pragma unroll
-                    for (int r = 0; r < RPT; ++r)
-                        t[u][r] = ok[r] ? tp[r * RW + kc * ldt] : make_double2(0.0, 0.0);
-                }
-#pragma unroll
-                for (int u = 0; u < RS_KD; ++u) {
-                    if (kk0 + u < kend) {
-#pragma unroll
-                        for (int c = 0; c < LC; ++c) {
-                            const double2 x = xs[kk0 + u][c];
-#pragma unroll
-                            for (int r = 0; r < RPT; ++r) acc[r][c] = cfma(acc[r][c], t[u][r], x);
-                        }
-                    }
-                }
+            for (int x = 0; x < RB; ++x) {
+                t[g][x] = Tb[rr[x] + (long)kc * ldt];
+                if (kk >= k1) t[g][x] = make_double2(0.0, 0.0);
             }
         }
-        __syncthreads();
-    }
+        // the first operand carries X, so that a lane's output runs along the rows of T X
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int x = 0; x < RB; ++x) {
+                accR[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[g].x, t[g][x].x, accR[x], 0, 0, 0);
+                accI[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[g].y, t[g][x].x, accI[x], 0, 0, 0);
+                accR[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xv[g].y, t[g][x].y, accR[x], 0, 0, 0);
+                accI[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[g].x, t[g][x].y, accI[x], 0, 0, 0);
+            }
+    };
+    int k = k0;
+    for (; k + 8 <= k1; k += 8) step(k, std::integral_constant<int, 2>{});
+    for (; k < k1; k += 4) step(k, std::integral_constant<int, 1>{});
+    double2 acc[RB * 4];   // lane li: row, register r: column kq + 4 r
+#pragma unroll
+    for (int x = 0; x < RB; ++x)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[x * 4 + r] = make_double2(accR[x][r], accI[x][r]);
+    wave_partials<RB * 4, W>(acc, part, wave, lane);
+    if (wave > 0) return;
     double2* Rb = R + b * sR;
     const double2* Ub = U ? U + b * sU : nullptr;
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        if (!ok[r]) continue;
-        const int row = row0 + r * RW;
+    for (int x = 0; x < RB; ++x) {
+        const int row = row0 + 16 * x;
+        if (row >= n) continue;
 #pragma unroll
-        for (int c = 0; c < LC; ++c)
+        for (int r = 0; r < 4; ++r) {
+            const int c = kq + 4 * r;
             if (c < L) {
-                if (!Ub) {  // R = T X
-                    Rb[row + (long)c * ldr] = acc[r][c];
-                } else {
-                    const double2 u = Ub[row + (long)c * ldu];
-                    Rb[row + (long)c * ldr] = make_double2(u.x - acc[r][c].x, u.y - acc[r][c].y);
-                }
+                double2 v = acc[x * 4 + r];
+                if (Ub) v = csub(Ub[row + (long)c * ldu], v);
+                Rb[row + (long)c * ldr] = v;
             }
+        }
     }
 }
 
@@ -497,23 +590,25 @@ hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt,
                         long sX, const double2* U, int ldu, long sU, double2* R, int ldr, long sR, const int* active,
                         int B)
 {
-#define RS_L(LC, RW)                                                                                             \
-    do {                                                                                                         \
-        constexpr int RPT = (LC >= 8) ? 2 : (LC <= 2 ? 4 : 1);                                                                  \
-        hipLaunchKernelGGL((resid_skinny_kernel<LC, RW, RPT>), dim3((unsigned)((n + RW * RPT - 1) / (RW * RPT)), \
-                                                                    (unsigned)B),                               \
-                           dim3(RW), 0, st, n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active);      \
-    } while (0)
-    const bool small = n <= 1024;
+#define RS_L(LC, RPT, W)                                                                                             \
+    hipLaunchKernelGGL((resid_stream_kernel<LC, RPT, W>), dim3((unsigned)((n + 64 * RPT - 1) / (64 * RPT)),          \
+                                                               (unsigned)B),                                        \
+                       dim3(64 * W), 0, st, n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
+#define RS_M(W)                                                                                                      \
+    hipLaunchKernelGGL(resid_mfma_kernel<W>, dim3((unsigned)((n + 63) / 64), (unsigned)B), dim3(64 * W), 0, st, n, L, \
+                       T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
+    // few row blocks (fewer than two per CU): the columns are split over more waves
+    const bool few = (long)((n + 63) / 64) * B < 512;
     if (L <= 2) {
-        if (small) RS_L(2, 64); else RS_L(2, 256);
+        if (few) RS_L(2, 1, 8); else RS_L(2, 2, 4);
     } else if (L <= 4) {
-        if (small) RS_L(4, 64); else RS_L(4, 256);
+        if (few) RS_L(4, 1, 8); else RS_L(4, 2, 4);
     } else if (L <= 8) {
-        if (small) RS_L(8, 64); else RS_L(8, 256);
+        if (few) RS_L(8, 1, 8); else RS_L(8, 1, 4);
     } else {
-        if (small) RS_L(16, 64); else RS_L(16, 256);
+        RS_M(4);
     }
+#undef RS_M
 #undef RS_L
     return hipGetLastError();
 }
