@@ -306,7 +306,8 @@ struct SampleBufs {
     void* pair; void* pair2;
     hipStream_t la, upd; hipEvent_t la_a, la_b, la_c;
     int la_cols;
-    int ld, np, nb; long sT, sP, sPerm, nparts, sInv, sTmp, sPair;
+    void* pack;
+    int ld, np, nb; long sT, sP, sPerm, nparts, sInv, sTmp, sPair, sPack;
     LUWork lu(const int* act, UpdateRecorder* rec) const
     {
         LUWork w;
@@ -315,9 +316,18 @@ struct SampleBufs {
         w.pair = pair; w.sPair = sPair; w.ldpair = ld;
         w.pair2 = pair2; w.side = la; w.ev_a = la_a; w.ev_b = la_b; w.upd = upd; w.ev_c = la_c;
         w.la_cols = la_cols;
+        w.pack = pack; w.sPack = sPack;
         return w;
     }
 };
+
+// Bytes per point of the split operands of the trailing updates (two panels of 128 columns
+// deep); 0 where no update is large enough for them.
+static size_t pack_bytes(int n, int prec)
+{
+    constexpr int depth = 2 * max_panel<float>();
+    return prec == RSRR_PREC_C64_IR && split_ok(n - depth, n - depth, depth) ? split_pack_bytes(n, depth) : 0;
+}
 
 // Per-point bytes of the sampling buffers.
 static size_t per_point_bytes(int n, int L, int prec)
@@ -333,6 +343,7 @@ static size_t per_point_bytes(int n, int L, int prec)
         b += (size_t)np * 2 * 128 * 128 * 8 / 2;          // diagonal-block inverses (nb = 128: n/128 panels)
         b += (size_t)128 * std::max(n, L) * 8;            // scratch rows
         b += (size_t)lu_pair_elems(n, 128, (int)ld) * 8 * 2;  // paired trailing updates (two for the look-ahead)
+        b += pack_bytes(n, prec);
     }
     return b;
 }
@@ -352,6 +363,9 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     const bool la = fp32 && c->lookahead;
     s.pair = fp32 ? ws_get(c, WS_LUP, (size_t)B * s.sPair * 8 * (la ? 2 : 1)) : nullptr;
     if (fp32 && (!s.inv || !s.tmp || !s.pair)) return RSRR_ENOMEM;
+    s.sPack = (long)pack_bytes(n, prec);
+    s.pack = s.sPack ? ws_get(c, WS_PACK, (size_t)B * s.sPack) : nullptr;
+    if (s.sPack && !s.pack) return RSRR_ENOMEM;
     s.pair2 = la ? (char*)s.pair + (size_t)B * s.sPair * 8 : nullptr;
     s.la = la ? c->la : nullptr;
     s.la_a = c->la_a;
@@ -464,6 +478,7 @@ static LUWork lu_offset(const LUWork& w, long b0, int esz = 8)
     if (w.tmp) o.tmp = (char*)w.tmp + b0 * w.sTmp * esz;
     if (w.pair) o.pair = (char*)w.pair + b0 * w.sPair * esz;
     if (w.pair2) o.pair2 = (char*)w.pair2 + b0 * w.sPair * esz;
+    if (w.pack) o.pack = (char*)w.pack + b0 * w.sPack;
     if (w.active) o.active = w.active + b0;
     return o;
 }

@@ -34,6 +34,19 @@ void set_update_tile(int t);
 int get_update_tile();
 const char* update_tile_name(int t);
 
+// C -= A B in complex FP32 on the FP16 matrix cores with split operands (split.hip), for
+// the trailing update of a pivoted LU: |parts of A| <= sqrt(2), columns of B of any scale.
+// split_pack writes the operands of an M x N product of depth K into P (per matrix
+// split_pack_bytes(max(M, N), K) bytes, stride sP bytes); cgemm_split then updates the
+// columns j0 .. j0 + N - 1 (j0 a multiple of 32) of the product whose N at packing was
+// Npack (C at column j0).  split_ok: sizes for which it replaces cgemm.
+bool split_ok(int M, int N, int K);
+size_t split_pack_bytes(int n, int K);
+hipError_t split_pack(hipStream_t st, int M, int N, int K, const float2* A, int lda, long sA, const float2* B, int ldb,
+                      long sB, void* P, long sP, int batch);
+hipError_t cgemm_split(hipStream_t st, int M, int N, int K, int Npack, int j0, const void* P, long sP, float2* C,
+                       int ldc, long sC, int batch);
+
 // C = beta*C + alpha*op(A)*op(B), complex double on v_mfma_f64_16x16x4f64;
 // op = conjugate transpose when the flag is set.
 hipError_t zgemm(hipStream_t st, int opA, int opB, int M, int N, int K, double alpha,
@@ -84,6 +97,9 @@ struct LUWork {
     hipStream_t upd = nullptr;
     hipEvent_t ev_c = nullptr;
     int la_cols = 0;                   // columns of each overlapped update on `upd` (0: all)
+    // optional (complex FP32): split_pack_bytes(n, 2 nb) bytes per matrix (stride sPack bytes);
+    // the trailing updates then run with split operands on the FP16 matrix cores
+    void* pack = nullptr; long sPack = 0;
 };
 // Elements per matrix of the pair buffer for n x n matrices and panel width nb.
 inline long lu_pair_elems(int n, int nb, int ldpair) { return (long)ldpair * 2 * nb + (long)nb * nb; }

@@ -35,8 +35,8 @@ namespace rsrr {
 // interchanges give each of its rows and stores the row there at the end); the
 // search runs in registers (DPP) inside a wave; each wave publishes its candidate
 // with the candidate's row, so one barrier per column suffices and every thread
-// picks the winner itself; nothing is stored to memory inside the loop (a barrier
-// waits for stores).  Columns go in groups of GW: the chain of a column touches its
+// picks the winner itself; pivots and flags are written after the loop.  Columns go
+// in groups of GW: the chain of a column touches its
 // own group only, the columns after the group take its pivot rows and one rank-GW
 // update at the end of the group.  The loop over the groups is rolled (the registers
 // rotate by one group), so the code stays in the instruction cache.
@@ -995,12 +995,24 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     if (nb > max_panel<R>()) nb = max_panel<R>();
     if (nb < MIN_NB) nb = MIN_NB;  // perm/inv storage holds perm_panels(n) panels
     UpdateRecorder* rec = w.rec;
-    // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `st`, event-timed
+    // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `s`, event-timed.  An
+    // update done in column parts gives its whole width (Nall) and the part's first column
+    // (j0); with split operands the first part (j0 = 0) packs them for all parts.
     auto timed_update_on = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
-                               const C* Bop, C* Cop) {
+                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0) {
         const bool timed = rec && rec->used < rec->cap;
         if (timed) (void)hipEventRecord(rec->ev[2 * rec->used], s);
-        (void)gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1);
+        if (Nall == 0) Nall = N;
+        bool split = false;
+        if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
+            split = w.pack != nullptr && split_ok(M, Nall, kdepth);
+            if (split) {
+                if (j0 == 0)
+                    (void)split_pack(s, M, Nall, kdepth, Aop, ldaop, sAop, Bop, lda, sA, w.pack, w.sPack, batch);
+                (void)cgemm_split(s, M, N, kdepth, Nall, j0, w.pack, w.sPack, Cop, lda, sA, batch);
+            }
+        }
+        if (!split) (void)gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1);
         if (timed) {
             (void)hipEventRecord(rec->ev[2 * rec->used + 1], s);
             const double fl = (elem_traits<C>::complex ? 8.0 : 2.0) * M * (double)N * kdepth * batch;
@@ -1093,24 +1105,25 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
                 break;
             }
             const int wn = 2 * nb;
-            timed_update(rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop);
+            timed_update_on(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0);
             (void)hipEventRecord(w.ev_a, st);
             // the rest of the update is enqueued before the next pair's panels (a chain of
             // small launches), so the host never holds it back behind them
             if (w.upd && w.ev_c) {
                 // the first la_cols columns of the update on the CUs the side stream does not
                 // use (while the next panels are factored), the rest on every CU
-                const int n1 = w.la_cols > 0 ? std::min(rest - wn, w.la_cols) : rest - wn;
+                const int n1 = w.la_cols > 0 ? std::min(rest - wn, std::max(32, w.la_cols / 32 * 32)) : rest - wn;
                 (void)hipStreamWaitEvent(w.upd, w.ev_a, 0);
                 timed_update_on(w.upd, rest, n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
-                                Cop + (long)wn * lda);
+                                Cop + (long)wn * lda, rest, wn);
                 (void)hipEventRecord(w.ev_c, w.upd);
                 (void)hipStreamWaitEvent(st, w.ev_c, 0);
                 if (n1 < rest - wn)
-                    timed_update(rest, rest - wn - n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)(wn + n1) * lda,
-                                 Cop + (long)(wn + n1) * lda);
+                    timed_update_on(st, rest, rest - wn - n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)(wn + n1) * lda,
+                                    Cop + (long)(wn + n1) * lda, rest, wn + n1);
             } else {
-                timed_update(rest, rest - wn, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda, Cop + (long)wn * lda);
+                timed_update_on(st, rest, rest - wn, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
+                                Cop + (long)wn * lda, rest, wn);
             }
             (void)hipStreamWaitEvent(w.side, w.ev_a, 0);
             front(w.side, c2, p + 2, Wb[buf ^ 1]);

@@ -1,0 +1,291 @@
+// Complex FP32 product C -= A B on the FP16 matrix cores with split operands (the LU's
+// trailing update).
+//
+// v_mfma_f32_32x32x16_f16 multiplies at 16 times the rate of the FP32 instruction, with
+// exact products and FP32 sums.  Every real FP32 value, scaled by a power of two, is
+// held as hi + lo of two FP16 numbers: hi carries the leading 11 bits, lo the next 11, so
+// hi + lo is the value to within half a unit of FP32 and mostly exactly.  Three products,
+// hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.  The scale
+// makes the range safe: A is the unit lower factor of a pivoted LU, whose parts are at most
+// sqrt(2) (pivots are the largest |Re| + |Im|), scaled by 2^15; every column of B is scaled
+// by its own power of two to a largest part in [2^14, 2^15), and what is smaller than
+// 2^-40 of the column's largest part is lost.  The sums do not contain C (one
+// subtraction at the end), and 16 products enter them per rounding instead of 2, so
+// the error is below that of the FP32 kernel: against 64 bits, relative to
+// |C| + |A||B| and in units of u = 2^-24, at K = 64 .. 256 and with columns of B of one size
+// or spread over 8 to 24 decades: rms 0.3-1.4 (FP32 3M kernel 1.0-1.9), largest 1.7-12 (7-20).
+//
+// Bound by the matrix cores and by C, which is read and written once per update.  64
+// matrices, K = 256, n = 3840 / 2048 / 1024: 5.95 / 1.64 / 0.44 ms, 325 / 335 / 316 TFLOP/s in
+// the standard count of 8 flops per complex multiply-add (975 TFLOP/s in FP16, C at 2.6
+// TB/s), packing 0.36 / 0.19 / 0.10 ms; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
+//
+// The complex product is the 4M form with the interleaved parts as the inner index
+// (k' = 2k + part): Re C takes A' (Br, -Bi), Im C takes A' (Bi, Br), which is one sign
+// flip and one half-word rotation of the same registers.
+//
+// The operands are packed once per update into the order in which the instruction
+// takes them (a fragment: 32 rows x 8 complex k, 64 lanes x 16 bytes, 1 KB), so a tile is
+// staged with plain 16-byte global-to-LDS copies and read back without bank conflicts.
+#include "common.h"
+#include "kernels.h"
+
+namespace rsrr {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+
+constexpr int SP_KC = 8;          // complex k per fragment
+constexpr int SP_FRAG = 1024;     // bytes
+constexpr int SP_ASCALE = 15;     // log2 of the scale of A
+constexpr int SP_BTOP = 14;       // exponent that a column's largest part of B is scaled to
+constexpr int SP_KMAX = 256;
+
+// hi and lo parts of 4 complex values scaled by 2^e, interleaved (re, im) as one lane of a fragment
+RSRR_DEV void split4(const float2 (&v)[4], int e, uintx4* hi, uintx4* lo)
+{
+    half8 h, l;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float x = ldexpf(v[q].x, e), y = ldexpf(v[q].y, e);
+        h[2 * q] = (_Float16)x;
+        h[2 * q + 1] = (_Float16)y;
+        l[2 * q] = (_Float16)(x - (float)h[2 * q]);
+        l[2 * q + 1] = (_Float16)(y - (float)h[2 * q + 1]);
+    }
+    *hi = __builtin_bit_cast(uintx4, h);
+    *lo = __builtin_bit_cast(uintx4, l);
+}
+
+// A (M x K): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l holds
+// row l % 32 and the 4 complex k at 4 (l / 32).  One wave per row block and k chunk; rows past M are zero.
+__global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, const float2* __restrict__ A, int lda, long sA,
+                                                           char* __restrict__ P, long sP)
+{
+    const int b = blockIdx.y, lane = threadIdx.x & 63;
+    const int nkc = (K + SP_KC - 1) / SP_KC, nrb = (M + 31) / 32;
+    const long f = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (f >= (long)nrb * nkc) return;
+    const int rb = (int)(f / nkc), kc = (int)(f % nkc);
+    const int i = rb * 32 + (lane & 31), k = kc * SP_KC + 4 * (lane >> 5);
+    const float2* src = A + b * sA + i;
+    float2 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = (i < M && k + q < K) ? src[(long)(k + q) * lda] : make_float2(0.f, 0.f);
+    uintx4 hi, lo;
+    split4(v, SP_ASCALE, &hi, &lo);
+    uintx4* dst = reinterpret_cast<uintx4*>(P + b * sP + f * 2 * SP_FRAG);
+    dst[lane] = hi;
+    dst[64 + lane] = lo;
+}
+
+// B (K x N, K <= SP_KMAX): the same fragments with the columns in place of the rows, and the
+// exponent of each column's scale (expo[j]).  One workgroup per 32 columns, 8 threads per column.
+__global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, const float2* __restrict__ B, int ldb, long sB,
+                                                           char* __restrict__ P, long sP, long expo_off)
+{
+    const int b = blockIdx.y, t = threadIdx.x;
+    const int nkc = (K + SP_KC - 1) / SP_KC;
+    const int c = t >> 3, part = t & 7;
+    const int j = blockIdx.x * 32 + c;
+    const float2* src = B + b * sB + (long)j * ldb;
+    constexpr int Q = SP_KMAX / 32;
+    float2 v[Q][4];
+    float top = 0.f;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = 4 * (part + 8 * q) + u;
+            v[q][u] = (j < N && k < K) ? src[k] : make_float2(0.f, 0.f);
+            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+        }
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
+    // v_frexp_exp: top = m 2^e with m in [1/2, 1); a zero or non-finite column keeps its scale
+    const int e = (top > 0.f && isfinite(top)) ? SP_BTOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
+    char* Pb = P + b * sP;
+    if (part == 0) reinterpret_cast<int*>(Pb + expo_off)[j] = e;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int p = part + 8 * q, kc = p >> 1;
+        if (kc >= nkc) break;
+        uintx4 hi, lo;
+        split4(v[q], e, &hi, &lo);
+        uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)blockIdx.x * nkc + kc) * 2 * SP_FRAG);
+        dst[c + 32 * (p & 1)] = hi;
+        dst[64 + c + 32 * (p & 1)] = lo;
+    }
+}
+
+// Workgroup tile 128 x 128, four waves of 64 x 64 (2 x 2 blocks of 32 x 32, real and imaginary
+// accumulators: 128 registers, two waves per SIMD); stages of SP_ST k chunks in two LDS buffers
+// (64 KB, two workgroups per CU: one stores its tile while the other multiplies).
+constexpr int SP_ST = 2, SP_T = 128;
+
+__global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int nkc, const char* __restrict__ PA,
+                                                             long sPA, const char* __restrict__ PB, long sPB,
+                                                             long expo_off, int cb0, float2* __restrict__ C, int ldc,
+                                                             long sC, int tilesM, int tilesN, int batch, long total)
+{
+    constexpr int STAGE = 4 * SP_ST * 2 * SP_FRAG;   // bytes of one operand's stage
+    __shared__ __attribute__((aligned(16))) char lds[2][2][STAGE];
+
+    const long tile = xcd_remap(blockIdx.x, total);
+    const long per = (long)tilesM * tilesN;
+    const long b = tile / per;
+    if (b >= batch) return;
+    // groups of 8 row tiles sweep the columns together (shared slices in the XCD's L2)
+    constexpr int ROWS = 8;
+    const int t = (int)(tile - b * per);
+    const int span = ROWS * tilesN, g = t / span, first = g * ROWS, rows = min(tilesM - first, ROWS), in = t - g * span;
+    const int ti = first + in % rows, tj = in / rows;
+    const int nrb = (M + 31) / 32, ncb = (N + 31) / 32;
+
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wi = wave & 1, wj = wave >> 1;
+    // wave w stages row block w and column block w of the tile (blocks past the end: the last one again)
+    const char* ga = PA + b * sPA + (long)min(ti * 4 + wave, nrb - 1) * nkc * 2 * SP_FRAG + lane * 16;
+    const char* gb = PB + b * sPB + (long)(cb0 + min(tj * 4 + wave, ncb - 1)) * nkc * 2 * SP_FRAG + lane * 16;
+    auto stage = [&](int s, int buf) {
+#pragma unroll
+        for (int f = 0; f < 2 * SP_ST; ++f) {
+            const int kc = min(s * SP_ST + f / 2, nkc - 1);
+            const long o = ((long)kc * 2 + f % 2) * SP_FRAG;
+            const int l = (wave * 2 * SP_ST + f) * SP_FRAG;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ga + o),
+                                             (__attribute__((address_space(3))) void*)&lds[buf][0][l], 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(gb + o),
+                                             (__attribute__((address_space(3))) void*)&lds[buf][1][l], 16, 0, 0);
+        }
+    };
+    auto frag = [&](int buf, int op, int block, int f) {
+        return *reinterpret_cast<const uintx4*>(&lds[buf][op][(block * 2 * SP_ST + f) * SP_FRAG + lane * 16]);
+    };
+
+    floatx16 accR[2][2], accI[2][2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) accR[x][y][r] = accI[x][y][r] = 0.f;
+
+    const int nst = (nkc + SP_ST - 1) / SP_ST;
+    // a barrier orders LDS accesses but does not wait for copies into LDS in flight
+    auto arrived = [] { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); __syncthreads(); };
+    stage(0, 0);
+    arrived();
+    for (int s = 0; s < nst; ++s) {
+        const int buf = s & 1;
+        if (s + 1 < nst) stage(s + 1, buf ^ 1);
+#pragma unroll
+        for (int kc = 0; kc < SP_ST; ++kc) {
+            if (SP_ST > 1 && s * SP_ST + kc >= nkc) break;
+            uintx4 a[2][2], br[2][2], bi[2][2];   // [block][hi, lo]
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    a[x][h] = frag(buf, 0, wi * 2 + x, kc * 2 + h);
+                    const uintx4 v = frag(buf, 1, wj * 2 + x, kc * 2 + h);
+                    br[x][h] = v ^ 0x80000000u;                 // (Br, -Bi)
+                    bi[x][h] = (v << 16) | (v >> 16);           // (Bi, Br)
+                }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {   // lo hi, hi lo, hi hi
+                const int ha = p == 0, hb = p == 1;
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+#pragma unroll
+                    for (int y = 0; y < 2; ++y) {
+                        accR[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                            __builtin_bit_cast(half8, br[y][hb]), __builtin_bit_cast(half8, a[x][ha]), accR[x][y], 0,
+                            0, 0);
+                        accI[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                            __builtin_bit_cast(half8, bi[y][hb]), __builtin_bit_cast(half8, a[x][ha]), accI[x][y], 0,
+                            0, 0);
+                    }
+            }
+        }
+        arrived();
+    }
+
+    // C -= 2^-(scales) acc; lane li = row, register r = column 8 (r / 4) + 4 (lane / 32) + r % 4
+    float2* Cb = C + b * sC;
+    const int* ex = reinterpret_cast<const int*>(PB + b * sPB + expo_off) + cb0 * 32;
+    const int li = lane & 31, half = lane >> 5;
+#pragma unroll
+    for (int y = 0; y < 2; ++y) {
+        const int j0 = tj * SP_T + (wj * 2 + y) * 32 + 4 * half;
+        if (tj * SP_T + (wj * 2 + y) * 32 >= N) break;
+        int e[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) e[r] = -(SP_ASCALE + ex[min(j0 + 8 * (r >> 2) + (r & 3), N - 1)]);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const int i = ti * SP_T + (wi * 2 + x) * 32 + li;
+            if (i >= M) continue;
+            float2* col = Cb + i + (long)j0 * ldc;
+            if (tj * SP_T + (wj * 2 + y) * 32 + 32 <= N) {   // whole block: all loads in flight before the first store
+                float2 c[16];
+#pragma unroll
+                for (int r = 0; r < 16; ++r) c[r] = col[(long)(8 * (r >> 2) + (r & 3)) * ldc];
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    col[(long)(8 * (r >> 2) + (r & 3)) * ldc] = make_float2(c[r].x - ldexpf(accR[x][y][r], e[r]),
+                                                                            c[r].y - ldexpf(accI[x][y][r], e[r]));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int jr = 8 * (r >> 2) + (r & 3);
+                    if (j0 + jr < N) {
+                        const float2 c = col[(long)jr * ldc];
+                        col[(long)jr * ldc] = make_float2(c.x - ldexpf(accR[x][y][r], e[r]),
+                                                          c.y - ldexpf(accI[x][y][r], e[r]));
+                    }
+                }
+            }
+        }
+    }
+}
+
+static long sp_operand_bytes(int rows, int K) { return (long)((rows + 31) / 32) * ((K + SP_KC - 1) / SP_KC) * 2 * SP_FRAG; }
+
+size_t split_pack_bytes(int n, int K)
+{
+    return 2 * (size_t)sp_operand_bytes(n, K) + ((size_t)n + 31) / 32 * 32 * 4;
+}
+
+// Depths of at least one panel (the error is below the FP32 kernel's from K = 64 on); fewer
+// than 128 rows or columns leave most of a tile empty and do not pay for the packing.
+bool split_ok(int M, int N, int K) { return K >= 128 && K <= SP_KMAX && M >= 128 && N >= 128; }
+
+hipError_t split_pack(hipStream_t st, int M, int N, int K, const float2* A, int lda, long sA, const float2* B, int ldb,
+                      long sB, void* P, long sP, int batch)
+{
+    const long na = sp_operand_bytes(M, K), nb = sp_operand_bytes(N, K);
+    char* Pa = (char*)P;
+    const long frags = na / (2 * SP_FRAG);
+    hipLaunchKernelGGL(split_pack_a_kernel, dim3((unsigned)((frags + 3) / 4), batch), dim3(256), 0, st, M, K, A, lda,
+                       sA, Pa, sP);
+    hipLaunchKernelGGL(split_pack_b_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, B, ldb, sB, Pa + na, sP,
+                       nb);
+    return hipGetLastError();
+}
+
+hipError_t cgemm_split(hipStream_t st, int M, int N, int K, int Npack, int j0, const void* P, long sP, float2* C,
+                       int ldc, long sC, int batch)
+{
+    if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
+    if (j0 % 32 != 0 || j0 + N > Npack) return hipErrorInvalidValue;
+    const long na = sp_operand_bytes(M, K), nb = sp_operand_bytes(Npack, K);
+    const char* Pa = (const char*)P;
+    const int tm = (M + SP_T - 1) / SP_T, tn = (N + SP_T - 1) / SP_T;
+    const long total = round_up_l((long)tm * tn * batch, 8);
+    hipLaunchKernelGGL(cgemm_split_kernel, dim3((unsigned)total), dim3(256), 0, st, M, N, (K + SP_KC - 1) / SP_KC, Pa, sP,
+                       Pa + na, sP, nb, j0 / 32, C, ldc, sC, tm, tn, batch, total);
+    return hipGetLastError();
+}
+
+}  // namespace rsrr

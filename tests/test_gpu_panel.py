@@ -20,6 +20,9 @@ PRECS = {"c64": R.RSRR_PREC_C64_IR, "c128": R.RSRR_PREC_C128, "r32": R.RSRR_PREC
 @pytest.fixture(scope="module")
 def ctx():
     c = R.rsrr_create(0)
+    # a point is not handed to the FP64 path for a large ||u - T x|| / ||u||, which an ill-conditioned
+    # T gives with any arithmetic: the refined result itself is looked at, by its backward error
+    R.rsrr_set_options(c, fallback_resid=0.5)
     yield c
     c.close()
 
@@ -36,9 +39,7 @@ def _check(ctx, A, prec, L=3):
     z = np.array([0.25, -0.5], dtype=np.complex128)
     S, info, status = R.rsrr_sample(ctx, R.DeviceNEP(_nep(A)), z, U, prec=PRECS[prec])
     torch.cuda.synchronize()
-    # an ill-conditioned point may be redone in FP64 (4097 rows, real: one of the two is), not all of them
-    assert status in (R.RSRR_OK, R.RSRR_WARN_FALLBACK)
-    assert all(i["info"] == 0 for i in info) and not all(i["fallback"] for i in info)
+    assert status == R.RSRR_OK and all(i["info"] == 0 and i["fallback"] == 0 for i in info)
     X = R.from_colmajor(S, n)
     for k, zk in enumerate(z):
         T = A + zk * np.eye(n)
