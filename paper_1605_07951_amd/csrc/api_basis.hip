@@ -41,7 +41,7 @@ int jacobi_svd(rsrr_ctx* c, double2* A, int lda, int m, int m_apply, int p, int 
     int stall = 0;
     for (int sw = 0; sw < max_sweeps; ++sw) {
         for (int r = 0; r < rounds; ++r) {
-            if (jacobi_round(c->stream, A, lda, m, m_apply, p, r, 1, tol, zthr2, off + (size_t)r * pairs, work) !=
+            if (jacobi_round(c->stream, A, lda, m, m_apply, p, r, tol, zthr2, off + (size_t)r * pairs, work) !=
                 hipSuccess) {
                 *st = RSRR_EDEVICE;
                 return -1;
@@ -98,9 +98,13 @@ extern "C" rsrr_status rsrr_basis(rsrr_ctx* c, int n, int NL, double* S, int lds
     //   numerically independent columns kept, X = [S^H Q_Y; I_r]: Jacobi
     //   rotations J on the columns make the top part V Sigma (right singular
     //   vectors of B = Q_Y^H S) and the bottom part J = W, the left singular
-    //   vectors of B; S's left singular vectors are Q_Y W.  When NL >= 2r the
-    //   top part is replaced by R from S^H Q_Y = Q_X R (same Gram matrix, so the
-    //   same rotations and singular values, on r rows instead of NL).
+    //   vectors of B; S's left singular vectors are Q_Y W.  When NL >= 2r, QR
+    //   first, S^H Q_Y = Q_X R, and Jacobi on the columns of R^H (r rows): they
+    //   become W Sigma, so W needs no accumulation, and the rows of R, graded by
+    //   the Gram-Schmidt order, take fewer sweeps than its columns.  Columns that the
+    //   rotations leave out (at most eps ||R||_F) must not be among those returned;
+    //   should one be, the rotations are accumulated instead, on [R; I_r] (the Gram
+    //   matrix of S^H Q_Y, so the same singular values).
     // When l = min(n, NL) the sketch spans range(S) and this is the SVD of S.  A
     // smaller l is accepted when the sketch came out rank deficient (r < l) or its
     // smallest singular value is at the rounding floor (<= 1e-15 sigma_1);
@@ -113,7 +117,9 @@ extern "C" rsrr_status rsrr_basis(rsrr_ctx* c, int n, int NL, double* S, int lds
     std::vector<double> sv, hq;
     double2* Yu = nullptr;
     double2* X = nullptr;
-    int r = 0, xr = 0;  // X = [top (xr rows); W (r rows)] after the Jacobi sweeps
+    // after the Jacobi sweeps X (ld xld) = [top (xr rows); W (r rows)], or, direct, W Sigma
+    int r = 0, xr = 0, xld = 0;
+    bool direct = false;
     for (;;) {
         double2* Y = (double2*)ws_get(c, WS_TLU, (size_t)n * l * 16);
         double2* Om = (double2*)ws_get(c, WS_TRES, (size_t)std::max((long)NL * l, (long)n * l) * 16);
@@ -148,12 +154,12 @@ extern "C" rsrr_status rsrr_basis(rsrr_ctx* c, int n, int NL, double* S, int lds
             RSRR_HIP(hipStreamSynchronize(c->stream));
             Yu = Om;
         }
-        if (NL >= 2 * r) {
-            // QR first: B^H = S^H Q_Y = Q_X R (BCGS2), then the Jacobi rotations on
-            // [R; I_r]: R has the Gram matrix of B^H, so the rotations, singular
-            // values and W are those of B^H, on 2r rows instead of NL + r
-            double2* Xs = (double2*)ws_get(c, WS_B0, (size_t)NL * r * 16);
-            double2* Xq = (double2*)ws_get(c, WS_B1, (size_t)NL * r * 16);
+        double2 *Xs = nullptr, *Xq = nullptr;
+        const bool qr = NL >= 2 * r;
+        direct = qr;
+        if (qr) {
+            Xs = (double2*)ws_get(c, WS_B0, (size_t)NL * r * 16);
+            Xq = (double2*)ws_get(c, WS_B1, (size_t)NL * r * 16);
             void* Wq = ws_get(c, WS_D64, bcgs2_work_bytes(NL, r));
             double* nq = (double*)ws_get(c, WS_B7, (size_t)r * 8);
             X = (double2*)ws_get(c, WS_R, (size_t)2 * r * r * 16);
@@ -161,25 +167,43 @@ extern "C" rsrr_status rsrr_basis(rsrr_ctx* c, int n, int NL, double* S, int lds
             RSRR_HIP(zgemm(c->stream, 1, 0, NL, r, n, 1.0, A, lds, 0, Yu, n, 0, 0.0, Xs, NL, 0, 1));
             RSRR_HIP(copy_c128(c->stream, NL, r, Xs, NL, 0, Xq, NL, 0, 1));
             RSRR_HIP(bcgs2(c->stream, Xq, NL, NL, r, Wq, nq));
-            RSRR_HIP(zgemm(c->stream, 1, 0, r, r, NL, 1.0, Xq, NL, 0, Xs, NL, 0, 0.0, X, 2 * r, 0, 1));
-            xr = r;
         } else {
             X = (double2*)ws_get(c, WS_R, (size_t)(NL + r) * r * 16);
             if (!X) return RSRR_ENOMEM;
-            RSRR_HIP(zgemm(c->stream, 1, 0, NL, r, n, 1.0, A, lds, 0, Yu, n, 0, 0.0, X, NL + r, 0, 1));
-            xr = NL;
         }
-        RSRR_HIP(eye(c->stream, X, xr + r, xr, r));
-        if (jacobi_svd(c, X, xr + r, xr, xr + r, r, 80, tol, &st) < 0) return st;
-        double* cn = (double*)ws_get(c, WS_B5, (size_t)r * 8);
-        if (!cn) return RSRR_ENOMEM;
-        RSRR_HIP(colnorms(c->stream, xr, r, X, xr + r, 0, cn, 1));
-        sv.assign(r, 0.0);
-        RSRR_HIP(hipMemcpyAsync(sv.data(), cn, (size_t)r * 8, hipMemcpyDeviceToHost, c->stream));
-        RSRR_HIP(hipStreamSynchronize(c->stream));
-        o.resize(r);
-        std::iota(o.begin(), o.end(), 0);
-        std::stable_sort(o.begin(), o.end(), [&](int x, int y) { return sv[x] > sv[y]; });
+        for (;;) {
+            if (direct) {
+                RSRR_HIP(zgemm(c->stream, 1, 0, r, r, NL, 1.0, Xs, NL, 0, Xq, NL, 0, 0.0, X, r, 0, 1));
+                xr = 0;
+                xld = r;
+                if (jacobi_svd(c, X, r, r, r, r, 80, tol, &st) < 0) return st;
+            } else {
+                xr = qr ? r : NL;
+                xld = xr + r;
+                if (qr)
+                    RSRR_HIP(zgemm(c->stream, 1, 0, r, r, NL, 1.0, Xq, NL, 0, Xs, NL, 0, 0.0, X, xld, 0, 1));
+                else
+                    RSRR_HIP(zgemm(c->stream, 1, 0, NL, r, n, 1.0, A, lds, 0, Yu, n, 0, 0.0, X, xld, 0, 1));
+                RSRR_HIP(eye(c->stream, X, xld, xr, r));
+                if (jacobi_svd(c, X, xld, xr, xld, r, 80, tol, &st) < 0) return st;
+            }
+            double* cn = (double*)ws_get(c, WS_B5, (size_t)r * 8);
+            if (!cn) return RSRR_ENOMEM;
+            RSRR_HIP(colnorms(c->stream, direct ? r : xr, r, X, xld, 0, cn, 1));
+            sv.assign(r, 0.0);
+            RSRR_HIP(hipMemcpyAsync(sv.data(), cn, (size_t)r * 8, hipMemcpyDeviceToHost, c->stream));
+            RSRR_HIP(hipStreamSynchronize(c->stream));
+            o.resize(r);
+            std::iota(o.begin(), o.end(), 0);
+            std::stable_sort(o.begin(), o.end(), [&](int x, int y) { return sv[x] > sv[y]; });
+            if (!direct) break;
+            double fro2 = 0.0, least = 0.0;   // the smallest singular value that is returned with its vector
+            for (double v : sv) fro2 += v * v;
+            for (int i = 0; i < std::min(r, kmax); ++i)
+                if (sv[o[i]] > delta * sv[o[0]]) least = sv[o[i]];
+            if (least > 8.0 * 2.220446049250313e-16 * std::sqrt(fro2)) break;
+            direct = false;
+        }
         const double s1 = sv[o[0]], sl = sv[o[r - 1]];
         if (l >= m || r < l || !(s1 > 0.0) || sl <= 1e-15 * s1) break;
         l = std::min(m, 2 * l);
@@ -193,13 +217,15 @@ extern "C" rsrr_status rsrr_basis(rsrr_ctx* c, int n, int NL, double* S, int lds
     *k = kk;
     const int kw = std::min(kk, kmax);
     if (kw > 0) {
-        // W sorted by singular value (bottom r rows of X), then Q = Q_Y W
-        std::vector<double> ones(kw, 1.0);
+        // W sorted by singular value, then Q = Q_Y W
+        std::vector<double> f(kw, 1.0);
+        if (direct)
+            for (int i = 0; i < kw; ++i) f[i] = 1.0 / sv[o[i]];
         double2* Ws = (double2*)ws_get(c, WS_B2, (size_t)r * kw * 16);
         if (!Ws) return RSRR_ENOMEM;
         RSRR_HIP(hipMemcpyAsync(ord, o.data(), (size_t)kw * 4, hipMemcpyHostToDevice, c->stream));
-        RSRR_HIP(hipMemcpyAsync(inv, ones.data(), (size_t)kw * 8, hipMemcpyHostToDevice, c->stream));
-        RSRR_HIP(gather_scale(c->stream, X + xr, xr + r, r, ord, inv, Ws, r, kw));
+        RSRR_HIP(hipMemcpyAsync(inv, f.data(), (size_t)kw * 8, hipMemcpyHostToDevice, c->stream));
+        RSRR_HIP(gather_scale(c->stream, X + xr, xld, r, ord, inv, Ws, r, kw));
         RSRR_HIP(zgemm(c->stream, 0, 0, n, kw, r, 1.0, Yu, n, 0, Ws, r, 0, 0.0, (double2*)Q, ldq, 0, 1));
     }
     RSRR_HIP(hipStreamSynchronize(c->stream));

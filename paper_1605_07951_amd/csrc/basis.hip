@@ -12,11 +12,15 @@
 //      convergence measure of one-sided Jacobi; columns with |a|^2 <= zthr2,
 //      rounding level relative to ||A||_F, count as zero and are neither
 //      measured nor rotated, so exactly rank-deficient inputs converge),
-//      diagonalises G by cyclic two-sided Jacobi rotations (parallel
+//      applies one sweep of two-sided Jacobi rotations to G (parallel
 //      ordering) accumulating the unitary V, and applies
-//      [A_I A_J] <- [A_I A_J] V to its rows.  Every workgroup of a pair does
-//      the same small diagonalisation on the same data, so they agree
-//      bitwise; slice 0 records the measure.
+//      [A_I A_J] <- [A_I A_J] V to its rows.  The first round of a sweep
+//      rotates all pairs of the 2B columns, the others the pairs between the
+//      two blocks, so that every pair of columns is rotated once a sweep.
+//      Every workgroup of a pair does the same small sweep on the same data,
+//      so they agree bitwise; slice 0 records the measure.
+// Both products are on the FP64 matrix cores, straight from memory; a round is
+// then bound by the dependent steps of the small sweep.
 // Splitting the rows keeps every CU busy although a round has only p/(2B)
 // pairs.  When every pair's measure is below the tolerance the columns of A
 // are orthogonal: A = U Sigma with the column norms as singular values.
@@ -34,7 +38,7 @@ constexpr int JB_NT = 256;
 // block at tournament position pos in round r (nb even, position 0 fixed)
 RSRR_DEV int rr_block(int pos, int r, int nb) { return pos == 0 ? 0 : ((pos - 1 + r) % (nb - 1)) + 1; }
 
-constexpr int JR = 256;           // rows per slice of the rotation
+constexpr int JR = 64;            // rows per slice of the rotation (16 per wave)
 constexpr int JRG = 128;          // rows per slice of the Gram matrices
 
 RSRR_DEV int jac_col(int s, int bI, int bJ, int p)
@@ -44,72 +48,116 @@ RSRR_DEV int jac_col(int s, int bI, int bJ, int p)
 }
 
 // 1. partial Gram matrix of rows [slice*JRG, min(m, slice*JRG + JRG)) of pair blockIdx.x.
-// Chunks of JG_RC rows pass through LDS; the next chunk is fetched into
-// registers while the current one is multiplied.
-constexpr int JG_RC = 64;
-constexpr int JG_PER = JG_RC * JB_W / JB_NT;  // entries of a chunk per thread
-
+// The waves take chunks of 16 rows in turn; a lane loads four consecutive rows of its
+// column of either block, which are the four inner indices of its MFMA operands (any
+// order of the rows gives the same sum).  The blocks (I,I), (I,J) and (J,J) are formed,
+// the waves' sums added in order, (J,I) is the conjugate of (I,J).
 __global__ __launch_bounds__(JB_NT) void jacobi_gram_kernel(const double2* __restrict__ A, int lda, int m, int p,
                                                              int nb, int round, double2* __restrict__ Gp)
 {
-    __shared__ double2 tile[JG_RC][JB_W + 1];
+    constexpr int NW = JB_NT / 64;
+    __shared__ double2 part[NW][3][4][64];
     const int pr = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
     const int bI = rr_block(pr, round, nb), bJ = rr_block(nb - 1 - pr, round, nb);
-    const int gp = tid >> 3, gq0 = (tid & 7) * 4;  // each thread: G[gp][gq0..gq0+3]
     const int rlo = slice * JRG, rhi = min(m, rlo + JRG);
-    double2 acc[4];
+    const int cI = jac_col(li, bI, bJ, p), cJ = jac_col(JB_B + li, bI, bJ, p);
+    doublex4 re[3], im[3];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) acc[u] = make_double2(0.0, 0.0);
-    double2 nx[JG_PER];
-    auto fetch = [&](int r0) {
+    for (int t = 0; t < 3; ++t) re[t] = im[t] = doublex4{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-        for (int u = 0; u < JG_PER; ++u) {
-            const int e = tid + JB_NT * u, i = e % JG_RC, sc = e / JG_RC;
-            const int c = jac_col(sc, bI, bJ, p);
-            nx[u] = (c >= 0 && r0 + i < rhi) ? A[(r0 + i) + (long)c * lda] : make_double2(0.0, 0.0);
+    for (int ch = 0; ch < JRG / (16 * NW); ++ch) {
+        const int r0 = rlo + 16 * (wave + NW * ch) + 4 * kq;
+        double2 x[4], y[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            x[u] = (cI >= 0 && r0 + u < rhi) ? A[(r0 + u) + (long)cI * lda] : make_double2(0.0, 0.0);
+            y[u] = (cJ >= 0 && r0 + u < rhi) ? A[(r0 + u) + (long)cJ * lda] : make_double2(0.0, 0.0);
         }
-    };
-    fetch(rlo);
-    for (int r0 = rlo; r0 < rhi; r0 += JG_RC) {
-        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < JG_PER; ++u) {
-            const int e = tid + JB_NT * u;
-            tile[e % JG_RC][e / JG_RC] = nx[u];
-        }
-        __syncthreads();
-        if (r0 + JG_RC < rhi) fetch(r0 + JG_RC);
-#pragma unroll 4
-        for (int i = 0; i < JG_RC; ++i) {
-            const double2 a = tile[i][gp];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[u] = cfma_cj(acc[u], a, tile[i][gq0 + u]);
+        for (int u = 0; u < 4; ++u) {
+            // G_ij = sum conj(a_i) a_j: first operand i, second operand j
+            auto add = [&](int t, double2 a, double2 b) {
+                re[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.x, re[t], 0, 0, 0);
+                im[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.x, b.y, im[t], 0, 0, 0);
+                re[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a.y, b.y, re[t], 0, 0, 0);
+                im[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a.y, b.x, im[t], 0, 0, 0);
+            };
+            add(0, x[u], x[u]);
+            add(1, x[u], y[u]);
+            add(2, y[u], y[u]);
         }
     }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][t][r][lane] = make_double2(re[t][r], im[t][r]);
+    __syncthreads();
     double2* G = Gp + ((long)pr * gridDim.y + slice) * (JB_W * JB_W);
 #pragma unroll
-    for (int u = 0; u < 4; ++u) G[gp * JB_W + gq0 + u] = acc[u];
+    for (int q = 0; q < 3 * 4 * 64 / JB_NT; ++q) {
+        const int e = tid + JB_NT * q, l = e & 63, r = (e >> 6) & 3, t = e >> 8;
+        double2 v = part[0][t][r][l];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v = cadd(v, part[w][t][r][l]);
+        const int i = (l >> 4) + 4 * r, j = l & 15;   // register r of lane l: row l / 16 + 4 r, column l % 16
+        if (t == 0) G[i * JB_W + j] = v;
+        else if (t == 2) G[(JB_B + i) * JB_W + JB_B + j] = v;
+        else {
+            G[i * JB_W + JB_B + j] = v;
+            G[(JB_B + j) * JB_W + i] = cconj(v);
+        }
+    }
 }
 
-// 2. sum the Gram slices of pair blockIdx.x, measure, diagonalise, and rotate the
-// rows of slice blockIdx.y.  One step of the inner sweep applies JB_W / 2
-// disjoint rotations (a_k, b_k) from both sides at once; thread (pi, pj) owns
-// the 2 x 2 entries of G and of V at rows {a_pi, b_pi} x columns {a_pj, b_pj},
-// so the update is done in place and a step needs two barriers.
+// The rotation that makes columns a, b with Gram entries da, db (diagonal) and g = G_ab
+// orthogonal: x_a <- c x_a - conj(e) x_b, x_b <- e x_a + c x_b (e carries the sine).  With
+// tau = db - da and w = |tau| + sqrt(tau^2 + 4|g|^2) the tangent is 2|g|/w, so neither
+// |g| nor a division by it is needed: one square root, one division, one reciprocal root.
+struct JacRot { double c; double2 e; };
+RSRR_DEV JacRot jac_rot(double da, double db, double2 g, double zthr2, double thr2)
+{
+    JacRot r = {1.0, make_double2(0.0, 0.0)};
+    const double h2 = g.x * g.x + g.y * g.y;
+    if (da > zthr2 && db > zthr2 && h2 > thr2 * (da * db)) {
+        const double tau = db - da;
+        const double w = fabs(tau) + sqrt(tau * tau + 4.0 * h2);
+        const double q = (tau >= 0.0 ? 2.0 : -2.0) / w;
+        r.c = 1.0 / sqrt(1.0 + q * q * h2);
+        r.e = make_double2(r.c * q * g.x, r.c * q * g.y);
+    }
+    return r;
+}
+
+// 2. sum the Gram slices of pair blockIdx.x, measure, one sweep of rotations on G, and
+// rotate the rows of slice blockIdx.y.  A step of the sweep applies JB_W / 2 disjoint
+// rotations (a_k, b_k) from both sides at once; thread (qi, qj) owns the 2 x 2 entries of
+// G at rows {a_qi, b_qi} x columns {a_qj, b_qj}, works out both rotations itself from the
+// current G and writes its entries into the other of two buffers, so a step needs one
+// barrier.  240 columns of 240 rows: 22 us a round and 7 us for its Gram matrices (64 + 21 us with
+// two barriers a step, 31 steps every round, one division after the other in 16
+// threads, and both products on the vector units out of LDS).
 __global__ __launch_bounds__(JB_NT) void jacobi_rotate_kernel(double2* __restrict__ A, int lda, int m_apply, int p,
                                                                int nb, int round, const double2* __restrict__ Gp,
-                                                               int slices, int inner_sweeps, double tol, double zthr2,
+                                                               int slices, double tol, double zthr2,
                                                                double* __restrict__ offmax)
 {
     static_assert(JB_NT == (JB_W / 2) * (JB_W / 2), "one thread per 2 x 2 block of a step");
-    __shared__ double2 G[JB_W][JB_W + 1];
+    static_assert(JR == 16 * (JB_NT / 64), "16 rows per wave");
+    __shared__ double2 G[2][JB_W][JB_W + 1];
     __shared__ double2 V[JB_W][JB_W + 1];
-    __shared__ double2 tile[JG_RC][JB_W + 1];
-    __shared__ int pa[JB_W / 2], pb[JB_W / 2], pon[JB_W / 2];
-    __shared__ double pc[JB_W / 2], ps[JB_W / 2];
-    __shared__ double2 pe[JB_W / 2];
     __shared__ double wmax[JB_NT / 64];
     const int pr = blockIdx.x, slice = blockIdx.y, tid = threadIdx.x;
+    const int lane = tid & 63, wave = tid >> 6, li = lane & 15, kq = lane >> 4;
+    const int bI = rr_block(pr, round, nb), bJ = rr_block(nb - 1 - pr, round, nb);
+    // the wave's 16 rows (row li, column kq + 4 t), needed after the sweep
+    const int row = slice * JR + 16 * wave + li;
+    double2 x[JB_W / 4];
+#pragma unroll
+    for (int t = 0; t < JB_W / 4; ++t) {
+        const int c = jac_col(kq + 4 * t, bI, bJ, p);
+        x[t] = (c >= 0 && row < m_apply) ? A[row + (long)c * lda] : make_double2(0.0, 0.0);
+    }
     const double2* src = Gp + (long)pr * slices * (JB_W * JB_W);
     constexpr int PER = JB_W * JB_W / JB_NT;
     {
@@ -136,19 +184,19 @@ __global__ __launch_bounds__(JB_NT) void jacobi_rotate_kernel(double2* __restric
 #pragma unroll
         for (int t = 0; t < PER; ++t) {
             const int e = tid + JB_NT * t;
-            G[e / JB_W][e % JB_W] = g[t];
+            G[0][e / JB_W][e % JB_W] = g[t];
             V[e / JB_W][e % JB_W] = make_double2(e / JB_W == e % JB_W ? 1.0 : 0.0, 0.0);
         }
     }
     __syncthreads();
-    double off = 0.0;
+    double off = 0.0;   // the largest squared measure
     for (int e = tid; e < JB_W * JB_W; e += JB_NT) {
         const int i = e / JB_W, q = e % JB_W;
         if (i == q) continue;
-        const double dp = G[i][i].x, dq = G[q][q].x;
+        const double dp = G[0][i][i].x, dq = G[0][q][q].x;
         if (dp > zthr2 && dq > zthr2) {
-            const double2 g = G[i][q];
-            off = fmax(off, sqrt(g.x * g.x + g.y * g.y) / sqrt(dp * dq));
+            const double2 g = G[0][i][q];
+            off = fmax(off, (g.x * g.x + g.y * g.y) / (dp * dq));
         }
     }
     for (int o = 32; o >= 1; o >>= 1) off = fmax(off, __shfl_xor(off, o));
@@ -156,109 +204,81 @@ __global__ __launch_bounds__(JB_NT) void jacobi_rotate_kernel(double2* __restric
     __syncthreads();
     off = wmax[0];
     for (int w = 1; w < JB_NT / 64; ++w) off = fmax(off, wmax[w]);
+    off = sqrt(off);
     if (slice == 0 && tid == 0) offmax[pr] = off;
     if (off <= tol) return;  // pair already orthogonal: A stays unchanged (uniform over the workgroup)
 
     const int qi = tid / (JB_W / 2), qj = tid % (JB_W / 2);
-    for (int sw = 0; sw < inner_sweeps; ++sw) {
-        for (int st = 0; st < JB_W - 1; ++st) {
-            if (tid < JB_W / 2) {
-                const int ip = rr_block(tid, st, JB_W), iq = rr_block(JB_W - 1 - tid, st, JB_W);
-                const int a_ = ip < iq ? ip : iq, b_ = ip < iq ? iq : ip;
-                const double2 g = G[a_][b_];
-                const double h = sqrt(g.x * g.x + g.y * g.y);
-                const double dA = G[a_][a_].x, dB = G[b_][b_].x;
-                int on = 0;
-                double c = 1.0, s = 0.0;
-                double2 e = make_double2(1.0, 0.0);
-                if (dA > zthr2 && dB > zthr2 && h > 0.25 * tol * sqrt(dA * dB)) {
-                    const double zeta = (dB - dA) / (2.0 * h);
-                    const double t = (zeta >= 0 ? 1.0 : -1.0) / (fabs(zeta) + sqrt(1.0 + zeta * zeta));
-                    c = 1.0 / sqrt(1.0 + t * t);
-                    s = t * c;
-                    e = make_double2(g.x / h, g.y / h);
-                    on = 1;
-                }
-                pa[tid] = a_; pb[tid] = b_; pon[tid] = on; pc[tid] = c; ps[tid] = s; pe[tid] = e;
+    const double thr2 = 0.0625 * tol * tol;
+    const bool all = round == 0;
+    const int steps = all ? JB_W - 1 : JB_B;
+    int cur = 0;
+    for (int st = 0; st < steps; ++st) {
+        auto pair_of = [&](int k, int& a, int& b) {
+            if (all) {
+                const int u = rr_block(k, st, JB_W), v = rr_block(JB_W - 1 - k, st, JB_W);
+                a = min(u, v);
+                b = max(u, v);
+            } else {
+                a = k;
+                b = JB_B + ((k + st) & (JB_B - 1));
             }
-            __syncthreads();
-            // columns a, b (pair qj): x_a <- c x_a - s conj(e) x_b, x_b <- s e x_a + c x_b;
-            // rows a, b (pair qi):    r_a <- c r_a - s e r_b,       r_b <- s conj(e) r_a + c r_b
-            const int ra = pa[qi], rb = pb[qi], ca = pa[qj], cb = pb[qj];
-            const bool oi = pon[qi] != 0, oj = pon[qj] != 0;
-            if (oi || oj) {
-                double2 g00 = G[ra][ca], g01 = G[ra][cb], g10 = G[rb][ca], g11 = G[rb][cb];
-                double2 v00 = V[ra][ca], v01 = V[ra][cb], v10 = V[rb][ca], v11 = V[rb][cb];
-                if (oj) {
-                    const double c = pc[qj], s = ps[qj];
-                    const double2 e = pe[qj], ce = cconj(e);
-                    auto colop = [&](double2& xa, double2& xb) {
-                        const double2 ecq = cmul(ce, xb), exp_ = cmul(e, xa);
-                        const double2 na = make_double2(c * xa.x - s * ecq.x, c * xa.y - s * ecq.y);
-                        xb = make_double2(s * exp_.x + c * xb.x, s * exp_.y + c * xb.y);
-                        xa = na;
-                    };
-                    colop(g00, g01);
-                    colop(g10, g11);
-                    colop(v00, v01);
-                    colop(v10, v11);
-                    V[ra][ca] = v00; V[ra][cb] = v01; V[rb][ca] = v10; V[rb][cb] = v11;
-                }
-                if (oi) {
-                    const double c = pc[qi], s = ps[qi];
-                    const double2 e = pe[qi], ce = cconj(e);
-                    auto rowop = [&](double2& xa, double2& xb) {
-                        const double2 eq = cmul(e, xb), cep = cmul(ce, xa);
-                        const double2 na = make_double2(c * xa.x - s * eq.x, c * xa.y - s * eq.y);
-                        xb = make_double2(s * cep.x + c * xb.x, s * cep.y + c * xb.y);
-                        xa = na;
-                    };
-                    rowop(g00, g10);
-                    rowop(g01, g11);
-                }
-                if (qi == qj) {
-                    // the rotated pair's coupling is zero, its diagonal real
-                    g01 = make_double2(0.0, 0.0);
-                    g10 = make_double2(0.0, 0.0);
-                    g00.y = 0.0;
-                    g11.y = 0.0;
-                }
-                G[ra][ca] = g00; G[ra][cb] = g01; G[rb][ca] = g10; G[rb][cb] = g11;
-            }
-            __syncthreads();
+        };
+        int ra, rb, ca, cb;
+        pair_of(qi, ra, rb);
+        pair_of(qj, ca, cb);
+        const double2 (*Gc)[JB_W + 1] = G[cur];
+        double2 (*Gn)[JB_W + 1] = G[cur ^ 1];
+        double2 g00 = Gc[ra][ca], g01 = Gc[ra][cb], g10 = Gc[rb][ca], g11 = Gc[rb][cb];
+        double2 v00 = V[qi][ca], v01 = V[qi][cb], v10 = V[qi + JB_B][ca], v11 = V[qi + JB_B][cb];
+        const JacRot ri = jac_rot(Gc[ra][ra].x, Gc[rb][rb].x, Gc[ra][rb], zthr2, thr2);
+        const JacRot rj = jac_rot(Gc[ca][ca].x, Gc[cb][cb].x, Gc[ca][cb], zthr2, thr2);
+        // columns a, b: x_a <- c x_a - conj(e) x_b, x_b <- e x_a + c x_b
+        auto colop = [&](double2& xa, double2& xb) {
+            const double2 t = cmul(cconj(rj.e), xb), u = cmul(rj.e, xa);
+            xa = make_double2(rj.c * xa.x - t.x, rj.c * xa.y - t.y);
+            xb = make_double2(u.x + rj.c * xb.x, u.y + rj.c * xb.y);
+        };
+        colop(g00, g01);
+        colop(g10, g11);
+        colop(v00, v01);
+        colop(v10, v11);
+        // rows a, b: r_a <- c r_a - e r_b, r_b <- conj(e) r_a + c r_b
+        auto rowop = [&](double2& xa, double2& xb) {
+            const double2 t = cmul(ri.e, xb), u = cmul(cconj(ri.e), xa);
+            xa = make_double2(ri.c * xa.x - t.x, ri.c * xa.y - t.y);
+            xb = make_double2(u.x + ri.c * xb.x, u.y + ri.c * xb.y);
+        };
+        rowop(g00, g10);
+        rowop(g01, g11);
+        if (qi == qj) {
+            // a rotated pair's coupling is zero, its diagonal real
+            if (ri.e.x != 0.0 || ri.e.y != 0.0) g01 = g10 = make_double2(0.0, 0.0);
+            g00.y = 0.0;
+            g11.y = 0.0;
         }
+        Gn[ra][ca] = g00; Gn[ra][cb] = g01; Gn[rb][ca] = g10; Gn[rb][cb] = g11;
+        V[qi][ca] = v00; V[qi][cb] = v01; V[qi + JB_B][ca] = v10; V[qi + JB_B][cb] = v11;
+        cur ^= 1;
+        __syncthreads();
     }
-    // rotate the rows of this slice: [A_I A_J] <- [A_I A_J] V
-    const int bI = rr_block(pr, round, nb), bJ = rr_block(nb - 1 - pr, round, nb);
-    const int rlo = slice * JR, rhi = min(m_apply, rlo + JR);
-    double2 nxv[JG_PER];
-    auto fetch = [&](int r0) {
+    // [A_I A_J] <- [A_I A_J] V on the wave's rows; the first operand carries V, so that a
+    // lane's output runs along the rows: register r holds column lane / 16 + 4 r
 #pragma unroll
-        for (int u = 0; u < JG_PER; ++u) {
-            const int e = tid + JB_NT * u, i = e % JG_RC, sc = e / JG_RC;
-            const int c = jac_col(sc, bI, bJ, p);
-            nxv[u] = (c >= 0 && r0 + i < rhi) ? A[(r0 + i) + (long)c * lda] : make_double2(0.0, 0.0);
+    for (int h = 0; h < 2; ++h) {
+        doublex4 re = {0.0, 0.0, 0.0, 0.0}, im = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = 0; t < JB_W / 4; ++t) {
+            const double2 v = V[kq + 4 * t][h * JB_B + li];
+            re = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, x[t].x, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, x[t].y, im, 0, 0, 0);
+            re = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, x[t].y, re, 0, 0, 0);
+            im = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, x[t].x, im, 0, 0, 0);
         }
-    };
-    fetch(rlo);
-    for (int r0 = rlo; r0 < rhi; r0 += JG_RC) {
-        __syncthreads();
 #pragma unroll
-        for (int u = 0; u < JG_PER; ++u) {
-            const int e = tid + JB_NT * u;
-            tile[e % JG_RC][e / JG_RC] = nxv[u];
-        }
-        __syncthreads();
-        if (r0 + JG_RC < rhi) fetch(r0 + JG_RC);
-#pragma unroll
-        for (int u = 0; u < JG_PER; ++u) {
-            const int e = tid + JB_NT * u, i = e % JG_RC, sc = e / JG_RC;
-            const int c = jac_col(sc, bI, bJ, p);
-            if (c < 0 || r0 + i >= rhi) continue;
-            double2 v = make_double2(0.0, 0.0);
-#pragma unroll 8
-            for (int t = 0; t < JB_W; ++t) v = cfma(v, tile[i][t], V[t][sc]);
-            A[(r0 + i) + (long)c * lda] = v;
+        for (int r = 0; r < 4; ++r) {
+            const int c = jac_col(h * JB_B + kq + 4 * r, bI, bJ, p);
+            if (c >= 0 && row < m_apply) A[row + (long)c * lda] = make_double2(re[r], im[r]);
         }
     }
 }
@@ -655,15 +675,15 @@ size_t jacobi_work_bytes(int m, int m_apply, int p)
     return pairs * (slices + 1) * JB_W * JB_W * 16 + pairs * 4 + 256;
 }
 
-hipError_t jacobi_round(hipStream_t st, double2* A, int lda, int m, int m_apply, int p, int round, int inner,
-                        double tol, double zthr2, double* offmax, void* work)
+hipError_t jacobi_round(hipStream_t st, double2* A, int lda, int m, int m_apply, int p, int round, double tol,
+                        double zthr2, double* offmax, void* work)
 {
     const int nb = jacobi_blocks(p), pairs = nb / 2;
     const int gs = (std::max(m, 1) + JRG - 1) / JRG, as = (m_apply + JR - 1) / JR;
     double2* Gp = (double2*)work;
     hipLaunchKernelGGL(jacobi_gram_kernel, dim3(pairs, gs), dim3(JB_NT), 0, st, A, lda, m, p, nb, round, Gp);
     hipLaunchKernelGGL(jacobi_rotate_kernel, dim3(pairs, as), dim3(JB_NT), 0, st, A, lda, m_apply, p, nb, round, Gp,
-                       gs, inner, tol, zthr2, offmax);
+                       gs, tol, zthr2, offmax);
     return hipGetLastError();
 }
 

@@ -229,8 +229,8 @@ hipError_t ir_decide(hipStream_t st, int M, int Lmax, const double* rn, const do
 
 // ---- block one-sided Jacobi SVD (basis.hip) ----
 int jacobi_blocks(int p);  // number of column blocks (even) for p columns
-hipError_t jacobi_round(hipStream_t st, double2* A, int lda, int m, int m_apply, int p, int round, int inner,
-                        double tol, double zthr2, double* offmax, void* work);
+hipError_t jacobi_round(hipStream_t st, double2* A, int lda, int m, int m_apply, int p, int round, double tol,
+                        double zthr2, double* offmax, void* work);
 size_t jacobi_work_bytes(int m, int m_apply, int p);  // bytes of `work` for jacobi_round
 hipError_t gather_scale(hipStream_t st, const double2* A, int lda, int m, const int* order, const double* inv,
                         double2* Q, int ldq, int k);
