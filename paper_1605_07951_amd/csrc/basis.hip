@@ -404,8 +404,18 @@ hipError_t gaussian(hipStream_t st, double2* X, int n, int m, int ld, unsigned l
 // skinny (bw columns), so each is split along its long inner dimension into
 // slices that run as one batched MFMA GEMM, and the slices are summed in a
 // fixed order (deterministic).
-constexpr int PK_ROWS = 256;  // inner slice of W = Y^H Yj (rows of Y)
-constexpr int PK_COLS = 128;  // inner slice of Yj -= Y W (columns of Y)
+// The slices are as short as it takes to fill the chip: a 64 x 64 tile walks its slice at
+// 1.7 us per 16 inner indices, whatever else runs (256 rows a slice at n = 2048: 64
+// workgroups, 72 us a product; 64 rows a slice: 31 us, with the faster GEMM).
+constexpr int PK_MIN = 64, PK_TILES = 256;
+// inner slice of W = Y^H Yj (rows of Y) for j0 finished columns: about PK_TILES tiles
+static int pk_rows(int n, int j0)
+{
+    const long want = ((long)n * ((j0 + 63) / 64) / PK_TILES + PK_MIN - 1) / PK_MIN * PK_MIN;
+    return (int)std::max<long>(PK_MIN, want);
+}
+// inner slice of Yj -= Y W (columns of Y)
+static int pk_cols(int n) { return n <= 2048 ? 64 : 128; }
 
 __global__ __launch_bounds__(256) void sum_parts_kernel(const double2* __restrict__ part, int S, int rows, int cols,
                                                          double2* __restrict__ out, int ldo, int sub)
@@ -431,6 +441,7 @@ static hipError_t sum_parts(hipStream_t st, const double2* part, int S, int rows
 static hipError_t project_out(hipStream_t st, double2* Y, int ld, int n, int j0, int bw, double2* W, double2* part)
 {
     double2* Yj = Y + (long)j0 * ld;
+    const int PK_ROWS = pk_rows(n, j0), PK_COLS = pk_cols(n);
     const int S1 = n / PK_ROWS, r1 = n - S1 * PK_ROWS;
     hipError_t e = hipSuccess;
     if (S1 > 0)
@@ -464,115 +475,109 @@ static hipError_t project_out(hipStream_t st, double2* Y, int ld, int n, int j0,
 // The first column that is not dropped always has d_c = G_cc, so flag[0] > 0.
 // Rinv = R^-1 on the kept columns before the cut, so Yb Rinv has orthonormal
 // columns up to eps cond(Yb)^2 (a second pass brings that to eps).  flag[1] =
-// number of kept columns before the cut.  One workgroup; R in the upper
-// triangle of the LDS array, Rinv^T in its strict lower triangle with the
-// diagonal apart.
+// number of kept columns before the cut.
+//
+// One workgroup, bound by the chain of a column's steps.  The elimination G = L D L^H runs
+// on [G | I], so L^-1 (and with it Rinv = L^-H D^-1/2) comes out of the same steps:
+// thread (ti, tj) keeps the entries (ti + 16 a, tj + 16 b) in registers, the upper
+// triangle of G and below it L^-1, and step c publishes row c in one of two LDS buffers
+// and subtracts conj(G_ci) / d times it from every row i > c, one barrier a column
+// (72-115 us before, with three barriers a column, the triangle in LDS and Rinv by a
+// substitution of one thread per column afterwards; 28-39 us now).
 constexpr int QB = 64;        // columns per BCGS2 block
 constexpr int CH_NT = 256;
-constexpr int CH_EPT = (QB * (QB + 1) / 2 + CH_NT - 1) / CH_NT;   // triangle entries per thread
 
 __global__ __launch_bounds__(CH_NT) void block_chol_kernel(const double2* __restrict__ Gin, int bw,
                                                             const double* __restrict__ ref, double thr, double tau,
                                                             double2* __restrict__ Rinv, int* __restrict__ flag)
 {
-    __shared__ double2 A[QB][QB + 1];
-    __shared__ double gd[QB], rd[QB];
-    __shared__ double2 dinv[QB];
-    __shared__ int keep[QB];
-    __shared__ int s_cut;
-    const int tid = threadIdx.x;
-    // entries of the upper triangle owned by this thread: t = j (j + 1) / 2 + i (i <= j),
-    // t = tid, tid + CH_NT, ...; (-1, -1) past the end
-    int2 own[CH_EPT];
+    static_assert(CH_NT == 256 && QB == 64, "a 16 x 16 grid of threads with 4 x 4 entries each");
+    __shared__ double2 row[2][QB];
+    __shared__ double gd[QB], lim2[QB], rd[QB];   // rd: 1 / sqrt(d) of a kept column, 0 otherwise
+    const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+    double2 v[4][4];
 #pragma unroll
-    for (int q = 0; q < CH_EPT; ++q) {
-        const int t = tid + CH_NT * q;
-        int j = (int)((sqrtf(8.0f * (float)t + 1.0f) - 1.0f) * 0.5f);
-        while (j * (j + 1) / 2 > t) --j;
-        while ((j + 1) * (j + 2) / 2 <= t) ++j;
-        const int i = t - j * (j + 1) / 2;
-        own[q] = j < bw ? make_int2(i, j) : make_int2(-1, -1);
-        if (j < bw) A[i][j] = Gin[i + (long)j * bw];
-    }
-    if (tid < bw) gd[tid] = Gin[tid + (long)tid * bw].x;
-    if (tid == 0) s_cut = bw;
-    __syncthreads();
-    for (int c = 0; c < bw; ++c) {
-        if (tid == 0) {
-            const double d = A[c][c].x, g = gd[c];
-            const double lim = thr * (ref ? ref[c] : 1.0), lim2 = lim * lim;
-            int k = 1;
-            if (!(g > lim2) || !(d == d)) {
-                k = 0;                      // dependent on the earlier blocks (or not finite)
-            } else if (d < tau * g) {
-                k = 0;                      // the pivot is not resolved: cut here
-                s_cut = c;
-            } else if (d <= lim2) {
-                k = 0;                      // dependent on the earlier columns of the block
-            }
-            keep[c] = k;
-            rd[c] = k ? sqrt(d) : 0.0;
-        }
-        __syncthreads();
-        if (s_cut < bw) break;              // uniform: read from LDS after the barrier
-        if (!keep[c]) continue;
-        const double ri = 1.0 / rd[c];
-        for (int j = c + 1 + tid; j < bw; j += CH_NT) A[c][j] = make_double2(A[c][j].x * ri, A[c][j].y * ri);
-        if (tid == 0) A[c][c] = make_double2(rd[c], 0.0);
-        __syncthreads();
-        // the trailing triangle: each thread updates the entries it owns below row c
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int q = 0; q < CH_EPT; ++q) {
-            const int i = own[q].x, j = own[q].y;
-            if (i > c) {
-                const double2 a = A[c][i], b = A[c][j];
-                double2 t = A[i][j];
-                // t -= conj(a) b
-                t.x -= a.x * b.x + a.y * b.y;
-                t.y -= a.x * b.y - a.y * b.x;
-                A[i][j] = t;
-            }
+        for (int q = 0; q < 4; ++q) {
+            const int i = ti + 16 * a, j = tj + 16 * q;
+            v[a][q] = (i <= j && j < bw) ? Gin[i + (long)j * bw] : make_double2(0.0, 0.0);
         }
-        __syncthreads();
-    }
-    const int cut = s_cut;
-    for (int c = cut + tid; c < bw; c += CH_NT) {
-        keep[c] = 0;
-        rd[c] = 0.0;
-    }
-    __syncthreads();
-    // Rinv column j (thread j): Rinv_jj = 1 / R_jj, then upwards
-    // Rinv_ij = -(sum_{i<k<=j} R_ik Rinv_kj) / R_ii over the kept rows
     if (tid < bw) {
-        const int j = tid;
-        const bool kj = keep[j] != 0;
-        dinv[j] = make_double2(kj ? 1.0 / rd[j] : 0.0, 0.0);
-        for (int i = j - 1; i >= 0; --i) {
-            double2 v = make_double2(0.0, 0.0);
-            if (kj && keep[i]) {
-                double2 s = cmul(A[i][j], make_double2(1.0 / rd[j], 0.0));
-                for (int k = i + 1; k < j; ++k) s = cfma(s, A[i][k], A[j][k]);
-                v = make_double2(-s.x / rd[i], -s.y / rd[i]);
+        gd[tid] = Gin[tid + (long)tid * bw].x;
+        const double lim = thr * (ref ? ref[tid] : 1.0);
+        lim2[tid] = lim * lim;
+    }
+    if (tid < QB) rd[tid] = 0.0;
+    int cut = bw;
+#pragma unroll
+    for (int ca = 0; ca < 4; ++ca) {
+#pragma unroll 1
+        for (int ct = 0; ct < 16; ++ct) {
+            const int c = 16 * ca + ct;
+            if (c >= cut) break;   // uniform
+            double2* w = row[c & 1];
+            if (ti == ct) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) w[tj + 16 * q] = v[ca][q];
             }
-            A[j][i] = v;
+            __syncthreads();
+            // every thread takes the same decisions from the same values
+            const double d = w[c].x, g = gd[c];
+            if (!(g > lim2[c]) || !(d == d)) continue;   // dependent on the earlier blocks (or not finite)
+            if (d < tau * g) { cut = c; break; }         // the pivot is not resolved: cut here
+            if (d <= lim2[c]) continue;                  // dependent on the earlier columns of the block
+            if (tid == 0) rd[c] = 1.0 / sqrt(d);
+            const double di = 1.0 / d;
+            double2 f[4], x[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const double2 t = w[ti + 16 * a];
+                f[a] = make_double2(t.x * di, -t.y * di);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int j = tj + 16 * q;
+                x[q] = w[j];
+                if (j == c) x[q] = make_double2(1.0, 0.0);   // the diagonal of L^-1
+            }
+#pragma unroll
+            for (int a = ca; a < 4; ++a)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int i = ti + 16 * a, j = tj + 16 * q;
+                    if (i > c && (j >= i || j <= c)) v[a][q] = cfms(v[a][q], f[a], x[q]);
+                }
         }
+        if (cut < 16 * (ca + 1)) break;
     }
     __syncthreads();
-    for (int e = tid; e < bw * bw; e += CH_NT) {
-        const int i = e % bw, j = e / bw;
-        Rinv[e] = i < j ? A[j][i] : (i == j ? dinv[j] : make_double2(0.0, 0.0));
-    }
-    if (tid == 0) {
-        int kept = 0;
-        for (int c = 0; c < bw; ++c) kept += keep[c];
-        flag[0] = cut;
-        flag[1] = kept;
+    // Rinv_kj = conj((L^-1)_jk) / sqrt(d_j)
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = ti + 16 * a, k = tj + 16 * q;
+            if (j >= bw || k >= bw) continue;
+            const double s = j < cut ? rd[j] : 0.0;
+            double2 o = make_double2(0.0, 0.0);
+            if (k < j && s != 0.0) o = make_double2(v[a][q].x * s, -v[a][q].y * s);
+            if (k == j) o.x = s;
+            Rinv[k + (long)j * bw] = o;
+        }
+    if (tid < 64) {
+        const int kept = __popcll(__ballot(tid < cut && rd[tid] != 0.0));
+        if (tid == 0) {
+            flag[0] = cut;
+            flag[1] = kept;
+        }
     }
 }
 
 // G = Yb^H Yb for the bw columns of Yb, split along the rows like project_out.
 static hipError_t gram_block(hipStream_t st, const double2* Yb, int ld, int n, int bw, double2* G, double2* part)
 {
+    const int PK_ROWS = pk_rows(n, bw);
     const int S1 = n / PK_ROWS, r1 = n - S1 * PK_ROWS;
     const long bb = (long)bw * bw;
     hipError_t e = hipSuccess;
@@ -584,11 +589,20 @@ static hipError_t gram_block(hipStream_t st, const double2* Yb, int ld, int n, i
     return e;
 }
 
+// Entries of the partial products: at most PK_TILES tiles of 64 columns (and a slice's rest) of
+// W or of a Gram matrix, or the slices of Yj -= Y W.
+static size_t bcgs2_part(int n, int m)
+{
+    const size_t cols = (size_t)((std::max(m, QB) + 63) / 64) * 64;
+    const size_t p1 = std::min((size_t)(n / PK_MIN + 1) * cols, (size_t)(PK_TILES + 8) * 64 + 2 * cols) * QB;
+    const size_t p2 = (size_t)(m / pk_cols(n) + 1) * n * QB;
+    return std::max(p1, p2);
+}
+
 size_t bcgs2_work_bytes(int n, int m)
 {
     const size_t w = (size_t)m * QB;
-    const size_t p1 = (size_t)(n / PK_ROWS + 1) * std::max(m, QB) * QB, p2 = (size_t)(m / PK_COLS + 1) * n * QB;
-    return (w + std::max(p1, p2) + 2 * (size_t)QB * QB + (size_t)n * QB) * 16 + 512;
+    return (w + bcgs2_part(n, m) + 2 * (size_t)QB * QB + (size_t)n * QB) * 16 + 512;
 }
 
 // Block classical Gram-Schmidt with reorthogonalisation (BCGS2) of Y (n x m,
@@ -607,10 +621,9 @@ hipError_t bcgs2(hipStream_t st, double2* Y, int ld, int n, int m, void* work, d
 {
     const double thr = 4.0 * 2.220446049250313e-16 * sqrt((double)n);
     const double tau = 1e-6;
-    const size_t p1 = (size_t)(n / PK_ROWS + 1) * std::max(m, QB) * QB, p2 = (size_t)(m / PK_COLS + 1) * n * QB;
     double2* W = (double2*)work;
     double2* part = W + (size_t)m * QB;
-    double2* G = part + std::max(p1, p2);
+    double2* G = part + bcgs2_part(n, m);
     double2* Ri = G + (size_t)QB * QB;
     double2* T = Ri + (size_t)QB * QB;
     int* flag = (int*)(T + (size_t)n * QB);
