@@ -339,12 +339,12 @@ static size_t per_point_bytes(int n, int L, int prec)
     b += (size_t)n * 4 + np * 2 * MAX_NB * 8 + 16;
     b += ((size_t)n * n + 255) / 256 * 8 + 8;
     b += (size_t)ld * L * (8 + 16) + (size_t)L * 16;
-    if (prec != RSRR_PREC_C128) {
-        b += (size_t)np * 2 * 128 * 128 * 8 / 2;          // diagonal-block inverses (nb = 128: n/128 panels)
-        b += (size_t)128 * std::max(n, L) * 8;            // scratch rows
-        b += (size_t)lu_pair_elems(n, 128, (int)ld) * 8 * 2;  // paired trailing updates (two for the look-ahead)
-        b += pack_bytes(n, prec);
-    }
+    // diagonal-block inverses, scratch rows and the paired trailing updates (two for the look-ahead)
+    const size_t nb = prec == RSRR_PREC_C128 ? max_panel<double>() : max_panel<float>();
+    const size_t esz = prec == RSRR_PREC_C128 ? 16 : 8;
+    b += ((size_t)(n + nb - 1) / nb * 2 * nb * nb + nb * std::max(n, L)) * esz;
+    b += (size_t)lu_pair_elems(n, (int)nb, (int)ld) * esz * 2;
+    b += pack_bytes(n, prec);
     return b;
 }
 
@@ -354,19 +354,21 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     s.np = perm_panels(n);
     // the real FP32 path (R32_IR) uses the complex FP32 layout with real elements (half the bytes)
     const bool fp32 = prec != RSRR_PREC_C128;
+    const size_t esz = fp32 ? 8 : 16;
     s.nb = fp32 ? std::min(c->nb_c64, max_panel<float>()) : std::min(c->nb_c128, max_panel<double>());
-    s.sInv = fp32 ? (long)((n + s.nb - 1) / s.nb) * 2 * s.nb * s.nb : 0;
-    s.sTmp = fp32 ? (long)s.nb * std::max(n, L) : 0;
-    s.inv = fp32 ? ws_get(c, WS_B0, (size_t)B * s.sInv * 8) : nullptr;
-    s.tmp = fp32 ? ws_get(c, WS_B1, (size_t)B * s.sTmp * 8) : nullptr;
-    s.sPair = fp32 ? lu_pair_elems(n, max_panel<float>(), s.ld) : 0;  // any panel width the LU clamps to
-    const bool la = fp32 && c->lookahead;
-    s.pair = fp32 ? ws_get(c, WS_LUP, (size_t)B * s.sPair * 8 * (la ? 2 : 1)) : nullptr;
-    if (fp32 && (!s.inv || !s.tmp || !s.pair)) return RSRR_ENOMEM;
+    s.sInv = (long)((n + s.nb - 1) / s.nb) * 2 * s.nb * s.nb;
+    s.sTmp = (long)s.nb * std::max(n, L);
+    s.inv = ws_get(c, WS_B0, (size_t)B * s.sInv * esz);
+    s.tmp = ws_get(c, WS_B1, (size_t)B * s.sTmp * esz);
+    // any panel width the LU clamps to
+    s.sPair = lu_pair_elems(n, fp32 ? max_panel<float>() : max_panel<double>(), s.ld);
+    const bool la = c->lookahead;
+    s.pair = ws_get(c, WS_LUP, (size_t)B * s.sPair * esz * (la ? 2 : 1));
+    if (!s.inv || !s.tmp || !s.pair) return RSRR_ENOMEM;
     s.sPack = (long)pack_bytes(n, prec);
     s.pack = s.sPack ? ws_get(c, WS_PACK, (size_t)B * s.sPack) : nullptr;
     if (s.sPack && !s.pack) return RSRR_ENOMEM;
-    s.pair2 = la ? (char*)s.pair + (size_t)B * s.sPair * 8 : nullptr;
+    s.pair2 = la ? (char*)s.pair + (size_t)B * s.sPair * esz : nullptr;
     s.la = la ? c->la : nullptr;
     s.la_a = c->la_a;
     s.la_b = c->la_b;
@@ -377,7 +379,6 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     s.sP = n;
     s.sPerm = (long)s.np * 2 * MAX_NB;
     s.nparts = ((long)n * n + 255) / 256;
-    const size_t esz = prec == RSRR_PREC_C128 ? 16 : 8;
     s.Tlu = ws_get(c, WS_TLU, (size_t)B * s.sT * esz);
     s.Tres = (double2*)ws_get(c, WS_TRES, (size_t)B * s.sT * 16);
     s.ipiv = (int*)ws_get(c, WS_IPIV, (size_t)B * s.sP * 4);
@@ -565,7 +566,7 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
         st = split_groups(
             c, B,
             [&](hipStream_t sm, int b0, int nbg, hipEvent_t ev) -> rsrr_status {
-                LUWork wg = lu_offset(w, b0, prec == RSRR_PREC_R32_IR ? 4 : 8);
+                LUWork wg = lu_offset(w, b0, prec == RSRR_PREC_R32_IR ? 4 : prec == RSRR_PREC_C128 ? 16 : 8);
                 wg.first_panel = ev;
                 if (prec == RSRR_PREC_C128)
                     RSRR_HIP(getrf_batched<double>(sm, (double2*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb, wg, nbg));
@@ -602,7 +603,10 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
         {
             PhaseTimer t(c, &tm[2]);
             RSRR_HIP(bcast_c128(c->stream, n, L, U, ldu, S, lds, sX, B));
-            const LUWork w = s.lu(s.active, nullptr);
+            // the factorisation takes L11^-1 (multipliers of at most one) for its U rows; the solves,
+            // which nothing refines here, substitute: U11 may be as ill-conditioned as T
+            LUWork w = s.lu(s.active, nullptr);
+            w.inv = w.tmp = nullptr;
             st = split_groups(c, B, [&](hipStream_t sm, int b0, int nbg, hipEvent_t) -> rsrr_status {
                 RSRR_HIP(getrs_batched<double>(sm, (const double2*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb,
                                                lu_offset(w, b0), S + b0 * sX, sX, lds, L, nbg));

@@ -36,16 +36,24 @@ const char* update_tile_name(int t);
 
 // C -= A B in complex FP32 on the FP16 matrix cores with split operands (split.hip), for
 // the trailing update of a pivoted LU: |parts of A| <= sqrt(2), columns of B of any scale.
-// split_pack writes the operands of an M x N product of depth K into P (per matrix
-// split_pack_bytes(max(M, N), K) bytes, stride sP bytes); cgemm_split then updates the
+// split_pack_a and split_pack_b write the operands of an M x N product of depth K into P (per
+// matrix split_pack_bytes(max(M, N), K) bytes, stride sP bytes); cgemm_split then updates the
 // columns j0 .. j0 + N - 1 (j0 a multiple of 32) of the product whose N at packing was
 // Npack (C at column j0).  split_ok: sizes for which it replaces cgemm.
 bool split_ok(int M, int N, int K);
 size_t split_pack_bytes(int n, int K);
-hipError_t split_pack(hipStream_t st, int M, int N, int K, const float2* A, int lda, long sA, const float2* B, int ldb,
-                      long sB, void* P, long sP, int batch);
+hipError_t split_pack_a(hipStream_t st, int M, int K, const float2* A, int lda, long sA, void* P, long sP, int batch);
+hipError_t split_pack_b(hipStream_t st, int M, int N, int K, const float2* B, int ldb, long sB, void* P, long sP,
+                        int batch);
 hipError_t cgemm_split(hipStream_t st, int M, int N, int K, int Npack, int j0, const void* P, long sP, float2* C,
                        int ldc, long sC, int batch);
+// The U rows of a pair of 128-wide panels on N trailing columns (A: 256 x N at the pair's first
+// row, interchanged) in place, U0 = L0 A0 and U1 = L1 (A1 - T U0) with L0, T, L1 128 x 128, and
+// the B operand of the M x N update of depth 256 that follows (instead of split_pack_b).
+bool split_urows_ok(int nb, const float2* A, int lda, long sA);
+hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, long s0, const float2* T, int ldt,
+                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, void* P, long sP,
+                       int batch);
 
 // C = beta*C + alpha*op(A)*op(B), complex double on v_mfma_f64_16x16x4f64;
 // op = conjugate transpose when the flag is set.

@@ -997,9 +997,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     UpdateRecorder* rec = w.rec;
     // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `s`, event-timed.  An
     // update done in column parts gives its whole width (Nall) and the part's first column
-    // (j0); with split operands the first part (j0 = 0) packs them for all parts.
+    // (j0); with split operands the first part (j0 = 0) packs them for all parts (B unless the U
+    // rows came packed).
     auto timed_update_on = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
-                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0) {
+                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0, bool bpacked = false) {
         const bool timed = rec && rec->used < rec->cap;
         if (timed) (void)hipEventRecord(rec->ev[2 * rec->used], s);
         if (Nall == 0) Nall = N;
@@ -1007,8 +1008,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             split = w.pack != nullptr && split_ok(M, Nall, kdepth);
             if (split) {
-                if (j0 == 0)
-                    (void)split_pack(s, M, Nall, kdepth, Aop, ldaop, sAop, Bop, lda, sA, w.pack, w.sPack, batch);
+                if (j0 == 0) {
+                    (void)split_pack_a(s, M, kdepth, Aop, ldaop, sAop, w.pack, w.sPack, batch);
+                    if (!bpacked) (void)split_pack_b(s, M, Nall, kdepth, Bop, lda, sA, w.pack, w.sPack, batch);
+                }
                 (void)cgemm_split(s, M, N, kdepth, Nall, j0, w.pack, w.sPack, Cop, lda, sA, batch);
             }
         }
@@ -1045,6 +1048,23 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     // receive panel p's update from that copy; then A22 -= [L21_p' L21_{p+1}]
     // [U12_p; U12_{p+1}] in one product.
     const bool pairing = use_inv && w.pair != nullptr;
+    // The U rows of the pair (q0, q1 = q0 + nb) of full panels p, p + 1 on the columns from q2 on,
+    // with the rows' interchanges, by the split kernels: true when done (and the update's B packed).
+    auto split_pair_rows = [&](hipStream_t s, int q0, int p0, C* TL) -> bool {
+        if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
+            const int q2 = q0 + 2 * nb, rest = n - q2;
+            C* Ar = A + (long)q2 * lda;
+            if (!w.pack || !split_ok(rest, rest, 2 * nb) || !split_urows_ok(nb, Ar + q0, lda, sA)) return false;
+            const int2* pm0 = w.perm + (long)p0 * 2 * MAX_NB;
+            perm_rows<C>(s, pm0, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0, nb, rest, w.active, batch);
+            perm_rows<C>(s, pm0 + 2 * MAX_NB, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0 + nb, nb, rest, w.active,
+                         batch);
+            (void)split_urows(s, rest, rest, panel_inv<C>(w, p0, nb, 0), nb, w.sInv, TL, nb, w.sPair,
+                              panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, w.pack, w.sPack, batch);
+            return true;
+        }
+        return false;
+    };
     int c0 = 0, p = 0;
     // Look-ahead over full pairs (two nb-wide panels with a trailing block after
     // them).  A pair's work splits into a front part that touches only its own
@@ -1072,9 +1092,14 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             copy_rows<C>(s, q1, n, nb, A + (long)q0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
             perm_rows<C>(s, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, q1, nb, nb, w.active, batch);
         };
-        auto back = [&](int q0, int pp, C* Wp) {
+        auto back = [&](int q0, int pp, C* Wp) -> bool {
             const int q1 = q0 + nb, q2 = q1 + nb, rest = n - q2;
             C* TL = Wp + (long)ldw * 2 * nb;
+            if (split_pair_rows(st, q0, pp, TL)) {
+                copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
+                             batch);
+                return true;
+            }
             const int2* pm0 = w.perm + (long)pp * 2 * MAX_NB;
             const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
             C* Ar2 = A + (long)q2 * lda;
@@ -1087,25 +1112,26 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
                               w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0);
             copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
                          batch);
+            return false;
         };
         int buf = 0;
         front(st, 0, 0, Wb[0]);
         if (w.first_panel) (void)hipEventRecord(w.first_panel, st);
         for (;;) {
             const int c2 = c0 + 2 * nb, rest = n - c2;
-            back(c0, p, Wb[buf]);
+            const bool bpacked = back(c0, p, Wb[buf]);
             C* Aop = Wb[buf] + c2;
             const C* Bop = A + c0 + (long)c2 * lda;
             C* Cop = A + c2 + (long)c2 * lda;
             if (rest <= 2 * nb) {
                 // no full pair follows: one update, the loop below finishes the tail
-                timed_update(rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop);
+                timed_update_on(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
                 c0 = c2;
                 p += 2;
                 break;
             }
             const int wn = 2 * nb;
-            timed_update_on(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0);
+            timed_update_on(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
             (void)hipEventRecord(w.ev_a, st);
             // the rest of the update is enqueued before the next pair's panels (a chain of
             // small launches), so the host never holds it back behind them

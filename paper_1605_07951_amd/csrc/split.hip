@@ -57,6 +57,13 @@ RSRR_DEV void split4(const float2 (&v)[4], int e, uintx4* hi, uintx4* lo)
     *lo = __builtin_bit_cast(uintx4, l);
 }
 
+// Exponent that scales a largest part to [2^SP_BTOP, 2^(SP_BTOP + 1)); zero or non-finite: no scale.
+RSRR_DEV int split_expo(float top)
+{
+    // v_frexp_exp: top = m 2^e with m in [1/2, 1)
+    return (top > 0.f && isfinite(top)) ? SP_BTOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
+}
+
 // A (M x K): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l holds
 // row l % 32 and the 4 complex k at 4 (l / 32).  One wave per row block and k chunk; rows past M are zero.
 __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, const float2* __restrict__ A, int lda, long sA,
@@ -102,8 +109,7 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, const f
         }
 #pragma unroll
     for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
-    // v_frexp_exp: top = m 2^e with m in [1/2, 1); a zero or non-finite column keeps its scale
-    const int e = (top > 0.f && isfinite(top)) ? SP_BTOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
+    const int e = split_expo(top);
     char* Pb = P + b * sP;
     if (part == 0) reinterpret_cast<int*>(Pb + expo_off)[j] = e;
 #pragma unroll
@@ -116,6 +122,188 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, const f
         dst[c + 32 * (p & 1)] = hi;
         dst[64 + c + 32 * (p & 1)] = lo;
     }
+}
+
+// The U rows of a pair of 128-wide panels on the trailing columns, with the packed operand of the
+// update that follows: for every column x = [x0; x1] (the 256 rows of the pair after both panels'
+// interchanges)
+//     u0 = L0^-1 x0,   u1 = L1^-1 (x1 - T u0),
+// L0^-1 and L1^-1 the inverses of the panels' unit triangles and T the rows of L21 of the
+// first panel beside the second.  Three products of 128 x 128 on 32 columns per workgroup,
+// split like the update (their left factors packed once with a power of two per row, the
+// columns split here), instead of three GEMM launches and a packing pass that wrote and
+// read the 256 rows each time: bound by reading them once and writing them twice (U and
+// packed).  n = 4096, 64 matrices, all pairs: 5.3 ms a factorisation (three FP32 3M launches and
+// the packing pass 11 ms).
+constexpr int UR_NB = 128, UR_KC = UR_NB / SP_KC, UR_LD = UR_NB + 2;
+constexpr long UR_OPERAND = (long)(UR_NB / 32) * UR_KC * 2 * SP_FRAG;   // bytes of one packed factor
+
+// The three left factors (128 x 128, ld ldf[f]) packed with a scale per row; expo at eoff.  One
+// workgroup per 32 rows, factor and matrix: thread (row t % 32, 16 columns of part t / 32).
+struct UrFactors { const float2* p[3]; long stride[3]; int ld[3]; };
+__global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, char* __restrict__ P, long sP, long eoff)
+{
+    const int rb = blockIdx.x, f = blockIdx.y, b = blockIdx.z, t = threadIdx.x;
+    const int r = t & 31, part = t >> 5;
+    __shared__ float tops[8][32];
+    const float2* src = F.p[f] + b * F.stride[f] + rb * 32 + r;
+    float2 v[4][4];
+    float top = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            v[q][u] = src[(long)(16 * part + 4 * q + u) * F.ld[f]];
+            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+        }
+    tops[part][r] = top;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) top = fmaxf(top, tops[q][r]);
+    const int e = split_expo(top);
+    char* Pb = P + b * sP;
+    if (part == 0) reinterpret_cast<int*>(Pb + eoff)[f * UR_NB + rb * 32 + r] = e;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        uintx4 hi, lo;
+        split4(v[q], e, &hi, &lo);
+        uintx4* dst = reinterpret_cast<uintx4*>(Pb + f * UR_OPERAND +
+                                                ((long)rb * UR_KC + 2 * part + q / 2) * 2 * SP_FRAG);
+        dst[r + 32 * (q & 1)] = hi;
+        dst[64 + r + 32 * (q & 1)] = lo;
+    }
+}
+
+__global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict__ A, int lda, long sA, int ncols,
+                                                             const char* __restrict__ P3, long sP, long eoff,
+                                                             char* __restrict__ PB, long expo_off)
+{
+    __shared__ __attribute__((aligned(16))) char F[UR_KC * 2 * SP_FRAG];   // the split columns
+    __shared__ __attribute__((aligned(16))) float2 S[32 * UR_LD];          // a product, column by column
+    __shared__ int ex[32];
+    const int b = blockIdx.y, t = threadIdx.x;
+    const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int c = t >> 3, part = t & 7;   // column, and every eighth group of four rows of it
+    const int j = blockIdx.x * 32 + c;
+    const bool ok = j < ncols;
+    float2* col = A + b * sA + (long)j * lda;
+    auto fetch = [&](const float2* src, float2 (&v)[4][4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const floatx4* p = reinterpret_cast<const floatx4*>(src + 4 * (part + 8 * q));
+            const floatx4 x = p[0], y = p[1];
+            v[q][0] = make_float2(x[0], x[1]);
+            v[q][1] = make_float2(x[2], x[3]);
+            v[q][2] = make_float2(y[0], y[1]);
+            v[q][3] = make_float2(y[2], y[3]);
+        }
+    };
+    auto store = [&](float2* dst, const float2 (&v)[4][4]) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            floatx4* p = reinterpret_cast<floatx4*>(dst + 4 * (part + 8 * q));
+            p[0] = floatx4{v[q][0].x, v[q][0].y, v[q][1].x, v[q][1].y};
+            p[1] = floatx4{v[q][2].x, v[q][2].y, v[q][3].x, v[q][3].y};
+        }
+    };
+    auto top_of = [&](const float2 (&v)[4][4]) {
+        float top = 0.f;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
+        return top;
+    };
+    // four-row group q of the thread goes to fragment (part + 8 q) / 2 of dst
+    auto put = [&](char* dst, const float2 (&v)[4][4], int e) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int p = part + 8 * q;
+            uintx4 hi, lo;
+            split4(v[q], e, &hi, &lo);
+            uintx4* d = reinterpret_cast<uintx4*>(dst + (long)(p >> 1) * 2 * SP_FRAG);
+            d[c + 32 * (p & 1)] = hi;
+            d[64 + c + 32 * (p & 1)] = lo;
+        }
+    };
+    const char* Pb = P3 + b * sP;
+    const int li = lane & 31, half = lane >> 5;
+    // S = factor f times the split columns; wave w takes the rows 32 w .. 32 w + 31
+    auto product = [&](int f) {
+        const uintx4* fa = reinterpret_cast<const uintx4*>(Pb + f * UR_OPERAND + (long)wave * UR_KC * 2 * SP_FRAG) + lane;
+        const uintx4* fb = reinterpret_cast<const uintx4*>(F) + lane;
+        const int er = reinterpret_cast<const int*>(Pb + eoff)[f * UR_NB + wave * 32 + li];
+        floatx16 re, im;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) re[r] = im[r] = 0.f;
+#pragma unroll 4
+        for (int kc = 0; kc < UR_KC; ++kc) {
+            uintx4 a[2], br[2], bi[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                a[h] = fa[(kc * 2 + h) * 64];
+                const uintx4 v = fb[(kc * 2 + h) * 64];
+                br[h] = v ^ 0x80000000u;              // (Br, -Bi)
+                bi[h] = (v << 16) | (v >> 16);        // (Bi, Br)
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {   // lo hi, hi lo, hi hi
+                const int ha = p == 0, hb = p == 1;
+                re = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, br[hb]),
+                                                            __builtin_bit_cast(half8, a[ha]), re, 0, 0, 0);
+                im = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(half8, bi[hb]),
+                                                            __builtin_bit_cast(half8, a[ha]), im, 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int cc = 8 * (r >> 2) + 4 * half + (r & 3);
+            const int e = -(er + ex[cc]);
+            S[cc * UR_LD + wave * 32 + li] = make_float2(ldexpf(re[r], e), ldexpf(im[r], e));
+        }
+    };
+    float2 v0[4][4] = {}, v1[4][4] = {};
+    if (ok) {
+        fetch(col, v0);
+        fetch(col + UR_NB, v1);
+    }
+    auto split = [&](const float2 (&v)[4][4]) {
+        const int e = split_expo(top_of(v));
+        if (part == 0) ex[c] = e;
+        put(F, v, e);
+        __syncthreads();
+    };
+    split(v0);
+    product(0);
+    __syncthreads();
+    fetch(S + c * UR_LD, v0);
+    split(v0);
+    product(1);
+    __syncthreads();
+    {
+        float2 w[4][4];
+        fetch(S + c * UR_LD, w);
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v1[q][u] = csub(v1[q][u], w[q][u]);
+    }
+    split(v1);
+    product(2);
+    __syncthreads();
+    fetch(S + c * UR_LD, v1);
+    if (ok) {
+        store(col, v0);
+        store(col + UR_NB, v1);
+    }
+    // the update's operand: one scale for the 256 rows of the column
+    const int e = split_expo(fmaxf(top_of(v0), top_of(v1)));
+    char* dst = PB + b * sP + (long)blockIdx.x * 2 * UR_KC * 2 * SP_FRAG;
+    if (part == 0) reinterpret_cast<int*>(PB + b * sP + expo_off)[j] = e;
+    put(dst, v0, e);
+    put(dst + (long)UR_KC * 2 * SP_FRAG, v1, e);
 }
 
 // Workgroup tile 128 x 128, four waves of 64 x 64 (2 x 2 blocks of 32 x 32, real and imaginary
@@ -252,25 +440,54 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
 
 static long sp_operand_bytes(int rows, int K) { return (long)((rows + 31) / 32) * ((K + SP_KC - 1) / SP_KC) * 2 * SP_FRAG; }
 
+// Layout of the pack buffer: A, B, B's column exponents, then the three left factors of the U rows
+// with their row exponents (the offsets follow from the sizes of the product).
 size_t split_pack_bytes(int n, int K)
 {
-    return 2 * (size_t)sp_operand_bytes(n, K) + ((size_t)n + 31) / 32 * 32 * 4;
+    return 2 * (size_t)sp_operand_bytes(n, K) + ((size_t)n + 31) / 32 * 32 * 4 + 3 * UR_OPERAND + 3 * UR_NB * 4;
+}
+static long sp_factors_off(int M, int N, int K)
+{
+    return sp_operand_bytes(M, K) + sp_operand_bytes(N, K) + (long)(N + 31) / 32 * 32 * 4;
 }
 
 // Depths of at least one panel (the error is below the FP32 kernel's from K = 64 on); fewer
 // than 128 rows or columns leave most of a tile empty and do not pay for the packing.
 bool split_ok(int M, int N, int K) { return K >= 128 && K <= SP_KMAX && M >= 128 && N >= 128; }
 
-hipError_t split_pack(hipStream_t st, int M, int N, int K, const float2* A, int lda, long sA, const float2* B, int ldb,
-                      long sB, void* P, long sP, int batch)
+hipError_t split_pack_a(hipStream_t st, int M, int K, const float2* A, int lda, long sA, void* P, long sP, int batch)
 {
-    const long na = sp_operand_bytes(M, K), nb = sp_operand_bytes(N, K);
-    char* Pa = (char*)P;
-    const long frags = na / (2 * SP_FRAG);
+    const long frags = sp_operand_bytes(M, K) / (2 * SP_FRAG);
     hipLaunchKernelGGL(split_pack_a_kernel, dim3((unsigned)((frags + 3) / 4), batch), dim3(256), 0, st, M, K, A, lda,
-                       sA, Pa, sP);
-    hipLaunchKernelGGL(split_pack_b_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, B, ldb, sB, Pa + na, sP,
-                       nb);
+                       sA, (char*)P, sP);
+    return hipGetLastError();
+}
+
+hipError_t split_pack_b(hipStream_t st, int M, int N, int K, const float2* B, int ldb, long sB, void* P, long sP,
+                        int batch)
+{
+    hipLaunchKernelGGL(split_pack_b_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, B, ldb, sB,
+                       (char*)P + sp_operand_bytes(M, K), sP, sp_operand_bytes(N, K));
+    return hipGetLastError();
+}
+
+bool split_urows_ok(int nb, const float2* A, int lda, long sA)
+{
+    return nb == UR_NB && (((uintptr_t)A) & 15) == 0 && lda % 2 == 0 && sA % 2 == 0;
+}
+
+hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, long s0, const float2* T, int ldt,
+                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, void* P, long sP,
+                       int batch)
+{
+    constexpr int K = 2 * UR_NB;
+    char* Pc = (char*)P;
+    const long off = sp_factors_off(M, N, K);
+    const UrFactors F = {{L0, T, L1}, {s0, sT, s1}, {ld0, ldt, ld1}};
+    hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, Pc + off, sP,
+                       3 * UR_OPERAND);
+    hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, Pc + off, sP,
+                       3 * UR_OPERAND, Pc + sp_operand_bytes(M, K), sp_operand_bytes(N, K));
     return hipGetLastError();
 }
 
