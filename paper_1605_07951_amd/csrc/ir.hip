@@ -280,7 +280,7 @@ __global__ __launch_bounds__(EW_NT) void ir_decide_kernel(int M, int Lmax, const
 }
 
 
-// R_b = U_b - T_b X_b (U null: T_b X_b) in FP64 for at most 16 right-hand sides: the
+// R_b = U_b - T_b X_b (U null: T_b X_b) in FP64 for at most 32 right-hand sides: the
 // product is skinny, so it is a stream over T, bound by HBM where there are enough
 // rows.  A workgroup takes the rows of one row block of one matrix; its W waves split
 // the columns of T (a contiguous range each) and their partial sums are added in the
@@ -292,9 +292,11 @@ __global__ __launch_bounds__(EW_NT) void ir_decide_kernel(int M, int Lmax, const
 //
 // Up to 8 columns (resid_stream_kernel): a lane owns RPT rows, the loads of T are
 // coalesced, and X(k, c), the same for the whole wave, comes through the scalar cache.
-// 9 to 16 columns (resid_mfma_kernel): v_mfma_f64_16x16x4f64 on four 16-row blocks per
-// wave; a lane loads whole complex entries and the real and imaginary parts go through
-// separate instructions (inner index: four consecutive k).
+// 9 to 32 columns (resid_mfma_kernel): v_mfma_f64_16x16x4f64 on four 16-row blocks and one or
+// two 16-column blocks per wave; a lane loads whole complex entries and the real and
+// imaginary parts go through separate instructions (inner index: four consecutive k).
+// 17 to 32 columns fill half of a GEMM tile's 64: n = 1024, L = 32, 48 points 441 us there,
+// 335 us here (T read once takes 170 us at a copy's rate, the products 177 us).
 
 // The waves' partial sums (acc: NV values per lane) added in order into wave 0's.
 template <int NV, int W>
@@ -383,7 +385,7 @@ __global__ __launch_bounds__(64 * W) void resid_stream_kernel(int n, int L, cons
     }
 }
 
-template <int W>
+template <int CB, int W>
 __global__ __launch_bounds__(64 * W) void resid_mfma_kernel(int n, int L, const double2* __restrict__ T, int ldt,
                                                             long sT, const double2* __restrict__ X, int ldx, long sX,
                                                             const double2* __restrict__ U, int ldu, long sU,
@@ -391,7 +393,7 @@ __global__ __launch_bounds__(64 * W) void resid_mfma_kernel(int n, int L, const 
                                                             const int* __restrict__ active)
 {
     constexpr int RB = 4;   // 16-row blocks per wave
-    __shared__ double2 part[(W - 1) * RB * 4 * 64];
+    __shared__ double2 part[(W - 1) * RB * 4 * 64];   // one column block at a time
     const int b = blockIdx.y;
     if (active && !active[b]) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -400,21 +402,26 @@ __global__ __launch_bounds__(64 * W) void resid_mfma_kernel(int n, int L, const 
     const int per = ((n + W - 1) / W + 3) / 4 * 4;
     const int k0 = min(n, wave * per), k1 = min(n, k0 + per);
     const double2* Tb = T + b * sT;
-    const double2* Xc = X + b * sX + (long)min(li, L - 1) * ldx;   // columns past L are not stored
+    const double2* Xc[CB];   // columns past L are not stored
+#pragma unroll
+    for (int y = 0; y < CB; ++y) Xc[y] = X + b * sX + (long)min(16 * y + li, L - 1) * ldx;
     int rr[RB];
 #pragma unroll
     for (int x = 0; x < RB; ++x) rr[x] = min(row0 + 16 * x, n - 1);
-    doublex4 accR[RB], accI[RB];
+    doublex4 accR[RB][CB], accI[RB][CB];
 #pragma unroll
-    for (int x = 0; x < RB; ++x) accR[x] = accI[x] = doublex4{0.0, 0.0, 0.0, 0.0};
+    for (int x = 0; x < RB; ++x)
+#pragma unroll
+        for (int y = 0; y < CB; ++y) accR[x][y] = accI[x][y] = doublex4{0.0, 0.0, 0.0, 0.0};
     // G groups of four k: all loads first; past the wave's range T counts as zero
     auto step = [&](int k, auto groups) {
         constexpr int G = decltype(groups)::value;
-        double2 xv[G], t[G][RB];
+        double2 xv[G][CB], t[G][RB];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const int kk = k + 4 * g + kq, kc = min(kk, k1 - 1);
-            xv[g] = Xc[kc];
+#pragma unroll
+            for (int y = 0; y < CB; ++y) xv[g][y] = Xc[y][kc];
 #pragma unroll
             for (int x = 0; x < RB; ++x) {
                 t[g][x] = Tb[rr[x] + (long)kc * ldt];
@@ -425,36 +432,44 @@ __global__ __launch_bounds__(64 * W) void resid_mfma_kernel(int n, int L, const 
 #pragma unroll
         for (int g = 0; g < G; ++g)
 #pragma unroll
-            for (int x = 0; x < RB; ++x) {
-                accR[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[g].x, t[g][x].x, accR[x], 0, 0, 0);
-                accI[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[g].y, t[g][x].x, accI[x], 0, 0, 0);
-                accR[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(-xv[g].y, t[g][x].y, accR[x], 0, 0, 0);
-                accI[x] = __builtin_amdgcn_mfma_f64_16x16x4f64(xv[g].x, t[g][x].y, accI[x], 0, 0, 0);
-            }
+            for (int x = 0; x < RB; ++x)
+#pragma unroll
+                for (int y = 0; y < CB; ++y) {
+                    const double2 v = xv[g][y], a = t[g][x];
+                    accR[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, a.x, accR[x][y], 0, 0, 0);
+                    accI[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.y, a.x, accI[x][y], 0, 0, 0);
+                    accR[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(-v.y, a.y, accR[x][y], 0, 0, 0);
+                    accI[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(v.x, a.y, accI[x][y], 0, 0, 0);
+                }
     };
     int k = k0;
     for (; k + 8 <= k1; k += 8) step(k, std::integral_constant<int, 2>{});
     for (; k < k1; k += 4) step(k, std::integral_constant<int, 1>{});
-    double2 acc[RB * 4];   // lane li: row, register r: column kq + 4 r
-#pragma unroll
-    for (int x = 0; x < RB; ++x)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[x * 4 + r] = make_double2(accR[x][r], accI[x][r]);
-    wave_partials<RB * 4, W>(acc, part, wave, lane);
-    if (wave > 0) return;
     double2* Rb = R + b * sR;
     const double2* Ub = U ? U + b * sU : nullptr;
 #pragma unroll
-    for (int x = 0; x < RB; ++x) {
-        const int row = row0 + 16 * x;
-        if (row >= n) continue;
+    for (int y = 0; y < CB; ++y) {
+        double2 acc[RB * 4];   // lane li: row, register r: column kq + 4 r
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int c = kq + 4 * r;
-            if (c < L) {
-                double2 v = acc[x * 4 + r];
-                if (Ub) v = csub(Ub[row + (long)c * ldu], v);
-                Rb[row + (long)c * ldr] = v;
+        for (int x = 0; x < RB; ++x)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[x * 4 + r] = make_double2(accR[x][y][r], accI[x][y][r]);
+        if (y > 0) __syncthreads();   // wave 0 has read the previous block's sums
+        wave_partials<RB * 4, W>(acc, part, wave, lane);
+        if (wave == 0) {
+#pragma unroll
+            for (int x = 0; x < RB; ++x) {
+                const int row = row0 + 16 * x;
+                if (row >= n) continue;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int c = 16 * y + kq + 4 * r;
+                    if (c < L) {
+                        double2 v = acc[x * 4 + r];
+                        if (Ub) v = csub(Ub[row + (long)c * ldu], v);
+                        Rb[row + (long)c * ldr] = v;
+                    }
+                }
             }
         }
     }
@@ -584,7 +599,7 @@ hipError_t scale_cols(hipStream_t st, int n, int m, double2* X, int ldx, const d
 }
 
 
-bool resid_skinny_ok(int L) { return L >= 1 && L <= 16; }
+bool resid_skinny_ok(int L) { return L >= 1 && L <= 32; }
 
 hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt, long sT, const double2* X, int ldx,
                         long sX, const double2* U, int ldu, long sU, double2* R, int ldr, long sR, const int* active,
@@ -594,9 +609,9 @@ hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt,
     hipLaunchKernelGGL((resid_stream_kernel<LC, RPT, W>), dim3((unsigned)((n + 64 * RPT - 1) / (64 * RPT)),          \
                                                                (unsigned)B),                                        \
                        dim3(64 * W), 0, st, n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
-#define RS_M(W)                                                                                                      \
-    hipLaunchKernelGGL(resid_mfma_kernel<W>, dim3((unsigned)((n + 63) / 64), (unsigned)B), dim3(64 * W), 0, st, n, L, \
-                       T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
+#define RS_M(CB, W)                                                                                                  \
+    hipLaunchKernelGGL((resid_mfma_kernel<CB, W>), dim3((unsigned)((n + 63) / 64), (unsigned)B), dim3(64 * W), 0, st, \
+                       n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
     // few row blocks (fewer than two per CU): the columns are split over more waves
     const bool few = (long)((n + 63) / 64) * B < 512;
     if (L <= 2) {
@@ -605,8 +620,10 @@ hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt,
         if (few) RS_L(4, 1, 8); else RS_L(4, 2, 4);
     } else if (L <= 8) {
         if (few) RS_L(8, 1, 8); else RS_L(8, 1, 4);
+    } else if (L <= 16) {
+        RS_M(1, 4);
     } else {
-        RS_M(4);
+        RS_M(2, 4);
     }
 #undef RS_M
 #undef RS_L

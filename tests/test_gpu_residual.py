@@ -1,4 +1,4 @@
-"""GPU: the FP64 residual of at most 16 columns at the edges of its row blocks, column
+"""GPU: the FP64 residual of at most 32 columns at the edges of its row blocks, column
 counts and point counts (few points: the columns of T split over more waves).
 
 The refinement only converges on a right residual, and the residual it reports is
@@ -42,7 +42,7 @@ def _run(ctx, n, N, L, ldu=0):
         assert abs(info[k]["resid"] - rel) <= 8 * max(n, 4) * U64 * (den / np.linalg.norm(U, axis=0)).max()
 
 
-@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 8, 9, 15, 16, 17])
+@pytest.mark.parametrize("L", [1, 2, 3, 4, 5, 8, 9, 15, 16, 17, 31, 32, 33])
 @pytest.mark.parametrize("n", [1, 3, 31, 63, 65, 129, 515])
 def test_residual_edges(ctx, n, L):
     _run(ctx, n, 3, L)
