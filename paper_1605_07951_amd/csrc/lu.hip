@@ -1278,209 +1278,248 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
 // ----------------------------------------------------------------------------
 // The whole solve of getrs_impl (complex FP32, diagonal blocks by their
 // inverses) for one matrix per workgroup, for right-hand-side blocks that fit
-// in LDS: X (n x L, held row by row) is read once, every panel's forward step
-// (interchanges, X_p = L11^-1 X_p, rows below -= L21 X_p) and backward step
-// (X_p = U11^-1 X_p, rows above -= U12 X_p) runs out of LDS while the factor
-// columns stream from memory once, and X is written back at the end.  The
-// same operations as the launch-per-step chain, so the same result up to the
-// order of the sums; a matrix with active[b] == 0 is left as it is.
+// in LDS: X is read once, every panel's forward step (interchanges,
+// X_p = L11^-1 X_p, rows below -= L21 X_p) and backward step (X_p = U11^-1 X_p,
+// rows above -= U12 X_p) runs out of LDS while the factor columns stream from
+// memory once, and X is written back at the end.  The same operations as
+// the launch-per-step chain, so the same result up to the order of the sums;
+// a matrix with active[b] == 0 is left as it is.
 //
-// Work split: a product row is summed by kg adjacent lanes (lane g of the
-// group takes the columns k = g, g + kg, ...) whose partial sums are combined
-// by butterfly shuffles in a fixed order.  The diagonal blocks (at most 128
-// rows) use kg = 4, so every lane has its share of the block's columns in
-// flight at once; the off-diagonal updates use kg = 1, 2 or 4 as the number
-// of rows left shrinks, so the late panels of a sweep keep every lane busy.
-// The factor and the inverses are read straight from memory (no staging),
-// which leaves the LDS to X alone: n = 1024 with 8 right-hand sides takes
-// 64 KB, two workgroups per compute unit.
+// The products run on v_mfma_f32_16x16x4f32: the 16 columns of one operand are the real
+// and the imaginary parts of 8 right-hand sides, so one instruction for the real and one
+// for the imaginary parts of the factor give 16 rows of the complex product.  A
+// lane's factor entry (row lane % 16, column lane / 16 of four) goes from memory
+// into its registers, and the panel's X_p stays in registers for all rows of the update.
+// A row of X in LDS: per 8 right-hand sides 8 real, then 8 imaginary parts.
+//
+// Bound by the serial chain of panels and by what one compute unit streams and multiplies
+// (8 n^2 bytes, 8 right-hand sides: n^2 / 64 pairs of 32-cycle instructions on four SIMDs,
+// 109 us at n = 1000).  One launch for the 3 a panel step of the chain, so it is the faster
+// way wherever X fits.  Chain / this kernel / the same split on the vector unit, in us: n =
+// 256, 8 right-hand sides, 72 matrices 95 / 31 / 91, n = 1000 541 / 319 / 795 (1 matrix 460 / 252 /
+// 724, 256 matrices 795 / 409 / 875); 16 right-hand sides, 72 matrices, n = 512 241 / 136 / 534, n =
+// 1024 571 / 464 / 1580; n = 2048, 8 right-hand sides, 1 / 32 matrices 950 / 1081 (chain), 874 / 1031.
 // ----------------------------------------------------------------------------
-constexpr int GS_NT = 512;
-constexpr int GS_KU = 16;           // factor entries of one row in flight per lane
-constexpr int GS_DK = MAX_NB / 4;   // diagonal-block entries per lane (4 lanes per row)
+constexpr int GS_NT = 512, GS_NW = GS_NT / 64;
+constexpr int GS_G = 8;                      // groups of four columns per batch of loads
+constexpr int GS_Q = MAX_NB / (4 * GS_G);    // batches per panel
 
-// sum of v over the kg adjacent lanes of a group (kg a power of two <= 4; every
-// lane of the wave takes part)
-template <int LT>
-RSRR_DEV void group_sum(float2 (&v)[LT], int kg)
-{
-    for (int off = 1; off < kg; off <<= 1) {
-#pragma unroll
-        for (int l = 0; l < LT; ++l) {
-            v[l].x += __shfl_xor(v[l].x, off);
-            v[l].y += __shfl_xor(v[l].y, off);
-        }
-    }
-}
-
-// p[off] for a uniform base p and a 32-bit element offset (the byte offset
-// fits in 32 bits), so that the load takes the scalar-base form
-RSRR_DEV float2 ldg_off(const float2* __restrict__ p, unsigned off)
-{
-    return *(const float2*)((const char*)p + (size_t)(off * 8u));
-}
-
-// rows [r0, r1) of X (in LDS, LT per row) -= A(r0:r1, c0:c0+jb) X(c0:c0+jb),
-// KG lanes per row; the factor offsets fit in 32 bits (n <= 2048)
-template <int LT, int KG>
-RSRR_DEV void getrs_lds_update(const float2* __restrict__ A, int lda, float2* xs, int r0, int r1, int c0, int jb,
-                               int tid)
-{
-    constexpr int ROWS = GS_NT / KG;
-    const int i = tid / KG, g = tid % KG;
-    for (int rb = r0; rb < r1; rb += ROWS) {
-        const int r = rb + i;
-        const bool on = r < r1;
-        float2 acc[LT];
-#pragma unroll
-        for (int l = 0; l < LT; ++l) acc[l] = make_float2(0.f, 0.f);
-        for (int kb = 0; kb < jb; kb += GS_KU * KG) {
-            const unsigned rc = (unsigned)min(r, r1 - 1);
-            float2 a[GS_KU];
-#pragma unroll
-            for (int u = 0; u < GS_KU; ++u) {
-                const int k = kb + g + u * KG;
-                const float2 v = ldg_off(A, rc + (unsigned)(c0 + min(k, jb - 1)) * (unsigned)lda);
-                a[u] = (on && k < jb) ? v : make_float2(0.f, 0.f);
-            }
-#pragma unroll
-            for (int u = 0; u < GS_KU; ++u) {
-                const int k = kb + g + u * KG;
-                if (k < jb) {
-#pragma unroll
-                    for (int l = 0; l < LT; ++l) acc[l] = cfma(acc[l], a[u], xs[(c0 + k) * LT + l]);
-                }
-            }
-        }
-        group_sum<LT>(acc, KG);
-        if (on) {
-#pragma unroll
-            for (int l = 0; l < LT; ++l)
-                if (l % KG == g) {
-                    const float2 x = xs[r * LT + l];
-                    xs[r * LT + l] = make_float2(x.x - acc[l].x, x.y - acc[l].y);
-                }
-        }
-    }
-}
-
-template <int LT>
-__global__ __launch_bounds__(GS_NT) __attribute__((amdgpu_waves_per_eu(4))) void getrs_lds_kernel(const float2* __restrict__ LU, long sLU, int lda, int n,
-                                                          int nb, const int2* __restrict__ perm, long sPerm,
+// CB blocks of 8 right-hand sides
+template <int CB>
+__global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restrict__ LU, long sLU, int lda, int n, int nb,
+                                                          const int2* __restrict__ perm, long sPerm,
                                                           const float2* __restrict__ inv, long sInv,
                                                           float2* __restrict__ X, long sX, int ldx, int L,
                                                           const int* __restrict__ active)
 {
-    extern __shared__ float2 xs[];   // n x LT, row r at xs + r LT (columns >= L stay zero)
+    constexpr int LD = 16 * CB;              // floats per row of X
+    constexpr int NX = CB == 1 ? 2 : 1;      // blocks of rows per wave (two need more registers than there are)
+    extern __shared__ __attribute__((aligned(16))) float xs[];
     const int b = blockIdx.x, tid = threadIdx.x;
     if (active && !active[b]) return;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, g = lane >> 4;
     const float2* A = LU + (long)b * sLU;
     float2* Xb = X + (long)b * sX;
-    for (long e = tid; e < (long)n * LT; e += GS_NT) {
-        const int r = (int)(e / LT), l = (int)(e % LT);
-        xs[e] = l < L ? Xb[r + (long)l * ldx] : make_float2(0.f, 0.f);
-    }
-    __syncthreads();
+    // X in and out: 16 rows x 4 right-hand sides per wave
+    auto each = [&](auto f) {
+        const int nrb = (n + 15) / 16;
+        for (int e = wave; e < nrb * 2 * CB; e += GS_NW) {
+            const int r = e / (2 * CB) * 16 + li, l = e % (2 * CB) * 4 + g;
+            if (r < n) f(r, l, xs + r * LD + (l >> 3) * 16 + (l & 7));
+        }
+    };
+    each([&](int r, int l, float* x) {
+        const float2 v = l < L ? Xb[r + (long)l * ldx] : make_float2(0.f, 0.f);
+        x[0] = v.x;
+        x[8] = v.y;
+    });
     const int np = (n + nb - 1) / nb;
-    // X_p = D X_p for the jb x jb block D (ld nb) and rows c0 .. c0+jb
-    auto diag = [=](const float2* D, int c0, int jb) {
-        const int i = tid >> 2, g = tid & 3;
-        const bool on = i < jb;
-        const unsigned ic = (unsigned)min(i, jb - 1);
-        float2 acc[LT];
+
+    // X_p as the other operand for the real parts of the factor (b1); for the imaginary parts the
+    // two halves of 8 columns change places and the first changes sign
+    float b1[GS_Q][GS_G][CB];
+    const unsigned flip = li < 8 ? 0x80000000u : 0u;
+    auto turned = [&](float v) {   // row_ror:8, lane i of 16 takes lane i ^ 8
+        const unsigned o = (unsigned)__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, true);
+        return __uint_as_float(o ^ flip);
+    };
+    auto read_x = [&](int c0, int jb) {
+        if (jb == 4 * GS_G * GS_Q) {
+            const float* x = xs + (c0 + g) * LD + li;
 #pragma unroll
-        for (int l = 0; l < LT; ++l) acc[l] = make_float2(0.f, 0.f);
+            for (int q = 0; q < GS_Q; ++q)
 #pragma unroll
-        for (int h = 0; h < GS_DK; h += GS_DK / 2) {
-            float2 d[GS_DK / 2];
+                for (int i = 0; i < GS_G; ++i)
 #pragma unroll
-            for (int m = 0; m < GS_DK / 2; ++m) {
-                const int k = g + 4 * (h + m);
-                const unsigned kc = (unsigned)min(k, jb - 1);
-                const float2 v = ldg_off(D, ic + kc * (unsigned)nb);
-                d[m] = (on && k < jb) ? v : make_float2(0.f, 0.f);
+                    for (int c = 0; c < CB; ++c) b1[q][i][c] = x[(q * GS_G + i) * 4 * LD + c * 16];
+        } else {
+#pragma unroll
+            for (int q = 0; q < GS_Q; ++q)
+#pragma unroll
+                for (int i = 0; i < GS_G; ++i) {
+                    const int k = (q * GS_G + i) * 4 + g;
+                    const float* x = xs + (c0 + min(k, jb - 1)) * LD + li;
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) b1[q][i][c] = k < jb ? x[c * 16] : 0.f;
+                }
+        }
+    };
+    // entries (row, 4 (q GS_G + i) + g) of a block of jb columns (past the last: the last again, X is zero there)
+    auto load = [&](const float2* F, int ldf, int row, int q, int jb, float2 (&a)[GS_G]) {
+        if ((q + 1) * 4 * GS_G <= jb) {
+            const unsigned off = (unsigned)(g * ldf + row) * 8u;   // uniform base, 32-bit offset
+#pragma unroll
+            for (int i = 0; i < GS_G; ++i)
+                a[i] = *reinterpret_cast<const float2*>(
+                    reinterpret_cast<const char*>(F + (long)((q * GS_G + i) * 4) * ldf) + off);
+        } else {
+#pragma unroll
+            for (int i = 0; i < GS_G; ++i)
+                a[i] = F[(unsigned)row + (unsigned)(min((q * GS_G + i) * 4 + g, jb - 1) * ldf)];
+        }
+    };
+    auto mult = [&](const float2 (&a)[GS_G], int q, floatx4 (&acc)[CB]) {
+#pragma unroll
+        for (int i = 0; i < GS_G; ++i) {
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1[q][i][c], a[i].x, acc[c], 0, 0, 0);
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(turned(b1[q][i][c]), a[i].y, acc[c], 0, 0, 0);
+        }
+    };
+    // the jb x jb triangle D (ld nb), one block of 16 rows per wave; a batch of columns on the far
+    // side of the diagonal is zero
+    float2 d[GS_Q][GS_G];
+    auto diag_on = [&](int q, int jb, bool lower) {
+        return wave * 16 < jb && q * 4 * GS_G < jb &&
+               (lower ? q * 4 * GS_G < wave * 16 + 16 : (q + 1) * 4 * GS_G > wave * 16);
+    };
+    auto diag_load = [&](const float2* D, int jb, bool lower) {
+#pragma unroll
+        for (int q = 0; q < GS_Q; ++q)
+            if (diag_on(q, jb, lower)) load(D, nb, min(wave * 16 + li, jb - 1), q, jb, d[q]);
+    };
+    // X_p = D X_p (D loaded), then rows [r0, r1) -= F X_p, F the columns c0 .. c0+jb of the factor: a wave
+    // takes NX blocks of 16 rows at a time and loads one batch of columns ahead
+    auto panel = [&](int r0, int r1, int c0, int jb, bool lower) {
+        const int nblk = (r1 - r0 + 15) / 16;
+        const float2* F = A + (long)c0 * lda;
+        float2 a[2][NX][GS_G];   // [buffer][block]
+        auto load_batch = [&](int blk, int q) {
+#pragma unroll
+            for (int x = 0; x < NX; ++x)
+                if (blk + x * GS_NW < nblk)
+                    load(F, lda, min(r0 + (blk + x * GS_NW) * 16 + li, r1 - 1), q, jb, a[q & 1][x]);
+        };
+        read_x(c0, jb);
+        {
+            floatx4 acc[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c) acc[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < GS_Q; ++q)
+                if (diag_on(q, jb, lower)) mult(d[q], q, acc);
+            load_batch(wave, 0);
+            __syncthreads();   // every read of X_p precedes the first write
+            const int r = wave * 16 + li;
+            if (r < jb) {
+#pragma unroll
+                for (int c = 0; c < CB; ++c) *reinterpret_cast<floatx4*>(xs + (c0 + r) * LD + c * 16 + 4 * g) = acc[c];
             }
+            __syncthreads();
+        }
+        read_x(c0, jb);
+        for (int blk = wave; blk < nblk; blk += NX * GS_NW) {
+            floatx4 acc[NX][CB];
 #pragma unroll
-            for (int m = 0; m < GS_DK / 2; ++m) {
-                const int k = g + 4 * (h + m);
-                if (k < jb) {
+            for (int x = 0; x < NX; ++x)
 #pragma unroll
-                    for (int l = 0; l < LT; ++l) acc[l] = cfma(acc[l], d[m], xs[(c0 + k) * LT + l]);
+                for (int c = 0; c < CB; ++c) acc[x][c] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int q = 0; q < GS_Q; ++q) {
+                if (q * 4 * GS_G < jb) {
+                    if (q + 1 < GS_Q && (q + 1) * 4 * GS_G < jb) load_batch(blk, q + 1);
+#pragma unroll
+                    for (int x = 0; x < NX; ++x)
+                        if (x == 0 || blk + x * GS_NW < nblk) mult(a[q & 1][x], q, acc[x]);
+                }
+            }
+            load_batch(blk + NX * GS_NW, 0);
+#pragma unroll
+            for (int x = 0; x < NX; ++x) {
+                const int row = r0 + (blk + x * GS_NW) * 16 + li;
+                if (row < r1) {
+#pragma unroll
+                    for (int c = 0; c < CB; ++c) {
+                        floatx4* p = reinterpret_cast<floatx4*>(xs + row * LD + c * 16 + 4 * g);
+                        floatx4 v = *p;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] -= acc[x][c][i];
+                        *p = v;
+                    }
                 }
             }
         }
-        group_sum<LT>(acc, 4);
-        __syncthreads();   // every read of X_p precedes the first write
-        if (on) {
-#pragma unroll
-            for (int l = 0; l < LT; ++l)
-                if ((l & 3) == g) xs[(c0 + i) * LT + l] = acc[l];
-        }
-        __syncthreads();
     };
-    // rows [r0, r1) -= F X_p, F the column block of the factor at (r, c0 .. c0+jb)
-    auto update = [=](int r0, int r1, int c0, int jb) {
-        const int R = r1 - r0;
-        if (R <= GS_NT / 4) getrs_lds_update<LT, 4>(A, lda, xs, r0, r1, c0, jb, tid);
-        else if (R <= GS_NT / 2) getrs_lds_update<LT, 2>(A, lda, xs, r0, r1, c0, jb, tid);
-        else getrs_lds_update<LT, 1>(A, lda, xs, r0, r1, c0, jb, tid);
-        __syncthreads();
-    };
+    const float2* Db = inv + (long)b * sInv;
     for (int p = 0; p < np; ++p) {
         const int c0 = p * nb, jb = min(nb, n - c0);
+        diag_load(Db + (long)(2 * p) * nb * nb, jb, true);
         // this panel's interchanges: row pm[s].x receives old row pm[s].y
         const int2* pm = perm + (long)b * sPerm + (long)p * 2 * MAX_NB;
-        constexpr int PQ = (2 * MAX_NB * LT + GS_NT - 1) / GS_NT;
-        float2 v[PQ];
+        __syncthreads();
+        constexpr int W4 = 4 * CB, PQ = (2 * MAX_NB * W4 + GS_NT - 1) / GS_NT;
+        floatx4 v[PQ];
+        int dst[PQ];
 #pragma unroll
         for (int q = 0; q < PQ; ++q) {
             const int e = tid + GS_NT * q;
-            v[q] = make_float2(0.f, 0.f);
-            if (e < 2 * jb * LT) {
-                const int src = pm[e / LT].y;
-                if (src >= 0) v[q] = xs[src * LT + e % LT];
+            dst[q] = -1;
+            if (e < 2 * jb * W4) {
+                const int2 m = pm[e / W4];
+                if (m.y >= 0) {
+                    v[q] = *reinterpret_cast<const floatx4*>(xs + m.y * LD + 4 * (e % W4));
+                    dst[q] = m.x;
+                }
             }
         }
         __syncthreads();
 #pragma unroll
-        for (int q = 0; q < PQ; ++q) {
-            const int e = tid + GS_NT * q;
-            if (e < 2 * jb * LT) {
-                const int2 m = pm[e / LT];
-                if (m.y >= 0 && m.x >= 0) xs[m.x * LT + e % LT] = v[q];
-            }
-        }
+        for (int q = 0; q < PQ; ++q)
+            if (dst[q] >= 0) *reinterpret_cast<floatx4*>(xs + dst[q] * LD + 4 * ((tid + GS_NT * q) % W4)) = v[q];
         __syncthreads();
-        diag(inv + (long)b * sInv + (long)(2 * p) * nb * nb, c0, jb);
-        update(c0 + jb, n, c0, jb);
+        panel(c0 + jb, n, c0, jb, true);
     }
     for (int p = np - 1; p >= 0; --p) {
         const int c0 = p * nb, jb = min(nb, n - c0);
-        diag(inv + (long)b * sInv + (long)(2 * p + 1) * nb * nb, c0, jb);
-        update(0, c0, c0, jb);
+        diag_load(Db + (long)(2 * p + 1) * nb * nb, jb, false);
+        __syncthreads();
+        panel(0, c0, c0, jb, false);
     }
-    for (long e = tid; e < (long)n * L; e += GS_NT) {
-        const int r = (int)(e % n), l = (int)(e / n);
-        Xb[r + (long)l * ldx] = xs[r * LT + l];
-    }
+    __syncthreads();
+    each([&](int r, int l, float* x) {
+        if (l < L) Xb[r + (long)l * ldx] = make_float2(x[0], x[8]);
+    });
 }
 
-static int gs_width(int nrhs) { return nrhs <= 8 ? 8 : 16; }
-static size_t gs_lds(int n, int nrhs) { return (size_t)n * gs_width(nrhs) * 8; }
-bool getrs_lds_ok(int n, int nrhs) { return nrhs >= 1 && nrhs <= 16 && gs_lds(n, nrhs) <= (size_t)128 << 10; }
+static int gs_blocks(int nrhs) { return nrhs <= 8 ? 1 : 2; }
+static size_t gs_lds(int n, int nrhs) { return (size_t)n * gs_blocks(nrhs) * 64; }
+static bool getrs_lds_ok(int n, int nrhs) { return nrhs >= 1 && nrhs <= 16 && gs_lds(n, nrhs) <= (size_t)128 << 10; }
 
-hipError_t getrs_lds_batched(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
+static hipError_t getrs_lds_batched(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                              float2* X, long sX, int ldx, int nrhs, int batch)
 {
-    if (!getrs_lds_ok(n, nrhs)) return hipErrorInvalidValue;
     if (nb > max_panel<float>()) nb = max_panel<float>();
     if (nb < MIN_NB) nb = MIN_NB;
     const size_t lds = gs_lds(n, nrhs);
-    if (gs_width(nrhs) == 8)
-        hipLaunchKernelGGL(getrs_lds_kernel<8>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
+    if (gs_blocks(nrhs) == 1)
+        hipLaunchKernelGGL(getrs_lds_kernel<1>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
                            w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
     else
-        hipLaunchKernelGGL(getrs_lds_kernel<16>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
+        hipLaunchKernelGGL(getrs_lds_kernel<2>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
                            w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
     return hipGetLastError();
 }
@@ -1500,6 +1539,7 @@ template <>
 hipError_t getrs_batched<float>(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                                 float2* X, long sX, int ldx, int nrhs, int batch)
 {
+    if (getrs_lds_ok(n, nrhs)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
     return getrs_impl<float2>(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
 }
 template <>
