@@ -374,7 +374,7 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     s.la_b = c->la_b;
     s.la_c = c->la_c;
     s.upd = nullptr;  // set while the factorisation runs
-    s.la_cols = c->la_cols;
+    s.la_cols = c->la_cols >= 0 ? c->la_cols : (prec == RSRR_PREC_C64_IR ? 2048 : 0);
     s.sT = (long)s.ld * n;
     s.sP = n;
     s.sPerm = (long)s.np * 2 * MAX_NB;

@@ -31,8 +31,14 @@ struct rsrr_ctx {
     hipEvent_t la_a = nullptr, la_b = nullptr, la_c = nullptr;
     hipStream_t upd = nullptr;       // CU-masked stream for the overlapped updates (null: no mask)
     bool lookahead = true;           // RSRR_LOOKAHEAD=0 at creation turns it off
-    int la_cus = 32;                 // CUs the overlapped updates leave to the look-ahead (RSRR_LA_CUS)
-    int la_cols = 0;                 // columns of each overlapped update on the masked stream (RSRR_LA_COLS)
+    // CUs the overlapped updates leave to the look-ahead (RSRR_LA_CUS), and the columns of each that
+    // keep off them (RSRR_LA_COLS, 0: all; -1: 2048 in complex FP32, else all).  64 panels of 4096 rows take
+    // 1024 threads each, two rounds on 32 CUs; past 2048 columns the split update outlasts the
+    // panels, and the rest of it takes every CU.  4096 rows, 64 points: 116.0 ms with 32 CUs and all
+    // columns, 115.1 with 64, 113.5 with 64 and 2048 (1024 119, 2560 114.6; 96 CUs 115.9); FP64 and
+    // real cases within 0.5% of each other except 80 CUs and more (1-5% slower)
+    int la_cus = 64;
+    int la_cols = -1;
     void* ws[WS_COUNT] = {};
     size_t ws_size[WS_COUNT] = {};
     hipEvent_t ev[2] = {};
