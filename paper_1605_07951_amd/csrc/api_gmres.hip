@@ -60,6 +60,12 @@ static int k_slice(long tiles, int K)
 }
 static int n_slices(int K, int Ks) { return (K + Ks - 1) / Ks; }
 
+// The preconditioner's product (n x n times cols) with split operands.  Faster at every measured
+// size from 32 columns on, in ms a call without / with: n = 300, 64 columns 4.74 / 4.53; n = 1000, 32
+// columns 10.8 / 10.5, 256 columns (sparse) 7.35 / 7.04; n = 2730, 64 / 128 / 256 columns 16.5 / 18.6 /
+// 21.5, 16.4 / 17.3 / 18.8.  Fewer columns leave seven eighths of a tile empty.
+static bool split_precond(int n, long cols) { return n >= 256 && cols >= 32; }
+
 struct GmChunk {
     int B, C;                      // points, columns (B * L)
     int ldy, Kop, Kso;             // separable: stacked scaled copies (J*n rows), K-slice of the operator
@@ -191,9 +197,24 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
     const int np = perm_panels(n);
     const long sInv = (long)((n + nb - 1) / nb) * 2 * nb * nb;
     const long sPerm = (long)np * 2 * MAX_NB;
-    float2* Tf = (float2*)ws_get(c, WS_GMF, (size_t)nf * sT * 8);
+    // A reference that serves several points is applied as an explicit inverse
+    // (one complex FP32 product per application instead of a chain of n/nb
+    // triangular steps); the inverse costs about as much as 4n/(3L') solves.
+    const bool use_inv = N >= 4 * nf;
+    // With enough columns the inverse is packed once for the split kernels, in slabs of Kpk columns,
+    // over the factors (which the solves below no longer need)
+    int most = 0;
+    for (int f = 0; f < nf; ++f) most = std::max(most, (int)std::count(rk.begin(), rk.end(), used[f]));
+    const long pcols = std::min<long>((long)most * L, 1 << 20);
+    const bool pcs = use_inv && split_precond(n, pcols);
+    const int Kpk = pcs ? std::min(256, k_slice((long)((n + 127) / 128) * ((pcols + 127) / 128), n)) : n;
+    const int Spk = pcs ? n_slices(n, Kpk) : 0;
+    const long bPk = pcs ? split_operand_bytes(n, Kpk) : 0;   // bytes of one slab
+    float2* Tf = (float2*)ws_get(c, WS_GMF, std::max((size_t)nf * sT * 8, (size_t)nf * Spk * bPk));
+    const long sPack = split_ok(n - nb, n - nb, nb) ? (long)split_pack_bytes(n, std::min(2 * nb, 256)) : 0;
     size_t fw = a256((size_t)nf * n * 4) + a256((size_t)nf * sPerm * 8) +
-                a256((size_t)nf * 4) + a256((size_t)nf * sInv * 8) + a256((size_t)nf * nb * n * 8);
+                a256((size_t)nf * 4) + a256((size_t)nf * sInv * 8) + a256((size_t)nf * nb * n * 8) +
+                a256((size_t)nf * sPack);
     Carve fc{(char*)ws_get(c, WS_GMW, fw)};
     if (!Tf || !fc.base) return RSRR_ENOMEM;
     LUWork w;
@@ -202,6 +223,7 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
     w.info = fc.take<int>(nf);
     w.inv = fc.take<float2>((size_t)nf * sInv); w.sInv = sInv;
     w.tmp = fc.take<float2>((size_t)nf * nb * n); w.sTmp = (long)nb * n;
+    w.pack = sPack ? fc.take<char>((size_t)nf * sPack) : nullptr; w.sPack = sPack;
     {
         EvPair ev;
         RSRR_HIP(hipEventRecord(ev.a, c->stream));
@@ -253,10 +275,6 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
             if (hinfo[f] > 0) return RSRR_ESINGULAR;
         }
     }
-    // A reference that serves several points is applied as an explicit inverse
-    // (one complex FP32 GEMM per application instead of a chain of n/nb
-    // triangular steps); the inverse costs about as much as 4n/(3L') solves.
-    const bool use_inv = N >= 4 * nf;
     float2* Pinv = nullptr;
     if (use_inv) {
         EvPair ev;
@@ -265,6 +283,9 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
         if (!Pinv) return RSRR_ENOMEM;
         RSRR_HIP(gm_eye_c64(c->stream, n, Pinv, ld, sT, nf));
         RSRR_HIP(getrs_batched<float>(c->stream, Tf, sT, ld, n, nb, w, Pinv, sT, ld, n, nf));
+        for (int f = 0; pcs && f < nf; ++f)
+            RSRR_HIP(split_pack_a(c->stream, n, Kpk, Pinv + f * sT, ld, (long)Kpk * ld, (char*)Tf + (size_t)f * Spk * bPk,
+                                  bPk, Spk, n, Kpk));
         RSRR_HIP(hipEventRecord(ev.b, c->stream));
         RSRR_HIP(hipEventSynchronize(ev.b));
         c->timings[0] += ev.ms();
@@ -283,7 +304,8 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
     const size_t per_col = (size_t)(2 * M + 3) * ld * 16 + (size_t)ld * 16 +
                            ((size_t)ns * (M + 1) * 16 + (size_t)(M + 1) * 16 * 3 + (size_t)M * M * 16 +
                             (size_t)M * 40 + 64) + (size_t)nb * 8 +
-                           (size_t)(nep->kind == RSRR_T_SEPARABLE ? nep->J * n : 0) * 16 + (size_t)16 * ld * 24;
+                           (size_t)(nep->kind == RSRR_T_SEPARABLE ? nep->J * n : 0) * 16 + (size_t)16 * ld * 16 +
+                           (size_t)std::max(16, Spk) * ld * 8 + (size_t)Spk * (round_up_l(Kpk, 8) * 8 + 4);
     size_t budget = c->ws_budget;
     if (!budget) {
         size_t fr = 0, tot = 0;
@@ -334,12 +356,14 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
         k.Kso = sep ? k_slice((long)((n + 63) / 64) * ((C + 63) / 64), k.Kop) : k.Kop;
         const int Sop = sep ? n_slices(k.Kop, k.Kso) : 0;
         const int bn = maxrun * L <= 32 ? 32 : (maxrun * L <= 64 ? 64 : 128);
-        const int Kpc = use_inv ? k_slice((long)((n + 127) / 128) * ((maxrun * L + bn - 1) / bn), n) : n;
+        const int Kpc = pcs ? Kpk : use_inv ? k_slice((long)((n + 127) / 128) * ((maxrun * L + bn - 1) / bn), n) : n;
         const int Spc = use_inv ? n_slices(n, Kpc) : 0;
+        const int Scp = pcs || Spc > 1 ? Spc : 0;   // blocks of partial products
+        const size_t pbbytes = (size_t)Spk * split_operand_bytes(maxrun * L, Kpk);
         const size_t ybytes = sep ? (size_t)k.ldy * C * 16 : vb * 16;
         const size_t kbytes = a256((size_t)(M + 1) * vb * 16) + a256((size_t)M * vb * 16) + a256(ybytes) +
                               a256(vb * 16) + a256(vb * 8) * 2 + a256((size_t)(equal ? nrun : 1) * sTmp * 8) +
-                              a256((size_t)(Sop > 1 ? Sop : 0) * vb * 16) + a256((size_t)(Spc > 1 ? Spc : 0) * vb * 8);
+                              a256((size_t)(Sop > 1 ? Sop : 0) * vb * 16) + a256((size_t)Scp * vb * 8) + a256(pbbytes);
         Carve kc{(char*)ws_get(c, WS_GMK, kbytes)};
         if (!kc.base) return RSRR_ENOMEM;
         k.V = kc.take<double2>((size_t)(M + 1) * vb);
@@ -350,7 +374,8 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
         k.D2 = kc.take<float2>(vb);
         k.tmp = kc.take<float2>((size_t)(equal ? nrun : 1) * sTmp);
         k.P = kc.take<double2>((size_t)(Sop > 1 ? Sop : 0) * vb);
-        float2* Pp = kc.take<float2>((size_t)(Spc > 1 ? Spc : 0) * vb);
+        float2* Pp = kc.take<float2>((size_t)Scp * vb);
+        char* PB = kc.take<char>(pbbytes);
         const size_t sbytes = a256((size_t)ns * (M + 1) * C * 16) + a256((size_t)(M + 1) * C * 16) * 3 +
                               a256((size_t)M * M * C * 16) + a256((size_t)M * C * 16) * 2 + a256((size_t)M * C * 8) +
                               a256((size_t)C * 8) * 4 + a256((size_t)C * 4) * 4 + a256(64) +
@@ -469,7 +494,19 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
                 RSRR_HIP(gm_narrow(c->stream, n, C, Vj, ld, k.D, ld));
                 float2* Dz = k.D;
                 bool widened = false;
-                if (use_inv && Spc > 1) {
+                if (pcs) {
+                    // Z_j = P^-1 V_j, each reference group's product as slabs with split operands
+                    for (int r = 0; r < nrun; ++r) {
+                        const int cols = (run0[r + 1] - run0[r]) * L;
+                        const size_t o = (size_t)run0[r] * L * ld;
+                        const long bB = split_operand_bytes(cols, Kpk);
+                        RSRR_HIP(split_pack_b(c->stream, cols, Kpk, k.D + o, ld, Kpk, PB, bB, Spk, n, Kpk));
+                        RSRR_HIP(cgemm_split(c->stream, n, cols, Kpk, (char*)Tf + (size_t)runf[r] * Spk * bPk, bPk, PB,
+                                             bB, cols, 0, false, Pp + o, ld, (long)vb, Spk));
+                    }
+                    RSRR_HIP(gm_sum_widen(c->stream, n, C, Pp, ld, (long)vb, Spk, Zj, ld));
+                    widened = true;
+                } else if (use_inv && Spc > 1) {
                     // Z_j = P^-1 V_j, each reference group's product split into K slices
                     const int S1 = n / Kpc, r1 = n - S1 * Kpc;
                     for (int r = 0; r < nrun; ++r) {

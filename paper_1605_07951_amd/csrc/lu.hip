@@ -1008,11 +1008,12 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             split = w.pack != nullptr && split_ok(M, Nall, kdepth);
             if (split) {
+                char* PB = (char*)w.pack + split_operand_bytes(M, kdepth);
                 if (j0 == 0) {
                     (void)split_pack_a(s, M, kdepth, Aop, ldaop, sAop, w.pack, w.sPack, batch);
-                    if (!bpacked) (void)split_pack_b(s, M, Nall, kdepth, Bop, lda, sA, w.pack, w.sPack, batch);
+                    if (!bpacked) (void)split_pack_b(s, Nall, kdepth, Bop, lda, sA, PB, w.sPack, batch);
                 }
-                (void)cgemm_split(s, M, N, kdepth, Nall, j0, w.pack, w.sPack, Cop, lda, sA, batch);
+                (void)cgemm_split(s, M, N, kdepth, w.pack, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch);
             }
         }
         if (!split) (void)gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1);
@@ -1216,6 +1217,13 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     return hipGetLastError();
 }
 
+// Right-hand sides, and those of all matrices, from which the solves' products pack their operands (the
+// factor is read once more and written once for that, two launches more a product).  FP32 / split, ms: 128
+// right-hand sides 1.03 / 1.04 (n = 1024, 32 matrices) and 2.07 / 2.07 (2048, 16), 256 1.32 / 1.24 and
+// 2.66 / 2.37, 512 1.97 / 1.74 and 3.76 / 3.02; one matrix, n = 500 0.39 / 0.41 and n = 2730
+// 2.48 / 2.49 at 512, 3.52 / 2.91 at 2730.
+constexpr int SPLIT_RHS = 256, SPLIT_RHS_ALL = 2048;
+
 template <typename C>
 static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int n, int nb,
                          const LUWork& w, C* X, long sX, int ldx, int nrhs, int batch)
@@ -1225,6 +1233,21 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
     if (nb > max_panel<R>()) nb = max_panel<R>();
     if (nb < MIN_NB) nb = MIN_NB;
     const int np = (n + nb - 1) / nb;
+    // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0
+    auto off_diag = [&](int r0, int m, int K, const C* F, int c0) {
+        if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
+            const long na = split_operand_bytes(m, K);
+            if (w.pack && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
+                na + split_operand_bytes(nrhs, K) <= w.sPack) {
+                char* PB = (char*)w.pack + na;
+                (void)split_pack_a(st, m, K, F, lda, sLU, w.pack, w.sPack, batch);
+                (void)split_pack_b(st, nrhs, K, X + c0, ldx, sX, PB, w.sPack, batch);
+                (void)cgemm_split(st, m, nrhs, K, w.pack, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch);
+                return;
+            }
+        }
+        (void)gemm_sub<C>(st, m, nrhs, K, F, lda, sLU, X + c0, ldx, sX, X + r0, ldx, sX, batch);
+    };
     for (int p = 0; p < np; ++p) {
         const int c0 = p * nb, jb = (n - c0 < nb) ? n - c0 : nb;
         const int2* pm = w.perm + (long)p * 2 * MAX_NB;
@@ -1237,9 +1260,7 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
                 perm_trsm(st, LU, sLU, lda, pm, w.sPerm, X, sX, ldx, c0, jb, nrhs, 1, w.active, batch);
         }
         const int rest = n - c0 - jb;
-        if (rest > 0)
-            (void)gemm_sub<C>(st, rest, nrhs, jb, LU + (c0 + jb) + (long)c0 * lda, lda, sLU, X + c0, ldx, sX,
-                              X + c0 + jb, ldx, sX, batch);
+        if (rest > 0) off_diag(c0 + jb, rest, jb, LU + (c0 + jb) + (long)c0 * lda, c0);
     }
     // Backward sweep with U11.  Panels are taken in pairs (p, p-1): after both
     // diagonal solves (the second preceded by the small coupling product with
@@ -1261,12 +1282,9 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
         diag_solve(p);
         if (p >= 1) {
             const int c1 = c0 - nb;  // panel p-1 is a full panel of width nb
-            (void)gemm_sub<C>(st, nb, nrhs, jb, LU + c1 + (long)c0 * lda, lda, sLU, X + c0, ldx, sX, X + c1, ldx, sX,
-                              batch);
+            off_diag(c1, nb, jb, LU + c1 + (long)c0 * lda, c0);
             diag_solve(p - 1);
-            if (c1 > 0)
-                (void)gemm_sub<C>(st, c1, nrhs, nb + jb, LU + (long)c1 * lda, lda, sLU, X + c1, ldx, sX, X, ldx, sX,
-                                  batch);
+            if (c1 > 0) off_diag(0, c1, nb + jb, LU + (long)c1 * lda, c1);
             p -= 2;
         } else {
             p -= 1;

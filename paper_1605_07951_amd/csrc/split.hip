@@ -1,16 +1,16 @@
-// Complex FP32 product C -= A B on the FP16 matrix cores with split operands (the LU's
-// trailing update).
+// Complex FP32 products C -= A B and C = A B on the FP16 matrix cores with split operands (the
+// LU's trailing updates, the wide solves and the preconditioner of the iterative sampling).
 //
 // v_mfma_f32_32x32x16_f16 multiplies at 16 times the rate of the FP32 instruction, with
 // exact products and FP32 sums.  Every real FP32 value, scaled by a power of two, is
 // held as hi + lo of two FP16 numbers: hi carries the leading 11 bits, lo the next 11, so
 // hi + lo is the value to within half a unit of FP32 and mostly exactly.  Three products,
-// hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.  The scale
-// makes the range safe: A is the unit lower factor of a pivoted LU, whose parts are at most
-// sqrt(2) (pivots are the largest |Re| + |Im|), scaled by 2^15; every column of B is scaled
-// by its own power of two to a largest part in [2^14, 2^15), and what is smaller than
-// 2^-40 of the column's largest part is lost.  The sums do not contain C (one
-// subtraction at the end), and 16 products enter them per rounding instead of 2, so
+// hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.  The scales
+// make the range safe: every row of A and every column of B has its own power of two, to
+// a largest part in [2^14, 2^15) (depths of at most 256; a deeper product is a sum of slabs
+// with scales of their own), and what is smaller than 2^-40 of the row's or
+// column's largest part is lost.  The sums do not contain C (one subtraction at the
+// end), and 16 products enter them per rounding instead of 2, so
 // the error is below that of the FP32 kernel: against 64 bits, relative to
 // |C| + |A||B| and in units of u = 2^-24, at K = 64 .. 256 and with columns of B of one size
 // or spread over 8 to 24 decades: rms 0.3-1.4 (FP32 3M kernel 1.0-1.9), largest 1.7-12 (7-20).
@@ -37,8 +37,7 @@ typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int SP_KC = 8;          // complex k per fragment
 constexpr int SP_FRAG = 1024;     // bytes
-constexpr int SP_ASCALE = 15;     // log2 of the scale of A
-constexpr int SP_BTOP = 14;       // exponent that a column's largest part of B is scaled to
+constexpr int SP_TOP = 14;        // exponent that a row's or column's largest part is scaled to
 constexpr int SP_KMAX = 256;
 
 // hi and lo parts of 4 complex values scaled by 2^e, interleaved (re, im) as one lane of a fragment
@@ -57,42 +56,70 @@ RSRR_DEV void split4(const float2 (&v)[4], int e, uintx4* hi, uintx4* lo)
     *lo = __builtin_bit_cast(uintx4, l);
 }
 
-// Exponent that scales a largest part to [2^SP_BTOP, 2^(SP_BTOP + 1)); zero or non-finite: no scale.
+// Exponent that scales a largest part to [2^SP_TOP, 2^(SP_TOP + 1)); zero or non-finite: no scale.
 RSRR_DEV int split_expo(float top)
 {
     // v_frexp_exp: top = m 2^e with m in [1/2, 1)
-    return (top > 0.f && isfinite(top)) ? SP_BTOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
+    return (top > 0.f && isfinite(top)) ? SP_TOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
 }
 
-// A (M x K): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l holds
-// row l % 32 and the 4 complex k at 4 (l / 32).  One wave per row block and k chunk; rows past M are zero.
-__global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, const float2* __restrict__ A, int lda, long sA,
+// Bytes of the fragments of an operand of `rows` rows (A) or columns (B); its exponents follow.
+static __host__ __device__ long sp_frag_bytes(int rows, int K)
+{
+    return (long)((rows + 31) / 32) * ((K + SP_KC - 1) / SP_KC) * 2 * SP_FRAG;
+}
+
+// A (M x K, K <= SP_KMAX): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l
+// holds row l % 32 and the 4 complex k at 4 (l / 32); then the exponent of each row's scale.  One
+// workgroup per 32 rows, thread (row t % 32, groups of 4 columns t / 32 + 8 q); rows past M are zero.
+// Of a deeper product, slab b holds the columns b kstep .. (past Ktot: zero).
+__global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Ktot, int kstep,
+                                                           const float2* __restrict__ A, int lda, long sA,
                                                            char* __restrict__ P, long sP)
 {
-    const int b = blockIdx.y, lane = threadIdx.x & 63;
-    const int nkc = (K + SP_KC - 1) / SP_KC, nrb = (M + 31) / 32;
-    const long f = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (f >= (long)nrb * nkc) return;
-    const int rb = (int)(f / nkc), kc = (int)(f % nkc);
-    const int i = rb * 32 + (lane & 31), k = kc * SP_KC + 4 * (lane >> 5);
+    const int rb = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
+    const int nkc = (K + SP_KC - 1) / SP_KC, Kb = min(K, Ktot - b * kstep);
+    const int r = t & 31, part = t >> 5, i = rb * 32 + r;
+    __shared__ float tops[8][32];
     const float2* src = A + b * sA + i;
-    float2 v[4];
+    constexpr int Q = SP_KMAX / 32;
+    float2 v[Q][4];
+    float top = 0.f;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) v[q] = (i < M && k + q < K) ? src[(long)(k + q) * lda] : make_float2(0.f, 0.f);
-    uintx4 hi, lo;
-    split4(v, SP_ASCALE, &hi, &lo);
-    uintx4* dst = reinterpret_cast<uintx4*>(P + b * sP + f * 2 * SP_FRAG);
-    dst[lane] = hi;
-    dst[64 + lane] = lo;
+    for (int q = 0; q < Q; ++q)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int k = 4 * (part + 8 * q) + u;
+            v[q][u] = (i < M && k < Kb) ? src[(long)k * lda] : make_float2(0.f, 0.f);
+            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+        }
+    tops[part][r] = top;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 8; ++q) top = fmaxf(top, tops[q][r]);
+    const int e = split_expo(top);
+    char* Pb = P + b * sP;
+    if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes(M, K))[i] = e;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const int p = part + 8 * q, kc = p >> 1;
+        if (kc >= nkc) break;
+        uintx4 hi, lo;
+        split4(v[q], e, &hi, &lo);
+        uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)rb * nkc + kc) * 2 * SP_FRAG);
+        dst[r + 32 * (p & 1)] = hi;
+        dst[64 + r + 32 * (p & 1)] = lo;
+    }
 }
 
 // B (K x N, K <= SP_KMAX): the same fragments with the columns in place of the rows, and the
-// exponent of each column's scale (expo[j]).  One workgroup per 32 columns, 8 threads per column.
-__global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, const float2* __restrict__ B, int ldb, long sB,
-                                                           char* __restrict__ P, long sP, long expo_off)
+// exponent of each column's scale.  One workgroup per 32 columns, 8 threads per column.
+__global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Ktot, int kstep,
+                                                           const float2* __restrict__ B, int ldb, long sB,
+                                                           char* __restrict__ P, long sP)
 {
     const int b = blockIdx.y, t = threadIdx.x;
-    const int nkc = (K + SP_KC - 1) / SP_KC;
+    const int nkc = (K + SP_KC - 1) / SP_KC, Kb = min(K, Ktot - b * kstep);
     const int c = t >> 3, part = t & 7;
     const int j = blockIdx.x * 32 + c;
     const float2* src = B + b * sB + (long)j * ldb;
@@ -104,14 +131,14 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, const f
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
             const int k = 4 * (part + 8 * q) + u;
-            v[q][u] = (j < N && k < K) ? src[k] : make_float2(0.f, 0.f);
+            v[q][u] = (j < N && k < Kb) ? src[k] : make_float2(0.f, 0.f);
             top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
         }
 #pragma unroll
     for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
     const int e = split_expo(top);
     char* Pb = P + b * sP;
-    if (part == 0) reinterpret_cast<int*>(Pb + expo_off)[j] = e;
+    if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes(N, K))[j] = e;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int p = part + 8 * q, kc = p >> 1;
@@ -311,10 +338,13 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
 // (64 KB, two workgroups per CU: one stores its tile while the other multiplies).
 constexpr int SP_ST = 2, SP_T = 128;
 
+// SUB: C -= A B, else C = A B.
+template <bool SUB>
 __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int nkc, const char* __restrict__ PA,
-                                                             long sPA, const char* __restrict__ PB, long sPB,
-                                                             long expo_off, int cb0, float2* __restrict__ C, int ldc,
-                                                             long sC, int tilesM, int tilesN, int batch, long total)
+                                                             long sPA, long expo_a, const char* __restrict__ PB,
+                                                             long sPB, long expo_b, int cb0, float2* __restrict__ C,
+                                                             int ldc, long sC, int tilesM, int tilesN, int batch,
+                                                             long total)
 {
     constexpr int STAGE = 4 * SP_ST * 2 * SP_FRAG;   // bytes of one operand's stage
     __shared__ __attribute__((aligned(16))) char lds[2][2][STAGE];
@@ -399,38 +429,46 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
         arrived();
     }
 
-    // C -= 2^-(scales) acc; lane li = row, register r = column 8 (r / 4) + 4 (lane / 32) + r % 4
+    // 2^-(scales) acc; lane li = row, register r = column 8 (r / 4) + 4 (lane / 32) + r % 4
     float2* Cb = C + b * sC;
-    const int* ex = reinterpret_cast<const int*>(PB + b * sPB + expo_off) + cb0 * 32;
+    const int* ea = reinterpret_cast<const int*>(PA + b * sPA + expo_a);
+    const int* ex = reinterpret_cast<const int*>(PB + b * sPB + expo_b) + cb0 * 32;
     const int li = lane & 31, half = lane >> 5;
+    int er[2];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) er[x] = ea[min(ti * SP_T + (wi * 2 + x) * 32 + li, M - 1)];
 #pragma unroll
     for (int y = 0; y < 2; ++y) {
         const int j0 = tj * SP_T + (wj * 2 + y) * 32 + 4 * half;
         if (tj * SP_T + (wj * 2 + y) * 32 >= N) break;
         int e[16];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) e[r] = -(SP_ASCALE + ex[min(j0 + 8 * (r >> 2) + (r & 3), N - 1)]);
+        for (int r = 0; r < 16; ++r) e[r] = ex[min(j0 + 8 * (r >> 2) + (r & 3), N - 1)];
 #pragma unroll
         for (int x = 0; x < 2; ++x) {
             const int i = ti * SP_T + (wi * 2 + x) * 32 + li;
             if (i >= M) continue;
             float2* col = Cb + i + (long)j0 * ldc;
+            auto value = [&](int r) {
+                const int s2 = -(er[x] + e[r]);
+                return make_float2(ldexpf(accR[x][y][r], s2), ldexpf(accI[x][y][r], s2));
+            };
             if (tj * SP_T + (wj * 2 + y) * 32 + 32 <= N) {   // whole block: all loads in flight before the first store
                 float2 c[16];
+                if constexpr (SUB) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) c[r] = col[(long)(8 * (r >> 2) + (r & 3)) * ldc];
+                    for (int r = 0; r < 16; ++r) c[r] = col[(long)(8 * (r >> 2) + (r & 3)) * ldc];
+                }
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
-                    col[(long)(8 * (r >> 2) + (r & 3)) * ldc] = make_float2(c[r].x - ldexpf(accR[x][y][r], e[r]),
-                                                                            c[r].y - ldexpf(accI[x][y][r], e[r]));
+                    col[(long)(8 * (r >> 2) + (r & 3)) * ldc] = SUB ? csub(c[r], value(r)) : value(r);
             } else {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int jr = 8 * (r >> 2) + (r & 3);
                     if (j0 + jr < N) {
-                        const float2 c = col[(long)jr * ldc];
-                        col[(long)jr * ldc] = make_float2(c.x - ldexpf(accR[x][y][r], e[r]),
-                                                          c.y - ldexpf(accI[x][y][r], e[r]));
+                        if constexpr (SUB) col[(long)jr * ldc] = csub(col[(long)jr * ldc], value(r));
+                        else col[(long)jr * ldc] = value(r);
                     }
                 }
             }
@@ -438,36 +476,29 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
     }
 }
 
-static long sp_operand_bytes(int rows, int K) { return (long)((rows + 31) / 32) * ((K + SP_KC - 1) / SP_KC) * 2 * SP_FRAG; }
+long split_operand_bytes(int rows, int K) { return sp_frag_bytes(rows, K) + (long)(rows + 31) / 32 * 32 * 4; }
 
-// Layout of the pack buffer: A, B, B's column exponents, then the three left factors of the U rows
-// with their row exponents (the offsets follow from the sizes of the product).
-size_t split_pack_bytes(int n, int K)
-{
-    return 2 * (size_t)sp_operand_bytes(n, K) + ((size_t)n + 31) / 32 * 32 * 4 + 3 * UR_OPERAND + 3 * UR_NB * 4;
-}
-static long sp_factors_off(int M, int N, int K)
-{
-    return sp_operand_bytes(M, K) + sp_operand_bytes(N, K) + (long)(N + 31) / 32 * 32 * 4;
-}
+// Layout of the LU's pack buffer: A, B, then the three left factors of the U rows with their row
+// exponents (the offsets follow from the sizes of the product).
+size_t split_pack_bytes(int n, int K) { return 2 * split_operand_bytes(n, K) + 3 * UR_OPERAND + 3 * UR_NB * 4; }
 
 // Depths of at least one panel (the error is below the FP32 kernel's from K = 64 on); fewer
 // than 128 rows or columns leave most of a tile empty and do not pay for the packing.
 bool split_ok(int M, int N, int K) { return K >= 128 && K <= SP_KMAX && M >= 128 && N >= 128; }
 
-hipError_t split_pack_a(hipStream_t st, int M, int K, const float2* A, int lda, long sA, void* P, long sP, int batch)
+hipError_t split_pack_a(hipStream_t st, int M, int K, const float2* A, int lda, long sA, void* P, long sP, int batch,
+                        int Ktot, int kstep)
 {
-    const long frags = sp_operand_bytes(M, K) / (2 * SP_FRAG);
-    hipLaunchKernelGGL(split_pack_a_kernel, dim3((unsigned)((frags + 3) / 4), batch), dim3(256), 0, st, M, K, A, lda,
-                       sA, (char*)P, sP);
+    hipLaunchKernelGGL(split_pack_a_kernel, dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K, Ktot ? Ktot : K, kstep,
+                       A, lda, sA, (char*)P, sP);
     return hipGetLastError();
 }
 
-hipError_t split_pack_b(hipStream_t st, int M, int N, int K, const float2* B, int ldb, long sB, void* P, long sP,
-                        int batch)
+hipError_t split_pack_b(hipStream_t st, int N, int K, const float2* B, int ldb, long sB, void* P, long sP, int batch,
+                        int Ktot, int kstep)
 {
-    hipLaunchKernelGGL(split_pack_b_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, B, ldb, sB,
-                       (char*)P + sp_operand_bytes(M, K), sP, sp_operand_bytes(N, K));
+    hipLaunchKernelGGL(split_pack_b_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, Ktot ? Ktot : K, kstep,
+                       B, ldb, sB, (char*)P, sP);
     return hipGetLastError();
 }
 
@@ -482,26 +513,29 @@ hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, 
 {
     constexpr int K = 2 * UR_NB;
     char* Pc = (char*)P;
-    const long off = sp_factors_off(M, N, K);
+    const long offb = split_operand_bytes(M, K), off = offb + split_operand_bytes(N, K);
     const UrFactors F = {{L0, T, L1}, {s0, sT, s1}, {ld0, ldt, ld1}};
     hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, Pc + off, sP,
                        3 * UR_OPERAND);
     hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, Pc + off, sP,
-                       3 * UR_OPERAND, Pc + sp_operand_bytes(M, K), sp_operand_bytes(N, K));
+                       3 * UR_OPERAND, Pc + offb, sp_frag_bytes(N, K));
     return hipGetLastError();
 }
 
-hipError_t cgemm_split(hipStream_t st, int M, int N, int K, int Npack, int j0, const void* P, long sP, float2* C,
-                       int ldc, long sC, int batch)
+hipError_t cgemm_split(hipStream_t st, int M, int N, int K, const void* PA, long sPA, const void* PB, long sPB,
+                       int Npack, int j0, bool sub, float2* C, int ldc, long sC, int batch)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
     if (j0 % 32 != 0 || j0 + N > Npack) return hipErrorInvalidValue;
-    const long na = sp_operand_bytes(M, K), nb = sp_operand_bytes(Npack, K);
-    const char* Pa = (const char*)P;
     const int tm = (M + SP_T - 1) / SP_T, tn = (N + SP_T - 1) / SP_T;
     const long total = round_up_l((long)tm * tn * batch, 8);
-    hipLaunchKernelGGL(cgemm_split_kernel, dim3((unsigned)total), dim3(256), 0, st, M, N, (K + SP_KC - 1) / SP_KC, Pa, sP,
-                       Pa + na, sP, nb, j0 / 32, C, ldc, sC, tm, tn, batch, total);
+#define SP_L(S)                                                                                                     \
+    hipLaunchKernelGGL(cgemm_split_kernel<S>, dim3((unsigned)total), dim3(256), 0, st, M, N, (K + SP_KC - 1) / SP_KC, \
+                       (const char*)PA, sPA, sp_frag_bytes(M, K), (const char*)PB, sPB, sp_frag_bytes(Npack, K),     \
+                       j0 / 32, C, ldc, sC, tm, tn, batch, total)
+    if (sub) SP_L(true);
+    else SP_L(false);
+#undef SP_L
     return hipGetLastError();
 }
 

@@ -62,3 +62,23 @@ def test_split_update_reports_non_finite(ctx, bad):
     _, _, status = R.rsrr_sample(ctx, R.DeviceNEP(nep), np.array([1.0 + 0j]), np.ones((600, 1), dtype=complex),
                                  ok=(R.RSRR_ENAN,))
     assert status == R.RSRR_ENAN
+
+
+@pytest.mark.parametrize("n,L", [(383, 256), (384, 256), (400, 900), (515, 255), (520, 300), (700, 257)])
+def test_wide_solves(ctx, n, L):
+    """Solves of 256 and more right-hand sides (more than rows: beyond the packing buffer)."""
+    A = _matrix(n, 0)
+    nep = W.SeparableNEP(name="wide", A=[A], terms=[W.term(1.0, 1)])
+    rng = np.random.default_rng(n + L)
+    # columns of very different size: each has its own scale
+    U = (rng.standard_normal((n, L)) + 1j * rng.standard_normal((n, L))) * 10.0 ** rng.uniform(-6, 6, L)[None, :]
+    z = np.exp(1j * np.arange(9))
+    S, info, status = R.rsrr_sample(ctx, R.DeviceNEP(nep), z, U)
+    assert status == R.RSRR_OK
+    X = R.from_colmajor(S, n)
+    for k in range(9):
+        assert info[k]["ir_iters"] <= 3
+        x = X[:, k * L:(k + 1) * L]
+        r = np.linalg.norm(U - z[k] * (A @ x), axis=0)
+        den = np.linalg.norm(A) * np.linalg.norm(x, axis=0) + np.linalg.norm(U, axis=0)
+        assert (r / den).max() <= 8 * n * U64
