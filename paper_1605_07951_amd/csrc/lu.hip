@@ -824,139 +824,174 @@ static C* panel_inv(const LUWork& w, int p, int nb, int which)
     return (C*)w.inv + (long)(2 * p + which) * nb * nb;
 }
 
-// Inverses of the two triangles of the jb x jb diagonal block at (c0, c0):
-// L11^-1 (unit lower, which = 0) at inv + (2p) nb^2 and U11^-1 (upper,
-// which = 1) at inv + (2p+1) nb^2, ld nb, the other triangle zero.  By 32 x 32
-// blocks: one workgroup per (block column j, triangle, matrix).  Each needed
-// diagonal block is inverted by one wave, a lane per column (substitution in
-// registers, the triangle read from LDS by broadcast); then block column j of
-// the inverse follows by blocked substitution: for L, X_jj = L_jj^-1 and
-// X_ij = -L_ii^-1 sum_{j<=k<i} L_ik X_kj; for U, upwards from X_jj = U_jj^-1.
-// A zero diagonal entry of U is skipped (as in the solves).  Rows and columns
-// past jb are padded with the identity.
-constexpr int TI_B = 32, TI_MAXB = 4, TI_NT = 256;
+// 16 x 16 tiles of products of blocks in LDS (column-major, ld TI_LD) on the 16x16x4 matrix
+// instructions; the first operand carries the right factor, so that a lane's output runs down a column.
+template <typename C> constexpr int TI_N = max_panel<real_t<C>>();
+template <typename C> constexpr int TI_LD = TI_N<C> + 4;
+constexpr int TI_B = 16, TI_NT = 512;
+
+RSRR_DEV floatx4 mfma16(float x, float y, floatx4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(x, y, c, 0, 0, 0); }
+RSRR_DEV doublex4 mfma16(double x, double y, doublex4 c)
+{
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(x, y, c, 0, 0, 0);
+}
+template <typename R> struct vec4_of { typedef floatx4 T; };
+template <> struct vec4_of<double> { typedef doublex4 T; };
+// column of a lane's output r: four consecutive ones in FP32, every fourth in FP64
+template <typename R>
+RSRR_DEV int mfma16_col(int g, int r) { return sizeof(R) == 4 ? 4 * g + r : g + 4 * r; }
 
 template <typename C>
+struct Tile16 {
+    typedef real_t<C> R;
+    typename vec4_of<R>::T re = {0, 0, 0, 0}, im = {0, 0, 0, 0}, rn = {0, 0, 0, 0}, in = {0, 0, 0, 0};
+    // += A B, A 16 x K and B K x 16 in LDS (first elements, ld TI_LD and LB)
+    template <int LB>
+    RSRR_DEV void add(const C* A, const C* B, int K, int lane)
+    {
+        const int li = lane & 15, g = lane >> 4;
+        const C* pa = A + g * TI_LD<C> + li;
+        const C* pb = B + li * LB + g;
+        for (int k = 0; k < K; k += 16) {
+            C x[4], y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                x[u] = pa[(k + 4 * u) * TI_LD<C>];
+                y[u] = pb[k + 4 * u];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if constexpr (elem_traits<C>::complex) {
+                    re = mfma16(y[u].x, x[u].x, re);
+                    im = mfma16(y[u].y, x[u].x, im);
+                    rn = mfma16(y[u].y, x[u].y, rn);
+                    in = mfma16(y[u].x, x[u].y, in);
+                } else {
+                    re = mfma16(y[u], x[u], re);
+                }
+            }
+        }
+    }
+    // to LDS at D (ld LB), times sign
+    template <int LB>
+    RSRR_DEV void put(C* D, R sign, int lane) const
+    {
+        const int li = lane & 15, g = lane >> 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            C* p = D + mfma16_col<R>(g, r) * LB + li;
+            if constexpr (elem_traits<C>::complex) {
+                p->x = sign * (re[r] - rn[r]);
+                p->y = sign * (im[r] + in[r]);
+            } else {
+                *p = sign * re[r];
+            }
+        }
+    }
+};
+
+// Inverses of the two triangles of the jb x jb diagonal block at (c0, c0): L11^-1 (unit lower, which =
+// 0) at inv + (2p) nb^2 and U11^-1 (upper, which = 1) at inv + (2p+1) nb^2, ld nb, the other triangle
+// zero.  One workgroup per triangle and matrix, the triangle in LDS and inverted in place by 16 x 16
+// blocks: the diagonal ones by a lane per column (substitution in registers), then the block rows in
+// turn, a wave per block of the row, X_ij = -L_ii^-1 sum_{j<=k<i} L_ik X_kj on the matrix cores (U: upwards,
+// X_ij = -U_ii^-1 sum_{i<k<=j} U_ik X_kj).
+// A zero diagonal entry of U counts as one (as in the solves).  Rows and columns past jb are
+// padded with the identity.
+// Bound by latency (the load, 16 dependent rows, seven block rows with two barriers each):
+// complex FP32 128 rows, 1 / 64 / 256 matrices 27 / 30 / 66 us (32 x 32 blocks on the vector unit, a
+// workgroup per block column: 49 / 60 / 141), real FP32 14 / 16 / 21 (24 / 27 / 57), FP64 64 rows 12 / 13 /
+// 28 (28 / 31 / 98).  By halves (four products instead of fourteen in turn) 25 us, but up to twice
+// the error of L11^-1.  The parts of a complex product have accumulators of their own: one
+// chain for two of them measured 1.3 times the error.
+template <typename C>
 __global__ __launch_bounds__(TI_NT) void tri_inv_kernel(const C* __restrict__ LU, long sLU, int ldl, int c0, int jb,
-                                                         C* __restrict__ inv, long sInv, int nb,
-                                                         const int* __restrict__ active)
+                                                        C* __restrict__ inv, long sInv, int nb,
+                                                        const int* __restrict__ active)
 {
-    const int j = blockIdx.x, b = blockIdx.y, which = blockIdx.z;
+    constexpr int N = TI_N<C>, LD = TI_LD<C>;
+    const int b = blockIdx.x, which = blockIdx.y;
     if (active && !active[b]) return;
-    const int nbk = (jb + TI_B - 1) / TI_B;
     const C* A = LU + (long)b * sLU + c0 + (long)c0 * ldl;   // the diagonal block, A(r, c) = A[r + c*ldl]
     C* X = (C*)inv + (long)b * sInv + (long)(2 * (c0 / nb) + which) * nb * nb;
-    // D[i]: inverted diagonal block i until block i of column j of the inverse is
-    // known, then that block (its last use as a diagonal inverse is in computing it)
-    __shared__ C D[TI_MAXB][TI_B][TI_B + 1];
-    __shared__ C Tt[TI_B][TI_B + 1];           // an off-diagonal block of the triangle
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    auto entry = [&](int r, int c) -> C {        // padded triangle entry (r, c < nbk * 32)
-        if (r < jb && c < jb) return A[r + (long)c * ldl];
-        return from_real<C>((real_t<C>)(r == c ? 1 : 0));
-    };
-    // 1. diagonal blocks i = j .. nbk-1 (L) or 0 .. j (U), staged in D[i], then inverted by
-    //    wave i (TI_MAXB waves), a lane per column
-    for (int e = tid; e < nbk * TI_B * TI_B; e += TI_NT) {
-        const int i = e / (TI_B * TI_B), r = e % TI_B, c = (e / TI_B) % TI_B;
-        D[i][r][c] = entry(i * TI_B + r, i * TI_B + c);
+    constexpr int PL = TI_B + 4;
+    __shared__ C S[N * LD], P[TI_NT / 64][TI_B * PL];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int np = (jb + TI_B - 1) / TI_B * TI_B;   // rows in use
+    constexpr int W = 8;                            // columns in flight per thread
+    const int r = tid % N;
+    for (int cc = tid / N; cc < np; cc += W * (TI_NT / N)) {
+        C v[W];
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const int c = cc + q * (TI_NT / N);
+            const bool in = r < jb && c < jb && (which == 0 ? r > c : r <= c);
+            v[q] = in ? A[r + (long)c * ldl] : from_real<C>((real_t<C>)(r == c ? 1 : 0));
+        }
+#pragma unroll
+        for (int q = 0; q < W; ++q) {
+            const int c = cc + q * (TI_NT / N);
+            if (c < np) S[c * LD + r] = v[q];
+        }
     }
     __syncthreads();
-    C x[TI_B];
-    const int i1 = wave, col = lane;
-    const bool mine = i1 < nbk && (which == 0 ? i1 >= j : i1 <= j) && col < TI_B;
-    if (mine) {
+    if (wave < N / TI_B && wave * TI_B < np) {
+        const int o = wave * TI_B, col = lane & 15;
+        const C* D = S + o * LD + o;
+        C x[TI_B];
         if (which == 0) {
 #pragma unroll
-            for (int r = 0; r < TI_B; ++r) {
-                C s = from_real<C>((real_t<C>)(r == col ? 1 : 0));
+            for (int i = 0; i < TI_B; ++i) {
+                C s = from_real<C>((real_t<C>)(i == col ? 1 : 0));
 #pragma unroll
-                for (int l = 0; l < r; ++l) s = cfms(s, D[i1][r][l], x[l]);
-                x[r] = s;
+                for (int l = 0; l < i; ++l) s = cfms(s, D[l * LD + i], x[l]);
+                x[i] = s;
             }
         } else {
+            // the lanes' own diagonal entry inverted at once, handed out by row
+            const C d = D[col * LD + col];
+            const C dr = is_zero(d) ? from_real<C>((real_t<C>)1) : crecip(d);
 #pragma unroll
-            for (int r = TI_B - 1; r >= 0; --r) {
-                C s = from_real<C>((real_t<C>)(r == col ? 1 : 0));
+            for (int i = TI_B - 1; i >= 0; --i) {
+                C s = from_real<C>((real_t<C>)(i == col ? 1 : 0));
 #pragma unroll
-                for (int l = r + 1; l < TI_B; ++l) s = cfms(s, D[i1][r][l], x[l]);
-                const C d = D[i1][r][r];
-                x[r] = is_zero(d) ? s : cmul(s, crecip(d));
+                for (int l = i + 1; l < TI_B; ++l) s = cfms(s, D[l * LD + i], x[l]);
+                x[i] = cmul(s, shfl_get(dr, i));
             }
+        }
+        // (a wave's reads of its block precede its writes)
+        if (lane < TI_B) {
+#pragma unroll
+            for (int i = 0; i < TI_B; ++i) S[(o + col) * LD + o + i] = x[i];
         }
     }
     __syncthreads();
-    if (mine) {
-#pragma unroll
-        for (int r = 0; r < TI_B; ++r) D[i1][r][col] = x[r];
-    }
-    __syncthreads();
-    // 2. block column j: X_jj = D[j] already; X_ij replaces D[i] in order of i
-    const int steps = which == 0 ? nbk - 1 - j : j;
-    for (int s = 1; s <= steps; ++s) {
-        const int i = which == 0 ? j + s : j - s;
-        // acc = sum_k T_ik X_kj over k between i and j (exclusive of i), 4 outputs per thread
-        C acc[TI_B * TI_B / TI_NT];
-#pragma unroll
-        for (int q = 0; q < TI_B * TI_B / TI_NT; ++q) acc[q] = czero<C>();
-        const int k0 = which == 0 ? j : i + 1, k1 = which == 0 ? i - 1 : j;
-        for (int k = k0; k <= k1; ++k) {
-            for (int e = tid; e < TI_B * TI_B; e += TI_NT) {
-                const int r = e % TI_B, c = e / TI_B;
-                Tt[r][c] = entry(i * TI_B + r, k * TI_B + c);
-            }
-            __syncthreads();
-#pragma unroll
-            for (int q = 0; q < TI_B * TI_B / TI_NT; ++q) {
-                const int e = tid + TI_NT * q;
-                const int r = e % TI_B, c = e / TI_B;
-                C a = acc[q];
-                for (int l = 0; l < TI_B; ++l) a = cfma(a, Tt[r][l], D[k][l][c]);
-                acc[q] = a;
-            }
-            __syncthreads();
-        }
-        // X_ij = -D[i] acc (acc staged through Tt), computed in registers, then
-        // written over D[i] once every thread has read it
-#pragma unroll
-        for (int q = 0; q < TI_B * TI_B / TI_NT; ++q) {
-            const int e = tid + TI_NT * q;
-            Tt[e % TI_B][e / TI_B] = acc[q];
+    const int nbk = np / TI_B;
+    for (int m = 1; m < nbk; ++m) {
+        const int i = which == 0 ? m : nbk - 1 - m, j = which == 0 ? wave : i + 1 + wave;
+        const bool on = wave < m;
+        Tile16<C> t, x;
+        if (on) {
+            if (which == 0) t.template add<LD>(S + j * TI_B * LD + i * TI_B, S + j * TI_B * LD + j * TI_B, (i - j) * TI_B, lane);
+            else t.template add<LD>(S + (i + 1) * TI_B * LD + i * TI_B, S + j * TI_B * LD + (i + 1) * TI_B, (j - i) * TI_B, lane);
+            t.template put<PL>(P[wave], (real_t<C>)1, lane);
         }
         __syncthreads();
-#pragma unroll
-        for (int q = 0; q < TI_B * TI_B / TI_NT; ++q) {
-            const int e = tid + TI_NT * q;
-            const int r = e % TI_B, c = e / TI_B;
-            C a = czero<C>();
-            for (int l = 0; l < TI_B; ++l) a = cfms(a, D[i][r][l], Tt[l][c]);
-            acc[q] = a;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int q = 0; q < TI_B * TI_B / TI_NT; ++q) {
-            const int e = tid + TI_NT * q;
-            D[i][e % TI_B][e / TI_B] = acc[q];
-        }
+        if (on) x.template add<PL>(S + i * TI_B * LD + i * TI_B, P[wave], TI_B, lane);
+        // (every read of the block row precedes the barrier above)
+        if (on) x.template put<LD>(S + j * TI_B * LD + i * TI_B, (real_t<C>)-1, lane);
         __syncthreads();
     }
-    // 3. write block column j (zeros in the other triangle), rows and columns < jb
-    for (int e = tid; e < nbk * TI_B * TI_B; e += TI_NT) {
-        const int rr = e % (nbk * TI_B), c = e / (nbk * TI_B);
-        const int gc = j * TI_B + c, i = rr / TI_B, r = rr % TI_B;
-        if (rr >= jb || gc >= jb) continue;
-        const bool in = which == 0 ? i >= j : i <= j;
-        X[rr + (long)gc * nb] = in ? D[i][r][c] : czero<C>();
-    }
+    for (int c = tid / N; c < jb; c += TI_NT / N)
+        if (r < jb) X[r + (long)c * nb] = S[c * LD + r];
 }
 
 template <typename C>
 static void tri_inv(hipStream_t st, const C* LU, long sLU, int ldl, int c0, int jb, C* inv, long sInv, int nb,
                     const int* active, int batch)
 {
-    const int nbk = (jb + TI_B - 1) / TI_B;
-    hipLaunchKernelGGL(tri_inv_kernel<C>, dim3(nbk, batch, 2), dim3(TI_NT), 0, st, LU, sLU, ldl, c0, jb, inv, sInv,
-                       nb, active);
+    hipLaunchKernelGGL(tri_inv_kernel<C>, dim3(batch, 2), dim3(TI_NT), 0, st, LU, sLU, ldl, c0, jb, inv, sInv, nb,
+                       active);
 }
 
 // D(r0.., 0..cols) = S(r0.., 0..cols): rows r0..n-1 of a column block, per matrix.
