@@ -209,9 +209,9 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
     const bool pcs = use_inv && split_precond(n, pcols);
     const int Kpk = pcs ? std::min(256, k_slice((long)((n + 127) / 128) * ((pcols + 127) / 128), n)) : n;
     const int Spk = pcs ? n_slices(n, Kpk) : 0;
-    const long bPk = pcs ? split_operand_bytes(n, Kpk) : 0;   // bytes of one slab
+    const long bPk = pcs ? split_operand_bytes<float2>(n, Kpk) : 0;   // bytes of one slab
     float2* Tf = (float2*)ws_get(c, WS_GMF, std::max((size_t)nf * sT * 8, (size_t)nf * Spk * bPk));
-    const long sPack = split_ok(n - nb, n - nb, nb) ? (long)split_pack_bytes(n, std::min(2 * nb, 256)) : 0;
+    const long sPack = split_ok(n - nb, n - nb, nb) ? (long)split_pack_bytes<float2>(n, std::min(2 * nb, 256)) : 0;
     size_t fw = a256((size_t)nf * n * 4) + a256((size_t)nf * sPerm * 8) +
                 a256((size_t)nf * 4) + a256((size_t)nf * sInv * 8) + a256((size_t)nf * nb * n * 8) +
                 a256((size_t)nf * sPack);
@@ -359,7 +359,7 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
         const int Kpc = pcs ? Kpk : use_inv ? k_slice((long)((n + 127) / 128) * ((maxrun * L + bn - 1) / bn), n) : n;
         const int Spc = use_inv ? n_slices(n, Kpc) : 0;
         const int Scp = pcs || Spc > 1 ? Spc : 0;   // blocks of partial products
-        const size_t pbbytes = (size_t)Spk * split_operand_bytes(maxrun * L, Kpk);
+        const size_t pbbytes = (size_t)Spk * split_operand_bytes<float2>(maxrun * L, Kpk);
         const size_t ybytes = sep ? (size_t)k.ldy * C * 16 : vb * 16;
         const size_t kbytes = a256((size_t)(M + 1) * vb * 16) + a256((size_t)M * vb * 16) + a256(ybytes) +
                               a256(vb * 16) + a256(vb * 8) * 2 + a256((size_t)(equal ? nrun : 1) * sTmp * 8) +
@@ -499,9 +499,9 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
                     for (int r = 0; r < nrun; ++r) {
                         const int cols = (run0[r + 1] - run0[r]) * L;
                         const size_t o = (size_t)run0[r] * L * ld;
-                        const long bB = split_operand_bytes(cols, Kpk);
+                        const long bB = split_operand_bytes<float2>(cols, Kpk);
                         RSRR_HIP(split_pack_b(c->stream, cols, Kpk, k.D + o, ld, Kpk, PB, bB, Spk, n, Kpk));
-                        RSRR_HIP(cgemm_split(c->stream, n, cols, Kpk, (char*)Tf + (size_t)runf[r] * Spk * bPk, bPk, PB,
+                        RSRR_HIP(gemm_split(c->stream, n, cols, Kpk, (char*)Tf + (size_t)runf[r] * Spk * bPk, bPk, PB,
                                              bB, cols, 0, false, Pp + o, ld, (long)vb, Spk));
                     }
                     RSRR_HIP(gm_sum_widen(c->stream, n, C, Pp, ld, (long)vb, Spk, Zj, ld));

@@ -326,7 +326,8 @@ struct SampleBufs {
 static size_t pack_bytes(int n, int prec)
 {
     constexpr int depth = 2 * max_panel<float>();
-    return prec == RSRR_PREC_C64_IR && split_ok(n - depth, n - depth, depth) ? split_pack_bytes(n, depth) : 0;
+    if (prec == RSRR_PREC_C128 || !split_ok(n - depth, n - depth, depth)) return 0;
+    return prec == RSRR_PREC_C64_IR ? split_pack_bytes<float2>(n, depth) : split_pack_bytes<float>(n, depth);
 }
 
 // Per-point bytes of the sampling buffers.

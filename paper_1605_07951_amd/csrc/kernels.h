@@ -34,22 +34,25 @@ void set_update_tile(int t);
 int get_update_tile();
 const char* update_tile_name(int t);
 
-// Complex FP32 products on the FP16 matrix cores with split operands (split.hip), K <= 256.
+// FP32 products (C = float2 or float) on the FP16 matrix cores with split operands (split.hip), K <= 256.
 // split_pack_a (M x K) and split_pack_b (K x N) write an operand (split_operand_bytes(rows or
-// columns, K) bytes, stride sP bytes); cgemm_split then gives C -= A B (sub) or C = A B for N
+// columns, K) bytes, stride sP bytes); gemm_split then gives C -= A B (sub) or C = A B for N
 // columns from column j0 (a multiple of 32; C at that column) of the Npack packed ones.  A deeper product
 // is a batch of slabs: matrix b at sA, of the columns (rows of B) b kstep .. of Ktot.
-// split_ok: sizes for which it replaces cgemm; split_pack_bytes: both operands of an LU update of
+// split_ok: sizes for which it replaces cgemm and sgemm; split_pack_bytes: both operands of an LU update of
 // depth K of at most n rows and columns, and the factors of split_urows.
 bool split_ok(int M, int N, int K);
-long split_operand_bytes(int rows, int K);
-size_t split_pack_bytes(int n, int K);
-hipError_t split_pack_a(hipStream_t st, int M, int K, const float2* A, int lda, long sA, void* P, long sP, int batch,
+template <typename C> long split_operand_bytes(int rows, int K);
+template <typename C> size_t split_pack_bytes(int n, int K);
+template <typename C>
+hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, void* P, long sP, int batch,
                         int Ktot = 0, int kstep = 0);
-hipError_t split_pack_b(hipStream_t st, int N, int K, const float2* B, int ldb, long sB, void* P, long sP, int batch,
+template <typename C>
+hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, void* P, long sP, int batch,
                         int Ktot = 0, int kstep = 0);
-hipError_t cgemm_split(hipStream_t st, int M, int N, int K, const void* PA, long sPA, const void* PB, long sPB,
-                       int Npack, int j0, bool sub, float2* C, int ldc, long sC, int batch);
+template <typename C>
+hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long sPA, const void* PB, long sPB,
+                      int Npack, int j0, bool sub, C* Cm, int ldc, long sC, int batch);
 // The U rows of a pair of 128-wide panels on N trailing columns (A: 256 x N at the pair's first
 // row, interchanged) in place, U0 = L0 A0 and U1 = L1 (A1 - T U0) with L0, T, L1 128 x 128, and
 // the B operand of the M x N update of depth 256 that follows (instead of split_pack_b).
@@ -108,8 +111,8 @@ struct LUWork {
     hipStream_t upd = nullptr;
     hipEvent_t ev_c = nullptr;
     int la_cols = 0;                   // columns of each overlapped update on `upd` (0: all)
-    // optional (complex FP32): split_pack_bytes(n, 2 nb) bytes per matrix (stride sPack bytes);
-    // the trailing updates, and solves of 128 and more right-hand sides, then run with split operands on
+    // optional (FP32): split_pack_bytes(n, 2 nb) bytes per matrix (stride sPack bytes); the
+    // trailing updates, and complex solves of many right-hand sides, then run with split operands on
     // the FP16 matrix cores
     void* pack = nullptr; long sPack = 0;
 };

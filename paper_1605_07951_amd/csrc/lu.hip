@@ -1040,15 +1040,15 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if (timed) (void)hipEventRecord(rec->ev[2 * rec->used], s);
         if (Nall == 0) Nall = N;
         bool split = false;
-        if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
+        if constexpr (sizeof(R) == 4) {
             split = w.pack != nullptr && split_ok(M, Nall, kdepth);
             if (split) {
-                char* PB = (char*)w.pack + split_operand_bytes(M, kdepth);
+                char* PB = (char*)w.pack + split_operand_bytes<C>(M, kdepth);
                 if (j0 == 0) {
                     (void)split_pack_a(s, M, kdepth, Aop, ldaop, sAop, w.pack, w.sPack, batch);
                     if (!bpacked) (void)split_pack_b(s, Nall, kdepth, Bop, lda, sA, PB, w.sPack, batch);
                 }
-                (void)cgemm_split(s, M, N, kdepth, w.pack, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch);
+                (void)gemm_split(s, M, N, kdepth, w.pack, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch);
             }
         }
         if (!split) (void)gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1);
@@ -1271,13 +1271,13 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
     // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0
     auto off_diag = [&](int r0, int m, int K, const C* F, int c0) {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
-            const long na = split_operand_bytes(m, K);
+            const long na = split_operand_bytes<C>(m, K);
             if (w.pack && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
-                na + split_operand_bytes(nrhs, K) <= w.sPack) {
+                na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
                 char* PB = (char*)w.pack + na;
                 (void)split_pack_a(st, m, K, F, lda, sLU, w.pack, w.sPack, batch);
                 (void)split_pack_b(st, nrhs, K, X + c0, ldx, sX, PB, w.sPack, batch);
-                (void)cgemm_split(st, m, nrhs, K, w.pack, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch);
+                (void)gemm_split(st, m, nrhs, K, w.pack, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch);
                 return;
             }
         }

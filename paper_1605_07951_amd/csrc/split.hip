@@ -1,5 +1,5 @@
-// Complex FP32 products C -= A B and C = A B on the FP16 matrix cores with split operands (the
-// LU's trailing updates, the wide solves and the preconditioner of the iterative sampling).
+// FP32 products C -= A B and C = A B on the FP16 matrix cores with split operands (the LU's
+// trailing updates, complex and real, and in complex FP32 the wide solves and the preconditioner of the iterative sampling).
 //
 // v_mfma_f32_32x32x16_f16 multiplies at 16 times the rate of the FP32 instruction, with
 // exact products and FP32 sums.  Every real FP32 value, scaled by a power of two, is
@@ -19,6 +19,10 @@
 // matrices, K = 256, n = 3840 / 2048 / 1024: 5.95 / 1.64 / 0.44 ms, 325 / 335 / 316 TFLOP/s in
 // the standard count of 8 flops per complex multiply-add (975 TFLOP/s in FP16, C at 2.6
 // TB/s), packing 0.36 / 0.19 / 0.10 ms; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
+//
+// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.52 / 0.17 / 0.045 / 0.019 ms and 0.12 / 0.07 /
+// 0.034 / 0.022 ms for the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045; rms error 0.26-2.2 u
+// (0.95-3.6).
 //
 // The complex product is the 4M form with the interleaved parts as the inner index
 // (k' = 2k + part): Re C takes A' (Br, -Bi), Im C takes A' (Bi, Br), which is one sign
@@ -64,33 +68,49 @@ RSRR_DEV int split_expo(float top)
 }
 
 // Bytes of the fragments of an operand of `rows` rows (A) or columns (B); its exponents follow.
+// Real operands: two consecutive k in place of the parts of one, 16 k per fragment.
+template <typename C>
+static __host__ __device__ constexpr int sp_chunks(int K)
+{
+    return sizeof(C) == sizeof(float2) ? (K + SP_KC - 1) / SP_KC : (K + 2 * SP_KC - 1) / (2 * SP_KC);
+}
+template <typename C>
 static __host__ __device__ long sp_frag_bytes(int rows, int K)
 {
-    return (long)((rows + 31) / 32) * ((K + SP_KC - 1) / SP_KC) * 2 * SP_FRAG;
+    return (long)((rows + 31) / 32) * sp_chunks<C>(K) * 2 * SP_FRAG;
+}
+// entry k of a row or column with K entries ld apart (real: entries 2 k and 2 k + 1), zero past the end
+RSRR_DEV float2 sp_entry(const float2* src, int k, long ld, int K)
+{
+    return k < K ? src[k * ld] : make_float2(0.f, 0.f);
+}
+RSRR_DEV float2 sp_entry(const float* src, int k, long ld, int K)
+{
+    return make_float2(2 * k < K ? src[2 * k * ld] : 0.f, 2 * k + 1 < K ? src[(2 * k + 1) * ld] : 0.f);
 }
 
 // A (M x K, K <= SP_KMAX): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l
 // holds row l % 32 and the 4 complex k at 4 (l / 32); then the exponent of each row's scale.  One
 // workgroup per 32 rows, thread (row t % 32, groups of 4 columns t / 32 + 8 q); rows past M are zero.
 // Of a deeper product, slab b holds the columns b kstep .. (past Ktot: zero).
+template <typename C>
 __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Ktot, int kstep,
-                                                           const float2* __restrict__ A, int lda, long sA,
+                                                           const C* __restrict__ A, int lda, long sA,
                                                            char* __restrict__ P, long sP)
 {
     const int rb = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
-    const int nkc = (K + SP_KC - 1) / SP_KC, Kb = min(K, Ktot - b * kstep);
+    const int nkc = sp_chunks<C>(K), Kb = min(K, Ktot - b * kstep);
     const int r = t & 31, part = t >> 5, i = rb * 32 + r;
     __shared__ float tops[8][32];
-    const float2* src = A + b * sA + i;
-    constexpr int Q = SP_KMAX / 32;
+    const C* src = A + b * sA + i;
+    constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
     float2 v[Q][4];
     float top = 0.f;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int k = 4 * (part + 8 * q) + u;
-            v[q][u] = (i < M && k < Kb) ? src[(long)k * lda] : make_float2(0.f, 0.f);
+            v[q][u] = i < M ? sp_entry(src, 4 * (part + 8 * q) + u, lda, Kb) : make_float2(0.f, 0.f);
             top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
         }
     tops[part][r] = top;
@@ -99,7 +119,7 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
     for (int q = 0; q < 8; ++q) top = fmaxf(top, tops[q][r]);
     const int e = split_expo(top);
     char* Pb = P + b * sP;
-    if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes(M, K))[i] = e;
+    if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes<C>(M, K))[i] = e;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int p = part + 8 * q, kc = p >> 1;
@@ -114,31 +134,31 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
 
 // B (K x N, K <= SP_KMAX): the same fragments with the columns in place of the rows, and the
 // exponent of each column's scale.  One workgroup per 32 columns, 8 threads per column.
+template <typename C>
 __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Ktot, int kstep,
-                                                           const float2* __restrict__ B, int ldb, long sB,
+                                                           const C* __restrict__ B, int ldb, long sB,
                                                            char* __restrict__ P, long sP)
 {
     const int b = blockIdx.y, t = threadIdx.x;
-    const int nkc = (K + SP_KC - 1) / SP_KC, Kb = min(K, Ktot - b * kstep);
+    const int nkc = sp_chunks<C>(K), Kb = min(K, Ktot - b * kstep);
     const int c = t >> 3, part = t & 7;
     const int j = blockIdx.x * 32 + c;
-    const float2* src = B + b * sB + (long)j * ldb;
-    constexpr int Q = SP_KMAX / 32;
+    const C* src = B + b * sB + (long)j * ldb;
+    constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
     float2 v[Q][4];
     float top = 0.f;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int k = 4 * (part + 8 * q) + u;
-            v[q][u] = (j < N && k < Kb) ? src[k] : make_float2(0.f, 0.f);
+            v[q][u] = j < N ? sp_entry(src, 4 * (part + 8 * q) + u, 1, Kb) : make_float2(0.f, 0.f);
             top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
         }
 #pragma unroll
     for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
     const int e = split_expo(top);
     char* Pb = P + b * sP;
-    if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes(N, K))[j] = e;
+    if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes<C>(N, K))[j] = e;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
         const int p = part + 8 * q, kc = p >> 1;
@@ -338,14 +358,15 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
 // (64 KB, two workgroups per CU: one stores its tile while the other multiplies).
 constexpr int SP_ST = 2, SP_T = 128;
 
-// SUB: C -= A B, else C = A B.
-template <bool SUB>
-__global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int nkc, const char* __restrict__ PA,
+// SUB: C -= A B, else C = A B; E: float2 or float.
+template <typename E, bool SUB>
+__global__ __launch_bounds__(256, 2) void gemm_split_kernel(int M, int N, int nkc, const char* __restrict__ PA,
                                                              long sPA, long expo_a, const char* __restrict__ PB,
-                                                             long sPB, long expo_b, int cb0, float2* __restrict__ C,
+                                                             long sPB, long expo_b, int cb0, E* __restrict__ C,
                                                              int ldc, long sC, int tilesM, int tilesN, int batch,
                                                              long total)
 {
+    constexpr bool CX = elem_traits<E>::complex;
     constexpr int STAGE = 4 * SP_ST * 2 * SP_FRAG;   // bytes of one operand's stage
     __shared__ __attribute__((aligned(16))) char lds[2][2][STAGE];
 
@@ -407,7 +428,7 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
                 for (int h = 0; h < 2; ++h) {
                     a[x][h] = frag(buf, 0, wi * 2 + x, kc * 2 + h);
                     const uintx4 v = frag(buf, 1, wj * 2 + x, kc * 2 + h);
-                    br[x][h] = v ^ 0x80000000u;                 // (Br, -Bi)
+                    br[x][h] = CX ? v ^ 0x80000000u : v;        // (Br, -Bi)
                     bi[x][h] = (v << 16) | (v >> 16);           // (Bi, Br)
                 }
 #pragma unroll
@@ -420,7 +441,7 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
                         accR[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
                             __builtin_bit_cast(half8, br[y][hb]), __builtin_bit_cast(half8, a[x][ha]), accR[x][y], 0,
                             0, 0);
-                        accI[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                        if constexpr (CX) accI[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
                             __builtin_bit_cast(half8, bi[y][hb]), __builtin_bit_cast(half8, a[x][ha]), accI[x][y], 0,
                             0, 0);
                     }
@@ -430,7 +451,7 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
     }
 
     // 2^-(scales) acc; lane li = row, register r = column 8 (r / 4) + 4 (lane / 32) + r % 4
-    float2* Cb = C + b * sC;
+    E* Cb = C + b * sC;
     const int* ea = reinterpret_cast<const int*>(PA + b * sPA + expo_a);
     const int* ex = reinterpret_cast<const int*>(PB + b * sPB + expo_b) + cb0 * 32;
     const int li = lane & 31, half = lane >> 5;
@@ -448,13 +469,14 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
         for (int x = 0; x < 2; ++x) {
             const int i = ti * SP_T + (wi * 2 + x) * 32 + li;
             if (i >= M) continue;
-            float2* col = Cb + i + (long)j0 * ldc;
+            E* col = Cb + i + (long)j0 * ldc;
             auto value = [&](int r) {
                 const int s2 = -(er[x] + e[r]);
-                return make_float2(ldexpf(accR[x][y][r], s2), ldexpf(accI[x][y][r], s2));
+                if constexpr (CX) return make_float2(ldexpf(accR[x][y][r], s2), ldexpf(accI[x][y][r], s2));
+                else return ldexpf(accR[x][y][r], s2);
             };
             if (tj * SP_T + (wj * 2 + y) * 32 + 32 <= N) {   // whole block: all loads in flight before the first store
-                float2 c[16];
+                E c[16];
                 if constexpr (SUB) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) c[r] = col[(long)(8 * (r >> 2) + (r & 3)) * ldc];
@@ -476,29 +498,39 @@ __global__ __launch_bounds__(256, 2) void cgemm_split_kernel(int M, int N, int n
     }
 }
 
-long split_operand_bytes(int rows, int K) { return sp_frag_bytes(rows, K) + (long)(rows + 31) / 32 * 32 * 4; }
+template <typename C>
+long split_operand_bytes(int rows, int K)
+{
+    return sp_frag_bytes<C>(rows, K) + (long)(rows + 31) / 32 * 32 * 4;
+}
 
-// Layout of the LU's pack buffer: A, B, then the three left factors of the U rows with their row
-// exponents (the offsets follow from the sizes of the product).
-size_t split_pack_bytes(int n, int K) { return 2 * split_operand_bytes(n, K) + 3 * UR_OPERAND + 3 * UR_NB * 4; }
+// Layout of the LU's pack buffer: A, B, then (complex) the three left factors of the U rows with
+// their row exponents (the offsets follow from the sizes of the product).
+template <typename C>
+size_t split_pack_bytes(int n, int K)
+{
+    return 2 * split_operand_bytes<C>(n, K) + (elem_traits<C>::complex ? 3 * UR_OPERAND + 3 * UR_NB * 4 : 0);
+}
 
 // Depths of at least one panel (the error is below the FP32 kernel's from K = 64 on); fewer
 // than 128 rows or columns leave most of a tile empty and do not pay for the packing.
 bool split_ok(int M, int N, int K) { return K >= 128 && K <= SP_KMAX && M >= 128 && N >= 128; }
 
-hipError_t split_pack_a(hipStream_t st, int M, int K, const float2* A, int lda, long sA, void* P, long sP, int batch,
+template <typename C>
+hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, void* P, long sP, int batch,
                         int Ktot, int kstep)
 {
-    hipLaunchKernelGGL(split_pack_a_kernel, dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K, Ktot ? Ktot : K, kstep,
-                       A, lda, sA, (char*)P, sP);
+    hipLaunchKernelGGL(split_pack_a_kernel<C>, dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K, Ktot ? Ktot : K,
+                       kstep, A, lda, sA, (char*)P, sP);
     return hipGetLastError();
 }
 
-hipError_t split_pack_b(hipStream_t st, int N, int K, const float2* B, int ldb, long sB, void* P, long sP, int batch,
+template <typename C>
+hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, void* P, long sP, int batch,
                         int Ktot, int kstep)
 {
-    hipLaunchKernelGGL(split_pack_b_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, Ktot ? Ktot : K, kstep,
-                       B, ldb, sB, (char*)P, sP);
+    hipLaunchKernelGGL(split_pack_b_kernel<C>, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, Ktot ? Ktot : K,
+                       kstep, B, ldb, sB, (char*)P, sP);
     return hipGetLastError();
 }
 
@@ -513,30 +545,42 @@ hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, 
 {
     constexpr int K = 2 * UR_NB;
     char* Pc = (char*)P;
-    const long offb = split_operand_bytes(M, K), off = offb + split_operand_bytes(N, K);
+    const long offb = split_operand_bytes<float2>(M, K), off = offb + split_operand_bytes<float2>(N, K);
     const UrFactors F = {{L0, T, L1}, {s0, sT, s1}, {ld0, ldt, ld1}};
     hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, Pc + off, sP,
                        3 * UR_OPERAND);
     hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, Pc + off, sP,
-                       3 * UR_OPERAND, Pc + offb, sp_frag_bytes(N, K));
+                       3 * UR_OPERAND, Pc + offb, sp_frag_bytes<float2>(N, K));
     return hipGetLastError();
 }
 
-hipError_t cgemm_split(hipStream_t st, int M, int N, int K, const void* PA, long sPA, const void* PB, long sPB,
-                       int Npack, int j0, bool sub, float2* C, int ldc, long sC, int batch)
+template <typename C>
+hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long sPA, const void* PB, long sPB,
+                      int Npack, int j0, bool sub, C* Cm, int ldc, long sC, int batch)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
     if (j0 % 32 != 0 || j0 + N > Npack) return hipErrorInvalidValue;
     const int tm = (M + SP_T - 1) / SP_T, tn = (N + SP_T - 1) / SP_T;
     const long total = round_up_l((long)tm * tn * batch, 8);
-#define SP_L(S)                                                                                                     \
-    hipLaunchKernelGGL(cgemm_split_kernel<S>, dim3((unsigned)total), dim3(256), 0, st, M, N, (K + SP_KC - 1) / SP_KC, \
-                       (const char*)PA, sPA, sp_frag_bytes(M, K), (const char*)PB, sPB, sp_frag_bytes(Npack, K),     \
-                       j0 / 32, C, ldc, sC, tm, tn, batch, total)
+#define SP_L(S)                                                                                                   \
+    hipLaunchKernelGGL((gemm_split_kernel<C, S>), dim3((unsigned)total), dim3(256), 0, st, M, N, sp_chunks<C>(K), \
+                       (const char*)PA, sPA, sp_frag_bytes<C>(M, K), (const char*)PB, sPB,                        \
+                       sp_frag_bytes<C>(Npack, K), j0 / 32, Cm, ldc, sC, tm, tn, batch, total)
     if (sub) SP_L(true);
     else SP_L(false);
 #undef SP_L
     return hipGetLastError();
 }
+
+#define SP_INST(C)                                                                                                  \
+    template long split_operand_bytes<C>(int, int);                                                                 \
+    template size_t split_pack_bytes<C>(int, int);                                                                  \
+    template hipError_t split_pack_a<C>(hipStream_t, int, int, const C*, int, long, void*, long, int, int, int);    \
+    template hipError_t split_pack_b<C>(hipStream_t, int, int, const C*, int, long, void*, long, int, int, int);    \
+    template hipError_t gemm_split<C>(hipStream_t, int, int, int, const void*, long, const void*, long, int, int,   \
+                                      bool, C*, int, long, int);
+SP_INST(float2)
+SP_INST(float)
+#undef SP_INST
 
 }  // namespace rsrr

@@ -82,3 +82,22 @@ def test_wide_solves(ctx, n, L):
         r = np.linalg.norm(U - z[k] * (A @ x), axis=0)
         den = np.linalg.norm(A) * np.linalg.norm(x, axis=0) + np.linalg.norm(U, axis=0)
         assert (r / den).max() <= 8 * n * U64
+
+
+@pytest.mark.parametrize("n", [383, 384, 385, 416, 513, 641, 770, 1100])
+def test_split_update_real(ctx, n):
+    """The real factorisation: two k in place of the parts of one, odd depths included."""
+    rng = np.random.default_rng(n)
+    A = rng.standard_normal((n, n)) + 2.0 * np.sqrt(n) * np.eye(n)
+    nep = W.SeparableNEP(name="split", A=[A.astype(complex)], terms=[W.term(1.0, 1)])
+    U = rng.standard_normal((n, 3)).astype(complex)
+    z = np.array([1.0, -0.5])
+    S, info, status = R.rsrr_sample(ctx, R.DeviceNEP(nep), z, U, prec=R.RSRR_PREC_R32_IR)
+    assert status == R.RSRR_OK
+    X = R.from_colmajor(S, n)
+    for k, zk in enumerate(z):
+        x = X[:, 3 * k:3 * k + 3]
+        r = np.linalg.norm(U - zk * (A @ x), axis=0)
+        den = np.linalg.norm(A) * abs(zk) * np.linalg.norm(x, axis=0) + np.linalg.norm(U, axis=0)
+        assert (r / den).max() <= 8 * n * U64
+        assert info[k]["ir_iters"] <= 3
