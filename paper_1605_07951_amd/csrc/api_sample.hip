@@ -418,31 +418,29 @@ static rsrr_status upload_coef(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, in
 static rsrr_status assemble_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, int B, int prec, SampleBufs& s)
 {
     const int n = nep->n;
-    float2* T64 = prec == RSRR_PREC_C64_IR ? (float2*)s.Tlu : nullptr;
-    double2* Tlu128 = prec == RSRR_PREC_C128 ? (double2*)s.Tlu : nullptr;
+    const LuCopy form = prec == RSRR_PREC_C64_IR ? LU_C64 : prec == RSRR_PREC_R32_IR ? LU_R32 : LU_C128;
     if (nep->kind == RSRR_T_SEPARABLE) {
         RSRR_TRY(upload_coef(c, nep, z, B, s.coef));
-        RSRR_HIP(assemble_separable(c->stream, n, nep->J, (const double2*)nep->A, nep->lda, s.coef, B, T64, s.ld,
-                                    s.sT, s.Tres, s.ld, s.sT, s.frobp, s.frob));
-        if (Tlu128) RSRR_HIP(copy_c128(c->stream, n, n, s.Tres, s.ld, s.sT, Tlu128, s.ld, s.sT, B));
-        if (prec == RSRR_PREC_R32_IR) RSRR_HIP(narrow_real(c->stream, n, s.Tres, s.ld, s.sT, (float*)s.Tlu, s.ld, s.sT, B));
+        RSRR_HIP(assemble_separable(c->stream, n, nep->J, (const double2*)nep->A, nep->lda, s.coef, B, s.Tlu, s.ld,
+                                    s.sT, s.Tres, s.ld, s.sT, s.frobp, s.frob, form));
     } else if (nep->kind == RSRR_T_SPARSE) {
         // the FP64 copy is formed from the sparse rows, the LU input from it
         RSRR_TRY(upload_coef(c, nep, z, B, s.coef));
         CsrDev d;
         RSRR_TRY(csr_upload(c, nep, d));
-        RSRR_HIP(assemble_sparse(c->stream, n, nep->J, d.terms, s.coef, B, T64, s.ld, s.sT, s.Tres, s.ld, s.sT,
-                                 s.frobp, s.frob, d.bad));
+        RSRR_HIP(assemble_sparse(c->stream, n, nep->J, d.terms, s.coef, B,
+                                 form == LU_C64 ? (float2*)s.Tlu : nullptr, s.ld, s.sT, s.Tres, s.ld, s.sT, s.frobp,
+                                 s.frob, d.bad));
         RSRR_TRY(csr_check(c, d));
-        if (Tlu128) RSRR_HIP(copy_c128(c->stream, n, n, s.Tres, s.ld, s.sT, Tlu128, s.ld, s.sT, B));
+        if (form == LU_C128)
+            RSRR_HIP(copy_c128(c->stream, n, n, s.Tres, s.ld, s.sT, (double2*)s.Tlu, s.ld, s.sT, B));
     } else {
         std::vector<double2> zz(B);
         for (int k = 0; k < B; ++k) zz[k] = make_double2(z[k].real(), z[k].imag());
         RSRR_HIP(hipMemcpyAsync(s.zdev, zz.data(), (size_t)B * 16, hipMemcpyHostToDevice, c->stream));
         RSRR_HIP(hipStreamSynchronize(c->stream));
-        RSRR_HIP(assemble_helmholtz(c->stream, n, nep->points, nep->w, s.zdev, B, T64, s.ld, s.sT, s.Tres, s.ld, s.sT,
-                                    s.frobp, s.frob));
-        if (Tlu128) RSRR_HIP(copy_c128(c->stream, n, n, s.Tres, s.ld, s.sT, Tlu128, s.ld, s.sT, B));
+        RSRR_HIP(assemble_helmholtz(c->stream, n, nep->points, nep->w, s.zdev, B, s.Tlu, s.ld, s.sT, s.Tres, s.ld,
+                                    s.sT, s.frobp, s.frob, form));
     }
     return RSRR_OK;
 }

@@ -22,13 +22,24 @@ constexpr int AS_NT = 256;
 constexpr int AS_PG = 24;     // points per thread pass
 constexpr int AS_MAXJ = 64;   // separable terms held in LDS
 
+// The LU's copy of an entry: none, complex FP32, the real part in FP32, or complex FP64 (written here: a
+// pass of its own read the FP64 matrices again, 1.0 ms of 64 real matrices with n = 2025, 0.7 ms of 32
+// complex ones with n = 2048)
+template <int OL>
+RSRR_DEV void put_lu(void* T, long e, double2 t)
+{
+    if constexpr (OL == LU_C64) ((float2*)T)[e] = to_c64(t);
+    if constexpr (OL == LU_R32) ((float*)T)[e] = (float)t.x;
+    if constexpr (OL == LU_C128) ((double2*)T)[e] = t;
+}
+
 // element e of a column-major n x n matrix: (e % n, e / n)
-template <bool O64, bool O128>
+template <int OL, bool O128>
 __global__ __launch_bounds__(AS_NT) void assemble_sep_kernel(
     int n, int J, const double2* __restrict__ A, int lda, long sAj,
     const double2* __restrict__ coef,   // [J][B] complex, point-fastest
     int B, int k0,                      // this launch handles points k0 .. k0+PG-1 (< B)
-    float2* __restrict__ T64, int ld64, long s64,
+    void* __restrict__ TL, int ldl, long sL,
     double2* __restrict__ T128, int ld128, long s128,
     double* __restrict__ frob_part, int nparts)
 {
@@ -60,7 +71,7 @@ __global__ __launch_bounds__(AS_NT) void assemble_sep_kernel(
         for (int p = 0; p < AS_PG; ++p) {
             if (p < npts) {
                 const long k = k0 + p;
-                if (O64) T64[k * s64 + i + (long)c * ld64] = to_c64(t[p]);
+                put_lu<OL>(TL, k * sL + i + (long)c * ldl, t[p]);
                 if (O128) T128[k * s128 + i + (long)c * ld128] = t[p];
                 acc[p] = t[p].x * t[p].x + t[p].y * t[p].y;
             }
@@ -82,11 +93,11 @@ __global__ __launch_bounds__(AS_NT) void assemble_sep_kernel(
     }
 }
 
-template <bool O64, bool O128>
+template <int OL, bool O128>
 __global__ __launch_bounds__(AS_NT) void assemble_helm_kernel(
     int n, const double* __restrict__ pts, double w,
     const double2* __restrict__ z, int B, int k0,
-    float2* __restrict__ T64, int ld64, long s64,
+    void* __restrict__ TL, int ldl, long sL,
     double2* __restrict__ T128, int ld128, long s128,
     double* __restrict__ frob_part, int nparts)
 {
@@ -125,7 +136,7 @@ __global__ __launch_bounds__(AS_NT) void assemble_helm_kernel(
                     // sqrt(w/pi)/2 + i z w/(4 pi)
                     t = make_double2(diag_re - zk.y * w * inv4pi, zk.x * w * inv4pi);
                 }
-                if (O64) T64[k * s64 + i + (long)c * ld64] = to_c64(t);
+                put_lu<OL>(TL, k * sL + i + (long)c * ldl, t);
                 if (O128) T128[k * s128 + i + (long)c * ld128] = t;
                 acc[p] = t.x * t.x + t.y * t.y;
             }
@@ -259,24 +270,24 @@ hipError_t assemble_separable_group(hipStream_t st, const SepInstance* ins, int 
 int assemble_max_terms() { return AS_MAXJ; }
 
 hipError_t assemble_separable(hipStream_t st, int n, int J, const double2* A, int lda, const double2* coef, int B,
-                              float2* T64, int ld64, long s64, double2* T128, int ld128, long s128,
-                              double* frob_part, double* frob)
+                              void* TL, int ldl, long sL, double2* T128, int ld128, long s128,
+                              double* frob_part, double* frob, LuCopy form)
 {
-    if (J > AS_MAXJ) return hipErrorInvalidValue;
+    if (J > AS_MAXJ || (form != LU_C64 && !T128)) return hipErrorInvalidValue;
     const long nn = (long)n * n;
     const int nparts = (int)((nn + AS_NT - 1) / AS_NT);
     const long sAj = (long)lda * n;
+#define AS_L(OL, O128)                                                                                         \
+    hipLaunchKernelGGL((assemble_sep_kernel<OL, O128>), dim3(nparts), dim3(AS_NT), 0, st, n, J, A, lda, sAj, coef, B, k0, \
+                       TL, ldl, sL, T128, ld128, s128, frob_part, nparts)
     for (int k0 = 0; k0 < B; k0 += AS_PG) {
-        if (T64 && T128)
-            hipLaunchKernelGGL((assemble_sep_kernel<true, true>), dim3(nparts), dim3(AS_NT), 0, st, n, J, A, lda, sAj,
-                               coef, B, k0, T64, ld64, s64, T128, ld128, s128, frob_part, nparts);
-        else if (T64)
-            hipLaunchKernelGGL((assemble_sep_kernel<true, false>), dim3(nparts), dim3(AS_NT), 0, st, n, J, A, lda,
-                               sAj, coef, B, k0, T64, ld64, s64, T128, ld128, s128, frob_part, nparts);
-        else
-            hipLaunchKernelGGL((assemble_sep_kernel<false, true>), dim3(nparts), dim3(AS_NT), 0, st, n, J, A, lda,
-                               sAj, coef, B, k0, T64, ld64, s64, T128, ld128, s128, frob_part, nparts);
+        if (!TL) AS_L(0, true);
+        else if (!T128) AS_L(LU_C64, false);
+        else if (form == LU_C64) AS_L(LU_C64, true);
+        else if (form == LU_R32) AS_L(LU_R32, true);
+        else AS_L(LU_C128, true);
     }
+#undef AS_L
     hipLaunchKernelGGL(frob_finish_kernel, dim3(B), dim3(64), 0, st, frob_part, nparts, frob);
     return hipGetLastError();
 }
@@ -336,22 +347,22 @@ hipError_t assemble_sparse(hipStream_t st, int n, int J, const CsrTerm* terms, c
 }
 
 hipError_t assemble_helmholtz(hipStream_t st, int n, const double* pts, double w, const double2* z, int B,
-                              float2* T64, int ld64, long s64, double2* T128, int ld128, long s128,
-                              double* frob_part, double* frob)
+                              void* TL, int ldl, long sL, double2* T128, int ld128, long s128,
+                              double* frob_part, double* frob, LuCopy form)
 {
+    if (form == LU_R32 || (form != LU_C64 && !T128)) return hipErrorInvalidValue;
     const long nn = (long)n * n;
     const int nparts = (int)((nn + AS_NT - 1) / AS_NT);
+#define AS_L(OL, O128)                                                                                         \
+    hipLaunchKernelGGL((assemble_helm_kernel<OL, O128>), dim3(nparts), dim3(AS_NT), 0, st, n, pts, w, z, B, k0, \
+                       TL, ldl, sL, T128, ld128, s128, frob_part, nparts)
     for (int k0 = 0; k0 < B; k0 += AS_PG) {
-        if (T64 && T128)
-            hipLaunchKernelGGL((assemble_helm_kernel<true, true>), dim3(nparts), dim3(AS_NT), 0, st, n, pts, w, z, B,
-                               k0, T64, ld64, s64, T128, ld128, s128, frob_part, nparts);
-        else if (T64)
-            hipLaunchKernelGGL((assemble_helm_kernel<true, false>), dim3(nparts), dim3(AS_NT), 0, st, n, pts, w, z,
-                               B, k0, T64, ld64, s64, T128, ld128, s128, frob_part, nparts);
-        else
-            hipLaunchKernelGGL((assemble_helm_kernel<false, true>), dim3(nparts), dim3(AS_NT), 0, st, n, pts, w, z,
-                               B, k0, T64, ld64, s64, T128, ld128, s128, frob_part, nparts);
+        if (!TL) AS_L(0, true);
+        else if (!T128) AS_L(LU_C64, false);
+        else if (form == LU_C64) AS_L(LU_C64, true);
+        else AS_L(LU_C128, true);
     }
+#undef AS_L
     hipLaunchKernelGGL(frob_finish_kernel, dim3(B), dim3(64), 0, st, frob_part, nparts, frob);
     return hipGetLastError();
 }

@@ -107,17 +107,6 @@ __global__ __launch_bounds__(EW_NT) void axpy_widen_kernel(int n, int L, const f
 // is not real after all, the refinement stalls and the point is redone on the
 // FP64 complex path.
 
-// Tr_k = (float) Re T_k.
-__global__ __launch_bounds__(EW_NT) void narrow_real_kernel(int n, const double2* __restrict__ T, int ldt, long sT,
-                                                             float* __restrict__ Tr, int ldr, long sTr)
-{
-    const int k = blockIdx.y;
-    const long e = (long)blockIdx.x * EW_NT + threadIdx.x;
-    if (e >= (long)n * n) return;
-    const int i = (int)(e % n), c = (int)(e / n);
-    Tr[k * sTr + i + (long)c * ldr] = (float)T[k * sT + i + (long)c * ldt].x;
-}
-
 // D_k(:, c) = (float) (Re R_k(:, c) * inv[k*L + c]) (inv = null: 1) for active points.
 __global__ __launch_bounds__(EW_NT) void scale_narrow_real_kernel(int n, int L, const double2* __restrict__ R, int ldr,
                                                                    long sR, const double* __restrict__ inv,
@@ -630,12 +619,6 @@ hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt,
     return hipGetLastError();
 }
 
-hipError_t narrow_real(hipStream_t st, int n, const double2* T, int ldt, long sT, float* Tr, int ldr, long sTr,
-                       int B)
-{
-    hipLaunchKernelGGL(narrow_real_kernel, ew_grid((long)n * n, B), dim3(EW_NT), 0, st, n, T, ldt, sT, Tr, ldr, sTr);
-    return hipGetLastError();
-}
 hipError_t scale_narrow_real(hipStream_t st, int n, int L, const double2* R, int ldr, long sR, const double* inv,
                              float* D, int ldd, long sD, const int* active, int B)
 {

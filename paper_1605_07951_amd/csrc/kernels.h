@@ -141,14 +141,18 @@ hipError_t sgemm(hipStream_t st, int M, int N, int K, float alpha, const float* 
                  const float* B, int ldb, long sB, float beta, float* C, int ldc, long sC, int batch, int tag = 0);
 
 // ---- assembly (assemble.hip) ----
-// T64/T128 may be null (not written); batch strides s64/s128 in elements.
+// The LU's copy TL (in `form`: complex FP32, the real part in FP32, complex FP64; null: none) and the
+// FP64 matrices T128 (null: none, complex FP32 copies only); batch strides in elements.
+enum LuCopy { LU_C64 = 1, LU_R32 = 2, LU_C128 = 3 };
 // frob_part: B * ceil(n*n/256) doubles of scratch; frob: B doubles (||T_k||_F).
 hipError_t assemble_separable(hipStream_t st, int n, int J, const double2* A, int lda, const double2* coef, int B,
-                              float2* T64, int ld64, long s64, double2* T128, int ld128, long s128,
-                              double* frob_part, double* frob);
+                              void* TL, int ldl, long sL, double2* T128, int ld128, long s128,
+                              double* frob_part, double* frob,
+                              LuCopy form = LU_C64);
 hipError_t assemble_helmholtz(hipStream_t st, int n, const double* pts, double w, const double2* z, int B,
-                              float2* T64, int ld64, long s64, double2* T128, int ld128, long s128,
-                              double* frob_part, double* frob);
+                              void* TL, int ldl, long sL, double2* T128, int ld128, long s128,
+                              double* frob_part, double* frob,
+                              LuCopy form = LU_C64);
 hipError_t helmholtz_taylor(hipStream_t st, int n, const double* pts, double w, double gre, double gim, int p,
                             double2* Tp, int ld);
 // Taylor terms p0 .. p0+G-1 of the Helmholtz matrix about gamma, term p0+g at Tp + g*sT.
@@ -208,11 +212,8 @@ hipError_t colnorms(hipStream_t st, int n, int L, const double2* X, int ldx, lon
 // skipped (active may be null); U null gives R_b = T_b X_b.  resid_skinny_ok(L)
 // tells whether it applies.
 bool resid_skinny_ok(int L);
-// Real FP32 corrections for a real NEP at real points: Tr = (float) Re T;
-// D = (float)(Re R * inv) (inv may be null: 1); X = (D, 0) (scale null) or
+// Real FP32 corrections for a real NEP at real points: D = (float)(Re R * inv) (inv may be null: 1); X = (D, 0) (scale null) or
 // Re X += scale * D.
-hipError_t narrow_real(hipStream_t st, int n, const double2* T, int ldt, long sT, float* Tr, int ldr, long sTr,
-                       int B);
 hipError_t scale_narrow_real(hipStream_t st, int n, int L, const double2* R, int ldr, long sR, const double* inv,
                              float* D, int ldd, long sD, const int* active, int B);
 hipError_t axpy_widen_real(hipStream_t st, int n, int L, const float* D, int ldd, long sD, const double* scale,
