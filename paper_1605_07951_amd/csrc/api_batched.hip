@@ -211,8 +211,8 @@ struct BucketBufs {
     void* T; double2* T128; double2* Ub; double2* Xb; double2* R; float2* D64; int* ipiv; int2* perm;
     int* info; void* inv; void* tmp; int* nk; double2* coef; double* frobp; double* frob; double* un; double* rn;
     double* xn; double* inv_s; double* scl; int* active; double* prev; double* resid; int* iters; double* ones;
-    void* pair; SepInstance* sep; RhsInstance* rhs;
-    long sT, sU, sP, sPerm, sInv, sTmp, sPair;
+    void* pair; void* pack; SepInstance* sep; RhsInstance* rhs;
+    long sT, sU, sP, sPerm, sInv, sTmp, sPair, sPack;
 };
 
 // Strides of one point's factor data in the bucket buffers and in a FactorStore.
@@ -301,6 +301,7 @@ rsrr_status run_bucket(rsrr_ctx* c, hipStream_t sm, const rsrr_instance* inst, c
     w.ipiv = b.ipiv; w.sP = b.sP; w.perm = b.perm; w.sPerm = b.sPerm;
     w.info = b.info; w.inv = b.inv; w.sInv = b.sInv; w.tmp = b.tmp; w.sTmp = b.sTmp;
     w.pair = b.pair; w.sPair = b.sPair; w.ldpair = P;
+    w.pack = b.pack; w.sPack = b.sPack;
     if (!from) {
         if (mixed) RSRR_HIP(getrf_batched<float>(sm, (float2*)b.T, b.sT, P, P, nb, w, (int)M));
         else RSRR_HIP(getrf_batched<double>(sm, (double2*)b.T, b.sT, P, P, nb, w, (int)M));
@@ -463,6 +464,11 @@ rsrr_status bucket_bufs(BatchedState& S, hipStream_t sm, int P, int Lmax, long M
     b.iters = (int*)bget(S, s++, (size_t)M * 4, sm);
     b.ones = (double*)bget(S, s++, (size_t)M * Lmax * 8, sm);
     b.pair = mixed && !from ? bget(S, s++, (size_t)M * b.sPair * 8, sm) : (void*)(s++, nullptr);
+    // split operands of the trailing updates (without them those run in FP32)
+    b.sPack = mixed && !from && split_ok(P - 2 * nbmax, P - 2 * nbmax, 2 * nbmax)
+                  ? (long)split_pack_bytes<float2>(P, 2 * nbmax)
+                  : 0;
+    b.pack = b.sPack ? bget(S, s++, (size_t)M * b.sPack, sm) : (void*)(s++, nullptr);
     b.sep = (SepInstance*)bget(S, s++, (size_t)nins * sizeof(SepInstance), sm);
     b.rhs = (RhsInstance*)bget(S, s++, (size_t)nins * sizeof(RhsInstance), sm);
     if ((!from && (!b.T || !b.perm || (mixed && (!b.inv || !b.pair)))) || !b.T128 || !b.Ub || !b.Xb || !b.R ||

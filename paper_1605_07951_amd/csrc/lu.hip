@@ -1034,7 +1034,7 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     // update done in column parts gives its whole width (Nall) and the part's first column
     // (j0); with split operands the first part (j0 = 0) packs them for all parts (B unless the U
     // rows came packed).
-    auto timed_update_on = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
+    auto timed_update = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
                                const C* Bop, C* Cop, int Nall = 0, int j0 = 0, bool bpacked = false) {
         const bool timed = rec && rec->used < rec->cap;
         if (timed) (void)hipEventRecord(rec->ev[2 * rec->used], s);
@@ -1063,9 +1063,6 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         } else if (rec) {
             rec->dropped++;
         }
-    };
-    auto timed_update = [&](int M, int N, int kdepth, const C* Aop, int ldaop, long sAop, const C* Bop, C* Cop) {
-        timed_update_on(st, M, N, kdepth, Aop, ldaop, sAop, Bop, Cop);
     };
     // panel p on stream s: factor, composed interchanges, diagonal-block inverses (FP32 paths)
     auto panel = [&](hipStream_t s, int c0, int jb, int p) -> int2* {
@@ -1101,55 +1098,55 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         }
         return false;
     };
-    int c0 = 0, p = 0;
-    // Look-ahead over full pairs (two nb-wide panels with a trailing block after
-    // them).  A pair's work splits into a front part that touches only its own
-    // 2 nb columns (panel p, its interchanges and U rows on panel p+1's columns,
-    // panel p+1's columns update, panel p+1, the interchanged copy of L21_p) and
-    // a back part on the trailing columns (the interchanges and U rows of both
-    // panels there, the copy of L21_{p+1}).  After the back part of pair i, the
-    // trailing update is split: first the 2 nb columns of pair i+1, then, while
-    // the rest of the update runs on `st`, pair i+1's front part runs on the side
-    // stream (its own pair buffer); the next back part waits for both.
-    if (pairing && w.side && w.pair2 && w.ev_a && w.ev_b && n > 2 * nb) {
-        C* Wb[2] = {(C*)w.pair, (C*)w.pair2};
-        const int ldw = w.ldpair;
-        auto front = [&](hipStream_t s, int q0, int pp, C* Wp) {
-            const int q1 = q0 + nb;
-            C* TL = Wp + (long)ldw * 2 * nb;
-            const int2* pm0 = panel(s, q0, nb, pp);
-            perm_rows<C>(s, pm0, w.sPerm, A + (long)q1 * lda, sA, lda, (C*)w.tmp, w.sTmp, nb, q0, nb, nb, w.active,
-                         batch);
-            (void)gemm_sub<C>(s, nb, nb, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                              A + q0 + (long)q1 * lda, lda, sA, batch, 0, -1.0, 0.0);
-            (void)gemm_sub<C>(s, n - q1, nb, nb, A + q1 + (long)q0 * lda, lda, sA, A + q0 + (long)q1 * lda, lda, sA,
-                              A + q1 + (long)q1 * lda, lda, sA, batch);
-            const int2* pm1 = panel(s, q1, nb, pp + 1);
-            copy_rows<C>(s, q1, n, nb, A + (long)q0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
-            perm_rows<C>(s, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, q1, nb, nb, w.active, batch);
-        };
-        auto back = [&](int q0, int pp, C* Wp) -> bool {
-            const int q1 = q0 + nb, q2 = q1 + nb, rest = n - q2;
-            C* TL = Wp + (long)ldw * 2 * nb;
-            if (split_pair_rows(st, q0, pp, TL)) {
-                copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
-                             batch);
-                return true;
-            }
-            const int2* pm0 = w.perm + (long)pp * 2 * MAX_NB;
-            const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
-            C* Ar2 = A + (long)q2 * lda;
-            perm_rows<C>(st, pm0, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, q0, nb, rest, w.active, batch);
-            (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                              Ar2 + q0, lda, sA, batch, 0, -1.0, 0.0);
-            perm_rows<C>(st, pm1, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, q1, nb, rest, w.active, batch);
-            (void)gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch);
-            (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
-                              w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0);
+    // A pair's work before its trailing update: a front part that touches only its own 2 nb columns
+    // (panel p, its interchanges and U rows on panel p+1's columns, panel p+1's columns update,
+    // panel p+1, the interchanged copy of L21_p) and a back part on the trailing columns (the
+    // interchanges and U rows of both panels there, the copy of L21_{p+1}).
+    const int ldw = w.ldpair;
+    auto front = [&](hipStream_t s, int q0, int pp, C* Wp) {
+        const int q1 = q0 + nb;
+        C* TL = Wp + (long)ldw * 2 * nb;
+        const int2* pm0 = panel(s, q0, nb, pp);
+        perm_rows<C>(s, pm0, w.sPerm, A + (long)q1 * lda, sA, lda, (C*)w.tmp, w.sTmp, nb, q0, nb, nb, w.active,
+                     batch);
+        (void)gemm_sub<C>(s, nb, nb, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                          A + q0 + (long)q1 * lda, lda, sA, batch, 0, -1.0, 0.0);
+        (void)gemm_sub<C>(s, n - q1, nb, nb, A + q1 + (long)q0 * lda, lda, sA, A + q0 + (long)q1 * lda, lda, sA,
+                          A + q1 + (long)q1 * lda, lda, sA, batch);
+        const int2* pm1 = panel(s, q1, nb, pp + 1);
+        copy_rows<C>(s, q1, n, nb, A + (long)q0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
+        perm_rows<C>(s, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, q1, nb, nb, w.active, batch);
+    };
+    auto back = [&](int q0, int pp, C* Wp) -> bool {
+        const int q1 = q0 + nb, q2 = q1 + nb, rest = n - q2;
+        C* TL = Wp + (long)ldw * 2 * nb;
+        if (split_pair_rows(st, q0, pp, TL)) {
             copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
                          batch);
-            return false;
-        };
+            return true;
+        }
+        const int2* pm0 = w.perm + (long)pp * 2 * MAX_NB;
+        const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
+        C* Ar2 = A + (long)q2 * lda;
+        perm_rows<C>(st, pm0, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, q0, nb, rest, w.active, batch);
+        (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                          Ar2 + q0, lda, sA, batch, 0, -1.0, 0.0);
+        perm_rows<C>(st, pm1, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, q1, nb, rest, w.active, batch);
+        (void)gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch);
+        (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
+                          w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0);
+        copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
+                     batch);
+        return false;
+    };
+    int c0 = 0, p = 0;
+    // Look-ahead over full pairs (two nb-wide panels with a trailing block after
+    // them).  After the back part of pair i, the trailing update is split: first
+    // the 2 nb columns of pair i+1, then, while the rest of the update runs on
+    // `st`, pair i+1's front part runs on the side stream (its own pair buffer);
+    // the next back part waits for both.
+    if (pairing && w.side && w.pair2 && w.ev_a && w.ev_b && n > 2 * nb) {
+        C* Wb[2] = {(C*)w.pair, (C*)w.pair2};
         int buf = 0;
         front(st, 0, 0, Wb[0]);
         if (w.first_panel) (void)hipEventRecord(w.first_panel, st);
@@ -1161,13 +1158,13 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             C* Cop = A + c2 + (long)c2 * lda;
             if (rest <= 2 * nb) {
                 // no full pair follows: one update, the loop below finishes the tail
-                timed_update_on(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
+                timed_update(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
                 c0 = c2;
                 p += 2;
                 break;
             }
             const int wn = 2 * nb;
-            timed_update_on(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
+            timed_update(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
             (void)hipEventRecord(w.ev_a, st);
             // the rest of the update is enqueued before the next pair's panels (a chain of
             // small launches), so the host never holds it back behind them
@@ -1176,15 +1173,15 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
                 // use (while the next panels are factored), the rest on every CU
                 const int n1 = w.la_cols > 0 ? std::min(rest - wn, std::max(32, w.la_cols / 32 * 32)) : rest - wn;
                 (void)hipStreamWaitEvent(w.upd, w.ev_a, 0);
-                timed_update_on(w.upd, rest, n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
+                timed_update(w.upd, rest, n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
                                 Cop + (long)wn * lda, rest, wn);
                 (void)hipEventRecord(w.ev_c, w.upd);
                 (void)hipStreamWaitEvent(st, w.ev_c, 0);
                 if (n1 < rest - wn)
-                    timed_update_on(st, rest, rest - wn - n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)(wn + n1) * lda,
+                    timed_update(st, rest, rest - wn - n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)(wn + n1) * lda,
                                     Cop + (long)(wn + n1) * lda, rest, wn + n1);
             } else {
-                timed_update_on(st, rest, rest - wn, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
+                timed_update(st, rest, rest - wn, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
                                 Cop + (long)wn * lda, rest, wn);
             }
             (void)hipStreamWaitEvent(w.side, w.ev_a, 0);
@@ -1196,58 +1193,33 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             buf ^= 1;
         }
     }
-    while (c0 < n) {
-        const int jb0 = (n - c0 < nb) ? n - c0 : nb;
-        const int c1 = c0 + jb0;
-        const int jb1 = pairing ? ((n - c1 < nb) ? n - c1 : nb) : 0;
-        const int2* pm0 = panel(st, c0, jb0, p);
-        const int rest0 = n - c1;
-        if (rest0 > 0) {
-            C* Ar = A + (long)c1 * lda;
-            if (use_inv) {
-                // interchanges on the right block (top rows to the scratch), then U12 = L11^-1 A12 on MFMA
-                perm_rows<C>(st, pm0, w.sPerm, Ar, sA, lda, (C*)w.tmp, w.sTmp, nb, c0, jb0, rest0, w.active, batch);
-                (void)gemm_sub<C>(st, jb0, rest0, jb0, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
-                                  w.sTmp, Ar + c0, lda, sA, batch, 0, -1.0, 0.0);
-            } else {
-                if constexpr (sizeof(C) == sizeof(double2))
-                    perm_trsm(st, A, sA, lda, pm0, w.sPerm, Ar, sA, lda, c0, jb0, rest0, 1, w.active, batch);
-            }
-            if (c0 == 0 && w.first_panel) (void)hipEventRecord(w.first_panel, st);
-        }
-        const int c2 = c1 + jb1, rest2 = n - c2;
-        if (jb1 <= 0 || rest2 <= 0) {
-            if (rest0 > 0)
-                timed_update(rest0, rest0, jb0, A + c1 + (long)c0 * lda, lda, sA, A + c0 + (long)c1 * lda,
-                             A + c1 + (long)c1 * lda);
-            c0 = c1;
-            p += 1;
-            continue;
-        }
+    // without look-ahead: the pairs in turn; then the last panels one by one
+    for (; pairing && n - c0 > 2 * nb; c0 += 2 * nb, p += 2) {
+        const int c2 = c0 + 2 * nb, rest = n - c2;
         C* Wp = (C*)w.pair;
-        const int ldw = w.ldpair;
-        C* TL = Wp + (long)ldw * 2 * nb;
-        // panel p+1's columns receive panel p's update, then panel p+1
-        (void)gemm_sub<C>(st, rest0, jb1, jb0, A + c1 + (long)c0 * lda, lda, sA, A + c0 + (long)c1 * lda, lda, sA,
-                          A + c1 + (long)c1 * lda, lda, sA, batch);
-        const int2* pm1 = panel(st, c1, jb1, p + 1);
-        // L21_p rows c1.. into the pair buffer, interchanged like panel p+1 (top rows to TL)
-        copy_rows<C>(st, c1, n, jb0, A + (long)c0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
-        perm_rows<C>(st, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, c1, jb1, jb0, w.active, batch);
-        // panel p+1's interchanges on the trailing columns; its U rows get panel p's update, then L11^-1
-        C* Ar2 = A + (long)c2 * lda;
-        perm_rows<C>(st, pm1, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, c1, jb1, rest2, w.active, batch);
-        (void)gemm_sub<C>(st, jb1, rest2, jb0, TL, nb, w.sPair, A + c0 + (long)c2 * lda, lda, sA, (C*)w.tmp, nb,
-                          w.sTmp, batch);
-        (void)gemm_sub<C>(st, jb1, rest2, jb1, panel_inv<C>(w, p + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
-                          w.sTmp, Ar2 + c1, lda, sA, batch, 0, -1.0, 0.0);
-        // [L21_p' L21_{p+1}] side by side, one update of depth jb0 + jb1
-        copy_rows<C>(st, c2, n, jb1, A + (long)c1 * lda, lda, sA, Wp + (long)ldw * jb0, ldw, w.sPair, w.active,
-                     batch);
-        timed_update(rest2, rest2, jb0 + jb1, Wp + c2, ldw, w.sPair, A + c0 + (long)c2 * lda,
-                     A + c2 + (long)c2 * lda);
-        c0 = c2;
-        p += 2;
+        front(st, c0, p, Wp);
+        if (c0 == 0 && w.first_panel) (void)hipEventRecord(w.first_panel, st);
+        const bool bpacked = back(c0, p, Wp);
+        timed_update(st, rest, rest, 2 * nb, Wp + c2, ldw, w.sPair, A + c0 + (long)c2 * lda, A + c2 + (long)c2 * lda,
+                        rest, 0, bpacked);
+    }
+    for (; c0 < n; c0 += nb, ++p) {
+        const int jb = std::min(nb, n - c0), c1 = c0 + jb, rest = n - c1;
+        const int2* pm = panel(st, c0, jb, p);
+        if (rest <= 0) break;
+        C* Ar = A + (long)c1 * lda;
+        if (use_inv) {
+            // interchanges on the right block (top rows to the scratch), then U12 = L11^-1 A12 on MFMA
+            perm_rows<C>(st, pm, w.sPerm, Ar, sA, lda, (C*)w.tmp, w.sTmp, nb, c0, jb, rest, w.active, batch);
+            (void)gemm_sub<C>(st, jb, rest, jb, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                              Ar + c0, lda, sA, batch, 0, -1.0, 0.0);
+        } else {
+            if constexpr (sizeof(C) == sizeof(double2))
+                perm_trsm(st, A, sA, lda, pm, w.sPerm, Ar, sA, lda, c0, jb, rest, 1, w.active, batch);
+        }
+        if (c0 == 0 && w.first_panel) (void)hipEventRecord(w.first_panel, st);
+        timed_update(st, rest, rest, jb, A + c1 + (long)c0 * lda, lda, sA, A + c0 + (long)c1 * lda,
+                        A + c1 + (long)c1 * lda);
     }
     return hipGetLastError();
 }
