@@ -34,6 +34,10 @@ sys.path.insert(0, ROOT)
 METRIC = "resolvent solves/sec (n=4096, L=64) & % MFMA peak; p50/p99 NEP latency"
 PEAK_FP32_MFMA_TFLOPS = 157.3
 PEAK_FP64_MFMA_TFLOPS = 78.6
+PEAK_FP16_MFMA_TFLOPS = 2516.6
+# FP32 products as three FP16 products of split operands (the LU's trailing updates of 384 rows and more)
+PEAK_SPLIT_TFLOPS = PEAK_FP16_MFMA_TFLOPS / 3
+SPLIT_MIN_N = 384
 PEAK_HBM_GBS = 8000.0
 
 
@@ -99,14 +103,14 @@ def build_workload(args):
 
 def _profile_figure(name, key, conv):
     """A figure from a committed rocprofv3 counter summary under profiles/, or None when the
-    kernel or the LU driver has changed since the counters were taken (hash of both files)."""
+    kernels or the LU driver have changed since the counters were taken (hash of the files)."""
     import hashlib
     path = os.path.join(ROOT, "profiles", name)
-    srcs = [os.path.join(ROOT, "paper_1605_07951_amd", "csrc", f) for f in ("gemm.hip", "lu.hip")]
+    srcs = [os.path.join(ROOT, "paper_1605_07951_amd", "csrc", f) for f in ("gemm.hip", "lu.hip", "split.hip")]
     try:
         txt = open(path).read()
         val = conv(txt.split(key + ":")[1].split()[0])
-        sha = txt.split("source_sha256_16 (csrc/gemm.hip + csrc/lu.hip):")[1].split()[0]
+        sha = txt.split("source_sha256_16 (csrc/gemm.hip + csrc/lu.hip + csrc/split.hip):")[1].split()[0]
         h = hashlib.sha256(b"".join(open(s, "rb").read() for s in srcs)).hexdigest()[:16]
     except (OSError, IndexError, ValueError):
         return None
@@ -314,7 +318,7 @@ def run_serve(args):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "c64 LU (f32 MFMA) + f64 refinement",
+        "dtype": "c64 LU (f32 panels and sums, split-f16 MFMA updates) + f64 refinement",
         "data": "synthetic (seeded serving stream: delay Laplacian and Helmholtz sphere NEPs, Gaussian probes)",
         "config": {"workload": f"serving stream: first {len(items)} of the seeded 2000-request stream, Poisson "
                                f"{args.rate}/s, 50/50 delay (n 512/1024/2048, N=48, L=32) / Helmholtz "
@@ -398,14 +402,15 @@ def run_batched(args):
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "c64 LU (f32 MFMA) + f64 refinement",
+        "dtype": "c64 LU (f32 panels and sums, split-f16 MFMA updates) + f64 refinement",
         "data": "synthetic (seeded rotated diagonal QEPs, complex Gaussian probes)",
         "config": {"workload": f"ragged batch: {len(sizes)} rotated diagonal QEPs, n ~ U{{64..1024}} "
                                f"(sum n = {sum(sizes)}), N={N}, L={L}, ellipse (5i; 4, 1)",
                    "step": "all points of all instances: assembly, LU, solves, refinement (hipGraph replay)"},
+        # buckets of 384 rows and more update with split FP16 operands, smaller ones in FP32
         "roofline": {"bound": "mfma", "kernel": "whole batched step (LU algorithmic flops / step time)",
-                     "achieved": round(achieved, 3), "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_FP32_MFMA_TFLOPS, 4), "traffic": None},
+                     "achieved": round(achieved, 3), "peak": round(PEAK_SPLIT_TFLOPS, 1), "unit": "TFLOP/s",
+                     "frac": round(achieved / PEAK_SPLIT_TFLOPS, 4), "traffic": None},
         "batched": {"graph_ms": round(1e3 * graph_s, 3), "eager_ms": round(1e3 * eager_s, 3),
                     "per_instance_loop_ms": round(1e3 * loop_s, 3), "capture_ms": round(1e3 * capture_s, 1),
                     "autotune_first_call_ms": round(1e3 * tune_s, 1),
@@ -457,7 +462,7 @@ def run_adaptive(args):
         "unit": "resolvent solves/s",
         "n_gpus": 1, "steps": 1, "warmup": 1, "ms_per_step": round(1e3 * t_two, 3),
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "c64 LU (f32 MFMA) + f64 refinement",
+        "dtype": "c64 LU (f32 panels and sums, split-f16 MFMA updates) + f64 refinement",
         "data": "synthetic (seeded Fibonacci-sphere Helmholtz single-layer NEP, complex Gaussian probes)",
         "config": {"workload": f"two-stage sampling, helmholtz_sphere n={n} L={U_host.shape[1]} "
                                f"ellipse(3.8;1.4,0.3), stage 1 on {args.n1} contour points",
@@ -582,19 +587,22 @@ def run_real(args):
                      "ir_iters_max": max(i["ir_iters"] for i in info)}
     r32 = out["r32"]
     achieved = r32["update_tflops"] or 0.0
+    split = n >= SPLIT_MIN_N
+    peak = PEAK_SPLIT_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
     res = {
         "metric": METRIC,
         "value": r32["solves_per_s"],
         "unit": "resolvent solves/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": r32["ms_per_step"],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f32 LU (f32 MFMA) + f64 refinement",
+        "dtype": "f32 LU (f32 panels and sums, split-f16 MFMA updates) + f64 refinement",
         "data": f"synthetic ({nep.name}, real Gaussian probes)",
         "config": {"workload": f"real sampling, {nep.name} n={n}, N={N} Chebyshev points of [{lo}, {hi}], L={L}",
                    "step": "rsrr_sample over all N points (assembly, real LU, solves, refinement)"},
-        "roofline": {"bound": "mfma", "kernel": "LU trailing update, real (sgemm_mfma_kernel<*,1>)",
-                     "achieved": achieved, "peak": PEAK_FP32_MFMA_TFLOPS, "unit": "TFLOP/s",
-                     "frac": round(achieved / PEAK_FP32_MFMA_TFLOPS, 4), "traffic": None},
+        "roofline": {"bound": "mfma", "kernel": "LU trailing update, real "
+                     + ("(gemm_split_kernel<float,true>)" if split else "(sgemm_mfma_kernel<*,1>)"),
+                     "achieved": achieved, "peak": round(peak, 1), "unit": "TFLOP/s",
+                     "frac": round(achieved / peak, 4), "traffic": None},
         "paths": out,
         "r32_over_c64": round(out["r32"]["solves_per_s"] / out["c64"]["solves_per_s"], 3),
         "r32_over_c128": round(out["r32"]["solves_per_s"] / out["c128"]["solves_per_s"], 3),
@@ -827,7 +835,9 @@ def main():
 
     value = N * args.steps / elapsed
     ms_per_step = 1e3 * elapsed / args.steps
-    peak = PEAK_FP32_MFMA_TFLOPS if prec == R.RSRR_PREC_C64_IR else PEAK_FP64_MFMA_TFLOPS
+    split = prec == R.RSRR_PREC_C64_IR and n >= SPLIT_MIN_N
+    peak = (PEAK_SPLIT_TFLOPS if split else
+            PEAK_FP32_MFMA_TFLOPS if prec == R.RSRR_PREC_C64_IR else PEAK_FP64_MFMA_TFLOPS)
     avg_ms = st["ms"] / max(1, st["launches"])
     achieved = (st["flops"] / (st["ms"] * 1e-3) / 1e12) if st["ms"] > 0 else 0.0
     info = last["info"]
@@ -842,13 +852,14 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "c64 LU (f32 MFMA) + f64 refinement" if prec == R.RSRR_PREC_C64_IR else "c128 (f64 MFMA)",
+        "dtype": "c64 LU (f32 panels and sums, split-f16 MFMA updates) + f64 refinement" if prec == R.RSRR_PREC_C64_IR else "c128 (f64 MFMA)",
         "data": "synthetic (seeded Fibonacci-sphere Helmholtz single-layer NEP, complex Gaussian probes)",
         "config": {"workload": desc, "n": n, "N": N, "L": L, "precision": args.prec,
                    "step": "rsrr_sample over all N points (assembly, LU, solves, refinement)"},
-        "roofline": {"bound": "mfma", "kernel": "LU trailing update (cgemm3m_mfma_kernel<4,1,1,2,*,1>)"
-                     if prec == R.RSRR_PREC_C64_IR else "LU trailing update (zgemm_mfma_kernel<0,0,1>)",
-                     "achieved": round(achieved, 3), "peak": peak, "unit": "TFLOP/s",
+        "roofline": {"bound": "mfma", "kernel": "LU trailing update (gemm_split_kernel<float2,true>)" if split else
+                     "LU trailing update (cgemm3m_mfma_kernel<4,1,1,2,*,1>)"
+                     if prec == R.RSRR_PREC_C64_IR else "LU trailing update (zgemm_mfma_kernel<0,0,128,1>)",
+                     "achieved": round(achieved, 3), "peak": round(peak, 1), "unit": "TFLOP/s",
                      "frac": round(achieved / peak, 4),
                      "traffic": (measured_traffic() if (prec == R.RSRR_PREC_C64_IR and args.workload == "helmholtz"
                                                         and n == 4096 and N == 64 and L == 64) else None),
@@ -856,19 +867,24 @@ def main():
                      "flops_per_launch": st["flops"] / max(1, st["launches"]),
                      "algorithmic_bytes_per_launch": st["bytes"] / max(1, st["launches"]),
                      **({"cu_masked_part": {
-                         "what": "the bulk of each update overlapped with the next panels runs on a stream "
-                                 "whose CU mask leaves one XCD to them: its rate is bounded by that CU share",
+                         "what": "the first columns of each update overlapped with the next panels run on a stream "
+                                 "whose CU mask leaves CUs to them: its rate is bounded by that CU share",
                          "cu_share": round(st["masked_cu_share"], 4),
                          "flops_share": round(st["masked_flops"] / st["flops"], 4) if st["flops"] else None,
                          "achieved": round(st["masked_flops"] / (st["masked_ms"] * 1e-3) / 1e12, 3),
                          "frac_of_its_cus": round(st["masked_flops"] / (st["masked_ms"] * 1e-3) / 1e12
                                                   / (peak * st["masked_cu_share"]), 4)}}
                         if st.get("masked_ms", 0) > 0 else {}),
-                     **({"form": "3M: three real MFMA products per complex multiply-add; achieved counts the "
-                                 "standard 8 real flops per complex multiply-add, the matrix cores execute 6",
-                         "mfma_executed_frac": round(0.75 * achieved / peak, 4),
+                     **({"form": "split operands: every real FP32 product is three FP16 products with FP32 sums; "
+                                 "achieved counts the standard 8 real flops per complex multiply-add, the matrix "
+                                 "cores execute 24, and peak is a third of their dense FP16 rate",
+                         "mfma_executed_frac": round(achieved / peak, 4),
                          "rocprof_mfma_util": (measured_mfma_util() if (args.workload == "helmholtz" and n == 4096
                                                                         and N == 64 and L == 64) else None)}
+                        if split else
+                        {"form": "3M: three real MFMA products per complex multiply-add; achieved counts the "
+                                 "standard 8 real flops per complex multiply-add, the matrix cores execute 6",
+                         "mfma_executed_frac": round(0.75 * achieved / peak, 4)}
                         if prec == R.RSRR_PREC_C64_IR else {})},
         "sample_solves_per_s": round(N * args.steps / (sample_ms * 1e-3), 3) if sample_ms > 0 else None,
         "rhs_columns_per_s": round(L * value, 1),
@@ -936,7 +952,7 @@ def main():
             pach = pst["flops"] / (pst["ms"] * 1e-3) / 1e12
             lu_all = N * (8.0 / 3.0) * float(n) ** 3
             res["plain_c128_roofline"] = {
-                "bound": "mfma", "kernel": "LU trailing update, complex FP64 (zgemm_mfma_kernel<0,0,1>)",
+                "bound": "mfma", "kernel": "LU trailing update, complex FP64 (zgemm_mfma_kernel<0,0,128,1>)",
                 "achieved": round(pach, 3), "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(pach / PEAK_FP64_MFMA_TFLOPS, 4), "launches": pst["launches"],
                 "avg_launch_ms": round(pst["ms"] / max(1, pst["launches"]), 4),

@@ -21,7 +21,7 @@ namespace rsrr {
 // complex FP32: v_mfma_f32_32x32x2f32.  The workgroup has WR x WC waves; each
 // wave owns BR x BC blocks of 32x32 outputs, so the WG tile is
 // (32 WR BR) x (32 WC BC).  In this 4M form it serves the 128x32 products of
-// the panel recursion; wider products go to the 3M kernel below.  The 4M
+// the panels; wider products go to the 3M kernel below.  The 4M
 // kernel is kept general (a 128x128 tile of 2x2 waves of 2x2 blocks runs at
 // two waves per SIMD).  beta*C is loaded into the accumulators before
 // the k loop (its latency overlaps the first LDS stage), alpha is folded
@@ -580,10 +580,10 @@ hipError_t cgemm(hipStream_t st, int M, int N, int K, float alpha,
     const bool vec = ((((uintptr_t)A) | ((uintptr_t)B)) & 15) == 0 && (lda % 2 == 0) && (ldb % 2 == 0)
                      && (sA % 2 == 0) && (sB % 2 == 0);
     // 128x16 tiles of 16x16 blocks for at most 16 columns, 128x32 tiles in the
-    // 4M form up to 32 columns (the narrow products of the panel recursion and
+    // 4M form up to 32 columns (the narrow products of the panels and
     // of narrow probe blocks); 64x64 tiles in the 3M form up to 64 columns (the
-    // solves at L = 64); 128x64 tiles in the 3M form for everything wider (trailing
-    // updates, U12 products): with two 32x32 blocks per wave the three
+    // solves at L = 64); 128x64 tiles in the 3M form for everything wider that the
+    // split kernels do not take (small trailing updates, U12 products): with two 32x32 blocks per wave the three
     // accumulator sets still leave two waves per SIMD, which measured faster
     // than 128x128 tiles in either form.  The trailing update's tile can be
     // changed per bucket by the ragged batch's autotuner (set_update_tile).

@@ -2,12 +2,14 @@
 //
 // Factorisation (right-looking, blocked, RSRR Step 2 needs one LU per
 // sampling point): for each outer panel of nb columns
-//   1. the panel (all rows below the diagonal) is factored by a recursive
-//      split into halves down to a register-resident base kernel;
+//   1. the panel (all rows below the diagonal) is factored in blocks of up to
+//      32 columns by a register-resident base kernel, right-looking inside;
 //   2. the panel's row interchanges are composed into a permutation of at
 //      most 2*nb rows (perm_build) and applied to the columns right of the
 //      panel together with the unit-lower triangular solve U12 = L11^-1 A12;
-//   3. the trailing matrix is updated on the matrix cores, A22 -= L21 U12.
+//   3. the trailing matrix is updated on the matrix cores, A22 -= L21 U12,
+//      for two panels at once where there are two (in FP32 of 384 rows and
+//      more on the FP16 matrix cores with split operands).
 // Columns left of the panel are never interchanged ("lazy" left swaps): the
 // solve applies each panel's permutation just before that panel's forward
 // elimination step, which reproduces the elimination order exactly.  Inside

@@ -567,7 +567,8 @@ hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long 
                        (const char*)PA, sPA, sp_frag_bytes<C>(M, K), (const char*)PB, sPB,                        \
                        sp_frag_bytes<C>(Npack, K), j0 / 32, Cm, ldc, sC, tm, tn, batch, total)
     if (sub) SP_L(true);
-    else SP_L(false);
+    else if constexpr (elem_traits<C>::complex) SP_L(false);
+    else return hipErrorInvalidValue;   // no real caller
 #undef SP_L
     return hipGetLastError();
 }
