@@ -465,9 +465,7 @@ rsrr_status bucket_bufs(BatchedState& S, hipStream_t sm, int P, int Lmax, long M
     b.ones = (double*)bget(S, s++, (size_t)M * Lmax * 8, sm);
     b.pair = mixed && !from ? bget(S, s++, (size_t)M * b.sPair * 8, sm) : (void*)(s++, nullptr);
     // split operands of the trailing updates (without them those run in FP32)
-    b.sPack = mixed && !from && split_ok(P - 2 * nbmax, P - 2 * nbmax, 2 * nbmax)
-                  ? (long)split_pack_bytes<float2>(P, 2 * nbmax)
-                  : 0;
+    b.sPack = mixed && !from ? (long)lu_pack_bytes<float2>(P) : 0;
     b.pack = b.sPack ? bget(S, s++, (size_t)M * b.sPack, sm) : (void*)(s++, nullptr);
     b.sep = (SepInstance*)bget(S, s++, (size_t)nins * sizeof(SepInstance), sm);
     b.rhs = (RhsInstance*)bget(S, s++, (size_t)nins * sizeof(RhsInstance), sm);

@@ -321,13 +321,11 @@ struct SampleBufs {
     }
 };
 
-// Bytes per point of the split operands of the trailing updates (two panels of 128 columns
-// deep); 0 where no update is large enough for them.
+// Bytes per point of the split operands of the trailing updates.
 static size_t pack_bytes(int n, int prec)
 {
-    constexpr int depth = 2 * max_panel<float>();
-    if (prec == RSRR_PREC_C128 || !split_ok(n - depth, n - depth, depth)) return 0;
-    return prec == RSRR_PREC_C64_IR ? split_pack_bytes<float2>(n, depth) : split_pack_bytes<float>(n, depth);
+    if (prec == RSRR_PREC_C128) return 0;
+    return prec == RSRR_PREC_C64_IR ? lu_pack_bytes<float2>(n) : lu_pack_bytes<float>(n);
 }
 
 // Per-point bytes of the sampling buffers.

@@ -118,6 +118,13 @@ struct LUWork {
 };
 // Elements per matrix of the pair buffer for n x n matrices and panel width nb.
 inline long lu_pair_elems(int n, int nb, int ldpair) { return (long)ldpair * 2 * nb + (long)nb * nb; }
+// Bytes per matrix of LUWork::pack for the widest panels; 0 where no update is large enough for it.
+template <typename C>
+inline size_t lu_pack_bytes(int n)
+{
+    constexpr int depth = 2 * max_panel<float>();
+    return split_ok(n - depth, n - depth, depth) ? split_pack_bytes<C>(n, depth) : 0;
+}
 
 // Blocked LU with partial pivoting of `batch` n x n matrices (stride sA).
 template <typename R>

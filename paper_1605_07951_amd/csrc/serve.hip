@@ -167,7 +167,12 @@ size_t point_bytes(int n, int L, bool mixed)
     size_t b = P * P * (mixed ? 8 + 16 : 16 + 16);           // T and its FP64 copy
     b += P * (size_t)L * (3 * 16 + 8) + P * 4;               // U, X, R, narrow RHS, pivots
     b += npan * 2 * MAX_NB * 8;                               // permutations
-    if (mixed) b += 2 * MAX_NB * (P + MAX_NB) * 8 + MAX_NB * std::max(P, (size_t)L) * 8;  // inverses, scratch
+    if (mixed) {
+        b += 2 * MAX_NB * (P + MAX_NB) * 8 + MAX_NB * std::max(P, (size_t)L) * 8;  // inverses, scratch
+        // panel pairs and packed operands: a launch that fills the cap without them would have its buffers
+        // freed and allocated again every time
+        b += (size_t)lu_pair_elems((int)P, MAX_NB, (int)P) * 8 + lu_pack_bytes<float2>((int)P);
+    }
     b += (P * P + 255) / 256 * 8 + (size_t)L * 6 * 8 + 64;   // norms and refinement state
     return b;
 }
