@@ -1304,8 +1304,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
 
 // ----------------------------------------------------------------------------
 // The whole solve of getrs_impl (complex FP32, diagonal blocks by their
-// inverses) for one matrix per workgroup, for right-hand-side blocks that fit
-// in LDS: X is read once, every panel's forward step (interchanges,
+// inverses) for one matrix (and at most 16 right-hand sides) per workgroup, for right-hand-side
+// blocks that fit in LDS: X is read once, every panel's forward step (interchanges,
 // X_p = L11^-1 X_p, rows below -= L21 X_p) and backward step (X_p = U11^-1 X_p,
 // rows above -= U12 X_p) runs out of LDS while the factor columns stream from
 // memory once, and X is written back at the end.  The same operations as
@@ -1327,6 +1327,7 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
 // 724, 256 matrices 795 / 409 / 875); 16 right-hand sides, 72 matrices, n = 512 241 / 136 / 534, n =
 // 1024 571 / 464 / 1580; n = 2048, 8 right-hand sides, 1 / 32 matrices 950 / 1081 (chain), 874 / 1031.
 // ----------------------------------------------------------------------------
+constexpr int GS_MAX_RHS = 64, GS_MAX_WG = 512;
 constexpr int GS_NT = 512, GS_NW = GS_NT / 64;
 constexpr int GS_G = 8;                      // groups of four columns per batch of loads
 constexpr int GS_Q = MAX_NB / (4 * GS_G);    // batches per panel
@@ -1347,7 +1348,8 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
     const float2* A = LU + (long)b * sLU;
-    float2* Xb = X + (long)b * sX;
+    float2* Xb = X + (long)b * sX + (long)(blockIdx.y * 8 * CB) * ldx;   // this workgroup's right-hand sides
+    L = min(L - (int)blockIdx.y * 8 * CB, 8 * CB);
     // X in and out: 16 rows x 4 right-hand sides per wave
     auto each = [&](auto f) {
         const int nrb = (n + 15) / 16;
@@ -1534,10 +1536,17 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
 
 static int gs_blocks(int nrhs) { return nrhs <= 8 ? 1 : 2; }
 static size_t gs_lds(int n, int nrhs) { return (size_t)n * gs_blocks(nrhs) * 64; }
-static bool getrs_lds_ok(int n, int nrhs) { return nrhs >= 1 && nrhs <= 16 && gs_lds(n, nrhs) <= (size_t)128 << 10; }
+// At most 16 right-hand sides that fit: always (above).  17 to 64 in groups of 16, a workgroup each, which
+// read the factor once per group, up to two workgroups per CU (64 right-hand sides, chain / groups: 48
+// matrices n = 256 125 / 52 us, n = 1024 769 / 470, 128 matrices 141 / 102 and 1124 / 973).
+static bool getrs_lds_ok(int n, int nrhs, int batch)
+{
+    if (nrhs < 1 || nrhs > GS_MAX_RHS || gs_lds(n, nrhs) > (size_t)128 << 10) return false;
+    return nrhs <= 16 || (long)batch * ((nrhs + 15) / 16) <= GS_MAX_WG;
+}
 
-static hipError_t getrs_lds_batched(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
-                             float2* X, long sX, int ldx, int nrhs, int batch)
+static hipError_t getrs_lds_batched(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb,
+                                    const LUWork& w, float2* X, long sX, int ldx, int nrhs, int batch)
 {
     if (nb > max_panel<float>()) nb = max_panel<float>();
     if (nb < MIN_NB) nb = MIN_NB;
@@ -1546,8 +1555,8 @@ static hipError_t getrs_lds_batched(hipStream_t st, const float2* LU, long sLU, 
         hipLaunchKernelGGL(getrs_lds_kernel<1>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
                            w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
     else
-        hipLaunchKernelGGL(getrs_lds_kernel<2>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
-                           w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
+        hipLaunchKernelGGL(getrs_lds_kernel<2>, dim3(batch, (nrhs + 15) / 16), dim3(GS_NT), lds, st, LU, sLU, lda, n,
+                           nb, w.perm, w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
     return hipGetLastError();
 }
 
@@ -1566,7 +1575,7 @@ template <>
 hipError_t getrs_batched<float>(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                                 float2* X, long sX, int ldx, int nrhs, int batch)
 {
-    if (getrs_lds_ok(n, nrhs)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
+    if (getrs_lds_ok(n, nrhs, batch)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
     return getrs_impl<float2>(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
 }
 template <>

@@ -1,4 +1,4 @@
-"""GPU: the complex FP32 solve of at most 16 right-hand sides in one workgroup per matrix, at the edges of
+"""GPU: the complex FP32 solve of at most 64 right-hand sides in one workgroup per 16 and matrix, at the edges of
 its panels, row blocks and right-hand-side blocks and on both sides of its size limit.
 
 T = diagonally dominant, so that kappa(T) is below 4 and a right FP32 solve leaves a relative
@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,L", [(15, 8), (16, 9), (17, 1), (127, 8), (128, 16), (144, 8), (145, 9), (256, 7),
-                                 (257, 8), (385, 16), (1024, 16), (1025, 16), (1100, 3), (2048, 8), (2049, 8)])
+                                 (257, 8), (385, 16), (1024, 16), (1025, 16), (1100, 3), (2048, 8), (2049, 8),
+                                 (1, 17), (130, 17), (131, 32), (300, 33), (513, 49), (1024, 64), (1025, 64), (600, 65)])
 def test_whole_solve(n, L):
     ctx = R.rsrr_create(0)
     rng = np.random.default_rng(100 * n + L)
