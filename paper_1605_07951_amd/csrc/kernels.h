@@ -131,7 +131,7 @@ template <typename R>
 hipError_t getrf_batched(hipStream_t st, typename cpx<R>::T* A, long sA, int lda, int n, int nb, const LUWork& w,
                          int batch);
 
-// X <- T^-1 X for the factors of getrf_batched (same nb and workspace).  Complex FP32 blocks of
+// X <- T^-1 X for the factors of getrf_batched (same nb and workspace).  FP32 blocks of
 // at most 64 right-hand sides, 16 of which fit in LDS, run the whole solve of a matrix in one workgroup per 16.
 template <typename R>
 hipError_t getrs_batched(hipStream_t st, const typename cpx<R>::T* LU, long sLU, int lda, int n, int nb,

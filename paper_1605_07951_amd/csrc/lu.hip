@@ -1303,8 +1303,7 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
 }
 
 // ----------------------------------------------------------------------------
-// The whole solve of getrs_impl (complex FP32, diagonal blocks by their
-// inverses) for one matrix (and at most 16 right-hand sides) per workgroup, for right-hand-side
+// The whole solve of getrs_impl (FP32, diagonal blocks by their inverses) for one matrix (and at most 16 right-hand sides) per workgroup, for right-hand-side
 // blocks that fit in LDS: X is read once, every panel's forward step (interchanges,
 // X_p = L11^-1 X_p, rows below -= L21 X_p) and backward step (X_p = U11^-1 X_p,
 // rows above -= U12 X_p) runs out of LDS while the factor columns stream from
@@ -1314,7 +1313,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
 //
 // The products run on v_mfma_f32_16x16x4f32: the 16 columns of one operand are the real
 // and the imaginary parts of 8 right-hand sides, so one instruction for the real and one
-// for the imaginary parts of the factor give 16 rows of the complex product.  A
+// for the imaginary parts of the factor give 16 rows of the complex product (real FP32: 16
+// right-hand sides, one instruction).  A
 // lane's factor entry (row lane % 16, column lane / 16 of four) goes from memory
 // into its registers, and the panel's X_p stays in registers for all rows of the update.
 // A row of X in LDS: per 8 right-hand sides 8 real, then 8 imaginary parts.
@@ -1326,42 +1326,50 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
 // 256, 8 right-hand sides, 72 matrices 95 / 31 / 91, n = 1000 541 / 319 / 795 (1 matrix 460 / 252 /
 // 724, 256 matrices 795 / 409 / 875); 16 right-hand sides, 72 matrices, n = 512 241 / 136 / 534, n =
 // 1024 571 / 464 / 1580; n = 2048, 8 right-hand sides, 1 / 32 matrices 950 / 1081 (chain), 874 / 1031.
+// Real, 16 right-hand sides, 64 matrices, chain / this kernel: n = 256 75 / 21, n = 1024 421 / 194, n =
+// 2025 1117 / 779 (4 right-hand sides, 16 matrices 834 / 707; 64 and 64 1755 / 687).
 // ----------------------------------------------------------------------------
 constexpr int GS_MAX_RHS = 64, GS_MAX_WG = 512;
 constexpr int GS_NT = 512, GS_NW = GS_NT / 64;
 constexpr int GS_G = 8;                      // groups of four columns per batch of loads
 constexpr int GS_Q = MAX_NB / (4 * GS_G);    // batches per panel
 
-// CB blocks of 8 right-hand sides
-template <int CB>
-__global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restrict__ LU, long sLU, int lda, int n, int nb,
+// C = float2: CB blocks of 8 right-hand sides; float: CB blocks of 16
+template <typename C, int CB>
+__global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const C* __restrict__ LU, long sLU, int lda, int n, int nb,
                                                           const int2* __restrict__ perm, long sPerm,
-                                                          const float2* __restrict__ inv, long sInv,
-                                                          float2* __restrict__ X, long sX, int ldx, int L,
+                                                          const C* __restrict__ inv, long sInv,
+                                                          C* __restrict__ X, long sX, int ldx, int L,
                                                           const int* __restrict__ active)
 {
+    constexpr bool CX = elem_traits<C>::complex;
     constexpr int LD = 16 * CB;              // floats per row of X
+    constexpr int NR = (CX ? 8 : 16) * CB;   // right-hand sides
     constexpr int NX = CB == 1 ? 2 : 1;      // blocks of rows per wave (two need more registers than there are)
     extern __shared__ __attribute__((aligned(16))) float xs[];
     const int b = blockIdx.x, tid = threadIdx.x;
     if (active && !active[b]) return;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, g = lane >> 4;
-    const float2* A = LU + (long)b * sLU;
-    float2* Xb = X + (long)b * sX + (long)(blockIdx.y * 8 * CB) * ldx;   // this workgroup's right-hand sides
-    L = min(L - (int)blockIdx.y * 8 * CB, 8 * CB);
+    const C* A = LU + (long)b * sLU;
+    C* Xb = X + (long)b * sX + (long)(blockIdx.y * NR) * ldx;   // this workgroup's right-hand sides
+    L = min(L - (int)blockIdx.y * NR, NR);
     // X in and out: 16 rows x 4 right-hand sides per wave
     auto each = [&](auto f) {
         const int nrb = (n + 15) / 16;
-        for (int e = wave; e < nrb * 2 * CB; e += GS_NW) {
-            const int r = e / (2 * CB) * 16 + li, l = e % (2 * CB) * 4 + g;
-            if (r < n) f(r, l, xs + r * LD + (l >> 3) * 16 + (l & 7));
+        for (int e = wave; e < nrb * (NR / 4); e += GS_NW) {
+            const int r = e / (NR / 4) * 16 + li, l = e % (NR / 4) * 4 + g;
+            if (r < n) f(r, l, xs + r * LD + (CX ? (l >> 3) * 16 + (l & 7) : l));
         }
     };
     each([&](int r, int l, float* x) {
-        const float2 v = l < L ? Xb[r + (long)l * ldx] : make_float2(0.f, 0.f);
-        x[0] = v.x;
-        x[8] = v.y;
+        const C v = l < L ? Xb[r + (long)l * ldx] : czero<C>();
+        if constexpr (CX) {
+            x[0] = v.x;
+            x[8] = v.y;
+        } else {
+            x[0] = v;
+        }
     });
     const int np = (n + nb - 1) / nb;
 
@@ -1395,12 +1403,12 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
         }
     };
     // entries (row, 4 (q GS_G + i) + g) of a block of jb columns (past the last: the last again, X is zero there)
-    auto load = [&](const float2* F, int ldf, int row, int q, int jb, float2 (&a)[GS_G]) {
+    auto load = [&](const C* F, int ldf, int row, int q, int jb, C (&a)[GS_G]) {
         if ((q + 1) * 4 * GS_G <= jb) {
-            const unsigned off = (unsigned)(g * ldf + row) * 8u;   // uniform base, 32-bit offset
+            const unsigned off = (unsigned)(g * ldf + row) * (unsigned)sizeof(C);   // uniform base, 32-bit offset
 #pragma unroll
             for (int i = 0; i < GS_G; ++i)
-                a[i] = *reinterpret_cast<const float2*>(
+                a[i] = *reinterpret_cast<const C*>(
                     reinterpret_cast<const char*>(F + (long)((q * GS_G + i) * 4) * ldf) + off);
         } else {
 #pragma unroll
@@ -1408,25 +1416,31 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
                 a[i] = F[(unsigned)row + (unsigned)(min((q * GS_G + i) * 4 + g, jb - 1) * ldf)];
         }
     };
-    auto mult = [&](const float2 (&a)[GS_G], int q, floatx4 (&acc)[CB]) {
+    auto mult = [&](const C (&a)[GS_G], int q, floatx4 (&acc)[CB]) {
 #pragma unroll
         for (int i = 0; i < GS_G; ++i) {
+            if constexpr (CX) {
 #pragma unroll
-            for (int c = 0; c < CB; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1[q][i][c], a[i].x, acc[c], 0, 0, 0);
+                for (int c = 0; c < CB; ++c)
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1[q][i][c], a[i].x, acc[c], 0, 0, 0);
 #pragma unroll
-            for (int c = 0; c < CB; ++c)
-                acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(turned(b1[q][i][c]), a[i].y, acc[c], 0, 0, 0);
+                for (int c = 0; c < CB; ++c)
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(turned(b1[q][i][c]), a[i].y, acc[c], 0, 0, 0);
+            } else {
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(b1[q][i][c], a[i], acc[c], 0, 0, 0);
+            }
         }
     };
     // the jb x jb triangle D (ld nb), one block of 16 rows per wave; a batch of columns on the far
     // side of the diagonal is zero
-    float2 d[GS_Q][GS_G];
+    C d[GS_Q][GS_G];
     auto diag_on = [&](int q, int jb, bool lower) {
         return wave * 16 < jb && q * 4 * GS_G < jb &&
                (lower ? q * 4 * GS_G < wave * 16 + 16 : (q + 1) * 4 * GS_G > wave * 16);
     };
-    auto diag_load = [&](const float2* D, int jb, bool lower) {
+    auto diag_load = [&](const C* D, int jb, bool lower) {
 #pragma unroll
         for (int q = 0; q < GS_Q; ++q)
             if (diag_on(q, jb, lower)) load(D, nb, min(wave * 16 + li, jb - 1), q, jb, d[q]);
@@ -1435,8 +1449,8 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
     // takes NX blocks of 16 rows at a time and loads one batch of columns ahead
     auto panel = [&](int r0, int r1, int c0, int jb, bool lower) {
         const int nblk = (r1 - r0 + 15) / 16;
-        const float2* F = A + (long)c0 * lda;
-        float2 a[2][NX][GS_G];   // [buffer][block]
+        const C* F = A + (long)c0 * lda;
+        C a[2][NX][GS_G];   // [buffer][block]
         auto load_batch = [&](int blk, int q) {
 #pragma unroll
             for (int x = 0; x < NX; ++x)
@@ -1493,7 +1507,7 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
             }
         }
     };
-    const float2* Db = inv + (long)b * sInv;
+    const C* Db = inv + (long)b * sInv;
     for (int p = 0; p < np; ++p) {
         const int c0 = p * nb, jb = min(nb, n - c0);
         diag_load(Db + (long)(2 * p) * nb * nb, jb, true);
@@ -1530,33 +1544,43 @@ __global__ __launch_bounds__(GS_NT) void getrs_lds_kernel(const float2* __restri
     }
     __syncthreads();
     each([&](int r, int l, float* x) {
-        if (l < L) Xb[r + (long)l * ldx] = make_float2(x[0], x[8]);
+        if (l >= L) return;
+        if constexpr (CX) Xb[r + (long)l * ldx] = make_float2(x[0], x[8]);
+        else Xb[r + (long)l * ldx] = x[0];
     });
 }
 
-static int gs_blocks(int nrhs) { return nrhs <= 8 ? 1 : 2; }
-static size_t gs_lds(int n, int nrhs) { return (size_t)n * gs_blocks(nrhs) * 64; }
+// LDS of a workgroup: complex 8 or 16, real 16 right-hand sides
+template <typename C>
+static size_t gs_lds(int n, int nrhs) { return (size_t)n * (elem_traits<C>::complex && nrhs > 8 ? 128 : 64); }
 // At most 16 right-hand sides that fit: always (above).  17 to 64 in groups of 16, a workgroup each, which
 // read the factor once per group, up to two workgroups per CU (64 right-hand sides, chain / groups: 48
 // matrices n = 256 125 / 52 us, n = 1024 769 / 470, 128 matrices 141 / 102 and 1124 / 973).
+template <typename C>
 static bool getrs_lds_ok(int n, int nrhs, int batch)
 {
-    if (nrhs < 1 || nrhs > GS_MAX_RHS || gs_lds(n, nrhs) > (size_t)128 << 10) return false;
+    if (nrhs < 1 || nrhs > GS_MAX_RHS || gs_lds<C>(n, nrhs) > (size_t)128 << 10) return false;
     return nrhs <= 16 || (long)batch * ((nrhs + 15) / 16) <= GS_MAX_WG;
 }
 
-static hipError_t getrs_lds_batched(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb,
-                                    const LUWork& w, float2* X, long sX, int ldx, int nrhs, int batch)
+template <typename C>
+static hipError_t getrs_lds_batched(hipStream_t st, const C* LU, long sLU, int lda, int n, int nb, const LUWork& w,
+                                    C* X, long sX, int ldx, int nrhs, int batch)
 {
     if (nb > max_panel<float>()) nb = max_panel<float>();
     if (nb < MIN_NB) nb = MIN_NB;
-    const size_t lds = gs_lds(n, nrhs);
-    if (gs_blocks(nrhs) == 1)
-        hipLaunchKernelGGL(getrs_lds_kernel<1>, dim3(batch), dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm,
-                           w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
-    else
-        hipLaunchKernelGGL(getrs_lds_kernel<2>, dim3(batch, (nrhs + 15) / 16), dim3(GS_NT), lds, st, LU, sLU, lda, n,
-                           nb, w.perm, w.sPerm, (const float2*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active);
+    const size_t lds = gs_lds<C>(n, nrhs);
+    const dim3 grid(batch, (nrhs + 15) / 16);
+#define GS_L(CB)                                                                                                   \
+    hipLaunchKernelGGL((getrs_lds_kernel<C, CB>), grid, dim3(GS_NT), lds, st, LU, sLU, lda, n, nb, w.perm, w.sPerm, \
+                       (const C*)w.inv, w.sInv, X, sX, ldx, nrhs, w.active)
+    if constexpr (elem_traits<C>::complex) {
+        if (nrhs > 8) GS_L(2);
+        else GS_L(1);
+    } else {
+        GS_L(1);
+    }
+#undef GS_L
     return hipGetLastError();
 }
 
@@ -1575,7 +1599,7 @@ template <>
 hipError_t getrs_batched<float>(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                                 float2* X, long sX, int ldx, int nrhs, int batch)
 {
-    if (getrs_lds_ok(n, nrhs, batch)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
+    if (getrs_lds_ok<float2>(n, nrhs, batch)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
     return getrs_impl<float2>(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
 }
 template <>
@@ -1591,6 +1615,7 @@ hipError_t getrf_real_batched(hipStream_t st, float* A, long sA, int lda, int n,
 hipError_t getrs_real_batched(hipStream_t st, const float* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                               float* X, long sX, int ldx, int nrhs, int batch)
 {
+    if (getrs_lds_ok<float>(n, nrhs, batch)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
     return getrs_impl<float>(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
 }
 
