@@ -13,8 +13,8 @@
 // wavefront per point) from the points copied next to it.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
-#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -68,49 +68,54 @@ __global__ __launch_bounds__(64) void moment_weights_kernel(const double2* __res
     }
 }
 
-// M = S Z for KC of the K moments: a thread per (row, probe column) walks the N
+// M = S Z for the KC moments from a0 on: a thread per (row, probe column) walks the N
 // points, reads S once, coalesced along the rows, and keeps its KC sums in registers;
 // the coefficients (cw, N x K with the moment fastest) are the same for every lane
-// and come through the scalar cache.  Bound by the stream over S: n = 4096, N = L = 64,
-// K = 16 (335 MB) 178 us as a GEMM, whose 64-wide tiles left three quarters of the
-// matrix core's columns empty, 72 us (4.7 TB/s) here.
-constexpr int MS_NT = 256;
+// and come through the scalar cache, those of a point as one block (a kernel per KC: with
+// indices clamped to K eight points' loads were not in flight at once, 110 against 72 us).
+// Bound by the stream over S: n = 4096, N = L = 64, K = 16 (335 MB) 178 us as a GEMM, whose
+// 64-wide tiles left three quarters of the matrix core's columns empty, 72 us (4.7 TB/s) here;
+// small ones by the latency of N / 8 loads in turn.
+constexpr int MS_NT = 256, MS_KMAX = 16;
 template <int KC>
 __global__ __launch_bounds__(MS_NT) void moments_stream_kernel(int n, int N, int L, const double2* __restrict__ S,
-                                                               int lds, const double2* __restrict__ cw, int K,
+                                                               int lds, const double2* __restrict__ cw, int K, int a0,
                                                                double2* __restrict__ M, int ldm)
 {
-    const int row = blockIdx.x * MS_NT + threadIdx.x, l = blockIdx.y, a0 = blockIdx.z * KC;
+    const int row = blockIdx.x * MS_NT + threadIdx.x, l = blockIdx.y;
     if (row >= n) return;
     const double2* s = S + row + (long)l * lds;
     const long step = (long)L * lds;
     double2 acc[KC];
 #pragma unroll
     for (int a = 0; a < KC; ++a) acc[a] = make_double2(0.0, 0.0);
-    auto add = [&](int i, auto whole) {
+#pragma unroll 8
+    for (int i = 0; i < N; ++i) {
         const double2 v = s[i * step];
         const double2* c = cw + (long)i * K + a0;
 #pragma unroll
         for (int a = 0; a < KC; ++a) {
-            const double2 w = c[decltype(whole)::value ? a : min(a, K - 1 - a0)];
+            const double2 w = c[a];
             acc[a].x = fma(w.x, v.x, acc[a].x);
             acc[a].y = fma(w.x, v.y, acc[a].y);
             acc[a].x = fma(-w.y, v.y, acc[a].x);
             acc[a].y = fma(w.y, v.x, acc[a].y);
         }
-    };
-    // whole chunks of moments read their coefficients as one block
-    if (a0 + KC <= K) {
-#pragma unroll 8
-        for (int i = 0; i < N; ++i) add(i, std::true_type{});
-    } else {
-#pragma unroll 2
-        for (int i = 0; i < N; ++i) add(i, std::false_type{});
     }
     double2* m = M + row + (long)l * ldm;
 #pragma unroll
-    for (int a = 0; a < KC; ++a)
-        if (a0 + a < K) m[(long)(a0 + a) * L * ldm] = acc[a];
+    for (int a = 0; a < KC; ++a) m[(long)(a0 + a) * L * ldm] = acc[a];
+}
+
+template <int KC>
+void moments_stream(hipStream_t st, int kc, int n, int N, int L, const double2* S, int lds, const double2* cw, int K,
+                    int a0, double2* M, int ldm)
+{
+    if constexpr (KC > 1) {
+        if (kc < KC) return moments_stream<KC - 1>(st, kc, n, N, L, S, lds, cw, K, a0, M, ldm);
+    }
+    hipLaunchKernelGGL(moments_stream_kernel<KC>, dim3((n + MS_NT - 1) / MS_NT, L), dim3(MS_NT), 0, st, n, N, L, S, lds,
+                       cw, K, a0, M, ldm);
 }
 
 rsrr_status check_args(rsrr_ctx* c, int n, int N, int L, const double* S, int lds, const double* z,
@@ -149,13 +154,9 @@ rsrr_status moments_run(rsrr_ctx* c, int n, int N, int L, const double* S, int l
                        capacity, cw, stream ? K : 1, stream ? 1 : N);
     RSRR_HIP(hipGetLastError());
     if (stream) {
-#define MS_L(KC)                                                                                                   \
-    hipLaunchKernelGGL(moments_stream_kernel<KC>, dim3((n + MS_NT - 1) / MS_NT, L, (K + KC - 1) / KC), dim3(MS_NT), \
-                       0, c->stream, n, N, L, (const double2*)S, lds, cw, K, (double2*)M, ldm)
-        if (K <= 4) MS_L(4);
-        else if (K <= 8) MS_L(8);
-        else MS_L(16);
-#undef MS_L
+        for (int a0 = 0; a0 < K; a0 += MS_KMAX)
+            moments_stream<MS_KMAX>(c->stream, std::min(MS_KMAX, K - a0), n, N, L, (const double2*)S, lds, cw, K, a0,
+                                    (double2*)M, ldm);
         RSRR_HIP(hipGetLastError());
     } else {
         // batch l: A = S + l lds (n x N, ld L lds), C = M + l ldm (n x K, ld L ldm)
