@@ -1025,10 +1025,13 @@ hipError_t zgemm(hipStream_t st, int opA, int opB, int M, int N, int K, double a
                  double beta, double2* C, int ldc, long sC, int batch, int tag)
 {
     if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
-    // 128 x 64 tiles where there are two for every CU; smaller products keep twice as many
-    // workgroups with 64 x 64
-    const long big = (long)((M + 127) / 128) * ((N + ZG_BN - 1) / ZG_BN) * batch;
-    if (M > 64 && big >= 512)
+    // 128 x 64 tiles where there are two for every CU and the rows they pad cost less than the
+    // 8% that they gain over 64 x 64; smaller products keep twice as many workgroups with 64 x 64
+    // (projection of 541 / 900 rows, 298 columns: 949 / 1986 us with 128 x 64, 841 / 1695 with 64 x 64;
+    // 2400 rows, equal padding, 9.05 ms against 9.67 with 64 x 64 before the larger tile)
+    const long t128 = (M + 127) / 128, t64 = (M + 63) / 64;
+    const long big = t128 * ((N + ZG_BN - 1) / ZG_BN) * batch;
+    if (big >= 512 && 2 * t128 * 20 <= t64 * 21)
         return zgemm_launch<128>(st, opA, opB, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, tag);
     return zgemm_launch<64>(st, opA, opB, M, N, K, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc, sC, batch, tag);
 }
