@@ -39,27 +39,33 @@ const char* update_tile_name(int t);
 // columns, K) bytes, stride sP bytes); gemm_split then gives C -= A B (sub) or C = A B for N
 // columns from column j0 (a multiple of 32; C at that column) of the Npack packed ones.  A deeper product
 // is a batch of slabs: matrix b at sA, of the columns (rows of B) b kstep .. of Ktot.
-// split_ok: sizes for which it replaces cgemm and sgemm; split_pack_bytes: both operands of an LU update of
-// depth K of at most n rows and columns, and the factors of split_urows.
+// split_ok: sizes for which it replaces cgemm and sgemm; split_pack_bytes: the inner exponents, both operands of
+// an LU update of depth K of at most n rows and columns, and the factors of split_urows.
 bool split_ok(int M, int N, int K);
 template <typename C> long split_operand_bytes(int rows, int K);
 template <typename C> size_t split_pack_bytes(int n, int K);
+// Both take the exponents of the inner index that split_inner forms from A (K per matrix, stride sE; of a
+// slab: those of its first column on): column k of A is multiplied by 2^E[k], row k of B by 2^-E[k].
+constexpr size_t SPLIT_INNER_BYTES = 1024;   // exponents of the deepest product
 template <typename C>
-hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, void* P, long sP, int batch,
-                        int Ktot = 0, int kstep = 0);
+hipError_t split_inner(hipStream_t st, int M, int K, const C* A, int lda, long sA, int* E, long sE, int batch);
 template <typename C>
-hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, void* P, long sP, int batch,
-                        int Ktot = 0, int kstep = 0);
+hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, const int* E, long sE, void* P,
+                        long sP, int batch, int Ktot = 0, int kstep = 0);
+template <typename C>
+hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, const int* E, long sE, void* P,
+                        long sP, int batch, int Ktot = 0, int kstep = 0);
 template <typename C>
 hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long sPA, const void* PB, long sPB,
                       int Npack, int j0, bool sub, C* Cm, int ldc, long sC, int batch);
 // The U rows of a pair of 128-wide panels on N trailing columns (A: 256 x N at the pair's first
 // row, interchanged) in place, U0 = L0 A0 and U1 = L1 (A1 - T U0) with L0, T, L1 128 x 128, and
-// the B operand of the M x N update of depth 256 that follows (instead of split_pack_b).
+// the B operand of the M x N update of depth 256 that follows (instead of split_pack_b); E: the inner
+// exponents of that update.
 bool split_urows_ok(int nb, const float2* A, int lda, long sA);
 hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, long s0, const float2* T, int ldt,
-                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, void* P, long sP,
-                       int batch);
+                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, const int* E, long sE,
+                       void* P, long sP, int batch);
 
 // C = beta*C + alpha*op(A)*op(B), complex double on v_mfma_f64_16x16x4f64;
 // op = conjugate transpose when the flag is set.

@@ -1034,8 +1034,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     UpdateRecorder* rec = w.rec;
     // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `s`, event-timed.  An
     // update done in column parts gives its whole width (Nall) and the part's first column
-    // (j0); with split operands the first part (j0 = 0) packs them for all parts (B unless the U
-    // rows came packed).
+    // (j0); with split operands the first part (j0 = 0) packs them for all parts (the inner
+    // exponents and B unless the U rows came packed).
     auto timed_update = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
                                const C* Bop, C* Cop, int Nall = 0, int j0 = 0, bool bpacked = false) {
         const bool timed = rec && rec->used < rec->cap;
@@ -1045,12 +1045,18 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if constexpr (sizeof(R) == 4) {
             split = w.pack != nullptr && split_ok(M, Nall, kdepth);
             if (split) {
-                char* PB = (char*)w.pack + split_operand_bytes<C>(M, kdepth);
+                int* E = (int*)w.pack;
+                const long sE = w.sPack / 4;
+                char* PA = (char*)w.pack + SPLIT_INNER_BYTES;
+                char* PB = PA + split_operand_bytes<C>(M, kdepth);
                 if (j0 == 0) {
-                    (void)split_pack_a(s, M, kdepth, Aop, ldaop, sAop, w.pack, w.sPack, batch);
-                    if (!bpacked) (void)split_pack_b(s, Nall, kdepth, Bop, lda, sA, PB, w.sPack, batch);
+                    if (!bpacked) {
+                        (void)split_inner(s, M, kdepth, Aop, ldaop, sAop, E, sE, batch);
+                        (void)split_pack_b(s, Nall, kdepth, Bop, lda, sA, E, sE, PB, w.sPack, batch);
+                    }
+                    (void)split_pack_a(s, M, kdepth, Aop, ldaop, sAop, E, sE, PA, w.sPack, batch);
                 }
-                (void)gemm_split(s, M, N, kdepth, w.pack, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch);
+                (void)gemm_split(s, M, N, kdepth, PA, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch);
             }
         }
         if (!split) (void)gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1);
@@ -1084,8 +1090,9 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     // [U12_p; U12_{p+1}] in one product.
     const bool pairing = use_inv && w.pair != nullptr;
     // The U rows of the pair (q0, q1 = q0 + nb) of full panels p, p + 1 on the columns from q2 on,
-    // with the rows' interchanges, by the split kernels: true when done (and the update's B packed).
-    auto split_pair_rows = [&](hipStream_t s, int q0, int p0, C* TL) -> bool {
+    // with the rows' interchanges, by the split kernels: true when done (and the update's inner exponents
+    // formed and its B packed).  Wp: the pair's buffer, with both panels' L21.
+    auto split_pair_rows = [&](hipStream_t s, int q0, int p0, const C* Wp, C* TL) -> bool {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const int q2 = q0 + 2 * nb, rest = n - q2;
             C* Ar = A + (long)q2 * lda;
@@ -1094,8 +1101,11 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             perm_rows<C>(s, pm0, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0, nb, rest, w.active, batch);
             perm_rows<C>(s, pm0 + 2 * MAX_NB, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0 + nb, nb, rest, w.active,
                          batch);
+            int* E = (int*)w.pack;
+            (void)split_inner(s, rest, 2 * nb, Wp + q2, w.ldpair, w.sPair, E, w.sPack / 4, batch);
             (void)split_urows(s, rest, rest, panel_inv<C>(w, p0, nb, 0), nb, w.sInv, TL, nb, w.sPair,
-                              panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, w.pack, w.sPack, batch);
+                              panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, E, w.sPack / 4,
+                              (char*)w.pack + SPLIT_INNER_BYTES, w.sPack, batch);
             return true;
         }
         return false;
@@ -1122,11 +1132,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     auto back = [&](int q0, int pp, C* Wp) -> bool {
         const int q1 = q0 + nb, q2 = q1 + nb, rest = n - q2;
         C* TL = Wp + (long)ldw * 2 * nb;
-        if (split_pair_rows(st, q0, pp, TL)) {
-            copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
-                         batch);
-            return true;
-        }
+        copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active, batch);
+        if (split_pair_rows(st, q0, pp, Wp, TL)) return true;
         const int2* pm0 = w.perm + (long)pp * 2 * MAX_NB;
         const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
         C* Ar2 = A + (long)q2 * lda;
@@ -1137,8 +1144,6 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         (void)gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch);
         (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
                           w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0);
-        copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active,
-                     batch);
         return false;
     };
     int c0 = 0, p = 0;
@@ -1247,11 +1252,15 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const long na = split_operand_bytes<C>(m, K);
             if (w.pack && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
-                na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
-                char* PB = (char*)w.pack + na;
-                (void)split_pack_a(st, m, K, F, lda, sLU, w.pack, w.sPack, batch);
-                (void)split_pack_b(st, nrhs, K, X + c0, ldx, sX, PB, w.sPack, batch);
-                (void)gemm_split(st, m, nrhs, K, w.pack, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch);
+                (long)SPLIT_INNER_BYTES + na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
+                int* E = (int*)w.pack;
+                const long sE = w.sPack / 4;
+                char* PA = (char*)w.pack + SPLIT_INNER_BYTES;
+                char* PB = PA + na;
+                (void)split_inner(st, m, K, F, lda, sLU, E, sE, batch);
+                (void)split_pack_a(st, m, K, F, lda, sLU, E, sE, PA, w.sPack, batch);
+                (void)split_pack_b(st, nrhs, K, X + c0, ldx, sX, E, sE, PB, w.sPack, batch);
+                (void)gemm_split(st, m, nrhs, K, PA, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch);
                 return;
             }
         }

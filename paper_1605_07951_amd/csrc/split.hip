@@ -3,26 +3,37 @@
 //
 // v_mfma_f32_32x32x16_f16 multiplies at 16 times the rate of the FP32 instruction, with
 // exact products and FP32 sums.  Every real FP32 value, scaled by a power of two, is
-// held as hi + lo of two FP16 numbers: hi carries the leading 11 bits, lo the next 11, so
-// hi + lo is the value to within half a unit of FP32 and mostly exactly.  Three products,
-// hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.  The scales
-// make the range safe: every row of A and every column of B has its own power of two, to
-// a largest part in [2^14, 2^15) (depths of at most 256; a deeper product is a sum of slabs
-// with scales of their own), and what is smaller than 2^-40 of the row's or
-// column's largest part is lost.  The sums do not contain C (one subtraction at the
-// end), and 16 products enter them per rounding instead of 2, so
-// the error is below that of the FP32 kernel: against 64 bits, relative to
-// |C| + |A||B| and in units of u = 2^-24, at K = 64 .. 256 and with columns of B of one size
-// or spread over 8 to 24 decades: rms 0.3-1.4 (FP32 3M kernel 1.0-1.9), largest 1.7-12 (7-20).
+// held as hi + lo of two FP16 numbers (the splitting of Markidis et al. 2018 and Ootomo and Yokota
+// 2022): hi carries the leading 11 bits, lo the next 11 and a sign, so hi + lo is the value
+// to within one unit of FP32 (exactly for three quarters of the values).  Three products,
+// hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.  The sums do not contain C
+// (one subtraction at the end), and 16 products enter them per rounding instead of 2.
+//
+// The range is that of FP16, so the operands carry powers of two, to a largest part in [2^14, 2^15):
+// one per row of A, one per column of B, and one per inner index k, which multiplies column k of A and
+// divides row k of B (split_inner: column k of A to a largest part of one).  An entry keeps its 22 bits
+// down to 2^-17 of the largest of its scaled row or column, then loses a bit per factor of two, and below 2^-40 it
+// is lost: the error is at most 2^-40 max_k |A_ik 2^e_k| max_k |B_kj 2^-e_k| a product beyond that of
+// the 22 bits.  A scaling T = D1 B D2 of the factored matrix goes into these powers: D2 into those of the
+// columns; D1 reaches the factors as L_ik ~ d_i / d_k and U_kj ~ d_k, small entries of a row of L against
+// large ones of a column of U, and without the powers of the inner index T with half of its rows 10^8 / 10^10
+// times the others took 3 / 6 to 10 corrections instead of 2 and 10^12 ended in the FP64 path.  What no
+// such powers can take out (three and more levels of entries in one matrix, min(s_i, s_j) B_ij) keeps the
+// bound above, not the error |A||B| of an FP32 product in every entry.
+//
+// Error against 64 bits, relative to |A||B| and in units of u = 2^-24, K = 128 and 256, split / FP32 kernels: complex, one size or
+// inner index, rows and columns spread over 12 to 16 decades: rms 0.32-0.34 / 0.51-0.53, largest 1.8-2.5 /
+// 3.1-4.9; the entries of A spread over 3 decades 0.6 / 0.95; both operands' over 3 decades 1.1 / 1.6-1.7, over
+// 8 decades 1.7-1.9 / 2.3-2.6, largest 12 / 24.  Real: 0.28-0.31 / 0.43; 0.53-0.56 / 0.78; 0.95 / 1.3; 1.5-1.7 / 1.7-2.0.
+// Depths of at most 256; a deeper product is a sum of slabs with scales of their own.
 //
 // Bound by the matrix cores and by C, which is read and written once per update.  64
-// matrices, K = 256, n = 3840 / 2048 / 1024: 5.95 / 1.64 / 0.44 ms, 325 / 335 / 316 TFLOP/s in
-// the standard count of 8 flops per complex multiply-add (975 TFLOP/s in FP16, C at 2.6
-// TB/s), packing 0.36 / 0.19 / 0.10 ms; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
+// matrices, K = 256, n = 3840 / 2048 / 1024: 6.0-6.5 / 1.7 / 0.44 ms, 297-325 / 318-335 / 318 TFLOP/s in
+// the standard count of 8 flops per complex multiply-add (up to 975 TFLOP/s in FP16, C at 2.6
+// TB/s); the inner exponents 0.09 / 0.06 / 0.03 ms, packing 0.41 / 0.22 / 0.11; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
 //
-// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.52 / 0.17 / 0.045 / 0.019 ms and 0.12 / 0.07 /
-// 0.034 / 0.022 ms for the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045; rms error 0.26-2.2 u
-// (0.95-3.6).
+// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.54 / 0.17 / 0.045 / 0.018 ms and 0.20 / 0.11 /
+// 0.06 / 0.044 ms for the exponents and the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045.
 //
 // The complex product is the 4M form with the interleaved parts as the inner index
 // (k' = 2k + part): Re C takes A' (Br, -Bi), Im C takes A' (Bi, Br), which is one sign
@@ -44,13 +55,13 @@ constexpr int SP_FRAG = 1024;     // bytes
 constexpr int SP_TOP = 14;        // exponent that a row's or column's largest part is scaled to
 constexpr int SP_KMAX = 256;
 
-// hi and lo parts of 4 complex values scaled by 2^e, interleaved (re, im) as one lane of a fragment
-RSRR_DEV void split4(const float2 (&v)[4], int e, uintx4* hi, uintx4* lo)
+// hi and lo parts of 4 complex values scaled by 2^(e + k), interleaved (re, im) as one lane of a fragment
+RSRR_DEV void split4(const float2 (&v)[4], int e, const int2 (&k)[4], uintx4* hi, uintx4* lo)
 {
     half8 h, l;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const float x = ldexpf(v[q].x, e), y = ldexpf(v[q].y, e);
+        const float x = ldexpf(v[q].x, e + k[q].x), y = ldexpf(v[q].y, e + k[q].y);
         h[2 * q] = (_Float16)x;
         h[2 * q + 1] = (_Float16)y;
         l[2 * q] = (_Float16)(x - (float)h[2 * q]);
@@ -60,12 +71,13 @@ RSRR_DEV void split4(const float2 (&v)[4], int e, uintx4* hi, uintx4* lo)
     *lo = __builtin_bit_cast(uintx4, l);
 }
 
-// Exponent that scales a largest part to [2^SP_TOP, 2^(SP_TOP + 1)); zero or non-finite: no scale.
-RSRR_DEV int split_expo(float top)
-{
-    // v_frexp_exp: top = m 2^e with m in [1/2, 1)
-    return (top > 0.f && isfinite(top)) ? SP_TOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
-}
+// Exponent of v's larger part times 2^k (v_frexp_exp: x = m 2^e with m in [1/2, 1); 0 for infinities
+// and NaN); zero: SP_NONE.
+constexpr int SP_NONE = -(1 << 20);
+RSRR_DEV int part_expo(float x, int k) { return x != 0.f ? __builtin_amdgcn_frexp_expf(x) + k : SP_NONE; }
+RSRR_DEV int part_expo(float2 v, int2 k) { return max(part_expo(v.x, k.x), part_expo(v.y, k.y)); }
+// Exponent that scales a largest part with exponent `top` to [2^SP_TOP, 2^(SP_TOP + 1)); zero: no scale.
+RSRR_DEV int split_expo(int top) { return top != SP_NONE ? SP_TOP + 1 - top : 0; }
 
 // Bytes of the fragments of an operand of `rows` rows (A) or columns (B); its exponents follow.
 // Real operands: two consecutive k in place of the parts of one, 16 k per fragment.
@@ -88,6 +100,42 @@ RSRR_DEV float2 sp_entry(const float* src, int k, long ld, int K)
 {
     return make_float2(2 * k < K ? src[2 * k * ld] : 0.f, 2 * k + 1 < K ? src[(2 * k + 1) * ld] : 0.f);
 }
+// the inner index's exponents of that entry's parts, times sign
+template <typename C>
+RSRR_DEV int2 sp_inner(const int* E, int k, int K, int sign)
+{
+    if (sizeof(C) == sizeof(float2)) {
+        const int e = k < K ? sign * E[k] : 0;
+        return make_int2(e, e);
+    }
+    return make_int2(2 * k < K ? sign * E[2 * k] : 0, 2 * k + 1 < K ? sign * E[2 * k + 1] : 0);
+}
+
+// Exponents of the inner index: E[k] scales column k of A (M x K) to a largest part in [1/2, 1); zero or
+// non-finite columns: 0.  One workgroup per column and matrix, bound by reading A once (64 matrices, K = 256,
+// n = 3840: 88 us, 5.7 TB/s).
+template <typename C>
+__global__ __launch_bounds__(256) void split_inner_kernel(int M, const C* __restrict__ A, int lda, long sA,
+                                                          int* __restrict__ E, long sE)
+{
+    const int k = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
+    const C* col = A + b * sA + (long)k * lda;
+    __shared__ float tops[4];
+    float top = 0.f;
+#pragma unroll 4
+    for (int i = t; i < M; i += 256) {
+        if constexpr (elem_traits<C>::complex) top = fmaxf(top, fmaxf(fabsf(col[i].x), fabsf(col[i].y)));
+        else top = fmaxf(top, fabsf(col[i]));
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
+    if ((t & 63) == 0) tops[t >> 6] = top;
+    __syncthreads();
+    if (t == 0) {
+        top = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
+        E[b * sE + k] = (top > 0.f && isfinite(top)) ? -__builtin_amdgcn_frexp_expf(top) : 0;
+    }
+}
 
 // A (M x K, K <= SP_KMAX): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l
 // holds row l % 32 and the 4 complex k at 4 (l / 32); then the exponent of each row's scale.  One
@@ -96,27 +144,31 @@ RSRR_DEV float2 sp_entry(const float* src, int k, long ld, int K)
 template <typename C>
 __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Ktot, int kstep,
                                                            const C* __restrict__ A, int lda, long sA,
+                                                           const int* __restrict__ E, long sE,
                                                            char* __restrict__ P, long sP)
 {
     const int rb = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
     const int nkc = sp_chunks<C>(K), Kb = min(K, Ktot - b * kstep);
     const int r = t & 31, part = t >> 5, i = rb * 32 + r;
-    __shared__ float tops[8][32];
+    __shared__ int tops[8][32];
     const C* src = A + b * sA + i;
     constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
     float2 v[Q][4];
-    float top = 0.f;
+    int2 ek[Q][4];
+    int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            v[q][u] = i < M ? sp_entry(src, 4 * (part + 8 * q) + u, lda, Kb) : make_float2(0.f, 0.f);
-            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+            const int k = 4 * (part + 8 * q) + u;
+            v[q][u] = i < M ? sp_entry(src, k, lda, Kb) : make_float2(0.f, 0.f);
+            ek[q][u] = sp_inner<C>(E + b * sE, k, Kb, 1);
+            top = max(top, part_expo(v[q][u], ek[q][u]));
         }
     tops[part][r] = top;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) top = fmaxf(top, tops[q][r]);
+    for (int q = 0; q < 8; ++q) top = max(top, tops[q][r]);
     const int e = split_expo(top);
     char* Pb = P + b * sP;
     if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes<C>(M, K))[i] = e;
@@ -125,7 +177,7 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
         const int p = part + 8 * q, kc = p >> 1;
         if (kc >= nkc) break;
         uintx4 hi, lo;
-        split4(v[q], e, &hi, &lo);
+        split4(v[q], e, ek[q], &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)rb * nkc + kc) * 2 * SP_FRAG);
         dst[r + 32 * (p & 1)] = hi;
         dst[64 + r + 32 * (p & 1)] = lo;
@@ -137,6 +189,7 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
 template <typename C>
 __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Ktot, int kstep,
                                                            const C* __restrict__ B, int ldb, long sB,
+                                                           const int* __restrict__ E, long sE,
                                                            char* __restrict__ P, long sP)
 {
     const int b = blockIdx.y, t = threadIdx.x;
@@ -146,16 +199,19 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Kto
     const C* src = B + b * sB + (long)j * ldb;
     constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
     float2 v[Q][4];
-    float top = 0.f;
+    int2 ek[Q][4];
+    int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            v[q][u] = j < N ? sp_entry(src, 4 * (part + 8 * q) + u, 1, Kb) : make_float2(0.f, 0.f);
-            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+            const int k = 4 * (part + 8 * q) + u;
+            v[q][u] = j < N ? sp_entry(src, k, 1, Kb) : make_float2(0.f, 0.f);
+            ek[q][u] = sp_inner<C>(E + b * sE, k, Kb, -1);
+            top = max(top, part_expo(v[q][u], ek[q][u]));
         }
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
+    for (int off = 1; off < 8; off <<= 1) top = max(top, __shfl_xor(top, off));
     const int e = split_expo(top);
     char* Pb = P + b * sP;
     if (part == 0) reinterpret_cast<int*>(Pb + sp_frag_bytes<C>(N, K))[j] = e;
@@ -164,7 +220,7 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Kto
         const int p = part + 8 * q, kc = p >> 1;
         if (kc >= nkc) break;
         uintx4 hi, lo;
-        split4(v[q], e, &hi, &lo);
+        split4(v[q], e, ek[q], &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)blockIdx.x * nkc + kc) * 2 * SP_FRAG);
         dst[c + 32 * (p & 1)] = hi;
         dst[64 + c + 32 * (p & 1)] = lo;
@@ -186,34 +242,40 @@ constexpr int UR_NB = 128, UR_KC = UR_NB / SP_KC, UR_LD = UR_NB + 2;
 constexpr long UR_OPERAND = (long)(UR_NB / 32) * UR_KC * 2 * SP_FRAG;   // bytes of one packed factor
 
 // The three left factors (128 x 128, ld ldf[f]) packed with a scale per row; expo at eoff.  One
-// workgroup per 32 rows, factor and matrix: thread (row t % 32, 16 columns of part t / 32).
+// workgroup per 32 rows, factor and matrix: thread (row t % 32, 16 columns of part t / 32).  E: the pair's
+// inner exponents (256), those of the first panel for L0^-1 and T.
 struct UrFactors { const float2* p[3]; long stride[3]; int ld[3]; };
-__global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, char* __restrict__ P, long sP, long eoff)
+__global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, const int* __restrict__ E, long sE,
+                                                              char* __restrict__ P, long sP, long eoff)
 {
     const int rb = blockIdx.x, f = blockIdx.y, b = blockIdx.z, t = threadIdx.x;
     const int r = t & 31, part = t >> 5;
-    __shared__ float tops[8][32];
+    __shared__ int tops[8][32];
     const float2* src = F.p[f] + b * F.stride[f] + rb * 32 + r;
+    const int* Ef = E + b * sE + (f == 2 ? UR_NB : 0);
     float2 v[4][4];
-    float top = 0.f;
+    int2 ek[4][4];
+    int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            v[q][u] = src[(long)(16 * part + 4 * q + u) * F.ld[f]];
-            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+            const int k = 16 * part + 4 * q + u;
+            v[q][u] = src[(long)k * F.ld[f]];
+            ek[q][u] = sp_inner<float2>(Ef, k, UR_NB, 1);
+            top = max(top, part_expo(v[q][u], ek[q][u]));
         }
     tops[part][r] = top;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) top = fmaxf(top, tops[q][r]);
+    for (int q = 0; q < 8; ++q) top = max(top, tops[q][r]);
     const int e = split_expo(top);
     char* Pb = P + b * sP;
     if (part == 0) reinterpret_cast<int*>(Pb + eoff)[f * UR_NB + rb * 32 + r] = e;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         uintx4 hi, lo;
-        split4(v[q], e, &hi, &lo);
+        split4(v[q], e, ek[q], &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + f * UR_OPERAND +
                                                 ((long)rb * UR_KC + 2 * part + q / 2) * 2 * SP_FRAG);
         dst[r + 32 * (q & 1)] = hi;
@@ -222,13 +284,17 @@ __global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, char*
 }
 
 __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict__ A, int lda, long sA, int ncols,
+                                                             const int* __restrict__ E, long sE,
                                                              const char* __restrict__ P3, long sP, long eoff,
                                                              char* __restrict__ PB, long expo_off)
 {
     __shared__ __attribute__((aligned(16))) char F[UR_KC * 2 * SP_FRAG];   // the split columns
     __shared__ __attribute__((aligned(16))) float2 S[32 * UR_LD];          // a product, column by column
     __shared__ int ex[32];
+    __shared__ __attribute__((aligned(16))) int inner[2 * UR_NB];
     const int b = blockIdx.y, t = threadIdx.x;
+    inner[t] = -E[b * sE + t];
+    __syncthreads();
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int c = t >> 3, part = t & 7;   // column, and every eighth group of four rows of it
     const int j = blockIdx.x * 32 + c;
@@ -253,23 +319,36 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
             p[1] = floatx4{v[q][2].x, v[q][2].y, v[q][3].x, v[q][3].y};
         }
     };
-    auto top_of = [&](const float2 (&v)[4][4]) {
-        float top = 0.f;
+    // inner exponents of the four-row group q of panel w's rows
+    auto inner_of = [&](int w, int q, int2 (&k)[4]) {
+        const int4 e = *reinterpret_cast<const int4*>(inner + w * UR_NB + 4 * (part + 8 * q));
+        k[0] = make_int2(e.x, e.x);
+        k[1] = make_int2(e.y, e.y);
+        k[2] = make_int2(e.z, e.z);
+        k[3] = make_int2(e.w, e.w);
+    };
+    auto top_of = [&](int w, const float2 (&v)[4][4]) {
+        int top = SP_NONE;
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; ++q) {
+            int2 k[4];
+            inner_of(w, q, k);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+            for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], k[u]));
+        }
 #pragma unroll
-        for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
+        for (int off = 1; off < 8; off <<= 1) top = max(top, __shfl_xor(top, off));
         return top;
     };
     // four-row group q of the thread goes to fragment (part + 8 q) / 2 of dst
-    auto put = [&](char* dst, const float2 (&v)[4][4], int e) {
+    auto put = [&](int w, char* dst, const float2 (&v)[4][4], int e) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int p = part + 8 * q;
             uintx4 hi, lo;
-            split4(v[q], e, &hi, &lo);
+            int2 k[4];
+            inner_of(w, q, k);
+            split4(v[q], e, k, &hi, &lo);
             uintx4* d = reinterpret_cast<uintx4*>(dst + (long)(p >> 1) * 2 * SP_FRAG);
             d[c + 32 * (p & 1)] = hi;
             d[64 + c + 32 * (p & 1)] = lo;
@@ -316,17 +395,17 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
         fetch(col, v0);
         fetch(col + UR_NB, v1);
     }
-    auto split = [&](const float2 (&v)[4][4]) {
-        const int e = split_expo(top_of(v));
+    auto split = [&](int w, const float2 (&v)[4][4]) {
+        const int e = split_expo(top_of(w, v));
         if (part == 0) ex[c] = e;
-        put(F, v, e);
+        put(w, F, v, e);
         __syncthreads();
     };
-    split(v0);
+    split(0, v0);
     product(0);
     __syncthreads();
     fetch(S + c * UR_LD, v0);
-    split(v0);
+    split(0, v0);
     product(1);
     __syncthreads();
     {
@@ -337,7 +416,7 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
 #pragma unroll
             for (int u = 0; u < 4; ++u) v1[q][u] = csub(v1[q][u], w[q][u]);
     }
-    split(v1);
+    split(1, v1);
     product(2);
     __syncthreads();
     fetch(S + c * UR_LD, v1);
@@ -346,11 +425,11 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
         store(col + UR_NB, v1);
     }
     // the update's operand: one scale for the 256 rows of the column
-    const int e = split_expo(fmaxf(top_of(v0), top_of(v1)));
+    const int e = split_expo(max(top_of(0, v0), top_of(1, v1)));
     char* dst = PB + b * sP + (long)blockIdx.x * 2 * UR_KC * 2 * SP_FRAG;
     if (part == 0) reinterpret_cast<int*>(PB + b * sP + expo_off)[j] = e;
-    put(dst, v0, e);
-    put(dst + (long)UR_KC * 2 * SP_FRAG, v1, e);
+    put(0, dst, v0, e);
+    put(1, dst + (long)UR_KC * 2 * SP_FRAG, v1, e);
 }
 
 // Workgroup tile 128 x 128, four waves of 64 x 64 (2 x 2 blocks of 32 x 32, real and imaginary
@@ -504,12 +583,14 @@ long split_operand_bytes(int rows, int K)
     return sp_frag_bytes<C>(rows, K) + (long)(rows + 31) / 32 * 32 * 4;
 }
 
-// Layout of the LU's pack buffer: A, B, then (complex) the three left factors of the U rows with
-// their row exponents (the offsets follow from the sizes of the product).
+// Layout of the LU's pack buffer: the inner exponents (SPLIT_INNER_BYTES), A, B, then (complex) the three left
+// factors of the U rows with their row exponents (the offsets follow from the sizes of the product).
+static_assert(SPLIT_INNER_BYTES == SP_KMAX * sizeof(int), "an exponent per inner index");
 template <typename C>
 size_t split_pack_bytes(int n, int K)
 {
-    return 2 * split_operand_bytes<C>(n, K) + (elem_traits<C>::complex ? 3 * UR_OPERAND + 3 * UR_NB * 4 : 0);
+    return SPLIT_INNER_BYTES + 2 * split_operand_bytes<C>(n, K) +
+           (elem_traits<C>::complex ? 3 * UR_OPERAND + 3 * UR_NB * 4 : 0);
 }
 
 // Depths of at least one panel (the error is below the FP32 kernel's from K = 64 on); fewer
@@ -517,20 +598,27 @@ size_t split_pack_bytes(int n, int K)
 bool split_ok(int M, int N, int K) { return K >= 128 && K <= SP_KMAX && M >= 128 && N >= 128; }
 
 template <typename C>
-hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, void* P, long sP, int batch,
-                        int Ktot, int kstep)
+hipError_t split_inner(hipStream_t st, int M, int K, const C* A, int lda, long sA, int* E, long sE, int batch)
 {
-    hipLaunchKernelGGL(split_pack_a_kernel<C>, dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K, Ktot ? Ktot : K,
-                       kstep, A, lda, sA, (char*)P, sP);
+    hipLaunchKernelGGL(split_inner_kernel<C>, dim3(K, batch), dim3(256), 0, st, M, A, lda, sA, E, sE);
     return hipGetLastError();
 }
 
 template <typename C>
-hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, void* P, long sP, int batch,
-                        int Ktot, int kstep)
+hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, const int* E, long sE, void* P,
+                        long sP, int batch, int Ktot, int kstep)
+{
+    hipLaunchKernelGGL(split_pack_a_kernel<C>, dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K, Ktot ? Ktot : K,
+                       kstep, A, lda, sA, E, sE, (char*)P, sP);
+    return hipGetLastError();
+}
+
+template <typename C>
+hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, const int* E, long sE, void* P,
+                        long sP, int batch, int Ktot, int kstep)
 {
     hipLaunchKernelGGL(split_pack_b_kernel<C>, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, Ktot ? Ktot : K,
-                       kstep, B, ldb, sB, (char*)P, sP);
+                       kstep, B, ldb, sB, E, sE, (char*)P, sP);
     return hipGetLastError();
 }
 
@@ -540,17 +628,17 @@ bool split_urows_ok(int nb, const float2* A, int lda, long sA)
 }
 
 hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, long s0, const float2* T, int ldt,
-                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, void* P, long sP,
-                       int batch)
+                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, const int* E, long sE,
+                       void* P, long sP, int batch)
 {
     constexpr int K = 2 * UR_NB;
     char* Pc = (char*)P;
     const long offb = split_operand_bytes<float2>(M, K), off = offb + split_operand_bytes<float2>(N, K);
     const UrFactors F = {{L0, T, L1}, {s0, sT, s1}, {ld0, ldt, ld1}};
-    hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, Pc + off, sP,
+    hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, E, sE, Pc + off, sP,
                        3 * UR_OPERAND);
-    hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, Pc + off, sP,
-                       3 * UR_OPERAND, Pc + offb, sp_frag_bytes<float2>(N, K));
+    hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, E, sE,
+                       Pc + off, sP, 3 * UR_OPERAND, Pc + offb, sp_frag_bytes<float2>(N, K));
     return hipGetLastError();
 }
 
@@ -576,8 +664,11 @@ hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long 
 #define SP_INST(C)                                                                                                  \
     template long split_operand_bytes<C>(int, int);                                                                 \
     template size_t split_pack_bytes<C>(int, int);                                                                  \
-    template hipError_t split_pack_a<C>(hipStream_t, int, int, const C*, int, long, void*, long, int, int, int);    \
-    template hipError_t split_pack_b<C>(hipStream_t, int, int, const C*, int, long, void*, long, int, int, int);    \
+    template hipError_t split_inner<C>(hipStream_t, int, int, const C*, int, long, int*, long, int);                \
+    template hipError_t split_pack_a<C>(hipStream_t, int, int, const C*, int, long, const int*, long, void*, long,  \
+                                        int, int, int);                                                             \
+    template hipError_t split_pack_b<C>(hipStream_t, int, int, const C*, int, long, const int*, long, void*, long,  \
+                                        int, int, int);                                                             \
     template hipError_t gemm_split<C>(hipStream_t, int, int, int, const void*, long, const void*, long, int, int,   \
                                       bool, C*, int, long, int);
 SP_INST(float2)
