@@ -121,6 +121,9 @@ struct LUWork {
     // trailing updates, and complex solves of many right-hand sides, then run with split operands on
     // the FP16 matrix cores
     void* pack = nullptr; long sPack = 0;
+    // the solves' kernels are chosen by (n, nrhs) alone, not by how many matrices share a launch: the ragged
+    // batch, whose requests get the same bits alone and in any mix
+    bool any_mix = false;
 };
 // Elements per matrix of the pair buffer for n x n matrices and panel width nb.
 inline long lu_pair_elems(int n, int nb, int ldpair) { return (long)ldpair * 2 * nb + (long)nb * nb; }
@@ -138,7 +141,7 @@ hipError_t getrf_batched(hipStream_t st, typename cpx<R>::T* A, long sA, int lda
                          int batch);
 
 // X <- T^-1 X for the factors of getrf_batched (same nb and workspace).  FP32 blocks of
-// at most 64 right-hand sides, 16 of which fit in LDS, run the whole solve of a matrix in one workgroup per 16.
+// at most 64 right-hand sides (any_mix: 16), 16 of which fit in LDS, run the whole solve of a matrix in one workgroup per 16.
 template <typename R>
 hipError_t getrs_batched(hipStream_t st, const typename cpx<R>::T* LU, long sLU, int lda, int n, int nb,
                          const LUWork& w, typename cpx<R>::T* X, long sX, int ldx, int nrhs, int batch);

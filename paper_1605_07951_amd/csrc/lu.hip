@@ -1251,7 +1251,7 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
     auto off_diag = [&](int r0, int m, int K, const C* F, int c0) {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const long na = split_operand_bytes<C>(m, K);
-            if (w.pack && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
+            if (w.pack && !w.any_mix && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
                 (long)SPLIT_INNER_BYTES + na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
                 int* E = (int*)w.pack;
                 const long sE = w.sPack / 4;
@@ -1564,12 +1564,14 @@ template <typename C>
 static size_t gs_lds(int n, int nrhs) { return (size_t)n * (elem_traits<C>::complex && nrhs > 8 ? 128 : 64); }
 // At most 16 right-hand sides that fit: always (above).  17 to 64 in groups of 16, a workgroup each, which
 // read the factor once per group, up to two workgroups per CU (64 right-hand sides, chain / groups: 48
-// matrices n = 256 125 / 52 us, n = 1024 769 / 470, 128 matrices 141 / 102 and 1124 / 973).
+// matrices n = 256 125 / 52 us, n = 1024 769 / 470, 128 matrices 141 / 102 and 1124 / 973).  With any_mix 17
+// and more take the chain, whatever the batch: of 2048 matrices with 32 right-hand sides the groups take
+// 1.1 (n = 1024) to 1.4 times as long (n = 128).
 template <typename C>
-static bool getrs_lds_ok(int n, int nrhs, int batch)
+static bool getrs_lds_ok(int n, int nrhs, int batch, bool any_mix)
 {
     if (nrhs < 1 || nrhs > GS_MAX_RHS || gs_lds<C>(n, nrhs) > (size_t)128 << 10) return false;
-    return nrhs <= 16 || (long)batch * ((nrhs + 15) / 16) <= GS_MAX_WG;
+    return nrhs <= 16 || (!any_mix && (long)batch * ((nrhs + 15) / 16) <= GS_MAX_WG);
 }
 
 template <typename C>
@@ -1608,7 +1610,8 @@ template <>
 hipError_t getrs_batched<float>(hipStream_t st, const float2* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                                 float2* X, long sX, int ldx, int nrhs, int batch)
 {
-    if (getrs_lds_ok<float2>(n, nrhs, batch)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
+    if (getrs_lds_ok<float2>(n, nrhs, batch, w.any_mix))
+        return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
     return getrs_impl<float2>(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
 }
 template <>
@@ -1624,7 +1627,8 @@ hipError_t getrf_real_batched(hipStream_t st, float* A, long sA, int lda, int n,
 hipError_t getrs_real_batched(hipStream_t st, const float* LU, long sLU, int lda, int n, int nb, const LUWork& w,
                               float* X, long sX, int ldx, int nrhs, int batch)
 {
-    if (getrs_lds_ok<float>(n, nrhs, batch)) return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
+    if (getrs_lds_ok<float>(n, nrhs, batch, w.any_mix))
+        return getrs_lds_batched(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
     return getrs_impl<float>(st, LU, sLU, lda, n, nb, w, X, sX, ldx, nrhs, batch);
 }
 
