@@ -271,27 +271,31 @@ __global__ __launch_bounds__(EW_NT) void ir_decide_kernel(int M, int Lmax, const
 
 // R_b = U_b - T_b X_b (U null: T_b X_b) in FP64 for at most 32 right-hand sides: the
 // product is skinny, so it is a stream over T, bound by HBM where there are enough
-// rows.  A workgroup takes the rows of one row block of one matrix; its W waves split
-// the columns of T (a contiguous range each) and their partial sums are added in the
-// order of the waves, so that small matrices and few points still keep many loads in
+// rows.  A workgroup takes 64 rows of one matrix; its W waves split
+// the columns of T (a contiguous range each) and their partial sums are added in a fixed
+// order, so that small matrices and few points still keep many loads in
 // flight (one workgroup per 1024 rows that walked all columns ran n = 3000, 32 points,
 // L = 2 at 3.7 TB/s on 96 workgroups; n = 200, L = 16, 32 points took 141 us).  Nothing
 // is shared before that sum, so there is no barrier in the loop.  Matrices with
-// active[b] == 0 are skipped.
+// active[b] == 0 are skipped.  The split depends on n and L alone, never on the number of matrices: a
+// point's residual has the same bits whatever shares its launch.
 //
-// Up to 8 columns (resid_stream_kernel): a lane owns RPT rows, the loads of T are
-// coalesced, and X(k, c), the same for the whole wave, comes through the scalar cache.
+// Up to 8 columns (resid_stream_kernel): a lane owns a row, the loads of T are
+// coalesced, and X(k, c), the same for the whole wave, comes through the scalar cache.  Eight waves at
+// every size: fewer matrices need them (2048 rows, one matrix, 8 columns 65 us, four waves 118), and
+// for many, four waves of one or two rows per lane take 0.91 to 1.13 times as long (1024 rows, 96 matrices, 4 columns
+// 267 us against 293; 256 rows, 384 matrices, 8 columns 91 against 85).
 // 9 to 32 columns (resid_mfma_kernel): v_mfma_f64_16x16x4f64 on four 16-row blocks and one or
 // two 16-column blocks per wave; a lane loads whole complex entries and the real and
 // imaginary parts go through separate instructions (inner index: four consecutive k).
 // 17 to 32 columns fill half of a GEMM tile's 64: n = 1024, L = 32, 48 points 441 us there,
 // 335 us here (T read once takes 170 us at a copy's rate, the products 177 us).
 
-// The waves' partial sums (acc: NV values per lane) added in order into wave 0's.
+// The partial sums of the first W waves (acc: NV values per lane) added in order into wave 0's.
 template <int NV, int W>
 RSRR_DEV void wave_partials(double2 (&acc)[NV], double2* lds, int wave, int lane)
 {
-    if (wave > 0) {
+    if (wave > 0 && wave < W) {
 #pragma unroll
         for (int v = 0; v < NV; ++v) lds[((wave - 1) * NV + v) * 64 + lane] = acc[v];
     }
@@ -304,74 +308,79 @@ RSRR_DEV void wave_partials(double2 (&acc)[NV], double2* lds, int wave, int lane
     }
 }
 
-template <int LC, int RPT, int W>
-__global__ __launch_bounds__(64 * W) void resid_stream_kernel(int n, int L, const double2* __restrict__ T, int ldt,
+constexpr int RS_W = 8;   // waves
+
+template <int LC>
+__global__ __launch_bounds__(64 * RS_W) void resid_stream_kernel(int n, int L, const double2* __restrict__ T, int ldt,
                                                               long sT, const double2* __restrict__ X, int ldx,
                                                               long sX, const double2* __restrict__ U, int ldu,
                                                               long sU, double2* __restrict__ R, int ldr, long sR,
                                                               const int* __restrict__ active)
 {
     constexpr int KU = LC <= 4 ? 4 : 2;   // columns of T in flight per row (X(k .. k+KU, :) fits the scalar registers)
-    __shared__ double2 part[(W - 1) * RPT * LC * 64];
+    constexpr bool TWO = LC > 4;          // waves 4 to 7 into 0 to 3 first: half the LDS (57 KB for 8 columns)
+    constexpr int W = RS_W, WS = TWO ? W / 2 : W;
+    __shared__ double2 part[(TWO ? WS : W - 1) * LC * 64];
     const int b = blockIdx.y;
     if (active && !active[b]) return;
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int row0 = blockIdx.x * 64 * RPT + lane;
+    const int row = blockIdx.x * 64 + lane;
     const int per = ((n + W - 1) / W + KU - 1) / KU * KU;
     const int k0 = min(n, wave * per), k1 = min(n, k0 + per);
     const double2* Xb = X + b * sX;
     const double2* Tb = T + b * sT;
-    int rr[RPT];   // rows past the end read the last row and are not stored
-#pragma unroll
-    for (int r = 0; r < RPT; ++r) rr[r] = min(row0 + 64 * r, n - 1);
+    const int rr = min(row, n - 1);   // rows past the end read the last row and are not stored
     int xc[LC];    // columns past L read the last one and are not stored
 #pragma unroll
     for (int c = 0; c < LC; ++c) xc[c] = min(c, L - 1);
-    double2 acc[RPT * LC];
+    double2 acc[LC];
 #pragma unroll
-    for (int v = 0; v < RPT * LC; ++v) acc[v] = make_double2(0.0, 0.0);
+    for (int v = 0; v < LC; ++v) acc[v] = make_double2(0.0, 0.0);
     auto step = [&](int k, auto ku) {
         constexpr int KN = decltype(ku)::value;
-        double2 t[KN][RPT];
+        double2 t[KN];
 #pragma unroll
-        for (int u = 0; u < KN; ++u)
-#pragma unroll
-            for (int r = 0; r < RPT; ++r) t[u][r] = Tb[rr[r] + (long)(k + u) * ldt];
+        for (int u = 0; u < KN; ++u) t[u] = Tb[rr + (long)(k + u) * ldt];
 #pragma unroll
         for (int c = 0; c < LC; ++c)
 #pragma unroll
             for (int u = 0; u < KN; ++u) {
                 const double2 x = Xb[(k + u) + (long)xc[c] * ldx];
-#pragma unroll
-                for (int r = 0; r < RPT; ++r) {
-                    double2& a = acc[r * LC + c];
-                    a.x = fma(t[u][r].x, x.x, a.x);
-                    a.y = fma(t[u][r].x, x.y, a.y);
-                    a.x = fma(-t[u][r].y, x.y, a.x);
-                    a.y = fma(t[u][r].y, x.x, a.y);
-                }
+                double2& a = acc[c];
+                a.x = fma(t[u].x, x.x, a.x);
+                a.y = fma(t[u].x, x.y, a.y);
+                a.x = fma(-t[u].y, x.y, a.x);
+                a.y = fma(t[u].y, x.x, a.y);
             }
     };
     int k = k0;
 #pragma unroll 2
     for (; k + KU <= k1; k += KU) step(k, std::integral_constant<int, KU>{});
     for (; k < k1; ++k) step(k, std::integral_constant<int, 1>{});
-    wave_partials<RPT * LC, W>(acc, part, wave, lane);
+    if constexpr (TWO) {
+        if (wave >= WS) {
+#pragma unroll
+            for (int c = 0; c < LC; ++c) part[((wave - WS) * LC + c) * 64 + lane] = acc[c];
+        }
+        __syncthreads();
+        if (wave < WS) {
+#pragma unroll
+            for (int c = 0; c < LC; ++c) acc[c] = cadd(acc[c], part[(wave * LC + c) * 64 + lane]);
+        }
+        __syncthreads();
+    }
+    wave_partials<LC, WS>(acc, part, wave, lane);
     if (wave > 0) return;
     double2* Rb = R + b * sR;
     const double2* Ub = U ? U + b * sU : nullptr;
+    if (row >= n) return;
 #pragma unroll
-    for (int r = 0; r < RPT; ++r) {
-        const int row = row0 + 64 * r;
-        if (row >= n) continue;
-#pragma unroll
-        for (int c = 0; c < LC; ++c)
-            if (c < L) {
-                double2 v = acc[r * LC + c];
-                if (Ub) v = csub(Ub[row + (long)c * ldu], v);
-                Rb[row + (long)c * ldr] = v;
-            }
-    }
+    for (int c = 0; c < LC; ++c)
+        if (c < L) {
+            double2 v = acc[c];
+            if (Ub) v = csub(Ub[row + (long)c * ldu], v);
+            Rb[row + (long)c * ldr] = v;
+        }
 }
 
 template <int CB, int W>
@@ -594,21 +603,18 @@ hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt,
                         long sX, const double2* U, int ldu, long sU, double2* R, int ldr, long sR, const int* active,
                         int B)
 {
-#define RS_L(LC, RPT, W)                                                                                             \
-    hipLaunchKernelGGL((resid_stream_kernel<LC, RPT, W>), dim3((unsigned)((n + 64 * RPT - 1) / (64 * RPT)),          \
-                                                               (unsigned)B),                                        \
-                       dim3(64 * W), 0, st, n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
+#define RS_L(LC)                                                                                                     \
+    hipLaunchKernelGGL(resid_stream_kernel<LC>, dim3((unsigned)((n + 63) / 64), (unsigned)B), dim3(64 * RS_W), 0, st, \
+                       n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
 #define RS_M(CB, W)                                                                                                  \
     hipLaunchKernelGGL((resid_mfma_kernel<CB, W>), dim3((unsigned)((n + 63) / 64), (unsigned)B), dim3(64 * W), 0, st, \
                        n, L, T, ldt, sT, X, ldx, sX, U, ldu, sU, R, ldr, sR, active)
-    // few row blocks (fewer than two per CU): the columns are split over more waves
-    const bool few = (long)((n + 63) / 64) * B < 512;
     if (L <= 2) {
-        if (few) RS_L(2, 1, 8); else RS_L(2, 2, 4);
+        RS_L(2);
     } else if (L <= 4) {
-        if (few) RS_L(4, 1, 8); else RS_L(4, 2, 4);
+        RS_L(4);
     } else if (L <= 8) {
-        if (few) RS_L(8, 1, 8); else RS_L(8, 1, 4);
+        RS_L(8);
     } else if (L <= 16) {
         RS_M(1, 4);
     } else {

@@ -52,3 +52,11 @@ def test_wide_solve():
 def test_fp64_product_tiles(n, L, count, prec):
     """Enough matrices for 128 x 64 tiles in the mix, 64 x 64 alone."""
     _same_alone(n, L, count, prec)
+
+
+# 512 blocks of 64 rows and more in the mix, fewer alone
+@pytest.mark.parametrize("n,L,count", [(60, 2, 22), (60, 8, 22), (300, 1, 5), (300, 3, 5), (300, 5, 5), (300, 8, 5),
+                                       (700, 4, 2), (120, 9, 12), (120, 20, 12)])
+@pytest.mark.parametrize("prec", [R.RSRR_PREC_C64_IR, R.RSRR_PREC_C128])
+def test_residual(n, L, count, prec):
+    _same_alone(n, L, count, prec)
