@@ -32,9 +32,9 @@ struct rsrr_ctx {
     hipStream_t upd = nullptr;       // CU-masked stream for the overlapped updates (null: no mask)
     bool lookahead = true;           // RSRR_LOOKAHEAD=0 at creation turns it off
     // CUs the overlapped updates leave to the look-ahead (RSRR_LA_CUS), and the columns of each that
-    // keep off them (RSRR_LA_COLS, 0: all; -1: 2048 in complex FP32, else all).  64 panels of 4096 rows take
-    // 1024 threads each, two rounds on 32 CUs; past 2048 columns the split update outlasts the
-    // panels, and the rest of it takes every CU.  4096 rows, 64 points: 116.0 ms with 32 CUs and all
+    // keep off them (RSRR_LA_COLS, 0: all; -1: 2048 in complex FP32 of 48 points and more, else all).  64
+    // panels of 4096 rows take 1024 threads each, two rounds on 32 CUs; past 2048 columns the split update
+    // of that many points outlasts the panels, and the rest of it takes every CU.  4096 rows, 64 points: 116.0 ms with 32 CUs and all
     // columns, 115.1 with 64, 113.5 with 64 and 2048 (1024 119, 2560 114.6; 96 CUs 115.9); FP64 and
     // real cases within 0.5% of each other except 80 CUs and more (1-5% slower)
     int la_cus = 64;
