@@ -1032,6 +1032,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     if (nb > max_panel<R>()) nb = max_panel<R>();
     if (nb < MIN_NB) nb = MIN_NB;  // perm/inv storage holds perm_panels(n) panels
     UpdateRecorder* rec = w.rec;
+    hipError_t err = hipSuccess;   // the first one
+    auto ok = [&](hipError_t e) { if (err == hipSuccess) err = e; };
     // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `s`, event-timed.  An
     // update done in column parts gives its whole width (Nall) and the part's first column
     // (j0); with split operands the first part (j0 = 0) packs them for all parts (the inner
@@ -1043,7 +1045,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if (Nall == 0) Nall = N;
         bool split = false;
         if constexpr (sizeof(R) == 4) {
-            split = w.pack != nullptr && split_ok(M, Nall, kdepth);
+            // (a part that starts inside a packed block of 32 columns runs in FP32)
+            split = w.pack != nullptr && split_ok(M, Nall, kdepth) && j0 % 32 == 0;
             if (split) {
                 int* E = (int*)w.pack;
                 const long sE = w.sPack / 4;
@@ -1051,15 +1054,15 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
                 char* PB = PA + split_operand_bytes<C>(M, kdepth);
                 if (j0 == 0) {
                     if (!bpacked) {
-                        (void)split_inner(s, M, kdepth, Aop, ldaop, sAop, E, sE, batch);
-                        (void)split_pack_b(s, Nall, kdepth, Bop, lda, sA, E, sE, PB, w.sPack, batch);
+                        ok(split_inner(s, M, kdepth, Aop, ldaop, sAop, E, sE, batch));
+                        ok(split_pack_b(s, Nall, kdepth, Bop, lda, sA, E, sE, PB, w.sPack, batch));
                     }
-                    (void)split_pack_a(s, M, kdepth, Aop, ldaop, sAop, E, sE, PA, w.sPack, batch);
+                    ok(split_pack_a(s, M, kdepth, Aop, ldaop, sAop, E, sE, PA, w.sPack, batch));
                 }
-                (void)gemm_split(s, M, N, kdepth, PA, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch);
+                ok(gemm_split(s, M, N, kdepth, PA, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch));
             }
         }
-        if (!split) (void)gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1);
+        if (!split) ok(gemm_sub<C>(s, M, N, kdepth, Aop, ldaop, sAop, Bop, lda, sA, Cop, lda, sA, batch, 1));
         if (timed) {
             (void)hipEventRecord(rec->ev[2 * rec->used + 1], s);
             const double fl = (elem_traits<C>::complex ? 8.0 : 2.0) * M * (double)N * kdepth * batch;
@@ -1102,10 +1105,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             perm_rows<C>(s, pm0 + 2 * MAX_NB, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0 + nb, nb, rest, w.active,
                          batch);
             int* E = (int*)w.pack;
-            (void)split_inner(s, rest, 2 * nb, Wp + q2, w.ldpair, w.sPair, E, w.sPack / 4, batch);
-            (void)split_urows(s, rest, rest, panel_inv<C>(w, p0, nb, 0), nb, w.sInv, TL, nb, w.sPair,
-                              panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, E, w.sPack / 4,
-                              (char*)w.pack + SPLIT_INNER_BYTES, w.sPack, batch);
+            ok(split_inner(s, rest, 2 * nb, Wp + q2, w.ldpair, w.sPair, E, w.sPack / 4, batch));
+            ok(split_urows(s, rest, rest, panel_inv<C>(w, p0, nb, 0), nb, w.sInv, TL, nb, w.sPair,
+                           panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, E, w.sPack / 4,
+                           (char*)w.pack + SPLIT_INNER_BYTES, w.sPack, batch));
             return true;
         }
         return false;
@@ -1121,10 +1124,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         const int2* pm0 = panel(s, q0, nb, pp);
         perm_rows<C>(s, pm0, w.sPerm, A + (long)q1 * lda, sA, lda, (C*)w.tmp, w.sTmp, nb, q0, nb, nb, w.active,
                      batch);
-        (void)gemm_sub<C>(s, nb, nb, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                          A + q0 + (long)q1 * lda, lda, sA, batch, 0, -1.0, 0.0);
-        (void)gemm_sub<C>(s, n - q1, nb, nb, A + q1 + (long)q0 * lda, lda, sA, A + q0 + (long)q1 * lda, lda, sA,
-                          A + q1 + (long)q1 * lda, lda, sA, batch);
+        ok(gemm_sub<C>(s, nb, nb, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                       A + q0 + (long)q1 * lda, lda, sA, batch, 0, -1.0, 0.0));
+        ok(gemm_sub<C>(s, n - q1, nb, nb, A + q1 + (long)q0 * lda, lda, sA, A + q0 + (long)q1 * lda, lda, sA,
+                       A + q1 + (long)q1 * lda, lda, sA, batch));
         const int2* pm1 = panel(s, q1, nb, pp + 1);
         copy_rows<C>(s, q1, n, nb, A + (long)q0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
         perm_rows<C>(s, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, q1, nb, nb, w.active, batch);
@@ -1138,12 +1141,12 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
         C* Ar2 = A + (long)q2 * lda;
         perm_rows<C>(st, pm0, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, q0, nb, rest, w.active, batch);
-        (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                          Ar2 + q0, lda, sA, batch, 0, -1.0, 0.0);
+        ok(gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                       Ar2 + q0, lda, sA, batch, 0, -1.0, 0.0));
         perm_rows<C>(st, pm1, w.sPerm, Ar2, sA, lda, (C*)w.tmp, w.sTmp, nb, q1, nb, rest, w.active, batch);
-        (void)gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch);
-        (void)gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
-                          w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0);
+        ok(gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch));
+        ok(gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
+                       w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0));
         return false;
     };
     int c0 = 0, p = 0;
@@ -1156,7 +1159,7 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         C* Wb[2] = {(C*)w.pair, (C*)w.pair2};
         int buf = 0;
         front(st, 0, 0, Wb[0]);
-        if (w.first_panel) (void)hipEventRecord(w.first_panel, st);
+        if (w.first_panel) ok(hipEventRecord(w.first_panel, st));
         for (;;) {
             const int c2 = c0 + 2 * nb, rest = n - c2;
             const bool bpacked = back(c0, p, Wb[buf]);
@@ -1172,18 +1175,18 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             }
             const int wn = 2 * nb;
             timed_update(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
-            (void)hipEventRecord(w.ev_a, st);
+            ok(hipEventRecord(w.ev_a, st));
             // the rest of the update is enqueued before the next pair's panels (a chain of
             // small launches), so the host never holds it back behind them
             if (w.upd && w.ev_c) {
                 // the first la_cols columns of the update on the CUs the side stream does not
                 // use (while the next panels are factored), the rest on every CU
                 const int n1 = w.la_cols > 0 ? std::min(rest - wn, std::max(32, w.la_cols / 32 * 32)) : rest - wn;
-                (void)hipStreamWaitEvent(w.upd, w.ev_a, 0);
+                ok(hipStreamWaitEvent(w.upd, w.ev_a, 0));
                 timed_update(w.upd, rest, n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
                                 Cop + (long)wn * lda, rest, wn);
-                (void)hipEventRecord(w.ev_c, w.upd);
-                (void)hipStreamWaitEvent(st, w.ev_c, 0);
+                ok(hipEventRecord(w.ev_c, w.upd));
+                ok(hipStreamWaitEvent(st, w.ev_c, 0));
                 if (n1 < rest - wn)
                     timed_update(st, rest, rest - wn - n1, 2 * nb, Aop, ldw, w.sPair, Bop + (long)(wn + n1) * lda,
                                     Cop + (long)(wn + n1) * lda, rest, wn + n1);
@@ -1191,10 +1194,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
                 timed_update(st, rest, rest - wn, 2 * nb, Aop, ldw, w.sPair, Bop + (long)wn * lda,
                                 Cop + (long)wn * lda, rest, wn);
             }
-            (void)hipStreamWaitEvent(w.side, w.ev_a, 0);
+            ok(hipStreamWaitEvent(w.side, w.ev_a, 0));
             front(w.side, c2, p + 2, Wb[buf ^ 1]);
-            (void)hipEventRecord(w.ev_b, w.side);
-            (void)hipStreamWaitEvent(st, w.ev_b, 0);
+            ok(hipEventRecord(w.ev_b, w.side));
+            ok(hipStreamWaitEvent(st, w.ev_b, 0));
             c0 = c2;
             p += 2;
             buf ^= 1;
@@ -1205,7 +1208,7 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         const int c2 = c0 + 2 * nb, rest = n - c2;
         C* Wp = (C*)w.pair;
         front(st, c0, p, Wp);
-        if (c0 == 0 && w.first_panel) (void)hipEventRecord(w.first_panel, st);
+        if (c0 == 0 && w.first_panel) ok(hipEventRecord(w.first_panel, st));
         const bool bpacked = back(c0, p, Wp);
         timed_update(st, rest, rest, 2 * nb, Wp + c2, ldw, w.sPair, A + c0 + (long)c2 * lda, A + c2 + (long)c2 * lda,
                         rest, 0, bpacked);
@@ -1218,17 +1221,18 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if (use_inv) {
             // interchanges on the right block (top rows to the scratch), then U12 = L11^-1 A12 on MFMA
             perm_rows<C>(st, pm, w.sPerm, Ar, sA, lda, (C*)w.tmp, w.sTmp, nb, c0, jb, rest, w.active, batch);
-            (void)gemm_sub<C>(st, jb, rest, jb, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                              Ar + c0, lda, sA, batch, 0, -1.0, 0.0);
+            ok(gemm_sub<C>(st, jb, rest, jb, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                           Ar + c0, lda, sA, batch, 0, -1.0, 0.0));
         } else {
             if constexpr (sizeof(C) == sizeof(double2))
                 perm_trsm(st, A, sA, lda, pm, w.sPerm, Ar, sA, lda, c0, jb, rest, 1, w.active, batch);
         }
-        if (c0 == 0 && w.first_panel) (void)hipEventRecord(w.first_panel, st);
+        if (c0 == 0 && w.first_panel) ok(hipEventRecord(w.first_panel, st));
         timed_update(st, rest, rest, jb, A + c1 + (long)c0 * lda, lda, sA, A + c0 + (long)c1 * lda,
                         A + c1 + (long)c1 * lda);
     }
-    return hipGetLastError();
+    ok(hipGetLastError());
+    return err;
 }
 
 // Right-hand sides, and those of all matrices, from which the solves' products pack their operands (the
@@ -1247,6 +1251,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
     if (nb > max_panel<R>()) nb = max_panel<R>();
     if (nb < MIN_NB) nb = MIN_NB;
     const int np = (n + nb - 1) / nb;
+    hipError_t err = hipSuccess;   // the first one
+    auto ok = [&](hipError_t e) { if (err == hipSuccess) err = e; };
     // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0
     auto off_diag = [&](int r0, int m, int K, const C* F, int c0) {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
@@ -1257,22 +1263,22 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
                 const long sE = w.sPack / 4;
                 char* PA = (char*)w.pack + SPLIT_INNER_BYTES;
                 char* PB = PA + na;
-                (void)split_inner(st, m, K, F, lda, sLU, E, sE, batch);
-                (void)split_pack_a(st, m, K, F, lda, sLU, E, sE, PA, w.sPack, batch);
-                (void)split_pack_b(st, nrhs, K, X + c0, ldx, sX, E, sE, PB, w.sPack, batch);
-                (void)gemm_split(st, m, nrhs, K, PA, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch);
+                ok(split_inner(st, m, K, F, lda, sLU, E, sE, batch));
+                ok(split_pack_a(st, m, K, F, lda, sLU, E, sE, PA, w.sPack, batch));
+                ok(split_pack_b(st, nrhs, K, X + c0, ldx, sX, E, sE, PB, w.sPack, batch));
+                ok(gemm_split(st, m, nrhs, K, PA, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch));
                 return;
             }
         }
-        (void)gemm_sub<C>(st, m, nrhs, K, F, lda, sLU, X + c0, ldx, sX, X + r0, ldx, sX, batch);
+        ok(gemm_sub<C>(st, m, nrhs, K, F, lda, sLU, X + c0, ldx, sX, X + r0, ldx, sX, batch));
     };
     for (int p = 0; p < np; ++p) {
         const int c0 = p * nb, jb = (n - c0 < nb) ? n - c0 : nb;
         const int2* pm = w.perm + (long)p * 2 * MAX_NB;
         if (use_inv) {
             perm_rows<C>(st, pm, w.sPerm, X, sX, ldx, (C*)w.tmp, w.sTmp, nb, c0, jb, nrhs, w.active, batch);
-            (void)gemm_sub<C>(st, jb, nrhs, jb, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                              X + c0, ldx, sX, batch, 0, -1.0, 0.0);
+            ok(gemm_sub<C>(st, jb, nrhs, jb, panel_inv<C>(w, p, nb, 0), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                           X + c0, ldx, sX, batch, 0, -1.0, 0.0));
         } else {
             if constexpr (sizeof(C) == sizeof(double2))
                 perm_trsm(st, LU, sLU, lda, pm, w.sPerm, X, sX, ldx, c0, jb, nrhs, 1, w.active, batch);
@@ -1288,8 +1294,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
         const int c0 = p * nb, jb = (n - c0 < nb) ? n - c0 : nb;
         if (use_inv) {
             perm_rows<C>(st, nullptr, 0, X, sX, ldx, (C*)w.tmp, w.sTmp, nb, c0, jb, nrhs, w.active, batch);
-            (void)gemm_sub<C>(st, jb, nrhs, jb, panel_inv<C>(w, p, nb, 1), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
-                              X + c0, ldx, sX, batch, 0, -1.0, 0.0);
+            ok(gemm_sub<C>(st, jb, nrhs, jb, panel_inv<C>(w, p, nb, 1), nb, w.sInv, (const C*)w.tmp, nb, w.sTmp,
+                           X + c0, ldx, sX, batch, 0, -1.0, 0.0));
         } else {
             if constexpr (sizeof(C) == sizeof(double2))
                 perm_trsm(st, LU, sLU, lda, nullptr, 0, X, sX, ldx, c0, jb, nrhs, 2, w.active, batch);
@@ -1308,7 +1314,8 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
             p -= 1;
         }
     }
-    return hipGetLastError();
+    ok(hipGetLastError());
+    return err;
 }
 
 // ----------------------------------------------------------------------------
