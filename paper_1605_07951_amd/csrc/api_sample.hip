@@ -307,6 +307,7 @@ struct SampleBufs {
     hipStream_t la, upd; hipEvent_t la_a, la_b, la_c;
     int la_cols;
     void* pack;
+    bool solve_inv;   // the solves multiply with the inverses of the diagonal blocks
     int ld, np, nb; long sT, sP, sPerm, nparts, sInv, sTmp, sPair, sPack;
     LUWork lu(const int* act, UpdateRecorder* rec) const
     {
@@ -317,6 +318,7 @@ struct SampleBufs {
         w.pair2 = pair2; w.side = la; w.ev_a = la_a; w.ev_b = la_b; w.upd = upd; w.ev_c = la_c;
         w.la_cols = la_cols;
         w.pack = pack; w.sPack = sPack;
+        w.solve_inv = solve_inv;
         return w;
     }
 };
@@ -354,6 +356,9 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     // the real FP32 path (R32_IR) uses the complex FP32 layout with real elements (half the bytes)
     const bool fp32 = prec != RSRR_PREC_C128;
     const size_t esz = fp32 ? 8 : 16;
+    // FP64: the factorisation takes L11^-1 (multipliers of at most one) for its U rows; the solves,
+    // which nothing refines, substitute: U11 may be as ill-conditioned as T
+    s.solve_inv = fp32;
     s.nb = fp32 ? std::min(c->nb_c64, max_panel<float>()) : std::min(c->nb_c128, max_panel<double>());
     s.sInv = (long)((n + s.nb - 1) / s.nb) * 2 * s.nb * s.nb;
     s.sTmp = (long)s.nb * std::max(n, L);
@@ -361,11 +366,11 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     s.tmp = ws_get(c, WS_B1, (size_t)B * s.sTmp * esz);
     // any panel width the LU clamps to
     s.sPair = lu_pair_elems(n, fp32 ? max_panel<float>() : max_panel<double>(), s.ld);
-    // In FP64 the look-ahead pays beyond about 2^26 entries (never one point): with it / without (pairs in turn), ms, 8 right-hand sides, n = 1000, 1 /
-    // 32 points 6.3 / 5.5, 8.2 / 8.1; n = 1500, 32 points 16.5 / 16.8; 2000, 1 / 16 14.8 / 12.8, 20.9 / 21.0; 2048, 32
-    // 29.6 / 30.3; 4000, 1 / 4 / 8 37.7 / 34.3, 46.3 / 45.9, 59.1 / 60.4.  A point redone in FP64 is such a call of one
-    // point; without the rule its masked stream cost a ragged batch with one such point 5 ms a call (4 x 8 points,
-    // n = 200: 7.3 / 2.0).
+    // In FP64 the look-ahead pays beyond about 2^26 entries (never one point): with it / without (pairs in
+    // turn), ms, 8 right-hand sides, n = 1000, 1 / 32 points 6.3 / 5.5, 8.2 / 8.1; n = 1500, 32 points 16.5 /
+    // 16.8; 2000, 1 / 16 14.8 / 12.8, 20.9 / 21.0; 2048, 32 29.6 / 30.3; 4000, 1 / 4 / 8 37.7 / 34.3, 46.3 /
+    // 45.9, 59.1 / 60.4.  A point redone in FP64 is such a call of one point; without the rule its masked
+    // stream cost a ragged batch with one such point 5 ms a call (4 x 8 points, n = 200: 7.3 / 2.0).
     const bool la = c->lookahead && (fp32 || (long)n * n * B > 1L << 26);
     s.pair = ws_get(c, WS_LUP, (size_t)B * s.sPair * esz * (la ? 2 : 1));
     if (!s.inv || !s.tmp || !s.pair) return RSRR_ENOMEM;
@@ -378,10 +383,11 @@ static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B,
     s.la_b = c->la_b;
     s.la_c = c->la_c;
     s.upd = nullptr;  // set while the factorisation runs
-    // from 48 complex FP32 points on 2048 columns of an update keep off the look-ahead's CUs, of fewer points all
-    // (the panels take as long for any number of points and the update outlasts them only with many).  2048 / all, ms, 16 right-hand
-    // sides: n = 4096, 32 / 48 / 64 points 56.1 / 55.2, 73.4 / 73.9, 91.4 / 92.5; 3000, 64 / 128 48.4 / 48.3, 87.2 /
-    // 87.9; 3500, 64 67.8 / 68.3; 6000, 16 / 32 87.0 / 80.9, 137.0 / 133.2; 8192, 4 / 16 88.8 / 82.1, 171.8 / 158.1
+    // from 48 complex FP32 points on 2048 columns of an update keep off the look-ahead's CUs, of fewer points
+    // all (the panels take as long for any number of points and the update outlasts them only with many).
+    // 2048 / all, ms, 16 right-hand sides: n = 4096, 32 / 48 / 64 points 56.1 / 55.2, 73.4 / 73.9, 91.4 /
+    // 92.5; 3000, 64 / 128 48.4 / 48.3, 87.2 / 87.9; 3500, 64 67.8 / 68.3; 6000, 16 / 32 87.0 / 80.9, 137.0 /
+    // 133.2; 8192, 4 / 16 88.8 / 82.1, 171.8 / 158.1
     s.la_cols = c->la_cols >= 0 ? c->la_cols : (prec == RSRR_PREC_C64_IR && B >= 48 ? 2048 : 0);
     s.sT = (long)s.ld * n;
     s.sP = n;
@@ -609,10 +615,7 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
         {
             PhaseTimer t(c, &tm[2]);
             RSRR_HIP(bcast_c128(c->stream, n, L, U, ldu, S, lds, sX, B));
-            // the factorisation takes L11^-1 (multipliers of at most one) for its U rows; the solves,
-            // which nothing refines here, substitute: U11 may be as ill-conditioned as T
-            LUWork w = s.lu(s.active, nullptr);
-            w.inv = w.tmp = nullptr;
+            const LUWork w = s.lu(s.active, nullptr);
             st = split_groups(c, B, [&](hipStream_t sm, int b0, int nbg, hipEvent_t) -> rsrr_status {
                 RSRR_HIP(getrs_batched<double>(sm, (const double2*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb,
                                                lu_offset(w, b0), S + b0 * sX, sX, lds, L, nbg));

@@ -91,7 +91,8 @@ struct UpdateRecorder {
 //  info  : 1 int, zero on entry            (getrf semantics; < 0: NaN/Inf pivot)
 //  inv   : FP32 paths, and FP64 when given together with tmp (the diagonal blocks are
 //          then solved by products with their inverses, as in FP32):
-//          panels*2*nb*nb elements (stride sInv), L11^-1, U11^-1
+//          panels*2*nb*nb elements (stride sInv), L11^-1, U11^-1 (solve_inv false, FP64: L11^-1 alone, for
+//          the factorisation's U rows; the solves substitute)
 //  tmp   : with inv: nb*max(n, nrhs) elements (stride sTmp)
 //  active: optional per-matrix mask; rec: optional trailing-update event recorder
 //  pair  : FP32 paths, optional: (ldpair*2*nb + nb*nb) elements per matrix (stride sPair,
@@ -101,6 +102,7 @@ struct LUWork {
     int2* perm = nullptr; long sPerm = 0;
     int* info = nullptr;
     void* inv = nullptr; long sInv = 0;
+    bool solve_inv = true;
     void* tmp = nullptr; long sTmp = 0;
     const int* active = nullptr;
     UpdateRecorder* rec = nullptr;

@@ -892,7 +892,7 @@ struct Tile16 {
     }
 };
 
-// Inverses of the two triangles of the jb x jb diagonal block at (c0, c0): L11^-1 (unit lower, which =
+// Inverses of the two triangles of the jb x jb diagonal block at (c0, c0), or (upper false) of L alone: L11^-1 (unit lower, which =
 // 0) at inv + (2p) nb^2 and U11^-1 (upper, which = 1) at inv + (2p+1) nb^2, ld nb, the other triangle
 // zero.  One workgroup per triangle and matrix, the triangle in LDS and inverted in place by 16 x 16
 // blocks: the diagonal ones by a lane per column (substitution in registers), then the block rows in
@@ -990,9 +990,9 @@ __global__ __launch_bounds__(TI_NT) void tri_inv_kernel(const C* __restrict__ LU
 
 template <typename C>
 static void tri_inv(hipStream_t st, const C* LU, long sLU, int ldl, int c0, int jb, C* inv, long sInv, int nb,
-                    const int* active, int batch)
+                    const int* active, int batch, bool upper)
 {
-    hipLaunchKernelGGL(tri_inv_kernel<C>, dim3(batch, 2), dim3(TI_NT), 0, st, LU, sLU, ldl, c0, jb, inv, sInv, nb,
+    hipLaunchKernelGGL(tri_inv_kernel<C>, dim3(batch, upper ? 2 : 1), dim3(TI_NT), 0, st, LU, sLU, ldl, c0, jb, inv, sInv, nb,
                        active);
 }
 
@@ -1081,7 +1081,8 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         factor_panel<C>(s, A, sA, lda, n, c0, jb, w.ipiv, w.sP, w.info, pm, w.sPerm, w.active, batch);
         hipLaunchKernelGGL(perm_build_kernel, dim3(batch), dim3(64), 0, s, w.ipiv, w.sP, c0, jb, pm, w.sPerm,
                            w.active);
-        if (use_inv) tri_inv<C>(s, A, sA, lda, c0, jb, (C*)w.inv, w.sInv, nb, w.active, batch);
+        if (use_inv)
+            tri_inv<C>(s, A, sA, lda, c0, jb, (C*)w.inv, w.sInv, nb, w.active, batch, sizeof(R) == 4 || w.solve_inv);
         return pm;
     };
     // Two panels may share one trailing update of depth jb0 + jb1 (the deeper
@@ -1247,7 +1248,7 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
                          const LUWork& w, C* X, long sX, int ldx, int nrhs, int batch)
 {
     typedef real_t<C> R;
-    const bool use_inv = sizeof(R) == 4 || (w.inv != nullptr && w.tmp != nullptr);
+    const bool use_inv = sizeof(R) == 4 || (w.inv != nullptr && w.tmp != nullptr && w.solve_inv);
     if (nb > max_panel<R>()) nb = max_panel<R>();
     if (nb < MIN_NB) nb = MIN_NB;
     const int np = (n + nb - 1) / nb;
