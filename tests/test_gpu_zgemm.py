@@ -70,3 +70,16 @@ def test_operand_aligned_to_8_bytes(ctx):
                                 C.byref(J), terms)
     assert code == R.RSRR_OK
     _check(nep, Q, AQ)
+
+
+@pytest.mark.parametrize("n,k", [(383, 383), (384, 384), (384, 377), (383, 321)])
+def test_tiles_of_128_rows(ctx, n, k):
+    """Both products on 128 x 64 tiles: at least 512 of them over the matrices, and no more rows padded than
+    with 64 x 64 (plain product n x k, Hermitian product k x k)."""
+    J = 32
+    for rows in (n, k):
+        t128, t64 = -(-rows // 128), -(-rows // 64)
+        assert t128 * -(-k // 64) * J >= 512 and 2 * t128 * 20 <= t64 * 21
+    nep, Q = _problem(n, k, J)
+    AQ, _ = R.rsrr_project(ctx, R.DeviceNEP(nep), R.colmajor(Q)[0], k, 0j, 1.0)
+    _check(nep, Q, AQ)
