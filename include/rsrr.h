@@ -407,7 +407,8 @@ enum {
  * for a size bucket times one bucket pass for every candidate configuration
  * (LU panel width 32/64/128 x workgroup tile of the complex FP32 trailing
  * update: 3M 128x64, 3M 64x64, 4M 128x128, 4M 64x64, all four waves and two
- * LDS stages; FP64: panel width 32/64) and keeps the fastest per (bucket,
+ * LDS stages; from 384 rows on panels of 64 and 128 have their updates on the FP16
+ * matrix cores, which use no such tile, and are timed once; FP64: panel width 32/64) and keeps the fastest per (bucket,
  * precision, device architecture); when the environment variable
  * RSRR_TUNE_FILE names a file the choices are read from and written to it as
  * JSON ({"arch": ..., "entries": [{"P", "prec", "nb", "update_tile",

@@ -653,7 +653,10 @@ rsrr_status batched_impl(rsrr_ctx* c, int count, const rsrr_instance* inst, int 
             RSRR_HIP(hipEventCreate(&e1));
             for (int cb : nbs) {
                 if (cb > nbmax) continue;
+                // with split operands the updates do not use the tile: the default one alone
+                const bool split = mixed && b.pack && split_ok(P - 2 * cb, P - 2 * cb, 2 * cb);
                 for (int ct : tiles) {
+                    if (split && ct != UPD_TILE_3M_128x64) continue;
                     // one full bucket pass (assembly, LU, one solve, one residual) per candidate
                     TileScope ts(ct);
                     RSRR_HIP(hipEventRecord(e0, sm));

@@ -145,3 +145,18 @@ def test_batched_every_panel_width(R, tmp_path, monkeypatch, nb, tile):
     assert code == R.RSRR_OK
     _check(R, items, hosts, infos)
     ctx.close()
+
+
+def test_batched_autotune_times_no_unused_tile(R, tmp_path, monkeypatch):
+    """From 384 rows on the updates of panels of 64 and 128 columns are split products, which use no tile: the
+    tuner keeps the default one instead of the winner of equal candidates."""
+    import json
+    f = tmp_path / "tune.json"
+    monkeypatch.setenv("RSRR_TUNE_FILE", str(f))
+    ctx = R.rsrr_create(0)
+    items, _ = _items(R, [384, 448, 512, 576, 640, 704], N=3, L=2, seed=5100)
+    R.rsrr_sample_batched(ctx, items, prec=1, flags=R.RSRR_BATCH_AUTOTUNE)
+    ctx.close()
+    entries = json.loads(f.read_text())["entries"]
+    assert len(entries) == 6
+    assert all(e["nb"] < 64 or e["update_tile"] == 0 for e in entries)
