@@ -46,9 +46,17 @@ template <typename C> long split_operand_bytes(int rows, int K);
 template <typename C> size_t split_pack_bytes(int n, int K);
 // Both take the exponents of the inner index that split_inner forms from A (K per matrix, stride sE; of a
 // slab: those of its first column on): column k of A is multiplied by 2^E[k], row k of B by 2^-E[k].
-constexpr size_t SPLIT_INNER_BYTES = 1024;   // exponents of the deepest product
 template <typename C>
 hipError_t split_inner(hipStream_t st, int M, int K, const C* A, int lda, long sA, int* E, long sE, int batch);
+// of the left factor W (M x 2 nb) of a pair of panels, whose second half is copied from A
+template <typename C>
+hipError_t split_inner_pair(hipStream_t st, int M, int nb, const C* A, int lda, long sA, C* W, int ldw, long sW, int* E,
+                            long sE, const int* active, int batch);
+// of every product of a solve with n x n factors: 2 n exponents, forward sweep, then backward
+hipError_t split_inner_solve(hipStream_t st, int n, int nb, const float2* LU, int ld, long sLU, int* E, long sE,
+                             int batch);
+// bytes in front of the operands in the pack buffer of n x n matrices (n >= 128)
+inline size_t split_inner_bytes(int n) { return (size_t)round_up_l(2L * n * (long)sizeof(int), 128); }
 template <typename C>
 hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, const int* E, long sE, void* P,
                         long sP, int batch, int Ktot = 0, int kstep = 0);

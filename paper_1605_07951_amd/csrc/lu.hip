@@ -1036,10 +1036,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     auto ok = [&](hipError_t e) { if (err == hipSuccess) err = e; };
     // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `s`, event-timed.  An
     // update done in column parts gives its whole width (Nall) and the part's first column
-    // (j0); with split operands the first part (j0 = 0) packs them for all parts (the inner
-    // exponents and B unless the U rows came packed).
+    // (j0); with split operands the first part (j0 = 0) packs them for all parts.  ready: 1 the inner
+    // exponents are formed, 2 B is packed as well.
     auto timed_update = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
-                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0, bool bpacked = false) {
+                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0, int ready = 0) {
         const bool timed = rec && rec->used < rec->cap;
         if (timed) (void)hipEventRecord(rec->ev[2 * rec->used], s);
         if (Nall == 0) Nall = N;
@@ -1050,13 +1050,11 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             if (split) {
                 int* E = (int*)w.pack;
                 const long sE = w.sPack / 4;
-                char* PA = (char*)w.pack + SPLIT_INNER_BYTES;
+                char* PA = (char*)w.pack + split_inner_bytes(n);
                 char* PB = PA + split_operand_bytes<C>(M, kdepth);
                 if (j0 == 0) {
-                    if (!bpacked) {
-                        ok(split_inner(s, M, kdepth, Aop, ldaop, sAop, E, sE, batch));
-                        ok(split_pack_b(s, Nall, kdepth, Bop, lda, sA, E, sE, PB, w.sPack, batch));
-                    }
+                    if (ready == 0) ok(split_inner(s, M, kdepth, Aop, ldaop, sAop, E, sE, batch));
+                    if (ready < 2) ok(split_pack_b(s, Nall, kdepth, Bop, lda, sA, E, sE, PB, w.sPack, batch));
                     ok(split_pack_a(s, M, kdepth, Aop, ldaop, sAop, E, sE, PA, w.sPack, batch));
                 }
                 ok(gemm_split(s, M, N, kdepth, PA, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch));
@@ -1094,22 +1092,20 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     // [U12_p; U12_{p+1}] in one product.
     const bool pairing = use_inv && w.pair != nullptr;
     // The U rows of the pair (q0, q1 = q0 + nb) of full panels p, p + 1 on the columns from q2 on,
-    // with the rows' interchanges, by the split kernels: true when done (and the update's inner exponents
-    // formed and its B packed).  Wp: the pair's buffer, with both panels' L21.
-    auto split_pair_rows = [&](hipStream_t s, int q0, int p0, const C* Wp, C* TL) -> bool {
+    // with the rows' interchanges, by the split kernels: true when done (and the update's B packed).  The
+    // update's inner exponents are formed.
+    auto split_pair_rows = [&](hipStream_t s, int q0, int p0, C* TL) -> bool {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const int q2 = q0 + 2 * nb, rest = n - q2;
             C* Ar = A + (long)q2 * lda;
-            if (!w.pack || !split_ok(rest, rest, 2 * nb) || !split_urows_ok(nb, Ar + q0, lda, sA)) return false;
+            if (!split_urows_ok(nb, Ar + q0, lda, sA)) return false;
             const int2* pm0 = w.perm + (long)p0 * 2 * MAX_NB;
             perm_rows<C>(s, pm0, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0, nb, rest, w.active, batch);
             perm_rows<C>(s, pm0 + 2 * MAX_NB, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0 + nb, nb, rest, w.active,
                          batch);
-            int* E = (int*)w.pack;
-            ok(split_inner(s, rest, 2 * nb, Wp + q2, w.ldpair, w.sPair, E, w.sPack / 4, batch));
             ok(split_urows(s, rest, rest, panel_inv<C>(w, p0, nb, 0), nb, w.sInv, TL, nb, w.sPair,
-                           panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, E, w.sPack / 4,
-                           (char*)w.pack + SPLIT_INNER_BYTES, w.sPack, batch));
+                           panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, (const int*)w.pack,
+                           w.sPack / 4, (char*)w.pack + split_inner_bytes(n), w.sPack, batch));
             return true;
         }
         return false;
@@ -1133,11 +1129,21 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         copy_rows<C>(s, q1, n, nb, A + (long)q0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
         perm_rows<C>(s, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, q1, nb, nb, w.active, batch);
     };
-    auto back = [&](int q0, int pp, C* Wp) -> bool {
+    // Returns timed_update's `ready`.
+    auto back = [&](int q0, int pp, C* Wp) -> int {
         const int q1 = q0 + nb, q2 = q1 + nb, rest = n - q2;
         C* TL = Wp + (long)ldw * 2 * nb;
-        copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active, batch);
-        if (split_pair_rows(st, q0, pp, Wp, TL)) return true;
+        bool inner = false;
+        if constexpr (sizeof(R) == 4) {
+            inner = w.pack && split_ok(rest, rest, 2 * nb);
+            if (inner) {
+                ok(split_inner_pair(st, rest, nb, A + q2 + (long)q1 * lda, lda, sA, Wp + q2, ldw, w.sPair, (int*)w.pack,
+                                    w.sPack / 4, w.active, batch));
+                if (split_pair_rows(st, q0, pp, TL)) return 2;
+            }
+        }
+        if (!inner)
+            copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active, batch);
         const int2* pm0 = w.perm + (long)pp * 2 * MAX_NB;
         const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
         C* Ar2 = A + (long)q2 * lda;
@@ -1148,7 +1154,7 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         ok(gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch));
         ok(gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
                        w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0));
-        return false;
+        return inner ? 1 : 0;
     };
     int c0 = 0, p = 0;
     // Look-ahead over full pairs (two nb-wide panels with a trailing block after
@@ -1163,19 +1169,19 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if (w.first_panel) ok(hipEventRecord(w.first_panel, st));
         for (;;) {
             const int c2 = c0 + 2 * nb, rest = n - c2;
-            const bool bpacked = back(c0, p, Wb[buf]);
+            const int ready = back(c0, p, Wb[buf]);
             C* Aop = Wb[buf] + c2;
             const C* Bop = A + c0 + (long)c2 * lda;
             C* Cop = A + c2 + (long)c2 * lda;
             if (rest <= 2 * nb) {
                 // no full pair follows: one update, the loop below finishes the tail
-                timed_update(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
+                timed_update(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, ready);
                 c0 = c2;
                 p += 2;
                 break;
             }
             const int wn = 2 * nb;
-            timed_update(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
+            timed_update(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, ready);
             ok(hipEventRecord(w.ev_a, st));
             // the rest of the update is enqueued before the next pair's panels (a chain of
             // small launches), so the host never holds it back behind them
@@ -1210,9 +1216,9 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         C* Wp = (C*)w.pair;
         front(st, c0, p, Wp);
         if (c0 == 0 && w.first_panel) ok(hipEventRecord(w.first_panel, st));
-        const bool bpacked = back(c0, p, Wp);
+        const int ready = back(c0, p, Wp);
         timed_update(st, rest, rest, 2 * nb, Wp + c2, ldw, w.sPair, A + c0 + (long)c2 * lda, A + c2 + (long)c2 * lda,
-                        rest, 0, bpacked);
+                        rest, 0, ready);
     }
     for (; c0 < n; c0 += nb, ++p) {
         const int jb = std::min(nb, n - c0), c1 = c0 + jb, rest = n - c1;
@@ -1254,17 +1260,20 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
     const int np = (n + nb - 1) / nb;
     hipError_t err = hipSuccess;   // the first one
     auto ok = [&](hipError_t e) { if (err == hipSuccess) err = e; };
-    // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0
+    // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0; the inner exponents of all split
+    // products are formed before the first
+    bool inner = false;
     auto off_diag = [&](int r0, int m, int K, const C* F, int c0) {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const long na = split_operand_bytes<C>(m, K);
             if (w.pack && !w.any_mix && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
-                (long)SPLIT_INNER_BYTES + na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
-                int* E = (int*)w.pack;
+                (long)split_inner_bytes(n) + na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
                 const long sE = w.sPack / 4;
-                char* PA = (char*)w.pack + SPLIT_INNER_BYTES;
+                if (!inner) ok(split_inner_solve(st, n, nb, LU, lda, sLU, (int*)w.pack, sE, batch));
+                inner = true;
+                const int* E = (const int*)w.pack + (r0 > c0 ? 0 : n) + c0;
+                char* PA = (char*)w.pack + split_inner_bytes(n);
                 char* PB = PA + na;
-                ok(split_inner(st, m, K, F, lda, sLU, E, sE, batch));
                 ok(split_pack_a(st, m, K, F, lda, sLU, E, sE, PA, w.sPack, batch));
                 ok(split_pack_b(st, nrhs, K, X + c0, ldx, sX, E, sE, PB, w.sPack, batch));
                 ok(gemm_split(st, m, nrhs, K, PA, w.sPack, PB, w.sPack, nrhs, 0, true, X + r0, ldx, sX, batch));

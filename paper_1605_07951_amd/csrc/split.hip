@@ -30,10 +30,10 @@
 // Bound by the matrix cores and by C, which is read and written once per update.  64
 // matrices, K = 256, n = 3840 / 2048 / 1024: 6.0-6.5 / 1.7 / 0.44 ms, 297-325 / 318-335 / 318 TFLOP/s in
 // the standard count of 8 flops per complex multiply-add (up to 975 TFLOP/s in FP16, C at 2.6
-// TB/s); the inner exponents 0.09 / 0.06 / 0.03 ms, packing 0.41 / 0.22 / 0.11; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
+// TB/s); the inner exponents 0.09 / 0.06 / 0.03 ms, packing 0.36 / 0.20 / 0.11; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
 //
-// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.54 / 0.17 / 0.045 / 0.018 ms and 0.20 / 0.11 /
-// 0.06 / 0.044 ms for the exponents and the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045.
+// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.54 / 0.17 / 0.045 / 0.018 ms and 0.16 / 0.09 /
+// 0.055 / 0.04 ms for the exponents and the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045.
 //
 // The complex product is the 4M form with the interleaved parts as the inner index
 // (k' = 2k + part): Re C takes A' (Br, -Bi), Im C takes A' (Bi, Br), which is one sign
@@ -100,32 +100,40 @@ RSRR_DEV float2 sp_entry(const float* src, int k, long ld, int K)
 {
     return make_float2(2 * k < K ? src[2 * k * ld] : 0.f, 2 * k + 1 < K ? src[(2 * k + 1) * ld] : 0.f);
 }
-// the inner index's exponents of that entry's parts, times sign
+// the inner index's exponents (LDS, 16-byte aligned) of the parts of entries 4 p .. 4 p + 3
 template <typename C>
-RSRR_DEV int2 sp_inner(const int* E, int k, int K, int sign)
+RSRR_DEV void sp_inner(const int* inner, int p, int2 (&k)[4])
 {
+    const int4* e = reinterpret_cast<const int4*>(inner) + (sizeof(C) == sizeof(float2) ? p : 2 * p);
+    const int4 x = e[0];
     if (sizeof(C) == sizeof(float2)) {
-        const int e = k < K ? sign * E[k] : 0;
-        return make_int2(e, e);
+        k[0] = make_int2(x.x, x.x);
+        k[1] = make_int2(x.y, x.y);
+        k[2] = make_int2(x.z, x.z);
+        k[3] = make_int2(x.w, x.w);
+    } else {
+        const int4 y = e[1];
+        k[0] = make_int2(x.x, x.y);
+        k[1] = make_int2(x.z, x.w);
+        k[2] = make_int2(y.x, y.y);
+        k[3] = make_int2(y.z, y.w);
     }
-    return make_int2(2 * k < K ? sign * E[2 * k] : 0, 2 * k + 1 < K ? sign * E[2 * k + 1] : 0);
 }
 
-// Exponents of the inner index: E[k] scales column k of A (M x K) to a largest part in [1/2, 1); zero or
-// non-finite columns: 0.  One workgroup per column and matrix, bound by reading A once (64 matrices, K = 256,
-// n = 3840: 88 us, 5.7 TB/s).
+// The exponent that scales M entries to a largest part in [1/2, 1) (none or non-finite: 0) into *E; one
+// workgroup.  D given: the entries are copied there.
 template <typename C>
-__global__ __launch_bounds__(256) void split_inner_kernel(int M, const C* __restrict__ A, int lda, long sA,
-                                                          int* __restrict__ E, long sE)
+RSRR_DEV void inner_expo(int M, const C* __restrict__ col, C* __restrict__ D, int* __restrict__ E)
 {
-    const int k = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
-    const C* col = A + b * sA + (long)k * lda;
+    const int t = threadIdx.x;
     __shared__ float tops[4];
     float top = 0.f;
 #pragma unroll 4
     for (int i = t; i < M; i += 256) {
-        if constexpr (elem_traits<C>::complex) top = fmaxf(top, fmaxf(fabsf(col[i].x), fabsf(col[i].y)));
-        else top = fmaxf(top, fabsf(col[i]));
+        const C v = col[i];
+        if (D) D[i] = v;
+        if constexpr (elem_traits<C>::complex) top = fmaxf(top, fmaxf(fabsf(v.x), fabsf(v.y)));
+        else top = fmaxf(top, fabsf(v));
     }
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
@@ -133,7 +141,52 @@ __global__ __launch_bounds__(256) void split_inner_kernel(int M, const C* __rest
     __syncthreads();
     if (t == 0) {
         top = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
-        E[b * sE + k] = (top > 0.f && isfinite(top)) ? -__builtin_amdgcn_frexp_expf(top) : 0;
+        *E = (top > 0.f && isfinite(top)) ? -__builtin_amdgcn_frexp_expf(top) : 0;
+    }
+}
+
+// Exponents of the inner index: E[k] of column k of A (M x K).  One workgroup per column and matrix, bound by reading A once (64
+// matrices, K = 256, n = 3840: 88 us, 5.7 TB/s).
+template <typename C>
+__global__ __launch_bounds__(256) void split_inner_kernel(int M, const C* __restrict__ A, int lda, long sA,
+                                                          int* __restrict__ E, long sE)
+{
+    const int k = blockIdx.x, b = blockIdx.y;
+    inner_expo<C>(M, A + b * sA + (long)k * lda, nullptr, E + b * sE + k);
+}
+
+// The same for a pair of panels of nb columns: W (M x 2 nb), whose first half is there and whose second half
+// is copied from A on the way (the copy and the exponents in two launches: headline +0.7 ms).
+template <typename C>
+__global__ __launch_bounds__(256) void split_inner_pair_kernel(int M, int nb, const C* __restrict__ A, int lda, long sA,
+                                                               C* __restrict__ W, int ldw, long sW,
+                                                               int* __restrict__ E, long sE,
+                                                               const int* __restrict__ active)
+{
+    const int k = blockIdx.x, b = blockIdx.y;
+    if (active && !active[b]) return;
+    C* w = W + b * sW + (long)k * ldw;
+    if (k < nb) inner_expo<C>(M, w, nullptr, E + b * sE + k);
+    else inner_expo<C>(M, A + b * sA + (long)(k - nb) * lda, w, E + b * sE + k);
+}
+
+// The inner exponents of all products of a solve with the n x n factors LU in panels of nb columns, one
+// workgroup per column and sweep: E[k] of the rows below column k's panel (forward), E[n + k] of the rows
+// above the pair of panels that is taken together in the backward sweep (pairs from the last panel on; of
+// the first pair the rows above the panel, which are those of the pair's own coupling).  One launch before
+// the sweeps; one before each of the 43 products of an inverse of 2730 rows: +0.2 ms.
+__global__ __launch_bounds__(256) void split_inner_solve_kernel(int n, int nb, const float2* __restrict__ LU, int ld,
+                                                                long sLU, int* __restrict__ E, long sE)
+{
+    const int k = blockIdx.x, b = blockIdx.z, p = k / nb;
+    const float2* col = LU + b * sLU + (long)k * ld;
+    int* e = E + b * sE + blockIdx.y * n + k;
+    if (blockIdx.y == 0) {
+        const int below = min(n, (p + 1) * nb);
+        inner_expo<float2>(n - below, col + below, nullptr, e);
+    } else {
+        const int last = (n + nb - 1) / nb - 1, first = p - ((last - p) & 1 ? 0 : 1);   // first panel of p's pair
+        inner_expo<float2>((first > 0 ? first : p) * nb, col, nullptr, e);
     }
 }
 
@@ -151,20 +204,26 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
     const int nkc = sp_chunks<C>(K), Kb = min(K, Ktot - b * kstep);
     const int r = t & 31, part = t >> 5, i = rb * 32 + r;
     __shared__ int tops[8][32];
+    __shared__ __attribute__((aligned(16))) int inner[SP_KMAX];
+    const int ei = t < Kb ? E[b * sE + t] : 0;
     const C* src = A + b * sA + i;
     constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
     float2 v[Q][4];
-    int2 ek[Q][4];
-    int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = 4 * (part + 8 * q) + u;
-            v[q][u] = i < M ? sp_entry(src, k, lda, Kb) : make_float2(0.f, 0.f);
-            ek[q][u] = sp_inner<C>(E + b * sE, k, Kb, 1);
-            top = max(top, part_expo(v[q][u], ek[q][u]));
-        }
+        for (int u = 0; u < 4; ++u)
+            v[q][u] = i < M ? sp_entry(src, 4 * (part + 8 * q) + u, lda, Kb) : make_float2(0.f, 0.f);
+    inner[t] = ei;
+    __syncthreads();
+    int top = SP_NONE;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        int2 ek[4];
+        sp_inner<C>(inner, part + 8 * q, ek);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], ek[u]));
+    }
     tops[part][r] = top;
     __syncthreads();
 #pragma unroll
@@ -177,7 +236,9 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
         const int p = part + 8 * q, kc = p >> 1;
         if (kc >= nkc) break;
         uintx4 hi, lo;
-        split4(v[q], e, ek[q], &hi, &lo);
+        int2 ek[4];
+        sp_inner<C>(inner, p, ek);
+        split4(v[q], e, ek, &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)rb * nkc + kc) * 2 * SP_FRAG);
         dst[r + 32 * (p & 1)] = hi;
         dst[64 + r + 32 * (p & 1)] = lo;
@@ -198,18 +259,24 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Kto
     const int j = blockIdx.x * 32 + c;
     const C* src = B + b * sB + (long)j * ldb;
     constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
+    __shared__ __attribute__((aligned(16))) int inner[SP_KMAX];
+    const int ei = t < Kb ? -E[b * sE + t] : 0;
     float2 v[Q][4];
-    int2 ek[Q][4];
-    int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = 4 * (part + 8 * q) + u;
-            v[q][u] = j < N ? sp_entry(src, k, 1, Kb) : make_float2(0.f, 0.f);
-            ek[q][u] = sp_inner<C>(E + b * sE, k, Kb, -1);
-            top = max(top, part_expo(v[q][u], ek[q][u]));
-        }
+        for (int u = 0; u < 4; ++u)
+            v[q][u] = j < N ? sp_entry(src, 4 * (part + 8 * q) + u, 1, Kb) : make_float2(0.f, 0.f);
+    inner[t] = ei;
+    __syncthreads();
+    int top = SP_NONE;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        int2 ek[4];
+        sp_inner<C>(inner, part + 8 * q, ek);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], ek[u]));
+    }
 #pragma unroll
     for (int off = 1; off < 8; off <<= 1) top = max(top, __shfl_xor(top, off));
     const int e = split_expo(top);
@@ -220,7 +287,9 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Kto
         const int p = part + 8 * q, kc = p >> 1;
         if (kc >= nkc) break;
         uintx4 hi, lo;
-        split4(v[q], e, ek[q], &hi, &lo);
+        int2 ek[4];
+        sp_inner<C>(inner, p, ek);
+        split4(v[q], e, ek, &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)blockIdx.x * nkc + kc) * 2 * SP_FRAG);
         dst[c + 32 * (p & 1)] = hi;
         dst[64 + c + 32 * (p & 1)] = lo;
@@ -252,19 +321,23 @@ __global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, const
     const int r = t & 31, part = t >> 5;
     __shared__ int tops[8][32];
     const float2* src = F.p[f] + b * F.stride[f] + rb * 32 + r;
-    const int* Ef = E + b * sE + (f == 2 ? UR_NB : 0);
+    __shared__ __attribute__((aligned(16))) int inner[UR_NB];
+    const int ei = t < UR_NB ? E[b * sE + (f == 2 ? UR_NB : 0) + t] : 0;
     float2 v[4][4];
-    int2 ek[4][4];
-    int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int k = 16 * part + 4 * q + u;
-            v[q][u] = src[(long)k * F.ld[f]];
-            ek[q][u] = sp_inner<float2>(Ef, k, UR_NB, 1);
-            top = max(top, part_expo(v[q][u], ek[q][u]));
-        }
+        for (int u = 0; u < 4; ++u) v[q][u] = src[(long)(16 * part + 4 * q + u) * F.ld[f]];
+    if (t < UR_NB) inner[t] = ei;
+    __syncthreads();
+    int top = SP_NONE;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        int2 ek[4];
+        sp_inner<float2>(inner, 4 * part + q, ek);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], ek[u]));
+    }
     tops[part][r] = top;
     __syncthreads();
 #pragma unroll
@@ -275,7 +348,9 @@ __global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, const
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         uintx4 hi, lo;
-        split4(v[q], e, ek[q], &hi, &lo);
+        int2 ek[4];
+        sp_inner<float2>(inner, 4 * part + q, ek);
+        split4(v[q], e, ek, &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + f * UR_OPERAND +
                                                 ((long)rb * UR_KC + 2 * part + q / 2) * 2 * SP_FRAG);
         dst[r + 32 * (q & 1)] = hi;
@@ -319,20 +394,13 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
             p[1] = floatx4{v[q][2].x, v[q][2].y, v[q][3].x, v[q][3].y};
         }
     };
-    // inner exponents of the four-row group q of panel w's rows
-    auto inner_of = [&](int w, int q, int2 (&k)[4]) {
-        const int4 e = *reinterpret_cast<const int4*>(inner + w * UR_NB + 4 * (part + 8 * q));
-        k[0] = make_int2(e.x, e.x);
-        k[1] = make_int2(e.y, e.y);
-        k[2] = make_int2(e.z, e.z);
-        k[3] = make_int2(e.w, e.w);
-    };
+    // (w: the panel of the rows)
     auto top_of = [&](int w, const float2 (&v)[4][4]) {
         int top = SP_NONE;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             int2 k[4];
-            inner_of(w, q, k);
+            sp_inner<float2>(inner + w * UR_NB, part + 8 * q, k);
 #pragma unroll
             for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], k[u]));
         }
@@ -347,7 +415,7 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
             const int p = part + 8 * q;
             uintx4 hi, lo;
             int2 k[4];
-            inner_of(w, q, k);
+            sp_inner<float2>(inner + w * UR_NB, p, k);
             split4(v[q], e, k, &hi, &lo);
             uintx4* d = reinterpret_cast<uintx4*>(dst + (long)(p >> 1) * 2 * SP_FRAG);
             d[c + 32 * (p & 1)] = hi;
@@ -583,13 +651,12 @@ long split_operand_bytes(int rows, int K)
     return sp_frag_bytes<C>(rows, K) + (long)(rows + 31) / 32 * 32 * 4;
 }
 
-// Layout of the LU's pack buffer: the inner exponents (SPLIT_INNER_BYTES), A, B, then (complex) the three left
-// factors of the U rows with their row exponents (the offsets follow from the sizes of the product).
-static_assert(SPLIT_INNER_BYTES == SP_KMAX * sizeof(int), "an exponent per inner index");
+// Layout of the LU's pack buffer: the inner exponents (of an update, or of the solves), A, B, then (complex) the
+// three left factors of the U rows with their row exponents (the offsets follow from the sizes of the product).
 template <typename C>
 size_t split_pack_bytes(int n, int K)
 {
-    return SPLIT_INNER_BYTES + 2 * split_operand_bytes<C>(n, K) +
+    return split_inner_bytes(n) + 2 * split_operand_bytes<C>(n, K) +
            (elem_traits<C>::complex ? 3 * UR_OPERAND + 3 * UR_NB * 4 : 0);
 }
 
@@ -601,6 +668,22 @@ template <typename C>
 hipError_t split_inner(hipStream_t st, int M, int K, const C* A, int lda, long sA, int* E, long sE, int batch)
 {
     hipLaunchKernelGGL(split_inner_kernel<C>, dim3(K, batch), dim3(256), 0, st, M, A, lda, sA, E, sE);
+    return hipGetLastError();
+}
+
+template <typename C>
+hipError_t split_inner_pair(hipStream_t st, int M, int nb, const C* A, int lda, long sA, C* W, int ldw, long sW, int* E,
+                            long sE, const int* active, int batch)
+{
+    hipLaunchKernelGGL(split_inner_pair_kernel<C>, dim3(2 * nb, batch), dim3(256), 0, st, M, nb, A, lda, sA, W, ldw, sW,
+                       E, sE, active);
+    return hipGetLastError();
+}
+
+hipError_t split_inner_solve(hipStream_t st, int n, int nb, const float2* LU, int ld, long sLU, int* E, long sE,
+                             int batch)
+{
+    hipLaunchKernelGGL(split_inner_solve_kernel, dim3(n, 2, batch), dim3(256), 0, st, n, nb, LU, ld, sLU, E, sE);
     return hipGetLastError();
 }
 
@@ -665,6 +748,8 @@ hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long 
     template long split_operand_bytes<C>(int, int);                                                                 \
     template size_t split_pack_bytes<C>(int, int);                                                                  \
     template hipError_t split_inner<C>(hipStream_t, int, int, const C*, int, long, int*, long, int);                \
+    template hipError_t split_inner_pair<C>(hipStream_t, int, int, const C*, int, long, C*, int, long, int*, long,  \
+                                            const int*, int);                                                       \
     template hipError_t split_pack_a<C>(hipStream_t, int, int, const C*, int, long, const int*, long, void*, long,  \
                                         int, int, int);                                                             \
     template hipError_t split_pack_b<C>(hipStream_t, int, int, const C*, int, long, const int*, long, void*, long,  \
