@@ -303,6 +303,12 @@ rsrr_status run_bucket(rsrr_ctx* c, hipStream_t sm, const rsrr_instance* inst, c
     w.pair = b.pair; w.sPair = b.sPair; w.ldpair = P;
     w.pack = b.pack; w.sPack = b.sPack;
     w.any_mix = true;
+    // rows of one size for the split products, kept with the factors; the padding rows stay out of it
+    if (mixed && nb >= 64 && lu_pack_bytes<float2>(P) > 0) {
+        w.rs = row_scale_of(b.perm, b.sPerm, P); w.sRs = 2 * b.sPerm;
+        w.frob = b.frob;
+        w.rows = b.nk;
+    }
     if (!from) {
         if (mixed) RSRR_HIP(getrf_batched<float>(sm, (float2*)b.T, b.sT, P, P, nb, w, (int)M));
         else RSRR_HIP(getrf_batched<double>(sm, (double2*)b.T, b.sT, P, P, nb, w, (int)M));
@@ -311,7 +317,7 @@ rsrr_status run_bucket(rsrr_ctx* c, hipStream_t sm, const rsrr_instance* inst, c
     w.active = b.active;
     // first solve
     if (mixed) {
-        RSRR_HIP(scale_narrow(sm, P, Lmax, b.Ub, P, b.sU, b.ones, b.D64, P, b.sU, nullptr, (int)M));
+        RSRR_HIP(scale_narrow(sm, P, Lmax, b.Ub, P, b.sU, b.ones, b.D64, P, b.sU, nullptr, (int)M, w.rs, w.sRs));
         RSRR_HIP(getrs_batched<float>(sm, (const float2*)b.T, b.sT, P, P, nb, w, b.D64, b.sU, P, Lmax, (int)M));
         RSRR_HIP(widen(sm, P, Lmax, b.D64, P, b.sU, b.Xb, P, b.sU, (int)M));
     } else {
@@ -335,7 +341,8 @@ rsrr_status run_bucket(rsrr_ctx* c, hipStream_t sm, const rsrr_instance* inst, c
         RSRR_HIP(ir_decide(sm, (int)M, Lmax, b.rn, b.xn, b.un, b.frob, tol_be, it, iters, b.active, b.prev, b.resid,
                            b.iters, b.inv_s, b.scl));
         if (it == iters) break;
-        RSRR_HIP(scale_narrow(sm, P, Lmax, b.R, P, b.sU, b.inv_s, b.D64, P, b.sU, b.active, (int)M));
+        RSRR_HIP(scale_narrow(sm, P, Lmax, b.R, P, b.sU, b.inv_s, b.D64, P, b.sU, b.active, (int)M, w.rs,
+                              w.sRs));
         RSRR_HIP(getrs_batched<float>(sm, (const float2*)b.T, b.sT, P, P, nb, w, b.D64, b.sU, P, Lmax, (int)M));
         RSRR_HIP(axpy_widen(sm, P, Lmax, b.D64, P, b.sU, b.scl, b.Xb, P, b.sU, b.active, (int)M));
     }

@@ -214,7 +214,7 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
     const long sPack = split_ok(n - nb, n - nb, nb) ? (long)split_pack_bytes<float2>(n, std::min(2 * nb, 256)) : 0;
     size_t fw = a256((size_t)nf * n * 4) + a256((size_t)nf * sPerm * 8) +
                 a256((size_t)nf * 4) + a256((size_t)nf * sInv * 8) + a256((size_t)nf * nb * n * 8) +
-                a256((size_t)nf * sPack) + a256((size_t)nf * Spk * Kpk * 4);
+                a256((size_t)nf * sPack);
     Carve fc{(char*)ws_get(c, WS_GMW, fw)};
     if (!Tf || !fc.base) return RSRR_ENOMEM;
     LUWork w;
@@ -224,7 +224,8 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
     w.inv = fc.take<float2>((size_t)nf * sInv); w.sInv = sInv;
     w.tmp = fc.take<float2>((size_t)nf * nb * n); w.sTmp = (long)nb * n;
     w.pack = sPack ? fc.take<char>((size_t)nf * sPack) : nullptr; w.sPack = sPack;
-    int* Epk = fc.take<int>((size_t)nf * Spk * Kpk);   // inner exponents of the inverses
+    // rows of one size for the split products (nb is 128); the basis vectors are scaled where they are narrowed
+    w.rs = sPack ? row_scale_of(w.perm, sPerm, n) : nullptr; w.sRs = 2 * sPerm;
     {
         EvPair ev;
         RSRR_HIP(hipEventRecord(ev.a, c->stream));
@@ -265,6 +266,7 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
                                         frob));
         }
         RSRR_HIP(hipMemsetAsync(w.info, 0, (size_t)nf * 4, c->stream));
+        w.frob = frob;
         RSRR_HIP(getrf_batched<float>(c->stream, Tf, sT, ld, n, nb, w, nf));
         std::vector<int> hinfo(nf);
         RSRR_HIP(hipMemcpyAsync(hinfo.data(), w.info, (size_t)nf * 4, hipMemcpyDeviceToHost, c->stream));
@@ -284,10 +286,9 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
         if (!Pinv) return RSRR_ENOMEM;
         RSRR_HIP(gm_eye_c64(c->stream, n, Pinv, ld, sT, nf));
         RSRR_HIP(getrs_batched<float>(c->stream, Tf, sT, ld, n, nb, w, Pinv, sT, ld, n, nf));
-        if (pcs) RSRR_HIP(split_inner(c->stream, n, n, Pinv, ld, sT, Epk, (long)Spk * Kpk, nf));
         for (int f = 0; pcs && f < nf; ++f)
-            RSRR_HIP(split_pack_a(c->stream, n, Kpk, Pinv + f * sT, ld, (long)Kpk * ld, Epk + (size_t)f * Spk * Kpk, Kpk,
-                                  (char*)Tf + (size_t)f * Spk * bPk, bPk, Spk, n, Kpk));
+            RSRR_HIP(split_pack_a<float2>(c->stream, n, Kpk, Pinv + f * sT, ld, (long)Kpk * ld, nullptr, 0,
+                                          (char*)Tf + (size_t)f * Spk * bPk, bPk, Spk, n, Kpk));
         RSRR_HIP(hipEventRecord(ev.b, c->stream));
         RSRR_HIP(hipEventSynchronize(ev.b));
         c->timings[0] += ev.ms();
@@ -493,7 +494,15 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
                 EvPair e1, e2;
                 // Z_j = P^-1 V_j (complex FP32 factors of the point's reference)
                 RSRR_HIP(hipEventRecord(e1.a, c->stream));
-                RSRR_HIP(gm_narrow(c->stream, n, C, Vj, ld, k.D, ld));
+                if (w.rs) {
+                    for (int r = 0; r < nrun; ++r) {
+                        const size_t o = (size_t)run0[r] * L * ld;
+                        RSRR_HIP(gm_narrow(c->stream, n, (run0[r + 1] - run0[r]) * L, Vj + o, ld, k.D + o, ld,
+                                           w.rs + runf[r] * w.sRs));
+                    }
+                } else {
+                    RSRR_HIP(gm_narrow(c->stream, n, C, Vj, ld, k.D, ld, nullptr));
+                }
                 float2* Dz = k.D;
                 bool widened = false;
                 if (pcs) {
@@ -502,8 +511,8 @@ extern "C" rsrr_status rsrr_sample_gmres(rsrr_ctx* c, const rsrr_nep* nep, int N
                         const int cols = (run0[r + 1] - run0[r]) * L;
                         const size_t o = (size_t)run0[r] * L * ld;
                         const long bB = split_operand_bytes<float2>(cols, Kpk);
-                        RSRR_HIP(split_pack_b(c->stream, cols, Kpk, k.D + o, ld, Kpk,
-                                              Epk + (size_t)runf[r] * Spk * Kpk, Kpk, PB, bB, Spk, n, Kpk));
+                        RSRR_HIP(split_pack_b<float2>(c->stream, cols, Kpk, k.D + o, ld, Kpk, nullptr, 0, PB, bB, Spk,
+                                                      n, Kpk));
                         RSRR_HIP(gemm_split(c->stream, n, cols, Kpk, (char*)Tf + (size_t)runf[r] * Spk * bPk, bPk, PB,
                                              bB, cols, 0, false, Pp + o, ld, (long)vb, Spk));
                     }

@@ -308,7 +308,7 @@ struct SampleBufs {
     int la_cols;
     void* pack;
     bool solve_inv;   // the solves multiply with the inverses of the diagonal blocks
-    int ld, np, nb; long sT, sP, sPerm, nparts, sInv, sTmp, sPair, sPack;
+    int n, ld, np, nb; long sT, sP, sPerm, nparts, sInv, sTmp, sPair, sPack;
     LUWork lu(const int* act, UpdateRecorder* rec) const
     {
         LUWork w;
@@ -319,6 +319,11 @@ struct SampleBufs {
         w.la_cols = la_cols;
         w.pack = pack; w.sPack = sPack;
         w.solve_inv = solve_inv;
+        if (pack) {
+            w.rs = row_scale_of(perm, sPerm, n);
+            w.sRs = 2 * sPerm;
+            w.frob = frob;
+        }
         return w;
     }
 };
@@ -351,6 +356,7 @@ static size_t per_point_bytes(int n, int L, int prec)
 
 static rsrr_status alloc_bufs(rsrr_ctx* c, int n, int L, int J, int prec, int B, SampleBufs& s)
 {
+    s.n = n;
     s.ld = ld_pad(n);
     s.np = perm_panels(n);
     // the real FP32 path (R32_IR) uses the complex FP32 layout with real elements (half the bytes)
@@ -492,6 +498,8 @@ static LUWork lu_offset(const LUWork& w, long b0, int esz = 8)
     if (w.pair) o.pair = (char*)w.pair + b0 * w.sPair * esz;
     if (w.pair2) o.pair2 = (char*)w.pair2 + b0 * w.sPair * esz;
     if (w.pack) o.pack = (char*)w.pack + b0 * w.sPack;
+    if (w.rs) o.rs = w.rs + b0 * w.sRs;
+    if (w.frob) o.frob = w.frob + b0;
     if (w.active) o.active = w.active + b0;
     return o;
 }
@@ -644,7 +652,8 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
         const LUWork w = s.lu(s.active, nullptr);
         if (prec == RSRR_PREC_R32_IR) {
             float* D = (float*)s.D64;
-            RSRR_HIP(scale_narrow_real(c->stream, n, L, U, ldu, 0, nullptr, D, s.ld, (long)s.ld * L, nullptr, B));
+            RSRR_HIP(scale_narrow_real(c->stream, n, L, U, ldu, 0, nullptr, D, s.ld, (long)s.ld * L, nullptr, B, w.rs,
+                                       w.sRs));
             st = split_groups(c, B, [&](hipStream_t sm, int b0, int nbg, hipEvent_t) -> rsrr_status {
                 RSRR_HIP(getrs_real_batched(sm, (const float*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb,
                                             lu_offset(w, b0, 4), D + b0 * (long)s.ld * L, (long)s.ld * L, s.ld, L,
@@ -654,7 +663,7 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
             if (st) return st;
             RSRR_HIP(axpy_widen_real(c->stream, n, L, D, s.ld, (long)s.ld * L, nullptr, S, lds, sX, nullptr, B));
         } else {
-            RSRR_HIP(bcast_to_c64(c->stream, n, L, U, ldu, s.D64, s.ld, (long)s.ld * L, B));
+            RSRR_HIP(bcast_to_c64(c->stream, n, L, U, ldu, s.D64, s.ld, (long)s.ld * L, B, w.rs, w.sRs));
             st = split_groups(c, B, [&](hipStream_t sm, int b0, int nbg, hipEvent_t) -> rsrr_status {
                 RSRR_HIP(getrs_batched<float>(sm, (const float2*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb,
                                               lu_offset(w, b0), s.D64 + b0 * (long)s.ld * L, (long)s.ld * L, s.ld,
@@ -713,7 +722,7 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
             if (prec == RSRR_PREC_R32_IR) {
                 float* D = (float*)s.D64;
                 RSRR_HIP(scale_narrow_real(c->stream, n, L, s.R, s.ld, (long)s.ld * L, sc, D, s.ld, (long)s.ld * L,
-                                           s.active, B));
+                                           s.active, B, w.rs, w.sRs));
                 st = split_groups(c, B, [&](hipStream_t sm, int b0, int nbg, hipEvent_t) -> rsrr_status {
                     RSRR_HIP(getrs_real_batched(sm, (const float*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb,
                                                 lu_offset(w, b0, 4), D + b0 * (long)s.ld * L, (long)s.ld * L, s.ld,
@@ -725,7 +734,7 @@ static rsrr_status sample_batch(rsrr_ctx* c, const rsrr_nep* nep, const zd* z, i
                 RSRR_HIP(axpy_widen_real(c->stream, n, L, D, s.ld, (long)s.ld * L, sc, S, lds, sX, s.active, B));
             } else {
                 RSRR_HIP(scale_narrow(c->stream, n, L, s.R, s.ld, (long)s.ld * L, sc, s.D64, s.ld, (long)s.ld * L,
-                                      s.active, B));
+                                      s.active, B, w.rs, w.sRs));
                 st = split_groups(c, B, [&](hipStream_t sm, int b0, int nbg, hipEvent_t) -> rsrr_status {
                     RSRR_HIP(getrs_batched<float>(sm, (const float2*)s.Tlu + b0 * s.sT, s.sT, s.ld, n, s.nb,
                                                   lu_offset(w, b0), s.D64 + b0 * (long)s.ld * L, (long)s.ld * L,

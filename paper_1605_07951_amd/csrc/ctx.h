@@ -109,7 +109,7 @@ rsrr_status noalloc_scratch_setup(int device, void** out);
 // without refactoring).  Layout in one caller-provided block, each part
 // 256-byte aligned: factors T (N matrices P x P, P = n rounded up to 64, stride
 // sT; complex FP32 or FP64 by prec), composed row interchanges perm (stride
-// sPerm) and, for complex FP32, the diagonal-block inverses inv (stride sInv),
+// sPerm; their last entries hold the rows' scales, row_scale_of) and, for complex FP32, the diagonal-block inverses inv (stride sInv),
 // with the panel width nb they were made with (set by the sampling call).
 struct FactorStore {
     void* T = nullptr;

@@ -43,12 +43,14 @@ __global__ __launch_bounds__(GM_NT) void gm_point_scale_kernel(int n, int C, int
 
 // D = (c64) V
 __global__ __launch_bounds__(GM_NT) void gm_narrow_kernel(int n, int C, const double2* __restrict__ V, int ldv,
-                                                           float2* __restrict__ D, int ldd)
+                                                           float2* __restrict__ D, int ldd, const int* __restrict__ rs)
 {
     const long e = (long)blockIdx.x * GM_NT + threadIdx.x;
     if (e >= (long)n * C) return;
     const int i = (int)(e % n), c = (int)(e / n);
-    D[i + (long)c * ldd] = to_c64(V[i + (long)c * ldv]);
+    double2 v = V[i + (long)c * ldv];
+    if (rs) v = make_double2(ldexp(v.x, -rs[i]), ldexp(v.y, -rs[i]));
+    D[i + (long)c * ldd] = to_c64(v);
 }
 
 // Z = (c128) D
@@ -410,9 +412,9 @@ hipError_t gm_point_scale(hipStream_t st, int n, int C, int L, const double2* Z,
                        ldy);
     return hipGetLastError();
 }
-hipError_t gm_narrow(hipStream_t st, int n, int C, const double2* V, int ldv, float2* D, int ldd)
+hipError_t gm_narrow(hipStream_t st, int n, int C, const double2* V, int ldv, float2* D, int ldd, const int* rs)
 {
-    hipLaunchKernelGGL(gm_narrow_kernel, flat_grid((long)n * C), dim3(GM_NT), 0, st, n, C, V, ldv, D, ldd);
+    hipLaunchKernelGGL(gm_narrow_kernel, flat_grid((long)n * C), dim3(GM_NT), 0, st, n, C, V, ldv, D, ldd, rs);
     return hipGetLastError();
 }
 hipError_t gm_widen(hipStream_t st, int n, int C, const float2* D, int ldd, double2* Z, int ldz)

@@ -10,15 +10,21 @@ namespace rsrr {
 
 constexpr int EW_NT = 256;
 
+// Right-hand sides of a factorisation with scaled rows: entry of row i times 2^-rs[i] (rs null: as it is).
+RSRR_DEV double row_scaled(double v, const int* rs, long i) { return rs ? ldexp(v, -rs[i]) : v; }
+
 // D_k = (c64) U for every point k.
 __global__ __launch_bounds__(EW_NT) void bcast_to_c64_kernel(int n, int L, const double2* __restrict__ U, int ldu,
-                                                              float2* __restrict__ D, int ldd, long sD)
+                                                              float2* __restrict__ D, int ldd, long sD,
+                                                              const int* __restrict__ rs, long sRs)
 {
     const int k = blockIdx.y;
     const int e = blockIdx.x * EW_NT + threadIdx.x;
     if (e >= n * L) return;
     const int i = e % n, c = e / n;
-    D[k * sD + i + (long)c * ldd] = to_c64(U[i + (long)c * ldu]);
+    const double2 u = U[i + (long)c * ldu];
+    D[k * sD + i + (long)c * ldd] =
+        make_float2((float)row_scaled(u.x, rs, k * sRs + i), (float)row_scaled(u.y, rs, k * sRs + i));
 }
 
 // R_k = U for every point k (FP64).
@@ -69,7 +75,8 @@ __global__ __launch_bounds__(EW_NT) void colnorm_kernel(int n, int L, const doub
 __global__ __launch_bounds__(EW_NT) void scale_narrow_kernel(int n, int L, const double2* __restrict__ R, int ldr,
                                                               long sR, const double* __restrict__ inv,
                                                               float2* __restrict__ D, int ldd, long sD,
-                                                              const int* __restrict__ active)
+                                                              const int* __restrict__ active,
+                                                              const int* __restrict__ rs, long sRs)
 {
     const int k = blockIdx.y;
     if (active && !active[k]) return;
@@ -78,7 +85,8 @@ __global__ __launch_bounds__(EW_NT) void scale_narrow_kernel(int n, int L, const
     const int i = e % n, c = e / n;
     const double s = inv[(long)k * L + c];
     const double2 r = R[k * sR + i + (long)c * ldr];
-    D[k * sD + i + (long)c * ldd] = make_float2((float)(r.x * s), (float)(r.y * s));
+    D[k * sD + i + (long)c * ldd] =
+        make_float2((float)row_scaled(r.x * s, rs, k * sRs + i), (float)row_scaled(r.y * s, rs, k * sRs + i));
 }
 
 // X_k(:, c) += scale[k*L + c] * D_k(:, c) for active points.
@@ -111,7 +119,8 @@ __global__ __launch_bounds__(EW_NT) void axpy_widen_kernel(int n, int L, const f
 __global__ __launch_bounds__(EW_NT) void scale_narrow_real_kernel(int n, int L, const double2* __restrict__ R, int ldr,
                                                                    long sR, const double* __restrict__ inv,
                                                                    float* __restrict__ D, int ldd, long sD,
-                                                                   const int* __restrict__ active)
+                                                                   const int* __restrict__ active,
+                                                                   const int* __restrict__ rs, long sRs)
 {
     const int k = blockIdx.y;
     if (active && !active[k]) return;
@@ -119,7 +128,7 @@ __global__ __launch_bounds__(EW_NT) void scale_narrow_real_kernel(int n, int L, 
     if (e >= n * L) return;
     const int i = e % n, c = e / n;
     const double s = inv ? inv[(long)k * L + c] : 1.0;
-    D[k * sD + i + (long)c * ldd] = (float)(R[k * sR + i + (long)c * ldr].x * s);
+    D[k * sD + i + (long)c * ldd] = (float)row_scaled(R[k * sR + i + (long)c * ldr].x * s, rs, k * sRs + i);
 }
 
 // X_k(:, c) = (D_k(:, c), 0) when scale is null, else Re X_k(:, c) += scale[k*L + c] * D_k(:, c),
@@ -550,9 +559,11 @@ hipError_t ir_decide(hipStream_t st, int M, int Lmax, const double* rn, const do
     return hipGetLastError();
 }
 
-hipError_t bcast_to_c64(hipStream_t st, int n, int L, const double2* U, int ldu, float2* D, int ldd, long sD, int B)
+hipError_t bcast_to_c64(hipStream_t st, int n, int L, const double2* U, int ldu, float2* D, int ldd, long sD, int B,
+                        const int* rs, long sRs)
 {
-    hipLaunchKernelGGL(bcast_to_c64_kernel, ew_grid((long)n * L, B), dim3(EW_NT), 0, st, n, L, U, ldu, D, ldd, sD);
+    hipLaunchKernelGGL(bcast_to_c64_kernel, ew_grid((long)n * L, B), dim3(EW_NT), 0, st, n, L, U, ldu, D, ldd, sD, rs,
+                       sRs);
     return hipGetLastError();
 }
 hipError_t bcast_c128(hipStream_t st, int n, int L, const double2* U, int ldu, double2* R, int ldr, long sR, int B)
@@ -571,10 +582,10 @@ hipError_t colnorms(hipStream_t st, int n, int L, const double2* X, int ldx, lon
     return hipGetLastError();
 }
 hipError_t scale_narrow(hipStream_t st, int n, int L, const double2* R, int ldr, long sR, const double* inv,
-                        float2* D, int ldd, long sD, const int* active, int B)
+                        float2* D, int ldd, long sD, const int* active, int B, const int* rs, long sRs)
 {
     hipLaunchKernelGGL(scale_narrow_kernel, ew_grid((long)n * L, B), dim3(EW_NT), 0, st, n, L, R, ldr, sR, inv, D,
-                       ldd, sD, active);
+                       ldd, sD, active, rs, sRs);
     return hipGetLastError();
 }
 hipError_t axpy_widen(hipStream_t st, int n, int L, const float2* D, int ldd, long sD, const double* scale,
@@ -626,10 +637,10 @@ hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt,
 }
 
 hipError_t scale_narrow_real(hipStream_t st, int n, int L, const double2* R, int ldr, long sR, const double* inv,
-                             float* D, int ldd, long sD, const int* active, int B)
+                             float* D, int ldd, long sD, const int* active, int B, const int* rs, long sRs)
 {
     hipLaunchKernelGGL(scale_narrow_real_kernel, ew_grid((long)n * L, B), dim3(EW_NT), 0, st, n, L, R, ldr, sR, inv,
-                       D, ldd, sD, active);
+                       D, ldd, sD, active, rs, sRs);
     return hipGetLastError();
 }
 hipError_t axpy_widen_real(hipStream_t st, int n, int L, const float* D, int ldd, long sD, const double* scale,

@@ -39,24 +39,16 @@ const char* update_tile_name(int t);
 // columns, K) bytes, stride sP bytes); gemm_split then gives C -= A B (sub) or C = A B for N
 // columns from column j0 (a multiple of 32; C at that column) of the Npack packed ones.  A deeper product
 // is a batch of slabs: matrix b at sA, of the columns (rows of B) b kstep .. of Ktot.
-// split_ok: sizes for which it replaces cgemm and sgemm; split_pack_bytes: the inner exponents, both operands of
+// split_ok: sizes for which it replaces cgemm and sgemm; split_pack_bytes: the solves' exponents, both operands of
 // an LU update of depth K of at most n rows and columns, and the factors of split_urows.
 bool split_ok(int M, int N, int K);
 template <typename C> long split_operand_bytes(int rows, int K);
 template <typename C> size_t split_pack_bytes(int n, int K);
-// Both take the exponents of the inner index that split_inner forms from A (K per matrix, stride sE; of a
-// slab: those of its first column on): column k of A is multiplied by 2^E[k], row k of B by 2^-E[k].
-template <typename C>
-hipError_t split_inner(hipStream_t st, int M, int K, const C* A, int lda, long sA, int* E, long sE, int batch);
-// of the left factor W (M x 2 nb) of a pair of panels, whose second half is copied from A
-template <typename C>
-hipError_t split_inner_pair(hipStream_t st, int M, int nb, const C* A, int lda, long sA, C* W, int ldw, long sW, int* E,
-                            long sE, const int* active, int batch);
-// of every product of a solve with n x n factors: 2 n exponents, forward sweep, then backward
-hipError_t split_inner_solve(hipStream_t st, int n, int nb, const float2* LU, int ld, long sLU, int* E, long sE,
-                             int batch);
-// bytes in front of the operands in the pack buffer of n x n matrices (n >= 128)
-inline size_t split_inner_bytes(int n) { return (size_t)round_up_l(2L * n * (long)sizeof(int), 128); }
+// Both may take exponents of the inner index (K per matrix, stride sE; null: none): column k of A is multiplied by
+// 2^E[k], row k of B by 2^-E[k].  split_columns forms those of the columns of U of n x n factors, for the
+// solves' backward sweep (n per matrix, the first split_column_bytes(n) bytes of a pack buffer).
+inline size_t split_column_bytes(int n) { return (size_t)round_up_l(n * (long)sizeof(int), 128); }
+hipError_t split_columns(hipStream_t st, int n, const float2* LU, int ld, long sLU, int* E, long sE, int batch);
 template <typename C>
 hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, const int* E, long sE, void* P,
                         long sP, int batch, int Ktot = 0, int kstep = 0);
@@ -68,12 +60,11 @@ hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long 
                       int Npack, int j0, bool sub, C* Cm, int ldc, long sC, int batch);
 // The U rows of a pair of 128-wide panels on N trailing columns (A: 256 x N at the pair's first
 // row, interchanged) in place, U0 = L0 A0 and U1 = L1 (A1 - T U0) with L0, T, L1 128 x 128, and
-// the B operand of the M x N update of depth 256 that follows (instead of split_pack_b); E: the inner
-// exponents of that update.
+// the B operand of the M x N update of depth 256 that follows (instead of split_pack_b).
 bool split_urows_ok(int nb, const float2* A, int lda, long sA);
 hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, long s0, const float2* T, int ldt,
-                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, const int* E, long sE,
-                       void* P, long sP, int batch);
+                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, void* P, long sP,
+                       int batch);
 
 // C = beta*C + alpha*op(A)*op(B), complex double on v_mfma_f64_16x16x4f64;
 // op = conjugate transpose when the flag is set.
@@ -131,6 +122,13 @@ struct LUWork {
     // trailing updates, and complex solves of many right-hand sides, then run with split operands on
     // the FP16 matrix cores
     void* pack = nullptr; long sPack = 0;
+    // optional (FP32, panels of at least 64 columns; row_scale_of): the factors are those of
+    // diag(2^-rs) T, whose rows are of one size (lu.hip), rs n ints per matrix (stride sRs; all zero without
+    // pack).  frob: ||T||_F per matrix (null: every T is read in full); rows: rows of T in the n (the rest is the
+    // identity; null: all).
+    int* rs = nullptr; long sRs = 0;
+    const double* frob = nullptr;
+    const int* rows = nullptr;
     // the solves' kernels are chosen by (n, nrhs) alone, not by how many matrices share a launch: the ragged
     // batch, whose requests get the same bits alone and in any mix
     bool any_mix = false;
@@ -144,6 +142,10 @@ inline size_t lu_pack_bytes(int n)
     constexpr int depth = 2 * max_panel<float>();
     return split_ok(n - depth, n - depth, depth) ? split_pack_bytes<C>(n, depth) : 0;
 }
+
+// Where LUWork::rs of n x n matrices lies in their perm storage (stride 2 sPerm ints): its last n ints, with
+// scratch of n / 64 + 2 ints before them.  Panels of at least 64 columns use half of that storage.
+inline int* row_scale_of(int2* perm, long sPerm, int n) { return (int*)(perm + sPerm) - n; }
 
 // Blocked LU with partial pivoting of `batch` n x n matrices (stride sA).
 template <typename R>
@@ -230,7 +232,9 @@ hipError_t copy_out_group(hipStream_t st, const RhsInstance* ins, int nins, int 
                           const double2* Xb, int ldb, long sB);
 
 // ---- element-wise helpers (ir.hip) ----
-hipError_t bcast_to_c64(hipStream_t st, int n, int L, const double2* U, int ldu, float2* D, int ldd, long sD, int B);
+// Narrowed right-hand sides are scaled by 2^-rs[i] (rs: n ints per matrix, stride sRs; null: not).
+hipError_t bcast_to_c64(hipStream_t st, int n, int L, const double2* U, int ldu, float2* D, int ldd, long sD, int B,
+                        const int* rs, long sRs);
 hipError_t bcast_c128(hipStream_t st, int n, int L, const double2* U, int ldu, double2* R, int ldr, long sR, int B);
 hipError_t widen(hipStream_t st, int n, int L, const float2* D, int ldd, long sD, double2* X, int ldx, long sX, int B);
 hipError_t colnorms(hipStream_t st, int n, int L, const double2* X, int ldx, long sX, double* out, int B);
@@ -238,17 +242,18 @@ hipError_t colnorms(hipStream_t st, int n, int L, const double2* X, int ldx, lon
 // skipped (active may be null); U null gives R_b = T_b X_b.  resid_skinny_ok(L)
 // tells whether it applies.
 bool resid_skinny_ok(int L);
-// Real FP32 corrections for a real NEP at real points: D = (float)(Re R * inv) (inv may be null: 1); X = (D, 0) (scale null) or
-// Re X += scale * D.
+// Real FP32 corrections for a real NEP at real points: D = (float)(Re R * inv) (inv may be null: 1);
+// X = (D, 0) (scale null) or Re X += scale * D.
 hipError_t scale_narrow_real(hipStream_t st, int n, int L, const double2* R, int ldr, long sR, const double* inv,
-                             float* D, int ldd, long sD, const int* active, int B);
+                             float* D, int ldd, long sD, const int* active, int B, const int* rs, long sRs);
 hipError_t axpy_widen_real(hipStream_t st, int n, int L, const float* D, int ldd, long sD, const double* scale,
                            double2* X, int ldx, long sX, const int* active, int B);
 hipError_t resid_skinny(hipStream_t st, int n, int L, const double2* T, int ldt, long sT, const double2* X, int ldx,
                         long sX, const double2* U, int ldu, long sU, double2* R, int ldr, long sR, const int* active,
                         int B);
 hipError_t scale_narrow(hipStream_t st, int n, int L, const double2* R, int ldr, long sR, const double* inv,
-                        float2* D, int ldd, long sD, const int* active, int B);
+                        float2* D, int ldd, long sD, const int* active, int B,
+                        const int* rs, long sRs);
 hipError_t axpy_widen(hipStream_t st, int n, int L, const float2* D, int ldd, long sD, const double* scale,
                       double2* X, int ldx, long sX, const int* active, int B);
 hipError_t copy_c128(hipStream_t st, int n, int m, const double2* X, int ldx, long sX, double2* Y, int ldy, long sY,
@@ -280,7 +285,7 @@ int gm_slices(int n);        // row slices of the column kernels (partials per c
 int gm_max_restart();        // longest restart cycle
 hipError_t gm_point_scale(hipStream_t st, int n, int C, int L, const double2* Z, int ldz, const double2* coef,
                           double2* Y, int ldy);
-hipError_t gm_narrow(hipStream_t st, int n, int C, const double2* V, int ldv, float2* D, int ldd);
+hipError_t gm_narrow(hipStream_t st, int n, int C, const double2* V, int ldv, float2* D, int ldd, const int* rs);
 hipError_t gm_widen(hipStream_t st, int n, int C, const float2* D, int ldd, double2* Z, int ldz);
 hipError_t gm_resid(hipStream_t st, int n, int C, int L, const double2* U, int ldu, double2* V, int ldv);
 hipError_t gm_scale(hipStream_t st, int n, int C, const double* s, double2* X, int ldx);

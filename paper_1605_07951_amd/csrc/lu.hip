@@ -1021,11 +1021,181 @@ static void copy_rows(hipStream_t st, int r0, int n, int cols, const C* S, int l
                        S, lds, sS, D, ldd, sD, active);
 }
 
+// ----------------------------------------------------------------------------
+// Rows of one size for the split products (FP32): the factorisation of T with w.rs is that of
+// diag(2^-rs) T, and the right-hand sides are scaled by 2^-rs where they are narrowed.  A T whose
+// largest entries per row lie within RW_SPREAD powers of two keeps rs = 0 and every bit.
+//
+// With rows of different size the small entries of a row of L meet the large ones of a column of U and fall out
+// of the range of FP16 (split.hip): T with half of its rows 10^8 / 10^10 times the others took 3 / 6 to 10
+// corrections instead of 2, at 10^12 the redo in FP64, and the preconditioner of the iterative sampling was
+// lost. Powers of two per inner index taken from the columns of L21 mend those, but lose columns that are only
+// weakly coupled to the rows below; the rows of T itself have no such case. In an emulation of 72 scaled,
+// penalised, sparse and block matrices the scaled form took no more corrections than an unscaled FP32
+// factorisation wherever that one succeeded, and left smaller errors in the small components.
+//
+// Whether T needs it is decided cheaply where that is safe: the largest of 64 entries and the
+// diagonal entry of a row bounds the row's size from below, ||T||_F every row's from above; within 2^14 nothing
+// of weight is lost (2^-40 2^14 = 2^-26).  Only other matrices are read in full.  64 matrices with n = 4096:
+// 0.07 ms of a call of 89.4 (16 right-hand sides); with half of the rows 10^10 times the others 1.5 ms for the
+// sizes and 3.8 for the scaling, 94.9 ms in all.
+// ----------------------------------------------------------------------------
+constexpr int RW_SPREAD = 10, RW_SURE = 14, RW_NONE = -(1 << 20);
+constexpr int RW_NT = 1024;
+
+RSRR_DEV float part_max(float2 v) { return fmaxf(fabsf(v.x), fabsf(v.y)); }
+RSRR_DEV float part_max(float v) { return fabsf(v); }
+
+// least[blk] = the smallest over 64 rows of the largest of a row's sampled entries (16 per wave)
+template <typename C>
+__global__ __launch_bounds__(256) void row_sample_kernel(const C* __restrict__ A, long sA, int lda, int n,
+                                                         const int* __restrict__ rows, float* __restrict__ least,
+                                                         long sL)
+{
+    const int b = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
+    const int m = rows ? rows[b] : n;
+    __shared__ float top[4][64];
+    const C* Ab = A + b * sA + min(i, n - 1);
+    float t = part_max(Ab[(long)min(i, n - 1) * lda]);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) t = fmaxf(t, part_max(Ab[(long)((g + 4 * q) * (long)m / 64) * lda]));
+    top[g][lane] = t;
+    __syncthreads();
+    if (g > 0) return;
+    t = i < m ? fmaxf(fmaxf(top[0][lane], top[1][lane]), fmaxf(top[2][lane], top[3][lane])) : INFINITY;
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) t = fminf(t, __shfl_xor(t, off));
+    if (lane == 0) least[b * sL + blockIdx.x] = t;
+}
+
+// every row of matrix b is surely within 2^RW_SURE of the largest (uniform; the whole workgroup calls it)
+RSRR_DEV bool rows_sure(const float* __restrict__ least, int nblk, double frob)
+{
+    __shared__ float lo;
+    if (threadIdx.x < 64) {
+        float t = INFINITY;
+        for (int i = threadIdx.x; i < nblk; i += 64) t = fminf(t, least[i]);
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) t = fminf(t, __shfl_xor(t, off));
+        if (threadIdx.x == 0) lo = t;
+    }
+    __syncthreads();
+    return (double)lo * (double)(1 << RW_SURE) >= frob;   // false for a norm that is not finite
+}
+
+// rs[i] = the exponent of row i's largest part (none, or not finite: RW_NONE), or 0 where every row is sure
+template <typename C>
+__global__ __launch_bounds__(RW_NT) void row_expo_kernel(const C* __restrict__ A, long sA, int lda, int n,
+                                                         const int* __restrict__ rows, const float* __restrict__ least,
+                                                         long sL, const double* __restrict__ frob, int* __restrict__ rs,
+                                                         long sR)
+{
+    constexpr int G = RW_NT / 64;
+    const int b = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
+    const int m = rows ? rows[b] : n;
+    __shared__ float top[G][64];
+    if (frob && rows_sure(least + b * sL, gridDim.x, frob[b])) {
+        if (g == 0 && i < n) rs[b * sR + i] = 0;
+        return;
+    }
+    const C* Ab = A + b * sA + min(i, n - 1);
+    float t = 0.f;
+#pragma unroll 8
+    for (int j = g; j < m; j += G) t = fmaxf(t, part_max(Ab[(long)j * lda]));
+    top[g][lane] = t;
+    __syncthreads();
+    if (g > 0 || i >= n) return;
+#pragma unroll
+    for (int q = 1; q < G; ++q) t = fmaxf(t, top[q][lane]);
+    rs[b * sR + i] = i < m && t > 0.f && isfinite(t) ? __builtin_amdgcn_frexp_expf(t) : RW_NONE;
+}
+
+// rs relative to the largest row, or 0 for all within RW_SPREAD; need[b] = whether anything is scaled.  At
+// most 2^96, so that scaled right-hand sides of norm one stay in the range of FP32.
+__global__ __launch_bounds__(256) void row_scale_kernel(int n, const float* __restrict__ least, long sL, int nblk,
+                                                        const double* __restrict__ frob, int* __restrict__ rs, long sR,
+                                                        int* __restrict__ need)
+{
+    const int b = blockIdx.x, t = threadIdx.x;
+    __shared__ int hi[256], lo[256];
+    int* r = rs + b * sR;
+    bool scale = !(frob && rows_sure(least + b * sL, nblk, frob[b]));
+    int h = RW_NONE, l = -RW_NONE;
+    if (scale) {
+        for (int i = t; i < n; i += 256)
+            if (r[i] != RW_NONE) {
+                h = max(h, r[i]);
+                l = min(l, r[i]);
+            }
+        hi[t] = h;
+        lo[t] = l;
+        __syncthreads();
+        for (int o = 128; o >= 1; o >>= 1) {
+            if (t < o) {
+                hi[t] = max(hi[t], hi[t + o]);
+                lo[t] = min(lo[t], lo[t + o]);
+            }
+            __syncthreads();
+        }
+        h = hi[0];
+        scale = h != RW_NONE && h - lo[0] > RW_SPREAD;
+        for (int i = t; i < n; i += 256) r[i] = scale && r[i] != RW_NONE ? max(r[i] - h, -96) : 0;
+    }
+    if (t == 0) need[b * sR] = scale;
+}
+
+template <typename C>
+__global__ __launch_bounds__(256) void row_apply_kernel(C* __restrict__ A, long sA, int lda, int n,
+                                                        const int* __restrict__ rs, long sR,
+                                                        const int* __restrict__ need)
+{
+    const int b = blockIdx.y;
+    if (!need[b * sR]) return;
+    for (int j = blockIdx.x; j < n; j += gridDim.x) {
+        C* col = A + b * sA + (long)j * lda;
+        for (int i = threadIdx.x; i < n; i += 256) {
+            const int e = -rs[b * sR + i];
+            if (e == 0) continue;
+            if constexpr (elem_traits<C>::complex) col[i] = make_float2(ldexpf(col[i].x, e), ldexpf(col[i].y, e));
+            else col[i] = ldexpf(col[i], e);
+        }
+    }
+}
+
+__global__ __launch_bounds__(256) void row_zero_kernel(int n, int* __restrict__ rs, long sR)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) rs[blockIdx.y * sR + i] = 0;
+}
+
+// w.rs and the scratch before it (row_scale_of); without split operands nothing is scaled
+template <typename C>
+static void scale_rows(hipStream_t st, C* A, long sA, int lda, int n, const LUWork& w, int batch)
+{
+    const int nblk = (n + 63) / 64;
+    int* need = w.rs - 1;
+    float* least = (float*)(need - nblk);
+    if (!w.pack) {
+        hipLaunchKernelGGL(row_zero_kernel, dim3((n + 255) / 256, batch), dim3(256), 0, st, n, w.rs, w.sRs);
+        return;
+    }
+    if (w.frob)
+        hipLaunchKernelGGL(row_sample_kernel<C>, dim3(nblk, batch), dim3(256), 0, st, A, sA, lda, n, w.rows, least, w.sRs);
+    hipLaunchKernelGGL(row_expo_kernel<C>, dim3(nblk, batch), dim3(RW_NT), 0, st, A, sA, lda, n, w.rows, least, w.sRs,
+                       w.frob, w.rs, w.sRs);
+    hipLaunchKernelGGL(row_scale_kernel, dim3(batch), dim3(256), 0, st, n, least, w.sRs, nblk, w.frob, w.rs, w.sRs,
+                       need);
+    hipLaunchKernelGGL(row_apply_kernel<C>, dim3(64, batch), dim3(256), 0, st, A, sA, lda, n, w.rs, w.sRs, need);
+}
+
 template <typename C>
 static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int nb, const LUWork& w,
                          int batch)
 {
     typedef real_t<C> R;
+    if constexpr (sizeof(R) == 4) {
+        if (w.rs) scale_rows<C>(st, A, sA, lda, n, w, batch);
+    }
     // diagonal-block inverses and products on the matrix cores: always in FP32, in
     // FP64 when the caller gives the inverse and scratch buffers
     const bool use_inv = sizeof(R) == 4 || (w.inv != nullptr && w.tmp != nullptr);
@@ -1036,10 +1206,10 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     auto ok = [&](hipError_t e) { if (err == hipSuccess) err = e; };
     // trailing update C(M x N) -= Aop(M x kdepth) Bop(kdepth x N) on `s`, event-timed.  An
     // update done in column parts gives its whole width (Nall) and the part's first column
-    // (j0); with split operands the first part (j0 = 0) packs them for all parts.  ready: 1 the inner
-    // exponents are formed, 2 B is packed as well.
+    // (j0); with split operands the first part (j0 = 0) packs them for all parts (B unless the U
+    // rows came packed).
     auto timed_update = [&](hipStream_t s, int M, int N, int kdepth, const C* Aop, int ldaop, long sAop,
-                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0, int ready = 0) {
+                               const C* Bop, C* Cop, int Nall = 0, int j0 = 0, bool bpacked = false) {
         const bool timed = rec && rec->used < rec->cap;
         if (timed) (void)hipEventRecord(rec->ev[2 * rec->used], s);
         if (Nall == 0) Nall = N;
@@ -1048,14 +1218,11 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
             // (a part that starts inside a packed block of 32 columns runs in FP32)
             split = w.pack != nullptr && split_ok(M, Nall, kdepth) && j0 % 32 == 0;
             if (split) {
-                int* E = (int*)w.pack;
-                const long sE = w.sPack / 4;
-                char* PA = (char*)w.pack + split_inner_bytes(n);
+                char* PA = (char*)w.pack + split_column_bytes(n);
                 char* PB = PA + split_operand_bytes<C>(M, kdepth);
                 if (j0 == 0) {
-                    if (ready == 0) ok(split_inner(s, M, kdepth, Aop, ldaop, sAop, E, sE, batch));
-                    if (ready < 2) ok(split_pack_b(s, Nall, kdepth, Bop, lda, sA, E, sE, PB, w.sPack, batch));
-                    ok(split_pack_a(s, M, kdepth, Aop, ldaop, sAop, E, sE, PA, w.sPack, batch));
+                    ok(split_pack_a<C>(s, M, kdepth, Aop, ldaop, sAop, nullptr, 0, PA, w.sPack, batch));
+                    if (!bpacked) ok(split_pack_b<C>(s, Nall, kdepth, Bop, lda, sA, nullptr, 0, PB, w.sPack, batch));
                 }
                 ok(gemm_split(s, M, N, kdepth, PA, w.sPack, PB, w.sPack, Nall, j0, true, Cop, lda, sA, batch));
             }
@@ -1092,20 +1259,19 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
     // [U12_p; U12_{p+1}] in one product.
     const bool pairing = use_inv && w.pair != nullptr;
     // The U rows of the pair (q0, q1 = q0 + nb) of full panels p, p + 1 on the columns from q2 on,
-    // with the rows' interchanges, by the split kernels: true when done (and the update's B packed).  The
-    // update's inner exponents are formed.
+    // with the rows' interchanges, by the split kernels: true when done (and the update's B packed).
     auto split_pair_rows = [&](hipStream_t s, int q0, int p0, C* TL) -> bool {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const int q2 = q0 + 2 * nb, rest = n - q2;
             C* Ar = A + (long)q2 * lda;
-            if (!split_urows_ok(nb, Ar + q0, lda, sA)) return false;
+            if (!w.pack || !split_ok(rest, rest, 2 * nb) || !split_urows_ok(nb, Ar + q0, lda, sA)) return false;
             const int2* pm0 = w.perm + (long)p0 * 2 * MAX_NB;
             perm_rows<C>(s, pm0, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0, nb, rest, w.active, batch);
             perm_rows<C>(s, pm0 + 2 * MAX_NB, w.sPerm, Ar, sA, lda, (C*)nullptr, 0, 0, q0 + nb, nb, rest, w.active,
                          batch);
             ok(split_urows(s, rest, rest, panel_inv<C>(w, p0, nb, 0), nb, w.sInv, TL, nb, w.sPair,
-                           panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA, (const int*)w.pack,
-                           w.sPack / 4, (char*)w.pack + split_inner_bytes(n), w.sPack, batch));
+                           panel_inv<C>(w, p0 + 1, nb, 0), nb, w.sInv, Ar + q0, lda, sA,
+                           (char*)w.pack + split_column_bytes(n), w.sPack, batch));
             return true;
         }
         return false;
@@ -1129,21 +1295,11 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         copy_rows<C>(s, q1, n, nb, A + (long)q0 * lda, lda, sA, Wp, ldw, w.sPair, w.active, batch);
         perm_rows<C>(s, pm1, w.sPerm, Wp, w.sPair, ldw, TL, w.sPair, nb, q1, nb, nb, w.active, batch);
     };
-    // Returns timed_update's `ready`.
-    auto back = [&](int q0, int pp, C* Wp) -> int {
+    auto back = [&](int q0, int pp, C* Wp) -> bool {
         const int q1 = q0 + nb, q2 = q1 + nb, rest = n - q2;
         C* TL = Wp + (long)ldw * 2 * nb;
-        bool inner = false;
-        if constexpr (sizeof(R) == 4) {
-            inner = w.pack && split_ok(rest, rest, 2 * nb);
-            if (inner) {
-                ok(split_inner_pair(st, rest, nb, A + q2 + (long)q1 * lda, lda, sA, Wp + q2, ldw, w.sPair, (int*)w.pack,
-                                    w.sPack / 4, w.active, batch));
-                if (split_pair_rows(st, q0, pp, TL)) return 2;
-            }
-        }
-        if (!inner)
-            copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active, batch);
+        copy_rows<C>(st, q2, n, nb, A + (long)q1 * lda, lda, sA, Wp + (long)ldw * nb, ldw, w.sPair, w.active, batch);
+        if (split_pair_rows(st, q0, pp, TL)) return true;
         const int2* pm0 = w.perm + (long)pp * 2 * MAX_NB;
         const int2* pm1 = w.perm + (long)(pp + 1) * 2 * MAX_NB;
         C* Ar2 = A + (long)q2 * lda;
@@ -1154,7 +1310,7 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         ok(gemm_sub<C>(st, nb, rest, nb, TL, nb, w.sPair, Ar2 + q0, lda, sA, (C*)w.tmp, nb, w.sTmp, batch));
         ok(gemm_sub<C>(st, nb, rest, nb, panel_inv<C>(w, pp + 1, nb, 0), nb, w.sInv, (const C*)w.tmp, nb,
                        w.sTmp, Ar2 + q1, lda, sA, batch, 0, -1.0, 0.0));
-        return inner ? 1 : 0;
+        return false;
     };
     int c0 = 0, p = 0;
     // Look-ahead over full pairs (two nb-wide panels with a trailing block after
@@ -1169,19 +1325,19 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         if (w.first_panel) ok(hipEventRecord(w.first_panel, st));
         for (;;) {
             const int c2 = c0 + 2 * nb, rest = n - c2;
-            const int ready = back(c0, p, Wb[buf]);
+            const bool bpacked = back(c0, p, Wb[buf]);
             C* Aop = Wb[buf] + c2;
             const C* Bop = A + c0 + (long)c2 * lda;
             C* Cop = A + c2 + (long)c2 * lda;
             if (rest <= 2 * nb) {
                 // no full pair follows: one update, the loop below finishes the tail
-                timed_update(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, ready);
+                timed_update(st, rest, rest, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
                 c0 = c2;
                 p += 2;
                 break;
             }
             const int wn = 2 * nb;
-            timed_update(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, ready);
+            timed_update(st, rest, wn, 2 * nb, Aop, ldw, w.sPair, Bop, Cop, rest, 0, bpacked);
             ok(hipEventRecord(w.ev_a, st));
             // the rest of the update is enqueued before the next pair's panels (a chain of
             // small launches), so the host never holds it back behind them
@@ -1216,9 +1372,9 @@ static hipError_t getrf_impl(hipStream_t st, C* A, long sA, int lda, int n, int 
         C* Wp = (C*)w.pair;
         front(st, c0, p, Wp);
         if (c0 == 0 && w.first_panel) ok(hipEventRecord(w.first_panel, st));
-        const int ready = back(c0, p, Wp);
+        const bool bpacked = back(c0, p, Wp);
         timed_update(st, rest, rest, 2 * nb, Wp + c2, ldw, w.sPair, A + c0 + (long)c2 * lda, A + c2 + (long)c2 * lda,
-                        rest, 0, ready);
+                        rest, 0, bpacked);
     }
     for (; c0 < n; c0 += nb, ++p) {
         const int jb = std::min(nb, n - c0), c1 = c0 + jb, rest = n - c1;
@@ -1260,19 +1416,20 @@ static hipError_t getrs_impl(hipStream_t st, const C* LU, long sLU, int lda, int
     const int np = (n + nb - 1) / nb;
     hipError_t err = hipSuccess;   // the first one
     auto ok = [&](hipError_t e) { if (err == hipSuccess) err = e; };
-    // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0; the inner exponents of all split
-    // products are formed before the first
-    bool inner = false;
+    // rows at r0 (m of them) -= F (m x K, ld lda) times the K rows of X at c0; the backward sweep's split
+    // products take a power of two per column of U, formed before the first
+    bool columns = false;
     auto off_diag = [&](int r0, int m, int K, const C* F, int c0) {
         if constexpr (sizeof(C) == sizeof(float2) && elem_traits<C>::complex) {
             const long na = split_operand_bytes<C>(m, K);
             if (w.pack && !w.any_mix && split_ok(m, nrhs, K) && nrhs >= SPLIT_RHS && (long)nrhs * batch >= SPLIT_RHS_ALL &&
-                (long)split_inner_bytes(n) + na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
+                (long)split_column_bytes(n) + na + split_operand_bytes<C>(nrhs, K) <= w.sPack) {
                 const long sE = w.sPack / 4;
-                if (!inner) ok(split_inner_solve(st, n, nb, LU, lda, sLU, (int*)w.pack, sE, batch));
-                inner = true;
-                const int* E = (const int*)w.pack + (r0 > c0 ? 0 : n) + c0;
-                char* PA = (char*)w.pack + split_inner_bytes(n);
+                const bool back = r0 < c0;
+                if (back && !columns) ok(split_columns(st, n, LU, lda, sLU, (int*)w.pack, sE, batch));
+                columns |= back;
+                const int* E = back ? (const int*)w.pack + c0 : nullptr;
+                char* PA = (char*)w.pack + split_column_bytes(n);
                 char* PB = PA + na;
                 ok(split_pack_a(st, m, K, F, lda, sLU, E, sE, PA, w.sPack, batch));
                 ok(split_pack_b(st, nrhs, K, X + c0, ldx, sX, E, sE, PB, w.sPack, batch));

@@ -1,39 +1,38 @@
-// FP32 products C -= A B and C = A B on the FP16 matrix cores with split operands (the LU's
-// trailing updates, complex and real, and in complex FP32 the wide solves and the preconditioner of the iterative sampling).
+// FP32 products C -= A B and C = A B on the FP16 matrix cores with split operands (the LU's trailing
+// updates, complex and real, and in complex FP32 the wide solves and the preconditioner of the iterative
+// sampling).
 //
-// v_mfma_f32_32x32x16_f16 multiplies at 16 times the rate of the FP32 instruction, with
-// exact products and FP32 sums.  Every real FP32 value, scaled by a power of two, is
-// held as hi + lo of two FP16 numbers (the splitting of Markidis et al. 2018 and Ootomo and Yokota
-// 2022): hi carries the leading 11 bits, lo the next 11 and a sign, so hi + lo is the value
-// to within one unit of FP32 (exactly for three quarters of the values).  Three products,
-// hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.  The sums do not contain C
-// (one subtraction at the end), and 16 products enter them per rounding instead of 2.
+// v_mfma_f32_32x32x16_f16 multiplies at 16 times the rate of the FP32 instruction, with exact products and
+// FP32 sums.  Every real FP32 value, scaled by a power of two, is held as hi + lo of two FP16 numbers (the
+// splitting of Markidis et al. 2018 and Ootomo and Yokota 2022): hi carries the leading 11 bits, lo the
+// next 11 and a sign, so hi + lo is the value to within one unit of FP32 (exactly for three quarters of the
+// values).  Three products, hi hi + hi lo + lo hi, are accumulated; lo lo is below 2^-22 of the product.
+// The sums do not contain C (one subtraction at the end), and 16 products enter them per rounding instead
+// of 2.
 //
-// The range is that of FP16, so the operands carry powers of two, to a largest part in [2^14, 2^15):
-// one per row of A, one per column of B, and one per inner index k, which multiplies column k of A and
-// divides row k of B (split_inner: column k of A to a largest part of one).  An entry keeps its 22 bits
-// down to 2^-17 of the largest of its scaled row or column, then loses a bit per factor of two, and below 2^-40 it
-// is lost: the error is at most 2^-40 max_k |A_ik 2^e_k| max_k |B_kj 2^-e_k| a product beyond that of
-// the 22 bits.  A scaling T = D1 B D2 of the factored matrix goes into these powers: D2 into those of the
-// columns; D1 reaches the factors as L_ik ~ d_i / d_k and U_kj ~ d_k, small entries of a row of L against
-// large ones of a column of U, and without the powers of the inner index T with half of its rows 10^8 / 10^10
-// times the others took 3 / 6 to 10 corrections instead of 2 and 10^12 ended in the FP64 path.  What no
-// such powers can take out (three and more levels of entries in one matrix, min(s_i, s_j) B_ij) keeps the
-// bound above, not the error |A||B| of an FP32 product in every entry.
+// The range is that of FP16, so every row of A and every column of B has its own power of two, to a largest
+// part in [2^14, 2^15) (depths of at most 256; a deeper product is a sum of slabs with scales of their
+// own).  An entry keeps its 22 bits down to 2^-17 of the largest of its row or column, then loses a bit per
+// factor of two, and below 2^-40 it is lost: beyond the error of the 22 bits a product is off by up to
+// 2^-40 max_k |A_ik| max_k |B_kj|.  Columns of T of different size are in the powers of B's columns.  Rows
+// of different size are not: they reach the factors as L_ik ~ d_i / d_k and U_kj ~ d_k, small entries of a
+// row of L against large ones of a column of U; so the factorisation takes such a T with its rows brought
+// to one size first (lu.hip), and |L| <= 1 then meets rows of U of T's size.  In the solves' backward sweep
+// the inner index runs over T's columns; there it takes a power of two of its own (split_columns).
 //
-// Error against 64 bits, relative to |A||B| and in units of u = 2^-24, K = 128 and 256, split / FP32 kernels: complex, one size or
-// inner index, rows and columns spread over 12 to 16 decades: rms 0.32-0.34 / 0.51-0.53, largest 1.8-2.5 /
-// 3.1-4.9; the entries of A spread over 3 decades 0.6 / 0.95; both operands' over 3 decades 1.1 / 1.6-1.7, over
-// 8 decades 1.7-1.9 / 2.3-2.6, largest 12 / 24.  Real: 0.28-0.31 / 0.43; 0.53-0.56 / 0.78; 0.95 / 1.3; 1.5-1.7 / 1.7-2.0.
-// Depths of at most 256; a deeper product is a sum of slabs with scales of their own.
+// Error against 64 bits, relative to |A||B| and in units of u = 2^-24, K = 128 and 256, split / FP32
+// kernels: complex, one size or rows and columns spread over 16 decades: rms 0.32-0.34 / 0.51-0.53, largest
+// 1.8-2.5 / 3.1-4.9; the entries of A spread over 3 decades 0.6 / 0.95; both operands' over 3 decades 1.1 /
+// 1.6-1.7, over 8 decades 1.7-1.9 / 2.3-2.6, largest 12 / 24.  Real: 0.28-0.31 / 0.43; 0.53-0.56 / 0.78;
+// 0.95 / 1.3; 1.5-1.7 / 1.7-2.0.
 //
-// Bound by the matrix cores and by C, which is read and written once per update.  64
-// matrices, K = 256, n = 3840 / 2048 / 1024: 6.0-6.5 / 1.7 / 0.44 ms, 297-325 / 318-335 / 318 TFLOP/s in
-// the standard count of 8 flops per complex multiply-add (up to 975 TFLOP/s in FP16, C at 2.6
-// TB/s); the inner exponents 0.09 / 0.06 / 0.03 ms, packing 0.36 / 0.20 / 0.11; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
+// Bound by the matrix cores and by C, which is read and written once per update.  64 matrices, K = 256, n =
+// 3840 / 2048 / 1024: 6.0-6.6 / 1.7-1.8 / 0.44 ms, 292-325 / 301-335 / 311-318 TFLOP/s in the standard
+// count of 8 flops per complex multiply-add (up to 975 TFLOP/s in FP16, C at 2.6 TB/s), packing 0.36 / 0.20
+// / 0.11 ms; the FP32 3M kernel 13.8 / 4.5 / 1.1 ms.
 //
-// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.54 / 0.17 / 0.045 / 0.018 ms and 0.16 / 0.09 /
-// 0.055 / 0.04 ms for the exponents and the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045.
+// Real: K = 256, 64 matrices, n = 1768 / 1024 / 512 / 256: 0.54 / 0.17 / 0.045 / 0.018 ms and 0.12 / 0.07 /
+// 0.04 / 0.026 ms for the packing, the FP32 kernel 1.48 / 0.52 / 0.14 / 0.045.
 //
 // The complex product is the 4M form with the interleaved parts as the inner index
 // (k' = 2k + part): Re C takes A' (Br, -Bi), Im C takes A' (Bi, Br), which is one sign
@@ -70,6 +69,18 @@ RSRR_DEV void split4(const float2 (&v)[4], int e, const int2 (&k)[4], uintx4* hi
     *hi = __builtin_bit_cast(uintx4, h);
     *lo = __builtin_bit_cast(uintx4, l);
 }
+RSRR_DEV void split4(const float2 (&v)[4], int e, uintx4* hi, uintx4* lo)
+{
+    const int2 none[4] = {{0, 0}, {0, 0}, {0, 0}, {0, 0}};
+    split4(v, e, none, hi, lo);
+}
+
+// Exponent that scales a largest part to [2^SP_TOP, 2^(SP_TOP + 1)); zero or non-finite: no scale.
+RSRR_DEV int split_expo(float top)
+{
+    // v_frexp_exp: top = m 2^e with m in [1/2, 1)
+    return (top > 0.f && isfinite(top)) ? SP_TOP + 1 - __builtin_amdgcn_frexp_expf(top) : 0;
+}
 
 // Exponent of v's larger part times 2^k (v_frexp_exp: x = m 2^e with m in [1/2, 1); 0 for infinities
 // and NaN); zero: SP_NONE.
@@ -100,6 +111,7 @@ RSRR_DEV float2 sp_entry(const float* src, int k, long ld, int K)
 {
     return make_float2(2 * k < K ? src[2 * k * ld] : 0.f, 2 * k + 1 < K ? src[(2 * k + 1) * ld] : 0.f);
 }
+
 // the inner index's exponents (LDS, 16-byte aligned) of the parts of entries 4 p .. 4 p + 3
 template <typename C>
 RSRR_DEV void sp_inner(const int* inner, int p, int2 (&k)[4])
@@ -120,81 +132,35 @@ RSRR_DEV void sp_inner(const int* inner, int p, int2 (&k)[4])
     }
 }
 
-// The exponent that scales M entries to a largest part in [1/2, 1) (none or non-finite: 0) into *E; one
-// workgroup.  D given: the entries are copied there.
-template <typename C>
-RSRR_DEV void inner_expo(int M, const C* __restrict__ col, C* __restrict__ D, int* __restrict__ E)
+// E[k] scales column k of U (k of the n x n factors) to a largest part in [1/2, 1) (zero or non-finite: 0), for
+// the products of the solves' backward sweep: their inner index runs over T's columns, whose sizes the rows of
+// U and the solution carry inversely to each other.  One workgroup per column, one launch before the sweep.
+__global__ __launch_bounds__(256) void split_columns_kernel(const float2* __restrict__ LU, int ld, long sLU,
+                                                            int* __restrict__ E, long sE)
 {
-    const int t = threadIdx.x;
+    const int k = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
+    const float2* col = LU + b * sLU + (long)k * ld;
     __shared__ float tops[4];
     float top = 0.f;
 #pragma unroll 4
-    for (int i = t; i < M; i += 256) {
-        const C v = col[i];
-        if (D) D[i] = v;
-        if constexpr (elem_traits<C>::complex) top = fmaxf(top, fmaxf(fabsf(v.x), fabsf(v.y)));
-        else top = fmaxf(top, fabsf(v));
-    }
+    for (int i = t; i <= k; i += 256) top = fmaxf(top, fmaxf(fabsf(col[i].x), fabsf(col[i].y)));
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) top = fmaxf(top, __shfl_xor(top, off));
     if ((t & 63) == 0) tops[t >> 6] = top;
     __syncthreads();
     if (t == 0) {
         top = fmaxf(fmaxf(tops[0], tops[1]), fmaxf(tops[2], tops[3]));
-        *E = (top > 0.f && isfinite(top)) ? -__builtin_amdgcn_frexp_expf(top) : 0;
+        E[b * sE + k] = (top > 0.f && isfinite(top)) ? -__builtin_amdgcn_frexp_expf(top) : 0;
     }
 }
 
-// Exponents of the inner index: E[k] of column k of A (M x K).  One workgroup per column and matrix, bound by reading A once (64
-// matrices, K = 256, n = 3840: 88 us, 5.7 TB/s).
-template <typename C>
-__global__ __launch_bounds__(256) void split_inner_kernel(int M, const C* __restrict__ A, int lda, long sA,
-                                                          int* __restrict__ E, long sE)
-{
-    const int k = blockIdx.x, b = blockIdx.y;
-    inner_expo<C>(M, A + b * sA + (long)k * lda, nullptr, E + b * sE + k);
-}
-
-// The same for a pair of panels of nb columns: W (M x 2 nb), whose first half is there and whose second half
-// is copied from A on the way (the copy and the exponents in two launches: headline +0.7 ms).
-template <typename C>
-__global__ __launch_bounds__(256) void split_inner_pair_kernel(int M, int nb, const C* __restrict__ A, int lda, long sA,
-                                                               C* __restrict__ W, int ldw, long sW,
-                                                               int* __restrict__ E, long sE,
-                                                               const int* __restrict__ active)
-{
-    const int k = blockIdx.x, b = blockIdx.y;
-    if (active && !active[b]) return;
-    C* w = W + b * sW + (long)k * ldw;
-    if (k < nb) inner_expo<C>(M, w, nullptr, E + b * sE + k);
-    else inner_expo<C>(M, A + b * sA + (long)(k - nb) * lda, w, E + b * sE + k);
-}
-
-// The inner exponents of all products of a solve with the n x n factors LU in panels of nb columns, one
-// workgroup per column and sweep: E[k] of the rows below column k's panel (forward), E[n + k] of the rows
-// above the pair of panels that is taken together in the backward sweep (pairs from the last panel on; of
-// the first pair the rows above the panel, which are those of the pair's own coupling).  One launch before
-// the sweeps; one before each of the 43 products of an inverse of 2730 rows: +0.2 ms.
-__global__ __launch_bounds__(256) void split_inner_solve_kernel(int n, int nb, const float2* __restrict__ LU, int ld,
-                                                                long sLU, int* __restrict__ E, long sE)
-{
-    const int k = blockIdx.x, b = blockIdx.z, p = k / nb;
-    const float2* col = LU + b * sLU + (long)k * ld;
-    int* e = E + b * sE + blockIdx.y * n + k;
-    if (blockIdx.y == 0) {
-        const int below = min(n, (p + 1) * nb);
-        inner_expo<float2>(n - below, col + below, nullptr, e);
-    } else {
-        const int last = (n + nb - 1) / nb - 1, first = p - ((last - p) & 1 ? 0 : 1);   // first panel of p's pair
-        inner_expo<float2>((first > 0 ? first : p) * nb, col, nullptr, e);
-    }
-}
-
+// INNER: with exponents of the inner index (E).
+//
 // A (M x K, K <= SP_KMAX): fragment (row block, k chunk, hi/lo) at ((rb * nkc + kc) * 2 + h) KB; lane l
 // holds row l % 32 and the 4 complex k at 4 (l / 32); then the exponent of each row's scale.  One
 // workgroup per 32 rows, thread (row t % 32, groups of 4 columns t / 32 + 8 q); rows past M are zero.
 // Of a deeper product, slab b holds the columns b kstep .. (past Ktot: zero).
-template <typename C>
+template <typename C, bool INNER>
 __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Ktot, int kstep,
                                                            const C* __restrict__ A, int lda, long sA,
                                                            const int* __restrict__ E, long sE,
@@ -204,8 +170,8 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
     const int nkc = sp_chunks<C>(K), Kb = min(K, Ktot - b * kstep);
     const int r = t & 31, part = t >> 5, i = rb * 32 + r;
     __shared__ int tops[8][32];
-    __shared__ __attribute__((aligned(16))) int inner[SP_KMAX];
-    const int ei = t < Kb ? E[b * sE + t] : 0;
+    __shared__ __attribute__((aligned(16))) int inner[INNER ? SP_KMAX : 4];
+    const int ei = INNER && t < Kb ? E[b * sE + t] : 0;
     const C* src = A + b * sA + i;
     constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
     float2 v[Q][4];
@@ -214,13 +180,15 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             v[q][u] = i < M ? sp_entry(src, 4 * (part + 8 * q) + u, lda, Kb) : make_float2(0.f, 0.f);
-    inner[t] = ei;
-    __syncthreads();
+    if constexpr (INNER) {
+        inner[t] = ei;
+        __syncthreads();
+    }
     int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        int2 ek[4];
-        sp_inner<C>(inner, part + 8 * q, ek);
+        int2 ek[4] = {};
+        if constexpr (INNER) sp_inner<C>(inner, part + 8 * q, ek);
 #pragma unroll
         for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], ek[u]));
     }
@@ -236,8 +204,8 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
         const int p = part + 8 * q, kc = p >> 1;
         if (kc >= nkc) break;
         uintx4 hi, lo;
-        int2 ek[4];
-        sp_inner<C>(inner, p, ek);
+        int2 ek[4] = {};
+        if constexpr (INNER) sp_inner<C>(inner, p, ek);
         split4(v[q], e, ek, &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)rb * nkc + kc) * 2 * SP_FRAG);
         dst[r + 32 * (p & 1)] = hi;
@@ -247,7 +215,7 @@ __global__ __launch_bounds__(256) void split_pack_a_kernel(int M, int K, int Kto
 
 // B (K x N, K <= SP_KMAX): the same fragments with the columns in place of the rows, and the
 // exponent of each column's scale.  One workgroup per 32 columns, 8 threads per column.
-template <typename C>
+template <typename C, bool INNER>
 __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Ktot, int kstep,
                                                            const C* __restrict__ B, int ldb, long sB,
                                                            const int* __restrict__ E, long sE,
@@ -259,21 +227,23 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Kto
     const int j = blockIdx.x * 32 + c;
     const C* src = B + b * sB + (long)j * ldb;
     constexpr int Q = sp_chunks<C>(SP_KMAX) / 4;
-    __shared__ __attribute__((aligned(16))) int inner[SP_KMAX];
-    const int ei = t < Kb ? -E[b * sE + t] : 0;
+    __shared__ __attribute__((aligned(16))) int inner[INNER ? SP_KMAX : 4];
+    const int ei = INNER && t < Kb ? -E[b * sE + t] : 0;
     float2 v[Q][4];
 #pragma unroll
     for (int q = 0; q < Q; ++q)
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             v[q][u] = j < N ? sp_entry(src, 4 * (part + 8 * q) + u, 1, Kb) : make_float2(0.f, 0.f);
-    inner[t] = ei;
-    __syncthreads();
+    if constexpr (INNER) {
+        inner[t] = ei;
+        __syncthreads();
+    }
     int top = SP_NONE;
 #pragma unroll
     for (int q = 0; q < Q; ++q) {
-        int2 ek[4];
-        sp_inner<C>(inner, part + 8 * q, ek);
+        int2 ek[4] = {};
+        if constexpr (INNER) sp_inner<C>(inner, part + 8 * q, ek);
 #pragma unroll
         for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], ek[u]));
     }
@@ -287,8 +257,8 @@ __global__ __launch_bounds__(256) void split_pack_b_kernel(int N, int K, int Kto
         const int p = part + 8 * q, kc = p >> 1;
         if (kc >= nkc) break;
         uintx4 hi, lo;
-        int2 ek[4];
-        sp_inner<C>(inner, p, ek);
+        int2 ek[4] = {};
+        if constexpr (INNER) sp_inner<C>(inner, p, ek);
         split4(v[q], e, ek, &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + ((long)blockIdx.x * nkc + kc) * 2 * SP_FRAG);
         dst[c + 32 * (p & 1)] = hi;
@@ -311,46 +281,34 @@ constexpr int UR_NB = 128, UR_KC = UR_NB / SP_KC, UR_LD = UR_NB + 2;
 constexpr long UR_OPERAND = (long)(UR_NB / 32) * UR_KC * 2 * SP_FRAG;   // bytes of one packed factor
 
 // The three left factors (128 x 128, ld ldf[f]) packed with a scale per row; expo at eoff.  One
-// workgroup per 32 rows, factor and matrix: thread (row t % 32, 16 columns of part t / 32).  E: the pair's
-// inner exponents (256), those of the first panel for L0^-1 and T.
+// workgroup per 32 rows, factor and matrix: thread (row t % 32, 16 columns of part t / 32).
 struct UrFactors { const float2* p[3]; long stride[3]; int ld[3]; };
-__global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, const int* __restrict__ E, long sE,
-                                                              char* __restrict__ P, long sP, long eoff)
+__global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, char* __restrict__ P, long sP, long eoff)
 {
     const int rb = blockIdx.x, f = blockIdx.y, b = blockIdx.z, t = threadIdx.x;
     const int r = t & 31, part = t >> 5;
-    __shared__ int tops[8][32];
+    __shared__ float tops[8][32];
     const float2* src = F.p[f] + b * F.stride[f] + rb * 32 + r;
-    __shared__ __attribute__((aligned(16))) int inner[UR_NB];
-    const int ei = t < UR_NB ? E[b * sE + (f == 2 ? UR_NB : 0) + t] : 0;
     float2 v[4][4];
+    float top = 0.f;
 #pragma unroll
     for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) v[q][u] = src[(long)(16 * part + 4 * q + u) * F.ld[f]];
-    if (t < UR_NB) inner[t] = ei;
-    __syncthreads();
-    int top = SP_NONE;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        int2 ek[4];
-        sp_inner<float2>(inner, 4 * part + q, ek);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], ek[u]));
-    }
+        for (int u = 0; u < 4; ++u) {
+            v[q][u] = src[(long)(16 * part + 4 * q + u) * F.ld[f]];
+            top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
+        }
     tops[part][r] = top;
     __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 8; ++q) top = max(top, tops[q][r]);
+    for (int q = 0; q < 8; ++q) top = fmaxf(top, tops[q][r]);
     const int e = split_expo(top);
     char* Pb = P + b * sP;
     if (part == 0) reinterpret_cast<int*>(Pb + eoff)[f * UR_NB + rb * 32 + r] = e;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         uintx4 hi, lo;
-        int2 ek[4];
-        sp_inner<float2>(inner, 4 * part + q, ek);
-        split4(v[q], e, ek, &hi, &lo);
+        split4(v[q], e, &hi, &lo);
         uintx4* dst = reinterpret_cast<uintx4*>(Pb + f * UR_OPERAND +
                                                 ((long)rb * UR_KC + 2 * part + q / 2) * 2 * SP_FRAG);
         dst[r + 32 * (q & 1)] = hi;
@@ -359,17 +317,13 @@ __global__ __launch_bounds__(256) void split_pack_rows_kernel(UrFactors F, const
 }
 
 __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict__ A, int lda, long sA, int ncols,
-                                                             const int* __restrict__ E, long sE,
                                                              const char* __restrict__ P3, long sP, long eoff,
                                                              char* __restrict__ PB, long expo_off)
 {
     __shared__ __attribute__((aligned(16))) char F[UR_KC * 2 * SP_FRAG];   // the split columns
     __shared__ __attribute__((aligned(16))) float2 S[32 * UR_LD];          // a product, column by column
     __shared__ int ex[32];
-    __shared__ __attribute__((aligned(16))) int inner[2 * UR_NB];
     const int b = blockIdx.y, t = threadIdx.x;
-    inner[t] = -E[b * sE + t];
-    __syncthreads();
     const int lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int c = t >> 3, part = t & 7;   // column, and every eighth group of four rows of it
     const int j = blockIdx.x * 32 + c;
@@ -394,29 +348,23 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
             p[1] = floatx4{v[q][2].x, v[q][2].y, v[q][3].x, v[q][3].y};
         }
     };
-    // (w: the panel of the rows)
-    auto top_of = [&](int w, const float2 (&v)[4][4]) {
-        int top = SP_NONE;
+    auto top_of = [&](const float2 (&v)[4][4]) {
+        float top = 0.f;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int2 k[4];
-            sp_inner<float2>(inner + w * UR_NB, part + 8 * q, k);
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-            for (int u = 0; u < 4; ++u) top = max(top, part_expo(v[q][u], k[u]));
-        }
+            for (int u = 0; u < 4; ++u) top = fmaxf(top, fmaxf(fabsf(v[q][u].x), fabsf(v[q][u].y)));
 #pragma unroll
-        for (int off = 1; off < 8; off <<= 1) top = max(top, __shfl_xor(top, off));
+        for (int off = 1; off < 8; off <<= 1) top = fmaxf(top, __shfl_xor(top, off));
         return top;
     };
     // four-row group q of the thread goes to fragment (part + 8 q) / 2 of dst
-    auto put = [&](int w, char* dst, const float2 (&v)[4][4], int e) {
+    auto put = [&](char* dst, const float2 (&v)[4][4], int e) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int p = part + 8 * q;
             uintx4 hi, lo;
-            int2 k[4];
-            sp_inner<float2>(inner + w * UR_NB, p, k);
-            split4(v[q], e, k, &hi, &lo);
+            split4(v[q], e, &hi, &lo);
             uintx4* d = reinterpret_cast<uintx4*>(dst + (long)(p >> 1) * 2 * SP_FRAG);
             d[c + 32 * (p & 1)] = hi;
             d[64 + c + 32 * (p & 1)] = lo;
@@ -463,17 +411,17 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
         fetch(col, v0);
         fetch(col + UR_NB, v1);
     }
-    auto split = [&](int w, const float2 (&v)[4][4]) {
-        const int e = split_expo(top_of(w, v));
+    auto split = [&](const float2 (&v)[4][4]) {
+        const int e = split_expo(top_of(v));
         if (part == 0) ex[c] = e;
-        put(w, F, v, e);
+        put(F, v, e);
         __syncthreads();
     };
-    split(0, v0);
+    split(v0);
     product(0);
     __syncthreads();
     fetch(S + c * UR_LD, v0);
-    split(0, v0);
+    split(v0);
     product(1);
     __syncthreads();
     {
@@ -484,7 +432,7 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
 #pragma unroll
             for (int u = 0; u < 4; ++u) v1[q][u] = csub(v1[q][u], w[q][u]);
     }
-    split(1, v1);
+    split(v1);
     product(2);
     __syncthreads();
     fetch(S + c * UR_LD, v1);
@@ -493,11 +441,11 @@ __global__ __launch_bounds__(256, 2) void split_urows_kernel(float2* __restrict_
         store(col + UR_NB, v1);
     }
     // the update's operand: one scale for the 256 rows of the column
-    const int e = split_expo(max(top_of(0, v0), top_of(1, v1)));
+    const int e = split_expo(fmaxf(top_of(v0), top_of(v1)));
     char* dst = PB + b * sP + (long)blockIdx.x * 2 * UR_KC * 2 * SP_FRAG;
     if (part == 0) reinterpret_cast<int*>(PB + b * sP + expo_off)[j] = e;
-    put(0, dst, v0, e);
-    put(1, dst + (long)UR_KC * 2 * SP_FRAG, v1, e);
+    put(dst, v0, e);
+    put(dst + (long)UR_KC * 2 * SP_FRAG, v1, e);
 }
 
 // Workgroup tile 128 x 128, four waves of 64 x 64 (2 x 2 blocks of 32 x 32, real and imaginary
@@ -651,12 +599,12 @@ long split_operand_bytes(int rows, int K)
     return sp_frag_bytes<C>(rows, K) + (long)(rows + 31) / 32 * 32 * 4;
 }
 
-// Layout of the LU's pack buffer: the inner exponents (of an update, or of the solves), A, B, then (complex) the
-// three left factors of the U rows with their row exponents (the offsets follow from the sizes of the product).
+// Layout of the LU's pack buffer: the solves' exponents, A, B, then (complex) the three left factors of the U
+// rows with their row exponents (the offsets follow from the sizes of the product).
 template <typename C>
 size_t split_pack_bytes(int n, int K)
 {
-    return split_inner_bytes(n) + 2 * split_operand_bytes<C>(n, K) +
+    return split_column_bytes(n) + 2 * split_operand_bytes<C>(n, K) +
            (elem_traits<C>::complex ? 3 * UR_OPERAND + 3 * UR_NB * 4 : 0);
 }
 
@@ -664,26 +612,9 @@ size_t split_pack_bytes(int n, int K)
 // than 128 rows or columns leave most of a tile empty and do not pay for the packing.
 bool split_ok(int M, int N, int K) { return K >= 128 && K <= SP_KMAX && M >= 128 && N >= 128; }
 
-template <typename C>
-hipError_t split_inner(hipStream_t st, int M, int K, const C* A, int lda, long sA, int* E, long sE, int batch)
+hipError_t split_columns(hipStream_t st, int n, const float2* LU, int ld, long sLU, int* E, long sE, int batch)
 {
-    hipLaunchKernelGGL(split_inner_kernel<C>, dim3(K, batch), dim3(256), 0, st, M, A, lda, sA, E, sE);
-    return hipGetLastError();
-}
-
-template <typename C>
-hipError_t split_inner_pair(hipStream_t st, int M, int nb, const C* A, int lda, long sA, C* W, int ldw, long sW, int* E,
-                            long sE, const int* active, int batch)
-{
-    hipLaunchKernelGGL(split_inner_pair_kernel<C>, dim3(2 * nb, batch), dim3(256), 0, st, M, nb, A, lda, sA, W, ldw, sW,
-                       E, sE, active);
-    return hipGetLastError();
-}
-
-hipError_t split_inner_solve(hipStream_t st, int n, int nb, const float2* LU, int ld, long sLU, int* E, long sE,
-                             int batch)
-{
-    hipLaunchKernelGGL(split_inner_solve_kernel, dim3(n, 2, batch), dim3(256), 0, st, n, nb, LU, ld, sLU, E, sE);
+    hipLaunchKernelGGL(split_columns_kernel, dim3(n, batch), dim3(256), 0, st, LU, ld, sLU, E, sE);
     return hipGetLastError();
 }
 
@@ -691,8 +622,12 @@ template <typename C>
 hipError_t split_pack_a(hipStream_t st, int M, int K, const C* A, int lda, long sA, const int* E, long sE, void* P,
                         long sP, int batch, int Ktot, int kstep)
 {
-    hipLaunchKernelGGL(split_pack_a_kernel<C>, dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K, Ktot ? Ktot : K,
-                       kstep, A, lda, sA, E, sE, (char*)P, sP);
+    if (E)
+        hipLaunchKernelGGL((split_pack_a_kernel<C, true>), dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K,
+                           Ktot ? Ktot : K, kstep, A, lda, sA, E, sE, (char*)P, sP);
+    else
+        hipLaunchKernelGGL((split_pack_a_kernel<C, false>), dim3((M + 31) / 32, batch), dim3(256), 0, st, M, K,
+                           Ktot ? Ktot : K, kstep, A, lda, sA, E, sE, (char*)P, sP);
     return hipGetLastError();
 }
 
@@ -700,8 +635,12 @@ template <typename C>
 hipError_t split_pack_b(hipStream_t st, int N, int K, const C* B, int ldb, long sB, const int* E, long sE, void* P,
                         long sP, int batch, int Ktot, int kstep)
 {
-    hipLaunchKernelGGL(split_pack_b_kernel<C>, dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K, Ktot ? Ktot : K,
-                       kstep, B, ldb, sB, E, sE, (char*)P, sP);
+    if (E)
+        hipLaunchKernelGGL((split_pack_b_kernel<C, true>), dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K,
+                           Ktot ? Ktot : K, kstep, B, ldb, sB, E, sE, (char*)P, sP);
+    else
+        hipLaunchKernelGGL((split_pack_b_kernel<C, false>), dim3((N + 31) / 32, batch), dim3(256), 0, st, N, K,
+                           Ktot ? Ktot : K, kstep, B, ldb, sB, E, sE, (char*)P, sP);
     return hipGetLastError();
 }
 
@@ -711,17 +650,17 @@ bool split_urows_ok(int nb, const float2* A, int lda, long sA)
 }
 
 hipError_t split_urows(hipStream_t st, int M, int N, const float2* L0, int ld0, long s0, const float2* T, int ldt,
-                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, const int* E, long sE,
-                       void* P, long sP, int batch)
+                       long sT, const float2* L1, int ld1, long s1, float2* A, int lda, long sA, void* P, long sP,
+                       int batch)
 {
     constexpr int K = 2 * UR_NB;
     char* Pc = (char*)P;
     const long offb = split_operand_bytes<float2>(M, K), off = offb + split_operand_bytes<float2>(N, K);
     const UrFactors F = {{L0, T, L1}, {s0, sT, s1}, {ld0, ldt, ld1}};
-    hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, E, sE, Pc + off, sP,
+    hipLaunchKernelGGL(split_pack_rows_kernel, dim3(UR_NB / 32, 3, batch), dim3(256), 0, st, F, Pc + off, sP,
                        3 * UR_OPERAND);
-    hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, E, sE,
-                       Pc + off, sP, 3 * UR_OPERAND, Pc + offb, sp_frag_bytes<float2>(N, K));
+    hipLaunchKernelGGL(split_urows_kernel, dim3((N + 31) / 32, batch), dim3(256), 0, st, A, lda, sA, N, Pc + off, sP,
+                       3 * UR_OPERAND, Pc + offb, sp_frag_bytes<float2>(N, K));
     return hipGetLastError();
 }
 
@@ -747,9 +686,6 @@ hipError_t gemm_split(hipStream_t st, int M, int N, int K, const void* PA, long 
 #define SP_INST(C)                                                                                                  \
     template long split_operand_bytes<C>(int, int);                                                                 \
     template size_t split_pack_bytes<C>(int, int);                                                                  \
-    template hipError_t split_inner<C>(hipStream_t, int, int, const C*, int, long, int*, long, int);                \
-    template hipError_t split_inner_pair<C>(hipStream_t, int, int, const C*, int, long, C*, int, long, int*, long,  \
-                                            const int*, int);                                                       \
     template hipError_t split_pack_a<C>(hipStream_t, int, int, const C*, int, long, const int*, long, void*, long,  \
                                         int, int, int);                                                             \
     template hipError_t split_pack_b<C>(hipStream_t, int, int, const C*, int, long, const int*, long, void*, long,  \

@@ -96,3 +96,58 @@ def test_gmres_preconditioner(ctx, n, scaled):
     _, infos, code = R.rsrr_sample_gmres(ctx, R.DeviceNEP(nep), z, U, [1.0 + 0j])
     assert code == R.RSRR_OK
     assert max(i["iters"] for i in infos) <= 6
+
+
+def test_weakly_coupled_columns(ctx):
+    """Rows of different size in a sparse T with columns that hold their diagonal entry alone."""
+    n = 640
+    rng = np.random.default_rng(7)
+    A = (rng.standard_normal((n, n)) + 1j * rng.standard_normal((n, n))) * (rng.random((n, n)) < 0.01)
+    A += np.diag(6 * np.exp(2j * np.pi * rng.random(n)))   # about as large as the rest of its row
+    alone = rng.permutation(n)[:n // 4]
+    A[:, alone] = 0
+    A[alone, alone] = 1
+    A *= _rows(rng, n, "spread", 5)[:, None]
+    X, U = _known(A, 3, rng)
+    nep = W.SeparableNEP(name="weak", A=[A], terms=[W.term(1.0, 1)])
+    S, info, status = R.rsrr_sample(ctx, R.DeviceNEP(nep), np.array([1.0 + 0j]), U)
+    assert status == R.RSRR_OK
+    assert info[0]["ir_iters"] <= 3
+    assert (np.abs(R.from_colmajor(S, n) - X) / np.abs(X)).max() <= (4e-10 if info[0]["ir_iters"] >= 2 else 7e-4)
+
+
+@pytest.mark.parametrize("flags", [0, R.RSRR_BATCH_GRAPH])
+def test_batch_rows_of_different_size(ctx, flags):
+    """The ragged batch refines at most three times; its padding rows are no rows of T."""
+    items, known = [], []
+    for n, d in ((390, 0), (400, 10), (447, 12)):
+        B, rng = _b(n)
+        A = _rows(rng, n, "half", d)[:, None] * B * 1e6
+        X, U = _known(A, 3, rng)
+        known.append(X)
+        nep = R.DeviceNEP(W.SeparableNEP(name="batch", A=[A], terms=[W.term(1.0, 1)]))
+        items.append(R.BatchItem(nep, np.exp(1j * np.arange(4)), U))
+    for _ in range(3 if flags else 1):
+        infos, status = R.rsrr_sample_batched(ctx, items, flags=flags)
+        assert status == R.RSRR_OK
+        for it, X, info in zip(items, known, infos):
+            x = R.from_colmajor(it.S, X.shape[0])
+            for k, zk in enumerate(it.z):
+                bar = 4e-10 if info[k]["ir_iters"] >= 2 else 7e-4
+                assert (np.abs(zk * x[:, 3 * k:3 * k + 3] - X) / np.abs(X)).max() <= bar
+            it.S.zero_()
+
+
+def test_reprobe_from_factors_with_scaled_rows():
+    """The scales are kept with a request's factors: the reserve columns are solved without a redo."""
+    nep, C, U16 = W.cfg_qep(n=400, N=32, L=16)
+    D = _rows(np.random.default_rng(3), 400, "half", 10)
+    nep.A = [D[:, None] * A for A in nep.A]
+    srv = R.Server(max_slots=1, arena_bytes=8 << 30, batch_bytes=4 << 30)
+    try:
+        res = srv.wait(srv.submit(R.DeviceNEP(nep), R.colmajor(D[:, None] * U16)[0], C.gamma, C.a, C.b, C.N,
+                                  max_eigs=128, L_extra=15), 120.0)
+    finally:
+        srv.close()
+    assert res["reprobes"] == 1
+    assert res["fallbacks"] == 0
