@@ -678,7 +678,7 @@ def run_gmres(args):
         # each apply streams the N assembled FP64 matrices once (plus the n x L blocks in and out)
         bytes_apply = N * 16.0 * n * n + 2 * 16.0 * n * N * L
         achieved = bytes_apply / (op_ms * 1e-3) / 1e9
-        roof = {"bound": "hbm", "kernel": "operator T(z_k) Z, FP64 (resid_skinny_kernel, R = T X form)",
+        roof = {"bound": "hbm", "kernel": "operator T(z_k) Z, FP64 (resid_stream_kernel, R = T X form)",
                 "achieved": round(achieved, 1), "peak": 8000.0, "unit": "GB/s",
                 "frac": round(achieved / 8000.0, 4), "traffic": None,
                 "bytes_per_apply": bytes_apply, "avg_apply_ms": round(op_ms, 4), "applies": applies}
@@ -750,7 +750,7 @@ def run_gmres(args):
         "unit": "resolvent solves/s",
         "n_gpus": 1, "steps": args.steps, "warmup": args.warmup, "ms_per_step": gres["ms_per_step"],
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": "f64 Krylov + operator, c64 LU preconditioner (f32 MFMA)",
+        "dtype": "f64 Krylov + operator, c64 LU preconditioner (f32 panels and sums, split-f16 MFMA products)",
         "data": f"synthetic ({getattr(nep, 'name', args.gmres_nep)}, complex Gaussian probes)",
         "config": {"workload": f"GMRES sampling, {args.gmres_nep} n={n}, N={N}, L={L}, "
                                f"{args.nref} reference factorisation(s), restart {args.restart}, tol {args.tol:g}"
