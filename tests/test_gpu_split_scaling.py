@@ -98,6 +98,23 @@ def test_gmres_preconditioner(ctx, n, scaled):
     assert max(i["iters"] for i in infos) <= 6
 
 
+@pytest.mark.parametrize("N,L", [(2, 2), (16, 1), (16, 4)])
+def test_gmres_references_with_rows_of_their_own(ctx, N, L):
+    """Two references whose rows have different sizes, each at half of the points: solves with the factors (two
+    points), the inverse in FP32 (8 columns a reference) and in split slabs (32)."""
+    n = 640
+    B, rng = _b(n)
+    big = rng.permutation(n) < n // 2
+    d1, d2 = np.where(big, 1e12, 1.0), np.where(big, 1e10, 1.0)
+    nep = W.SeparableNEP(name="refs", A=[d1[:, None] * B, d2[:, None] * B[:, ::-1]],
+                         terms=[W.term(-1.0, 1, 1.0), W.term(1.0, 1)])
+    U = d1[:, None] * (rng.standard_normal((n, L)) + 1j * rng.standard_normal((n, L)))
+    z = np.arange(N) % 2 + 0j
+    _, infos, code = R.rsrr_sample_gmres(ctx, R.DeviceNEP(nep), z, U, [0j, 1.0 + 0j])
+    assert code == R.RSRR_OK
+    assert max(i["iters"] for i in infos) <= 6
+
+
 def test_weakly_coupled_columns(ctx):
     """Rows of different size in a sparse T with columns that hold their diagonal entry alone."""
     n = 640
