@@ -104,7 +104,11 @@ typedef struct {
 /* Arithmetic of the sampling step.  C128: complex FP64 LU and solves.
  * C64_IR: complex FP32 LU on the matrix cores, then iterative refinement
  * against FP64 residuals until FP64 backward error; a point that does not
- * converge is redone with the C128 path (flagged in rsrr_point_info).
+ * converge is redone with the C128 path (flagged in rsrr_point_info).  From
+ * 384 rows on the LU's updates multiply their FP32 operands as sums of two
+ * FP16 parts, with FP32 sums and errors below those of FP32 products; a T
+ * whose rows' largest entries lie more than 2^10 apart is factored with its
+ * rows scaled by powers of two, the right-hand sides with them (R32_IR too).
  * R32_IR (rsrr_sample only): real sampling for a real NEP (Sec. 4.3 and
  * Sec. 5: real points, e.g. Chebyshev points of an interval): real FP32 LU
  * and solves, refined against the FP64 residual of the complex problem as
