@@ -144,7 +144,7 @@ inline size_t lu_pack_bytes(int n)
 }
 
 // Where LUWork::rs of n x n matrices lies in their perm storage (stride 2 sPerm ints): its last n ints, with
-// scratch of n / 64 + 2 ints before them.  Panels of at least 64 columns use half of that storage.
+// scratch of n + 1 ints before them.  Panels of at least 64 columns use half of that storage.
 inline int* row_scale_of(int2* perm, long sPerm, int n) { return (int*)(perm + sPerm) - n; }
 
 // Blocked LU with partial pivoting of `batch` n x n matrices (stride sA).
@@ -153,7 +153,8 @@ hipError_t getrf_batched(hipStream_t st, typename cpx<R>::T* A, long sA, int lda
                          int batch);
 
 // X <- T^-1 X for the factors of getrf_batched (same nb and workspace).  FP32 blocks of
-// at most 64 right-hand sides (any_mix: 16), 16 of which fit in LDS, run the whole solve of a matrix in one workgroup per 16.
+// at most 64 right-hand sides (any_mix: 16), 16 of which fit in LDS, run the whole solve of a matrix in one
+// workgroup per 16.
 template <typename R>
 hipError_t getrs_batched(hipStream_t st, const typename cpx<R>::T* LU, long sLU, int lda, int n, int nb,
                          const LUWork& w, typename cpx<R>::T* X, long sX, int ldx, int nrhs, int batch);

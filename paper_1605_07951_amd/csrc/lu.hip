@@ -1034,11 +1034,11 @@ static void copy_rows(hipStream_t st, int r0, int n, int cols, const C* S, int l
 // penalised, sparse and block matrices the scaled form took no more corrections than an unscaled FP32
 // factorisation wherever that one succeeded, and left smaller errors in the small components.
 //
-// Whether T needs it is decided cheaply where that is safe: the largest of 64 entries and the
+// Whether T needs it is decided cheaply where that is safe: the largest of 16 entries and the
 // diagonal entry of a row bounds the row's size from below, ||T||_F every row's from above; within 2^14 nothing
 // of weight is lost (2^-40 2^14 = 2^-26).  Only other matrices are read in full.  64 matrices with n = 4096:
-// 0.07 ms of a call of 89.4 (16 right-hand sides); with half of the rows 10^10 times the others 1.5 ms for the
-// sizes and 3.8 for the scaling, 94.9 ms in all.
+// 46 us (64 entries: 95) of a call of 88.9 ms with 16 right-hand sides; with half of the rows 10^10 times the
+// others 1.5 ms for the sizes and 3.8 for the scaling, 94.5 ms in all.
 // ----------------------------------------------------------------------------
 constexpr int RW_SPREAD = 10, RW_SURE = 14, RW_NONE = -(1 << 20);
 constexpr int RW_NT = 1024;
@@ -1046,58 +1046,49 @@ constexpr int RW_NT = 1024;
 RSRR_DEV float part_max(float2 v) { return fmaxf(fabsf(v.x), fabsf(v.y)); }
 RSRR_DEV float part_max(float v) { return fabsf(v); }
 
-// least[blk] = the smallest over 64 rows of the largest of a row's sampled entries (16 per wave)
+// need[b] = whether some row of matrix b may be beyond 2^RW_SURE of the largest; else rs = 0
 template <typename C>
-__global__ __launch_bounds__(256) void row_sample_kernel(const C* __restrict__ A, long sA, int lda, int n,
-                                                         const int* __restrict__ rows, float* __restrict__ least,
-                                                         long sL)
+__global__ __launch_bounds__(RW_NT) void row_sure_kernel(const C* __restrict__ A, long sA, int lda, int n,
+                                                         const int* __restrict__ rows, const double* __restrict__ frob,
+                                                         int* __restrict__ rs, long sR, int* __restrict__ need)
 {
-    const int b = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
+    const int b = blockIdx.x, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int m = rows ? rows[b] : n;
-    __shared__ float top[4][64];
-    const C* Ab = A + b * sA + min(i, n - 1);
-    float t = part_max(Ab[(long)min(i, n - 1) * lda]);
+    __shared__ float lo[RW_NT / 64];
+    float least = INFINITY;
+    if (frob)
+        for (int i0 = g * 64; i0 < m; i0 += RW_NT) {
+            const int i = min(i0 + lane, m - 1);
+            const C* Ab = A + b * sA + i;
+            float t = part_max(Ab[(long)i * lda]);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) t = fmaxf(t, part_max(Ab[(long)((g + 4 * q) * (long)m / 64) * lda]));
-    top[g][lane] = t;
+            for (int q = 0; q < 16; ++q) t = fmaxf(t, part_max(Ab[(long)((long)q * m / 16) * lda]));
+            least = fminf(least, t);
+        }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) least = fminf(least, __shfl_xor(least, off));
+    if (lane == 0) lo[g] = least;
     __syncthreads();
-    if (g > 0) return;
-    t = i < m ? fmaxf(fmaxf(top[0][lane], top[1][lane]), fmaxf(top[2][lane], top[3][lane])) : INFINITY;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) t = fminf(t, __shfl_xor(t, off));
-    if (lane == 0) least[b * sL + blockIdx.x] = t;
+    for (int q = 0; q < RW_NT / 64; ++q) least = fminf(least, lo[q]);
+    // false for a norm that is not finite
+    const bool sure = frob && (double)least * (double)(1 << RW_SURE) >= frob[b];
+    if (threadIdx.x == 0) need[b * sR] = !sure;
+    if (sure)
+        for (int i = threadIdx.x; i < n; i += RW_NT) rs[b * sR + i] = 0;
 }
 
-// every row of matrix b is surely within 2^RW_SURE of the largest (uniform; the whole workgroup calls it)
-RSRR_DEV bool rows_sure(const float* __restrict__ least, int nblk, double frob)
-{
-    __shared__ float lo;
-    if (threadIdx.x < 64) {
-        float t = INFINITY;
-        for (int i = threadIdx.x; i < nblk; i += 64) t = fminf(t, least[i]);
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) t = fminf(t, __shfl_xor(t, off));
-        if (threadIdx.x == 0) lo = t;
-    }
-    __syncthreads();
-    return (double)lo * (double)(1 << RW_SURE) >= frob;   // false for a norm that is not finite
-}
-
-// rs[i] = the exponent of row i's largest part (none, or not finite: RW_NONE), or 0 where every row is sure
+// ex[i] = the exponent of row i's largest part (none, or not finite: RW_NONE)
 template <typename C>
 __global__ __launch_bounds__(RW_NT) void row_expo_kernel(const C* __restrict__ A, long sA, int lda, int n,
-                                                         const int* __restrict__ rows, const float* __restrict__ least,
-                                                         long sL, const double* __restrict__ frob, int* __restrict__ rs,
-                                                         long sR)
+                                                         const int* __restrict__ rows, int* __restrict__ ex, long sR,
+                                                         const int* __restrict__ need)
 {
     constexpr int G = RW_NT / 64;
     const int b = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6, i = blockIdx.x * 64 + lane;
+    if (!need[b * sR]) return;
     const int m = rows ? rows[b] : n;
     __shared__ float top[G][64];
-    if (frob && rows_sure(least + b * sL, gridDim.x, frob[b])) {
-        if (g == 0 && i < n) rs[b * sR + i] = 0;
-        return;
-    }
     const C* Ab = A + b * sA + min(i, n - 1);
     float t = 0.f;
 #pragma unroll 8
@@ -1107,57 +1098,48 @@ __global__ __launch_bounds__(RW_NT) void row_expo_kernel(const C* __restrict__ A
     if (g > 0 || i >= n) return;
 #pragma unroll
     for (int q = 1; q < G; ++q) t = fmaxf(t, top[q][lane]);
-    rs[b * sR + i] = i < m && t > 0.f && isfinite(t) ? __builtin_amdgcn_frexp_expf(t) : RW_NONE;
+    ex[b * sR + i] = i < m && t > 0.f && isfinite(t) ? __builtin_amdgcn_frexp_expf(t) : RW_NONE;
 }
 
-// rs relative to the largest row, or 0 for all within RW_SPREAD; need[b] = whether anything is scaled.  At
-// most 2^96, so that scaled right-hand sides of norm one stay in the range of FP32.
-__global__ __launch_bounds__(256) void row_scale_kernel(int n, const float* __restrict__ least, long sL, int nblk,
-                                                        const double* __restrict__ frob, int* __restrict__ rs, long sR,
-                                                        int* __restrict__ need)
-{
-    const int b = blockIdx.x, t = threadIdx.x;
-    __shared__ int hi[256], lo[256];
-    int* r = rs + b * sR;
-    bool scale = !(frob && rows_sure(least + b * sL, nblk, frob[b]));
-    int h = RW_NONE, l = -RW_NONE;
-    if (scale) {
-        for (int i = t; i < n; i += 256)
-            if (r[i] != RW_NONE) {
-                h = max(h, r[i]);
-                l = min(l, r[i]);
-            }
-        hi[t] = h;
-        lo[t] = l;
-        __syncthreads();
-        for (int o = 128; o >= 1; o >>= 1) {
-            if (t < o) {
-                hi[t] = max(hi[t], hi[t + o]);
-                lo[t] = min(lo[t], lo[t + o]);
-            }
-            __syncthreads();
-        }
-        h = hi[0];
-        scale = h != RW_NONE && h - lo[0] > RW_SPREAD;
-        for (int i = t; i < n; i += 256) r[i] = scale && r[i] != RW_NONE ? max(r[i] - h, -96) : 0;
-    }
-    if (t == 0) need[b * sR] = scale;
-}
-
+// rs = ex relative to the largest row (0 for all within RW_SPREAD), and T scaled by it.  At most 2^96, so that
+// scaled right-hand sides of norm one stay in the range of FP32.
 template <typename C>
 __global__ __launch_bounds__(256) void row_apply_kernel(C* __restrict__ A, long sA, int lda, int n,
-                                                        const int* __restrict__ rs, long sR,
+                                                        const int* __restrict__ ex, int* __restrict__ rs, long sR,
                                                         const int* __restrict__ need)
 {
-    const int b = blockIdx.y;
+    const int b = blockIdx.y, t = threadIdx.x;
     if (!need[b * sR]) return;
+    const int* e = ex + b * sR;
+    __shared__ int hi[256], lo[256];
+    int h = RW_NONE, l = -RW_NONE;
+    for (int i = t; i < n; i += 256)
+        if (e[i] != RW_NONE) {
+            h = max(h, e[i]);
+            l = min(l, e[i]);
+        }
+    hi[t] = h;
+    lo[t] = l;
+    __syncthreads();
+    for (int o = 128; o >= 1; o >>= 1) {
+        if (t < o) {
+            hi[t] = max(hi[t], hi[t + o]);
+            lo[t] = min(lo[t], lo[t + o]);
+        }
+        __syncthreads();
+    }
+    h = hi[0];
+    const bool scale = h != RW_NONE && h - lo[0] > RW_SPREAD;
+    if (blockIdx.x == 0)
+        for (int i = t; i < n; i += 256) rs[b * sR + i] = scale && e[i] != RW_NONE ? max(e[i] - h, -96) : 0;
+    if (!scale) return;
     for (int j = blockIdx.x; j < n; j += gridDim.x) {
         C* col = A + b * sA + (long)j * lda;
-        for (int i = threadIdx.x; i < n; i += 256) {
-            const int e = -rs[b * sR + i];
-            if (e == 0) continue;
-            if constexpr (elem_traits<C>::complex) col[i] = make_float2(ldexpf(col[i].x, e), ldexpf(col[i].y, e));
-            else col[i] = ldexpf(col[i], e);
+        for (int i = t; i < n; i += 256) {
+            const int s = e[i] != RW_NONE ? min(h - e[i], 96) : 0;
+            if (s == 0) continue;
+            if constexpr (elem_traits<C>::complex) col[i] = make_float2(ldexpf(col[i].x, s), ldexpf(col[i].y, s));
+            else col[i] = ldexpf(col[i], s);
         }
     }
 }
@@ -1172,20 +1154,18 @@ __global__ __launch_bounds__(256) void row_zero_kernel(int n, int* __restrict__ 
 template <typename C>
 static void scale_rows(hipStream_t st, C* A, long sA, int lda, int n, const LUWork& w, int batch)
 {
-    const int nblk = (n + 63) / 64;
-    int* need = w.rs - 1;
-    float* least = (float*)(need - nblk);
+    int *need = w.rs - 1, *ex = need - n;
     if (!w.pack) {
         hipLaunchKernelGGL(row_zero_kernel, dim3((n + 255) / 256, batch), dim3(256), 0, st, n, w.rs, w.sRs);
         return;
     }
-    if (w.frob)
-        hipLaunchKernelGGL(row_sample_kernel<C>, dim3(nblk, batch), dim3(256), 0, st, A, sA, lda, n, w.rows, least, w.sRs);
-    hipLaunchKernelGGL(row_expo_kernel<C>, dim3(nblk, batch), dim3(RW_NT), 0, st, A, sA, lda, n, w.rows, least, w.sRs,
-                       w.frob, w.rs, w.sRs);
-    hipLaunchKernelGGL(row_scale_kernel, dim3(batch), dim3(256), 0, st, n, least, w.sRs, nblk, w.frob, w.rs, w.sRs,
+    hipLaunchKernelGGL(row_sure_kernel<C>, dim3(batch), dim3(RW_NT), 0, st, A, sA, lda, n, w.rows, w.frob, w.rs, w.sRs,
                        need);
-    hipLaunchKernelGGL(row_apply_kernel<C>, dim3(64, batch), dim3(256), 0, st, A, sA, lda, n, w.rs, w.sRs, need);
+    hipLaunchKernelGGL(row_expo_kernel<C>, dim3((n + 63) / 64, batch), dim3(RW_NT), 0, st, A, sA, lda, n, w.rows, ex,
+                       w.sRs, need);
+    // eight workgroups of a matrix or more, to fill the chip with few matrices too
+    hipLaunchKernelGGL(row_apply_kernel<C>, dim3(std::max(8, std::min(64, 2048 / batch)), batch), dim3(256), 0, st, A,
+                       sA, lda, n, ex, w.rs, w.sRs, need);
 }
 
 template <typename C>
